@@ -10,14 +10,16 @@
 // written in bytes: a slab row is 128 bytes = 64 bf16 or 128 int8, one MFMA eats 32 bytes of K
 // per row.
 //
-// Two kernels:
+// Three kernels:
 //   gemm_nt_dma_kernel     : aligned operands, K a whole number of 32-byte MFMA steps (the last
 //                            slab may be short).  Slabs go global -> LDS
 //                            directly (global_load_lds, 16 bytes per lane, no register staging);
 //                            because such a load writes 64 x 16 contiguous bytes, rows cannot be
 //                            padded, so bank conflicts are avoided by an XOR swizzle of the
 //                            16-byte columns instead.
-//   gemm_nt_checked_kernel : everything else (ragged K, unaligned rows), register-staged, checked.
+//   gemm_nt_any_kernel     : ragged K, unaligned rows: 16-byte loads at any address, register-staged.
+//   gemm_nt_ksplit_kernel  : few result tiles, any alignment: the K slabs of a small tile are dealt to
+//                            the waves of its workgroup.
 //
 // Result element (i, j) is stored at (j / jp) * (I * jp) + i * jp + (j % jp): jp = J gives the
 // plain row-major ((I, J), ()) result; jp = H'*W' with j = flattened (n, h', w') and i = o gives
@@ -89,112 +91,496 @@ __device__ inline TileBox tile_box(const GemmArgs& a, int64_t ti, int64_t tj) {
   return b;
 }
 
-// General (checked) load of one 16-byte chunk: zero beyond the row's K bytes, byte loads when the
-// rows are not 16-byte aligned.  Used by the edge/unaligned kernel only.
-template <bool VEC>
-__device__ inline i32x4 load_chunk_checked(const uint8_t* row_ptr, int64_t kb, int64_t Kb,
-                                           bool row_ok) {
-  i32x4 v = {0, 0, 0, 0};
-  if (!row_ok || kb >= Kb) return v;
-  const int64_t nvalid = Kb - kb;
-  if (VEC && nvalid >= 16) return *reinterpret_cast<const i32x4*>(row_ptr + kb);
-  uint32_t w[4] = {0, 0, 0, 0};
-  for (int t = 0; t < 16; ++t)
-    if (t < nvalid) w[t >> 2] |= uint32_t(row_ptr[kb + t]) << (8 * (t & 3));
-  v[0] = int32_t(w[0]); v[1] = int32_t(w[1]); v[2] = int32_t(w[2]); v[3] = int32_t(w[3]);
-  return v;
+// 16 bytes at any address: the memory pipeline takes any alignment.
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// Result write-back of one wave: acc[m][n] holds the 32x32 blocks of rows iw .. and columns jw ..
+// (a lane holds column lane % 32, rows 8*(v/4) + 4*(lane/32) + v%4 of a block).
+//
+// Vector form (a.vj = 8 or 4 consecutive columns j are contiguous and aligned in the result): the
+// wave stages one 32-row block of its results in `stage` (32 rows of WN * 4 + 16 bytes of LDS that
+// nobody else touches) as 32-bit values and writes it back a.vj columns per lane, so a store
+// instruction carries 16 (or 8) bytes per lane instead of one element.
+//
+// Row form (a.vj = 2: a plain row-major result of any row length and alignment): the same with
+// eight columns per lane wherever they lie; the group that the end of the result cuts is written
+// value by value.  Stores aligned to the element only are cheap here (rows of 1531 bfloat16: 12.7 us
+// for the product against 15.6 with groups moved to aligned addresses and 17.8 value by value).
+template <typename TR, int MI, int NJ>
+__device__ __forceinline__ void write_tile(const GemmArgs& a, const TileBox& box, typename TR::accv_t (&acc)[MI][NJ],
+                                           int64_t iw, int64_t jw, uint8_t* stage, int lane) {
+  constexpr int WN = NJ * 32;
+  // Results larger than the last-level cache are streamed past L2.
+  const bool stream_out = a.I * a.J * 4 > (int64_t(128) << 20);
+
+  if (a.vj >= 2) {
+    constexpr int RS = WN * 4 + 16;                 // staging row stride in bytes
+    const bool has_res = a.residual != nullptr;
+    auto write_back = [&](auto vj_, auto kind_, auto ragged_) {
+      constexpr bool RAGGED = decltype(ragged_)::value;
+      using v4 = std::conditional_t<RAGGED, i32x4_any, i32x4>;
+      constexpr int VJ = decltype(vj_)::value;       // columns per lane
+      constexpr int kind = decltype(kind_)::value;   // 0: int32, 1: f32, 2: bf16
+      constexpr int NV = VJ / 4;                     // 16-byte pieces of 32-bit values per lane
+      constexpr int LPR = WN / VJ, RPP = 64 / LPR, NP = 32 / RPP;   // lanes per row, rows per pass, passes
+      const int cq = lane % LPR, rsub = lane / LPR;
+      const int64_t jg = jw + cq * VJ;
+      const bool j_ok = jg < box.jlim;
+      const int64_t jq = j_ok ? jg : 0;
+      const int64_t jbase = (jq / a.jp) * (a.I * a.jp) + (jq % a.jp);
+      static_for<MI>([&](auto m_) {
+        constexpr int m = decltype(m_)::value;
+        static_for<NJ>([&](auto n_) {
+          constexpr int n = decltype(n_)::value;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            *reinterpret_cast<typename TR::acc_t*>(stage + r * RS + (n * 32 + (lane & 31)) * 4) = acc[m][n][v];
+          }
+        });
+        i32x4 raw[NP][NV];
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+          for (int q = 0; q < NV; ++q)
+            raw[p][q] = *reinterpret_cast<const i32x4*>(stage + (p * RPP + rsub) * RS + cq * VJ * 4 + q * 16);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const int64_t i = iw + m * 32 + p * RPP + rsub;
+          const bool ok = j_ok && i < box.ilim;
+          const int64_t addr = ok ? jbase + i * a.jp : 0;
+          if (RAGGED && jg + VJ > box.jlim) {
+            if (ok)
+#pragma unroll
+              for (int e = 0; e < VJ; ++e)
+                if (jg + e < box.jlim)
+                  store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, addr + e,
+                                                   __builtin_bit_cast(typename TR::acc_t, int32_t(raw[p][e >> 2][e & 3])), a.relu);
+            continue;
+          }
+          if constexpr (kind == 2) {
+            float f[VJ];
+#pragma unroll
+            for (int e = 0; e < VJ; ++e) f[e] = __int_as_float(raw[p][e >> 2][e & 3]);
+            if (has_res) {
+              uint32_t rq[VJ / 2];
+              if constexpr (VJ == 8) {
+                const i32x4 t = *reinterpret_cast<const v4*>(static_cast<const uint16_t*>(a.residual) + addr);
+                rq[0] = t[0]; rq[1] = t[1]; rq[2] = t[2]; rq[3] = t[3];
+              } else {
+                const i32x2 t = *reinterpret_cast<const i32x2*>(static_cast<const uint16_t*>(a.residual) + addr);
+                rq[0] = t[0]; rq[1] = t[1];
+              }
+#pragma unroll
+              for (int e = 0; e < VJ / 2; ++e) {
+                f[2 * e] += __uint_as_float(rq[e] << 16);
+                f[2 * e + 1] += __uint_as_float(rq[e] & 0xffff0000u);
+              }
+            }
+            uint32_t w[VJ / 2];
+#pragma unroll
+            for (int e = 0; e < VJ / 2; ++e) {
+              const float lo = a.relu ? fmaxf(f[2 * e], 0.0f) : f[2 * e];
+              const float hi = a.relu ? fmaxf(f[2 * e + 1], 0.0f) : f[2 * e + 1];
+              w[e] = pack_bf16x2(lo, hi);
+            }
+            if (ok) {
+              uint16_t* dst = static_cast<uint16_t*>(a.out) + addr;
+              if constexpr (VJ == 8) {
+                const v4 w4 = {int(w[0]), int(w[1]), int(w[2]), int(w[3])};
+                if (stream_out) __builtin_nontemporal_store(w4, reinterpret_cast<v4*>(dst));
+                else *reinterpret_cast<v4*>(dst) = w4;
+              } else {
+                const i32x2 w2 = {int(w[0]), int(w[1])};
+                if (stream_out) __builtin_nontemporal_store(w2, reinterpret_cast<i32x2*>(dst));
+                else *reinterpret_cast<i32x2*>(dst) = w2;
+              }
+            }
+          } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) {
+              v4 r4 = raw[p][q];
+              if (has_res) {
+                const v4 t = *reinterpret_cast<const v4*>(static_cast<const int32_t*>(a.residual) + addr + q * 4);
+                if constexpr (kind == 0) {
+                  r4 += t;
+                } else {
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) r4[e] = __float_as_int(__int_as_float(r4[e]) + __int_as_float(t[e]));
+                }
+              }
+              if (a.relu) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  if constexpr (kind == 0) r4[e] = r4[e] > 0 ? r4[e] : 0;
+                  else r4[e] = __float_as_int(fmaxf(__int_as_float(r4[e]), 0.0f));
+                }
+              }
+              if (ok) {
+                v4* dst = reinterpret_cast<v4*>(static_cast<int32_t*>(a.out) + addr + q * 4);
+                if (stream_out) __builtin_nontemporal_store(r4, dst);
+                else *dst = r4;
+              }
+            }
+          }
+        }
+      });
+    };
+    using c8 = std::integral_constant<int, 8>;
+    using c4 = std::integral_constant<int, 4>;
+    auto by_width = [&](auto kind_) {
+      if (a.vj == 8) write_back(c8{}, kind_, std::false_type{});
+      else if (a.vj == 4) write_back(c4{}, kind_, std::false_type{});
+      else write_back(c8{}, kind_, std::true_type{});
+    };
+    if constexpr (__is_same(typename TR::acc_t, int32_t)) by_width(std::integral_constant<int, 0>{});
+    else if (a.out_dtype == GS_BF16) by_width(std::integral_constant<int, 2>{});
+    else by_width(std::integral_constant<int, 1>{});
+    return;
+  }
+  static_for<NJ>([&](auto n_) {
+    constexpr int n = decltype(n_)::value;
+    const int64_t j = jw + n * 32 + (lane & 31);
+    const bool j_ok = j < box.jlim;
+    const int64_t jbase = (j / a.jp) * (a.I * a.jp) + (j % a.jp);
+    static_for<MI>([&](auto m_) {
+      constexpr int m = decltype(m_)::value;
+      const int64_t ibase = iw + m * 32 + 4 * (lane >> 5);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t i = ibase + 8 * (v >> 2) + (v & 3);
+        if (j_ok && i < box.ilim)
+          store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, jbase + i * a.jp,
+                                           acc[m][n][v], a.relu, stream_out);
+      }
+    });
+  });
 }
 
 // ---------------------------------------------------------------------------------------------
-// Checked kernel: any K, any alignment.  64x64 tile, 4 waves of 32x32, register-staged slabs.
+// Rows at any byte address: 16-byte pieces are loaded where they lie and pass through registers, so that LDS rows can be aligned and padded.
 // ---------------------------------------------------------------------------------------------
-template <typename TR, bool VEC>
-__global__ void __launch_bounds__(256) gemm_nt_checked_kernel(GemmArgs a) {
-  constexpr int BM = 64, BN = 64;
-  constexpr int XCH = BM * 8 / 256, YCH = BN * 8 / 256;   // 16-byte chunks per thread per slab
-  constexpr int kXBytes = BM * kRowBytes, kYBytes = BN * kRowBytes;
-  constexpr int kBuf = kXBytes + kYBytes;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kBuf];
+// The 16 bytes of a row that start at byte kb, zero beyond the row's Kb bytes, without touching a
+// byte outside the row: rows of at least 16 bytes are read at min(kb, Kb - 16) and the bytes moved
+// down afterwards (row_piece_fix), which only the last slab of a row needs.
+__device__ __forceinline__ i32x4 row_piece_fix(i32x4 v, int64_t over) {
+  if (over <= 0) return v;
+  uint64_t lo = uint32_t(v[0]) | (uint64_t(uint32_t(v[1])) << 32), hi = uint32_t(v[2]) | (uint64_t(uint32_t(v[3])) << 32);
+  if (over >= 16) {
+    lo = hi = 0;
+  } else if (over >= 8) {
+    lo = hi >> (8 * (over - 8));
+    hi = 0;
+  } else {
+    lo = (lo >> (8 * over)) | (hi << (64 - 8 * over));
+    hi >>= 8 * over;
+  }
+  return i32x4{int32_t(uint32_t(lo)), int32_t(uint32_t(lo >> 32)), int32_t(uint32_t(hi)), int32_t(uint32_t(hi >> 32))};
+}
+// Rows shorter than 16 bytes: every byte requested at once, the ones past the end replaced by zero.
+__device__ __forceinline__ i32x4 short_row_piece(const uint8_t* row, int64_t kb, int64_t Kb) {
+  uint32_t byte[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) byte[t] = row[t < Kb ? t : 0];
+  uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < 16; ++t) w[t >> 2] |= (kb + t < Kb ? byte[t] : 0u) << (8 * (t & 3));
+  return i32x4{int32_t(w[0]), int32_t(w[1]), int32_t(w[2]), int32_t(w[3])};
+}
+
+// Any alignment, any K of at least 16 bytes.  Slabs of 128 bytes of K go global -> registers -> LDS;
+// two slabs are in flight in registers while one is multiplied and the next sits in the other LDS
+// buffer.  Bound by LDS traffic (a slab of a 128x128 tile is written once, 436 cycles at 75 bytes per
+// cycle, and read as 98 KB of fragments, 610 at 160, against 256-512 of MFMAs).  2047 x 1531 x 1001:
+// e4m3 85 -> 13.8 us, bf16 18.7, int8 15.6 (before: 16-byte pieces gathered byte by byte).
+template <typename TR, int BM, int BN, int WGM, int WGN>
+__global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a) {
+  constexpr int NT = WGM * WGN * 64, D = 2;
+  constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
+  constexpr int XCH = BM * 8 / NT, YCH = BN * 8 / NT;   // 16-byte pieces per thread per slab
+  static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "whole pieces");
+  constexpr int kXBytes = BM * kRowBytes, kYBytes = BN * kRowBytes, kBuf = kXBytes + kYBytes;
+  static_assert(WGM * WGN * 32 * (WN * 4 + 16) <= 2 * kBuf, "write-back staging must fit in the slab buffers");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int64_t tiles_j = tile_count(a.J, a.bn, BN);
-  const TileBox box = tile_box<BM, BN>(a, blockIdx.x / tiles_j, blockIdx.x % tiles_j);
+  const int wm = wave / WGN, wn = wave % WGN;
+  int64_t ti, tj;
+  tile_of_block(blockIdx.x, gridDim.x, tile_count(a.I, a.bm, BM), tile_count(a.J, a.bn, BN), &ti, &tj);
+  const TileBox box = tile_box<BM, BN>(a, ti, tj);
   const int64_t i0 = box.i0, j0 = box.j0;
   if (i0 >= box.ilim || j0 >= box.jlim) return;          // past the end of a smaller last block
   const int64_t Kb = a.K * TR::kEsz;
-  const uint8_t* X = static_cast<const uint8_t*>(a.x);
-  const uint8_t* Y = static_cast<const uint8_t*>(a.y);
-  const int64_t ldxb = a.ldx * TR::kEsz, ldyb = a.ldy * TR::kEsz;
   const int nslab = int(ceil_div(Kb, kSlabBytes));
+  const int kc = (tid & 7) * 16;                         // NT % 8 == 0: the same column for every piece
+  // rows past the end of an operand are clamped: their products are never stored
+  const uint8_t *xp[XCH], *yp[YCH];
+#pragma unroll
+  for (int r = 0; r < XCH; ++r) {
+    const int64_t i = i0 + ((tid + NT * r) >> 3);
+    xp[r] = static_cast<const uint8_t*>(a.x) + (i < box.ilim ? i : box.ilim - 1) * a.ldx * TR::kEsz;
+  }
+#pragma unroll
+  for (int r = 0; r < YCH; ++r) {
+    const int64_t j = j0 + ((tid + NT * r) >> 3);
+    yp[r] = static_cast<const uint8_t*>(a.y) + (j < box.jlim ? j : box.jlim - 1) * a.ldy * TR::kEsz;
+  }
+
+  typename TR::accv_t acc[MI][NJ];
+  static_for<MI>([&](auto m_) {
+    static_for<NJ>([&](auto n_) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[decltype(m_)::value][decltype(n_)::value][v] = 0;
+    });
+  });
+
+  i32x4 piece[D][XCH + YCH];
+  auto load = [&](int slab, auto slot_) {
+    constexpr int slot = decltype(slot_)::value;
+    const int64_t kb = int64_t(slab < nslab ? slab : nslab - 1) * kSlabBytes + kc;
+    const int64_t at = kb < Kb - 16 ? kb : Kb - 16;
+#pragma unroll
+    for (int r = 0; r < XCH; ++r) piece[slot][r] = *reinterpret_cast<const i32x4_any*>(xp[r] + at);
+#pragma unroll
+    for (int r = 0; r < YCH; ++r) piece[slot][XCH + r] = *reinterpret_cast<const i32x4_any*>(yp[r] + at);
+  };
+  uint8_t* const mine = lds + (tid >> 3) * kRowBytes + kc;
+  auto store = [&](int slab, auto slot_, int buf) {
+    constexpr int slot = decltype(slot_)::value;
+    if (slab == nslab - 1) {                             // uniform: the end of the rows
+      const int64_t over = int64_t(slab) * kSlabBytes + kc - (Kb - 16);
+#pragma unroll
+      for (int r = 0; r < XCH + YCH; ++r) piece[slot][r] = row_piece_fix(piece[slot][r], over);
+    }
+    uint8_t* dst = mine + buf * kBuf;
+#pragma unroll
+    for (int r = 0; r < XCH; ++r) *reinterpret_cast<i32x4*>(dst + r * (NT / 8) * kRowBytes) = piece[slot][r];
+#pragma unroll
+    for (int r = 0; r < YCH; ++r)
+      *reinterpret_cast<i32x4*>(dst + kXBytes + r * (NT / 8) * kRowBytes) = piece[slot][XCH + r];
+  };
+  constexpr int KST = TR::kStep, P = KST / 32;           // bytes of K per MFMA step; 16-byte pieces per lane
+  const uint8_t* const frag = lds + (lane & 31) * kRowBytes + (lane >> 5) * (KST / 2);
+  auto multiply = [&](int buf) {
+    const uint8_t* xs = frag + buf * kBuf + wm * WM * kRowBytes;
+    const uint8_t* ys = frag + buf * kBuf + kXBytes + wn * WN * kRowBytes;
+#pragma unroll
+    for (int ks = 0; ks < kSlabBytes / KST; ++ks) {
+      i32x4 xf[MI * P], yf[NJ * P];
+#pragma unroll
+      for (int m = 0; m < MI; ++m)
+#pragma unroll
+        for (int f = 0; f < P; ++f)
+          xf[m * P + f] = *reinterpret_cast<const i32x4*>(xs + m * 32 * kRowBytes + ks * KST + f * 16);
+#pragma unroll
+      for (int n = 0; n < NJ; ++n)
+#pragma unroll
+        for (int f = 0; f < P; ++f)
+          yf[n * P + f] = *reinterpret_cast<const i32x4*>(ys + n * 32 * kRowBytes + ks * KST + f * 16);
+#pragma unroll
+      for (int m = 0; m < MI; ++m)
+#pragma unroll
+        for (int n = 0; n < NJ; ++n) acc[m][n] = mfma_pieces<TR>(&xf[m * P], &yf[n * P], acc[m][n]);
+    }
+  };
+
+  static_for<D>([&](auto d_) { load(decltype(d_)::value, d_); });
+  store(0, std::integral_constant<int, 0>{}, 0);
+  load(D, std::integral_constant<int, 0>{});
+  lds_barrier();
+  for (int s0 = 0; s0 < nslab; s0 += D) {
+    static_for<D>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      using Next = std::integral_constant<int, (i + 1) % D>;
+      const int s = s0 + i;
+      if (s < nslab) {                                   // uniform
+        if (s + 1 < nslab) {
+          store(s + 1, Next{}, (i + 1) & 1);
+          load(s + 1 + D, Next{});
+        }
+        multiply(i & 1);
+        lds_barrier();
+      }
+    });
+  }
+  write_tile<TR, MI, NJ>(a, box, acc, i0 + wm * WM, j0 + wn * WN, lds + wave * (32 * (WN * 4 + 16)), lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Few tiles: 32x32 result tiles whose K slabs are dealt to the NW waves of a workgroup.  A wave
+// moves and multiplies its own slabs in LDS of its own, two at a time, without any barrier; the
+// NW partial tiles are added pairwise at the end.  Bound by one memory latency, the launch and
+// the final exchange: with up to 2 NW slabs all of K is requested at once.  kDirect: aligned rows of whole MFMA steps,
+// transferred global -> LDS; kStaged: any alignment, through registers; kShortRows: rows of fewer
+// than 16 bytes (empty ones included).
+// ---------------------------------------------------------------------------------------------
+enum KsplitLoad { kDirect, kStaged, kShortRows };   // see gemm_nt_ksplit_kernel
+template <typename TR, int NW, KsplitLoad LOAD>
+__global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
+  constexpr int KST = TR::kStep, P = KST / 32, KS = kSlabBytes / KST;
+  constexpr int kOp = 32 * kSlabBytes;                   // bytes of one operand's slab
+  constexpr int kWaveBytes = 4 * kOp;                         // two slabs of both operands
+  constexpr int RS = 160;                                // row stride of a partial tile: both half-waves on other banks
+  static_assert(32 * RS <= kWaveBytes, "a partial tile takes the place of its wave's slabs");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t tiles_j = tile_count(a.J, a.bn, 32);
+  const TileBox box = tile_box<32, 32>(a, blockIdx.x / tiles_j, blockIdx.x % tiles_j);
+  const int64_t i0 = uniform64(box.i0), j0 = uniform64(box.j0);
+  if (i0 >= box.ilim || j0 >= box.jlim) return;          // past the end of a smaller last block
+  const int64_t Kb = a.K * TR::kEsz, ldxb = a.ldx * TR::kEsz, ldyb = a.ldy * TR::kEsz;
+  const int nslab = int(ceil_div(Kb, kSlabBytes));
+  const int cnt = nslab > wave ? (nslab - wave + NW - 1) / NW : 0;   // slabs wave, wave + NW, ...
+
+  // Piece q of a slab: row q * 8 + lane / 8; LDS rows of 128 bytes, 16-byte column c of row r at
+  // column c ^ ((r / 2) % 8) (conflict-free fragment reads).
+  const int col = lane & 7;
+  const uint8_t *xp[4], *yp[4];
+  int swz[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = q * 8 + (lane >> 3);
+    swz[q] = ((r / 2) & 7) ^ col;
+    const int64_t i = i0 + r < box.ilim ? i0 + r : box.ilim - 1, j = j0 + r < box.jlim ? j0 + r : box.jlim - 1;
+    xp[q] = static_cast<const uint8_t*>(a.x) + i * ldxb;
+    yp[q] = static_cast<const uint8_t*>(a.y) + j * ldyb;
+  }
+  uint8_t* const mine = lds + wave * kWaveBytes;
+  const uint32_t mine_addr = lds_addr_of(lds) + wave * kWaveBytes;
+
+  i32x4 piece[2][8];
+  auto issue = [&](int t, auto slot_) {                  // slab number t of this wave
+    constexpr int slot = decltype(slot_)::value;
+    const int64_t k0 = int64_t(wave + t * NW) * kSlabBytes;
+    if constexpr (LOAD == kDirect) {
+      // a transfer lands at lane * 16: the lane fetches the column that belongs there; columns past
+      // the end of a row are not multiplied and re-read column 0
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t at = k0 + (k0 + swz[q] * 16 < Kb ? swz[q] * 16 : 0);
+        lds_dma16(xp[q] + at, mine_addr + slot * 2 * kOp + q * 1024);
+        lds_dma16(yp[q] + at, mine_addr + slot * 2 * kOp + kOp + q * 1024);
+      }
+    } else {
+      const int64_t kb = k0 + col * 16;
+      if constexpr (LOAD == kStaged) {
+        const int64_t at = kb < Kb - 16 ? kb : Kb - 16;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          piece[slot][q] = *reinterpret_cast<const i32x4_any*>(xp[q] + at);
+          piece[slot][4 + q] = *reinterpret_cast<const i32x4_any*>(yp[q] + at);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          piece[slot][q] = short_row_piece(xp[q], kb, Kb);
+          piece[slot][4 + q] = short_row_piece(yp[q], kb, Kb);
+        }
+      }
+    }
+  };
 
   typename TR::accv_t acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0;
-
-  i32x4 xr[XCH], yr[YCH];
-  auto load_slab = [&](int slab) {
-    const int64_t k0 = int64_t(slab) * kSlabBytes;
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  if (cnt > 0) issue(0, S0{});
+  if (cnt > 1) issue(1, S1{});
+  asm volatile("" ::"s"(a.relu), "s"(a.vj), "s"(a.jp), "s"(a.residual), "s"(a.out), "s"(a.out_dtype));
+  for (int t0 = 0; t0 < cnt; t0 += 2) {
+    static_for<2>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      const int t = t0 + i;
+      if (t < cnt) {                                     // uniform
+        const int slab = wave + t * NW;
+        if constexpr (LOAD == kDirect) {
+          if (t + 1 < cnt) wait_vmem<8>();               // the next slab's transfers stay in flight
+          else wait_vmem<0>();
+        } else {
+          if (LOAD == kStaged && slab == nslab - 1) {
+            const int64_t over = int64_t(slab) * kSlabBytes + col * 16 - (Kb - 16);
 #pragma unroll
-    for (int r = 0; r < XCH; ++r) {
-      const int c = tid + 256 * r, row = c >> 3, kc = c & 7;
-      xr[r] = load_chunk_checked<VEC>(X + (i0 + row) * ldxb, k0 + kc * 16, Kb, i0 + row < box.ilim);
-    }
+            for (int q = 0; q < 8; ++q) piece[i][q] = row_piece_fix(piece[i][q], over);
+          }
 #pragma unroll
-    for (int r = 0; r < YCH; ++r) {
-      const int c = tid + 256 * r, row = c >> 3, kc = c & 7;
-      yr[r] = load_chunk_checked<VEC>(Y + (j0 + row) * ldyb, k0 + kc * 16, Kb, j0 + row < box.jlim);
-    }
-  };
-  auto store_slab = [&](int buf) {
-    uint8_t* xs = lds + buf * kBuf;
-    uint8_t* ys = xs + kXBytes;
+          for (int q = 0; q < 4; ++q) {
+            uint8_t* dst = mine + i * 2 * kOp + (q * 8 + (lane >> 3)) * kSlabBytes + swz[q] * 16;
+            *reinterpret_cast<i32x4*>(dst) = piece[i][q];
+            *reinterpret_cast<i32x4*>(dst + kOp) = piece[i][4 + q];
+          }
+        }
+        // K steps of this slab: the transferred form multiplies whole steps only, the staged form is zero past K
+        const int64_t left = Kb - int64_t(slab) * kSlabBytes;
+        const int steps = left >= kSlabBytes ? KS : int((left + KST - 1) / KST);
+        const uint8_t* xs = mine + i * 2 * kOp + (lane & 31) * kSlabBytes;
+        i32x4 xf[KS * P], yf[KS * P];
 #pragma unroll
-    for (int r = 0; r < XCH; ++r) {
-      const int c = tid + 256 * r;
-      *reinterpret_cast<i32x4*>(xs + (c >> 3) * kRowBytes + (c & 7) * 16) = xr[r];
-    }
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int r = 0; r < YCH; ++r) {
-      const int c = tid + 256 * r;
-      *reinterpret_cast<i32x4*>(ys + (c >> 3) * kRowBytes + (c & 7) * 16) = yr[r];
-    }
-  };
-
-  load_slab(0);
-  store_slab(0);
-  __syncthreads();
-  constexpr int KST = TR::kStep, P = KST / 32;    // bytes of K per MFMA step; 16-byte pieces per lane
-  const int frag_off = (lane & 31) * kRowBytes + (lane >> 5) * (KST / 2);
-  for (int slab = 0; slab < nslab; ++slab) {
-    if (slab + 1 < nslab) load_slab(slab + 1);
-    const uint8_t* xs = lds + (slab & 1) * kBuf + wm * 32 * kRowBytes + frag_off;
-    const uint8_t* ys = lds + (slab & 1) * kBuf + kXBytes + wn * 32 * kRowBytes + frag_off;
+          for (int f = 0; f < P; ++f) {
+            const int at = ((P * (2 * ks + (lane >> 5)) + f) ^ (((lane & 31) / 2) & 7)) << 4;
+            xf[ks * P + f] = *reinterpret_cast<const i32x4*>(xs + at);
+            yf[ks * P + f] = *reinterpret_cast<const i32x4*>(xs + kOp + at);
+          }
 #pragma unroll
-    for (int ks = 0; ks < kSlabBytes / KST; ++ks) {
-      i32x4 xf[P], yf[P];
-#pragma unroll
-      for (int f = 0; f < P; ++f) {
-        xf[f] = *reinterpret_cast<const i32x4*>(xs + ks * KST + f * 16);
-        yf[f] = *reinterpret_cast<const i32x4*>(ys + ks * KST + f * 16);
+        for (int ks = 0; ks < KS; ++ks)
+          if (ks < steps) acc = mfma_pieces<TR>(&xf[ks * P], &yf[ks * P], acc);
+        if (t + 2 < cnt) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // all fragments of this buffer have been read
+          issue(t + 2, i_);
+        }
       }
-      acc = mfma_pieces<TR>(xf, yf, acc);
-    }
-    if (slab + 1 < nslab) store_slab((slab + 1) & 1);
-    __syncthreads();
+    });
   }
-
-  const int64_t j = j0 + wn * 32 + (lane & 31);
-  if (j < box.jlim) {
-    const int64_t jbase = (j / a.jp) * (a.I * a.jp) + (j % a.jp);
+  // Partial tiles, each in its wave's own LDS; 256 threads add four neighbouring columns each.
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  typedef typename TR::acc_t acc4_t __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t i = i0 + wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      if (i < box.ilim)
-        store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, jbase + i * a.jp, acc[v],
-                                         a.relu);
+  for (int v = 0; v < 16; ++v)
+    *reinterpret_cast<typename TR::acc_t*>(mine + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * RS + (lane & 31) * 4) = acc[v];
+  __syncthreads();
+  if (tid >= 256) return;
+  const uint8_t* part = lds + (tid >> 3) * RS + (tid & 7) * 16;
+  acc4_t t[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) t[w] = *reinterpret_cast<const acc4_t*>(part + w * kWaveBytes);
+#pragma unroll
+  for (int step = 1; step < NW; step *= 2)               // pairwise: fewer roundings than a chain
+#pragma unroll
+    for (int w = 0; w < NW; w += 2 * step) t[w] += t[w + step];
+  acc4_t sum = t[0];
+  const int64_t i = i0 + (tid >> 3), j = j0 + (tid & 7) * 4;
+  if (i >= box.ilim || j >= box.jlim) return;
+  if (a.vj >= 4) {
+    const int64_t addr = j / a.jp * (a.I * a.jp) + i * a.jp + j % a.jp;
+    if constexpr (__is_same(typename TR::acc_t, float)) {
+      if (a.out_dtype == GS_BF16) {
+        if (a.residual) {
+          const uint2 t = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(a.residual) + addr);
+          sum += acc4_t{__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16),
+                        __uint_as_float(t.y & 0xffff0000u)};
+        }
+        if (a.relu)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[e] = fmaxf(sum[e], 0.0f);
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + addr) = uint2{pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3])};
+        return;
+      }
     }
+    if (a.residual) sum += *reinterpret_cast<const acc4_t*>(static_cast<const typename TR::acc_t*>(a.residual) + addr);
+    if (a.relu)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] = sum[e] > 0 ? sum[e] : 0;
+    *reinterpret_cast<acc4_t*>(static_cast<typename TR::acc_t*>(a.out) + addr) = sum;
+    return;
   }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (j + e < box.jlim)
+      store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, (j + e) / a.jp * (a.I * a.jp) + i * a.jp + (j + e) % a.jp,
+                                       sum[e], a.relu);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -415,181 +801,77 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_dma_kernel(GemmArgs a)
   });
   __syncthreads();   // every wave is done with the slabs: their memory becomes epilogue staging
 
-  // Epilogue: lane holds column (lane % 32), rows 8*(v/4) + 4*(lane/32) + v%4 of each block.
-  // Results larger than the last-level cache are streamed past L2.
-  const bool stream_out = a.I * a.J * 4 > (int64_t(128) << 20);
-
-  // Vector write-back (a.vj = 8 or 4 consecutive columns j are contiguous and aligned in the
-  // result): each wave stages one 32-row block of its results in the slab memory, which no wave
-  // reads any more, as 32-bit values and writes it back a.vj columns per lane, so a store
-  // instruction carries 16 (or 8) bytes per lane instead of one element.
-  if (a.vj > 1) {
-    constexpr int RS = WN * 4 + 16;                 // staging row stride in bytes
-    static_assert(NW * 32 * RS <= NS * (kXBytes + kYBytes), "staging must fit in the slab buffers");
-    uint8_t* stage = lds + wave * (32 * RS);
-    const bool has_res = a.residual != nullptr;
-    auto write_back = [&](auto vj_, auto kind_) {
-      constexpr int VJ = decltype(vj_)::value;       // columns per lane
-      constexpr int kind = decltype(kind_)::value;   // 0: int32, 1: f32, 2: bf16
-      constexpr int NV = VJ / 4;                     // 16-byte pieces of 32-bit values per lane
-      constexpr int LPR = WN / VJ, RPP = 64 / LPR, NP = 32 / RPP;   // lanes per row, rows per pass, passes
-      const int cq = lane % LPR, rsub = lane / LPR;
-      const int64_t jg = j0 + wn * WN + cq * VJ;
-      const bool j_ok = jg < box.jlim;
-      const int64_t jq = j_ok ? jg : 0;
-      const int64_t jbase = (jq / a.jp) * (a.I * a.jp) + (jq % a.jp);
-      static_for<MI>([&](auto m_) {
-        constexpr int m = decltype(m_)::value;
-        static_for<NJ>([&](auto n_) {
-          constexpr int n = decltype(n_)::value;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            *reinterpret_cast<typename TR::acc_t*>(stage + r * RS + (n * 32 + (lane & 31)) * 4) = acc[m][n][v];
-          }
-        });
-        i32x4 raw[NP][NV];
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-          for (int q = 0; q < NV; ++q)
-            raw[p][q] = *reinterpret_cast<const i32x4*>(stage + (p * RPP + rsub) * RS + cq * VJ * 4 + q * 16);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          const int64_t i = i0 + wm * WM + m * 32 + p * RPP + rsub;
-          const bool ok = j_ok && i < box.ilim;
-          const int64_t addr = ok ? jbase + i * a.jp : 0;
-          if constexpr (kind == 2) {
-            float f[VJ];
-#pragma unroll
-            for (int e = 0; e < VJ; ++e) f[e] = __int_as_float(raw[p][e >> 2][e & 3]);
-            if (has_res) {
-              uint32_t rq[VJ / 2];
-              if constexpr (VJ == 8) {
-                const i32x4 t = *reinterpret_cast<const i32x4*>(static_cast<const uint16_t*>(a.residual) + addr);
-                rq[0] = t[0]; rq[1] = t[1]; rq[2] = t[2]; rq[3] = t[3];
-              } else {
-                const uint2 t = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(a.residual) + addr);
-                rq[0] = t.x; rq[1] = t.y;
-              }
-#pragma unroll
-              for (int e = 0; e < VJ / 2; ++e) {
-                f[2 * e] += __uint_as_float(rq[e] << 16);
-                f[2 * e + 1] += __uint_as_float(rq[e] & 0xffff0000u);
-              }
-            }
-            uint32_t w[VJ / 2];
-#pragma unroll
-            for (int e = 0; e < VJ / 2; ++e) {
-              const float lo = a.relu ? fmaxf(f[2 * e], 0.0f) : f[2 * e];
-              const float hi = a.relu ? fmaxf(f[2 * e + 1], 0.0f) : f[2 * e + 1];
-              w[e] = pack_bf16x2(lo, hi);
-            }
-            if (ok) {
-              uint16_t* dst = static_cast<uint16_t*>(a.out) + addr;
-              if constexpr (VJ == 8) {
-                const i32x4 w4 = {int(w[0]), int(w[1]), int(w[2]), int(w[3])};
-                if (stream_out) __builtin_nontemporal_store(w4, reinterpret_cast<i32x4*>(dst));
-                else *reinterpret_cast<i32x4*>(dst) = w4;
-              } else {
-                const i32x2 w2 = {int(w[0]), int(w[1])};
-                if (stream_out) __builtin_nontemporal_store(w2, reinterpret_cast<i32x2*>(dst));
-                else *reinterpret_cast<i32x2*>(dst) = w2;
-              }
-            }
-          } else {
-#pragma unroll
-            for (int q = 0; q < NV; ++q) {
-              i32x4 r4 = raw[p][q];
-              if (has_res) {
-                const i32x4 t = *reinterpret_cast<const i32x4*>(static_cast<const int32_t*>(a.residual) + addr + q * 4);
-                if constexpr (kind == 0) {
-                  r4 += t;
-                } else {
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) r4[e] = __float_as_int(__int_as_float(r4[e]) + __int_as_float(t[e]));
-                }
-              }
-              if (a.relu) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  if constexpr (kind == 0) r4[e] = r4[e] > 0 ? r4[e] : 0;
-                  else r4[e] = __float_as_int(fmaxf(__int_as_float(r4[e]), 0.0f));
-                }
-              }
-              if (ok) {
-                i32x4* dst = reinterpret_cast<i32x4*>(static_cast<int32_t*>(a.out) + addr + q * 4);
-                if (stream_out) __builtin_nontemporal_store(r4, dst);
-                else *dst = r4;
-              }
-            }
-          }
-        }
-      });
-    };
-    using c8 = std::integral_constant<int, 8>;
-    using c4 = std::integral_constant<int, 4>;
-    if constexpr (__is_same(typename TR::acc_t, int32_t)) {
-      if (a.vj == 8) write_back(c8{}, std::integral_constant<int, 0>{});
-      else write_back(c4{}, std::integral_constant<int, 0>{});
-    } else if (a.out_dtype == GS_BF16) {
-      if (a.vj == 8) write_back(c8{}, std::integral_constant<int, 2>{});
-      else write_back(c4{}, std::integral_constant<int, 2>{});
-    } else {
-      if (a.vj == 8) write_back(c8{}, std::integral_constant<int, 1>{});
-      else write_back(c4{}, std::integral_constant<int, 1>{});
-    }
-    return;
-  }
-  static_for<NJ>([&](auto n_) {
-    constexpr int n = decltype(n_)::value;
-    const int64_t j = j0 + wn * WN + n * 32 + (lane & 31);
-    const bool j_ok = j < box.jlim;
-    const int64_t jbase = (j / a.jp) * (a.I * a.jp) + (j % a.jp);
-    static_for<MI>([&](auto m_) {
-      constexpr int m = decltype(m_)::value;
-      const int64_t ibase = i0 + wm * WM + m * 32 + 4 * (lane >> 5);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t i = ibase + 8 * (v >> 2) + (v & 3);
-        if (j_ok && i < box.ilim)
-          store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, jbase + i * a.jp,
-                                           acc[m][n][v], a.relu, stream_out);
-      }
-    });
-  });
+  static_assert(NW * 32 * (WN * 4 + 16) <= NS * (kXBytes + kYBytes), "staging must fit in the slab buffers");
+  write_tile<TR, MI, NJ>(a, box, acc, i0 + wm * WM, j0 + wn * WN, lds + wave * (32 * (WN * 4 + 16)), lane);
 }
 
+// Launch with `lds_bytes` of dynamic LDS, one workgroup per tile.
+template <auto KERN>
+static hipError_t launch_tiles(const GemmArgs& a, int bm, int bn, int threads, int lds_bytes, hipStream_t s) {
+  static std::once_flag once;
+  static hipError_t attr_status = hipSuccess;
+  std::call_once(once, [&]() {
+    attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  });
+  if (attr_status != hipSuccess) return attr_status;
+  const int64_t tiles = tile_count(a.I, a.bm, bm) * tile_count(a.J, a.bn, bn);
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(KERN, dim3(unsigned(tiles)), dim3(threads), lds_bytes, s, a);
+  return hipGetLastError();
+}
 template <typename TR, int BM, int BN, int WGM, int WGN, int SB, int NS>
 static hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   constexpr int lds_bytes = NS * (BM + BN) * SB;
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
-  auto kern = gemm_nt_dma_kernel<TR, BM, BN, WGM, WGN, SB, NS>;
-  static std::once_flag once;
-  static hipError_t attr_status = hipSuccess;
-  std::call_once(once, [&]() {
-    attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-  });
-  if (attr_status != hipSuccess) return attr_status;
-  const int64_t tiles = tile_count(a.I, a.bm, BM) * tile_count(a.J, a.bn, BN);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(WGM * WGN * 64), lds_bytes, s, a);
-  return hipGetLastError();
+  return launch_tiles<gemm_nt_dma_kernel<TR, BM, BN, WGM, WGN, SB, NS>>(a, BM, BN, WGM * WGN * 64, lds_bytes, s);
+}
+template <typename TR, int BM, int BN, int WGM, int WGN>
+static hipError_t launch_any(const GemmArgs& a, hipStream_t s) {
+  return launch_tiles<gemm_nt_any_kernel<TR, BM, BN, WGM, WGN>>(a, BM, BN, WGM * WGN * 64, 2 * (BM + BN) * kRowBytes, s);
+}
+template <typename TR, int NW, KsplitLoad LOAD>
+static hipError_t launch_ksplit(const GemmArgs& a, hipStream_t s) {
+  return launch_tiles<gemm_nt_ksplit_kernel<TR, NW, LOAD>>(a, 32, 32, NW * 64, NW * 4 * 32 * kSlabBytes, s);
 }
 
-// Tile choice of the direct-to-LDS kernel.
+// Few tiles: what a workgroup of the 64x64 kernels waits for is one slab after the other, so up to
+// 512 tiles of 32x32 the K slabs are dealt to waves instead (256 x 512 x 784 bf16: 4.2 us against
+// 6.4 in 32 tiles of 64x64; 512 x 1024 x 1024: 6.3 against 7.2; with twice the tiles 10.6 against
+// 7.4).  Eight waves need the LDS of a compute unit for themselves and pay from the ninth slab on
+// (300 x 300 x 8192 int8: 9.2 against 9.6 us; 512 tiles of eight slabs: 8.5 against 6.3).
+template <typename TR>
+static bool few_tiles(const GemmArgs& a, bool* eight) {
+  const int64_t t32 = tile_count(a.I, a.bm, 32) * tile_count(a.J, a.bn, 32);
+  *eight = t32 <= 256 && a.K * TR::kEsz > 8 * kSlabBytes;
+  return t32 <= 512;
+}
+
+// Tile choice of the direct-to-LDS kernel (times in us, bf16 unless said otherwise).
 template <typename TR>
 static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
+  const int64_t t64 = tile_count(a.I, a.bm, 64) * tile_count(a.J, a.bn, 64);
   const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
   const int64_t t256 = tile_count(a.I, a.bm, 256) * tile_count(a.J, a.bn, 256);
   // extent a tile can fill: the block when the result is cut into blocks
   const int64_t fi = a.bm > 0 && a.bm < a.I ? a.bm : a.I, fj = a.bn > 0 && a.bn < a.J ? a.bn : a.J;
   if (t256 >= 256 && fi >= 256 && fj >= 256) return launch_dma<TR, 256, 256, 2, 4, 128, 2>(a, s);
-  // few rows (a convolution's output channels against many positions): tiles 64 rows tall
+  // few rows (a convolution's output channels against many positions) or few columns (the im2col
+  // listing: 100352 x 64 x 576 takes 32.2 against 36.2 in half-empty 128x128 tiles)
   if (a.I <= 64 && ceil_div(fj, 256) * ceil_div(a.J, fj) >= 192) return launch_dma<TR, 64, 256, 1, 4, 128, 2>(a, s);
-  if (t128 >= 192 && (a.bm <= 0 || fi >= 128) && (a.bn <= 0 || fj >= 128)) return launch_dma<TR, 128, 128, 2, 2, 128, 2>(a, s);
-  return launch_dma<TR, 64, 64, 2, 2, 128, 2>(a, s);
+  if (a.J <= 64 && ceil_div(fi, 256) * ceil_div(a.I, fi) >= 192) return launch_dma<TR, 256, 64, 4, 1, 128, 2>(a, s);
+  bool eight;
+  if (few_tiles<TR>(a, &eight))
+    return eight ? launch_ksplit<TR, 8, kDirect>(a, s) : launch_ksplit<TR, 4, kDirect>(a, s);
+  if (t128 >= 192 && (a.bm <= 0 || fi >= 128) && (a.bn <= 0 || fj >= 128)) {
+    // one tile per compute unit: a third slab buffer takes the place of the second workgroup
+    // (2048^3: 25.3 against 29.9; with 512 tiles 49.2 against 40.1)
+    if (t128 <= 256) return launch_dma<TR, 128, 128, 2, 2, 128, 3>(a, s);
+    return launch_dma<TR, 128, 128, 2, 2, 128, 2>(a, s);
+  }
+  // 1024^3: 10.9 with two slab buffers, 7.9 with three, 7.4 with four; 1024 x 2048 x 1024, two
+  // workgroups per compute unit: 11.4, 9.6, 9.9
+  if (t64 <= 256) return launch_dma<TR, 64, 64, 2, 2, 128, 4>(a, s);
+  return launch_dma<TR, 64, 64, 2, 2, 128, 3>(a, s);
 }
 
 template <typename TR>
@@ -600,32 +882,33 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   // whole MFMA steps, and 256 rows of either operand within reach of a 32-bit byte offset
   const bool dma = vec && a.K > 0 && (a.K * TR::kEsz) % TR::kStep == 0 && a.ldx * TR::kEsz < (int64_t(1) << 23) &&
                    a.ldy * TR::kEsz < (int64_t(1) << 23);
-  if (dma) {
-    // Columns per lane of the vector write-back: groups of vj columns must not straddle a jp
-    // boundary or the end of the result, and must be 16-byte (8-byte for 4 bfloat16) aligned.
-    GemmArgs v = a;
-    v.vj = 1;
-    const size_t osz = dtype_size(a.out_dtype);
-    for (int cand = 8; cand >= 4 && v.vj == 1; cand /= 2) {
-      const size_t al = cand * osz < 16 ? cand * osz : 16;
-      if (a.jp % cand == 0 && a.J % cand == 0 && a.bn % cand == 0 && reinterpret_cast<uintptr_t>(a.out) % al == 0 &&
-          reinterpret_cast<uintptr_t>(a.residual) % al == 0)
-        v.vj = cand;
-    }
-    return launch_dma_tiles<TR>(v, s);
+  // Columns per lane of the vector write-back: groups of vj columns must not straddle a jp
+  // boundary or the end of the result, and must be 16-byte (8-byte for 4 bfloat16) aligned.
+  GemmArgs v = a;
+  v.vj = 1;
+  const size_t osz = dtype_size(a.out_dtype);
+  for (int cand = 8; cand >= 4 && v.vj == 1; cand /= 2) {
+    const size_t al = cand * osz < 16 ? cand * osz : 16;
+    if (a.jp % cand == 0 && a.J % cand == 0 && a.bn % cand == 0 && reinterpret_cast<uintptr_t>(a.out) % al == 0 &&
+        reinterpret_cast<uintptr_t>(a.residual) % al == 0)
+      v.vj = cand;
   }
-  const int64_t tiles = tile_count(a.I, a.bm, 64) * tile_count(a.J, a.bn, 64);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  if (vec)
-    hipLaunchKernelGGL((gemm_nt_checked_kernel<TR, true>), dim3(unsigned(tiles)), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_nt_checked_kernel<TR, false>), dim3(unsigned(tiles)), dim3(256), 0, s, a);
-  return hipGetLastError();
+  if (v.vj == 1 && a.jp >= a.J) v.vj = 2;    // plain rows
+  if (a.K * TR::kEsz < 16) return launch_ksplit<TR, 4, kShortRows>(v, s);
+  if (dma) return launch_dma_tiles<TR>(v, s);
+  bool eight;
+  if (few_tiles<TR>(v, &eight))
+    return eight ? launch_ksplit<TR, 8, kStaged>(v, s) : launch_ksplit<TR, 4, kStaged>(v, s);
+  // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.8 us
+  // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6
+  const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
+  if (t128 >= 160) return launch_any<TR, 128, 128, 2, 4>(v, s);
+  return launch_any<TR, 64, 64, 2, 2>(v, s);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.I == 0 || a.J == 0) return hipSuccess;
-  if (ceil_div(a.I, 64) * ceil_div(a.J, 64) > 0x7fffffff) return hipErrorInvalidValue;
+  if (ceil_div(a.I, 32) * ceil_div(a.J, 32) > 0x7fffffff) return hipErrorInvalidValue;
   if (a.in_dtype == GS_I8) return launch_t<I8Traits>(a, s);
   if (a.in_dtype == GS_F8) return launch_t<Fp8Traits>(a, s);
   return launch_t<Bf16Traits>(a, s);

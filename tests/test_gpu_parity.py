@@ -141,6 +141,30 @@ def test_cartesian_dot(case):
     assert_parity(got, prog.materialize(), what=str(case), slack=slack)
 
 
+# Edges of the contraction's tile rules: rows of any byte alignment and length (fewer than 16 bytes, one
+# byte more than a 16-byte piece or a 128-byte slab), one tile, the last few-tile shape and the first
+# beyond it, 64x64 and 128x128 tiles of both loaders, results cut inside a group of eight columns.
+DOT_EDGE_CASES = [
+    # m, n, k
+    (1, 1, 1), (31, 33, 15), (33, 31, 16), (32, 32, 17), (65, 10, 129), (1, 75, 648), (512, 1023, 130),
+    (513, 1025, 257), (700, 1001, 385), (1281, 2047, 255), (2050, 40, 64), (544, 1024, 192), (1700, 2048, 128),
+    (49153, 40, 64), (96, 65, 1984),
+]
+
+
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32), ("fp8", torch.bfloat16)])
+@pytest.mark.parametrize("mnk", DOT_EDGE_CASES)
+def test_cartesian_dot_tile_edges(mnk, dtype, odt):
+    m, n, k = mnk
+    a0, a1 = gen(dtype, (m, k), 1400 + m, 1.0), gen(dtype, (n, k), 1500 + n, 1.0 if dtype == "i8" else k ** -0.5)
+    # the result sits between guard values: nothing outside it may be written
+    buf = torch.full((m * n + 512,), 77, dtype=odt, device=DEV)
+    got = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), out=buf[256:256 + m * n].view(m, n))
+    x, y = to_oracle(a0), to_oracle(a1)
+    assert_parity(got, brute.matmul(x, y.T), what=str(mnk), slack=fp8_slack(x, y) if dtype == "fp8" else None)
+    assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
+
+
 def test_cartesian_dot_extreme_int8_values():
     """-128 * -128 * K stays exact in int32."""
     a0 = torch.full((40, 512), -128, dtype=torch.int8)
