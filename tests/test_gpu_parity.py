@@ -539,6 +539,25 @@ def test_max_pool_fused_and_unfused(case):
     assert torch.equal(fused, unfused)
 
 
+# Planes pooled several to a workgroup: a last workgroup with fewer planes, runs that start off a 16-byte
+# boundary, planes just below and above the size of one workgroup's share, and few planes cut into bands.
+@pytest.mark.parametrize("dtype", ["bf16", "i8", "f32"])
+@pytest.mark.parametrize("shape,win,stride,pad", [((3, 5, 7, 7), 2, 2, 0), ((7, 3, 13, 11), 3, 2, 1), ((2, 3, 63, 65), 3, 1, 1),
+                                                  ((1, 3, 64, 64), 2, 2, 0), ((1, 2, 1, 1), 1, 1, 0), ((37, 9, 5, 3), 3, 3, 2),
+                                                  ((1, 5, 155, 157), 3, 2, 1), ((1, 7, 96, 112), 3, 2, 1)])
+def test_pool_of_whole_planes(shape, win, stride, pad, dtype):
+    x = gen(dtype, shape, 2300 + shape[2], 3.0)
+    for op, fill in ((gs.GS_MAX, -np.inf), (gs.GS_SUM, 0)):
+        got = gs.windows_reduce(x.to(DEV), 2, (win, win), (stride, stride), (pad, pad), (pad, pad), op)
+        cells = np.pad(to_oracle(x).astype(np.float64), ((0, 0), (0, 0), (pad, pad), (pad, pad)), constant_values=fill)
+        want = np.lib.stride_tricks.sliding_window_view(cells, (win, win), axis=(2, 3))[:, :, ::stride, ::stride]
+        want = want.max(axis=(4, 5)) if op == gs.GS_MAX else want.sum(axis=(4, 5))
+        if dtype == "i8":
+            np.testing.assert_array_equal(to_oracle(got), want.astype(np.int64))
+        else:
+            assert_parity(got, want, what=f"{shape} {op}")
+
+
 def test_sum_pool_and_1d_windows_reduce():
     x = gen("f32", (3, 40), 1950)
     got = gs.windows_reduce(x.to(DEV), 1, (5,), (3,), (2,), (2,), gs.GS_SUM, scale=0.2)
