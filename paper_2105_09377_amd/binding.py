@@ -1,9 +1,10 @@
-"""ctypes binding of `libglenside.so` (declared in include/glenside.h).
+"""Binding of `libglenside.so` (declared in include/glenside.h).
 
 Argument marshalling only: every function here builds `gs_ap` descriptors from torch tensors
 (device memory and the current stream come from torch), calls the C entry point of the same
-name, and raises `GlensideError` on a non-zero status.  No arithmetic happens in Python.  There is no
-fallback: if the library has not been built, loading fails with an error.
+name, and raises `GlensideError` on a non-zero status.  No arithmetic happens in Python.  The calls
+that networks repeat are marshalled by the extension module `_marshal` (csrc/marshal.cpp), the others
+through ctypes.  There is no fallback: if the libraries have not been built, loading fails with an error.
 """
 
 from __future__ import annotations
@@ -62,6 +63,7 @@ class GlensideError(RuntimeError):
 
 
 _lib = None
+_native = None      # the extension module, once the library is loaded
 
 
 def lib() -> ctypes.CDLL:
@@ -108,8 +110,25 @@ def lib() -> ctypes.CDLL:
         L.glenside_pair.argtypes = [ap_p, ap_p, ap_p, vp]
         L.glenside_cartesian_dot_blocked.argtypes = [ap_p, ap_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ap_p, vp]
         L.glenside_depthwise_conv2d.argtypes = [ap_p, ap_p, i64_p, i64_p, ctypes.c_int, ap_p, vp]
+        _bind_native(L)
         _lib = L
     return _lib
+
+
+def _bind_native(L: ctypes.CDLL) -> None:
+    global _native
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError("the extension module _marshal is missing: run `python -m paper_2105_09377_amd.build`") from e
+    _marshal.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS}, GlensideError)
+    _native = _marshal
+
+
+def _m():
+    if _native is None:
+        lib()
+    return _native
 
 
 def status_string(status: int) -> str:
@@ -168,51 +187,14 @@ def windows_out_shape(in_shape: Sequence[int], n_access: int, window, stride, pa
 def access_windows(x: torch.Tensor, n_access: int, window, stride, pad_lo=None, pad_hi=None,
                    pad_mode: int = GS_PAD_ZERO, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """`windows` over the compute dims of (access x n_access); returns a tensor of shape S_A ++ b' ++ w."""
-    shape, _ = windows_out_shape(x.shape, n_access, window, stride, pad_lo, pad_hi)
-    if out is None:
-        out = torch.empty(shape, dtype=x.dtype, device=x.device)
-    o = make_ap(out, n_access + len(window))
-    _check(lib().glenside_access_windows(ctypes.byref(make_ap(x, n_access)), _i64(window), _i64(stride),
-                                         _i64(pad_lo), _i64(pad_hi), pad_mode, ctypes.byref(o),
-                                         _stream(x)), "access_windows")
-    return out
+    return _m().access_windows(x, n_access, window, stride, pad_lo, pad_hi, pad_mode, out)
 
 
 def cartesian_dot(a0: torch.Tensor, a1: torch.Tensor, n_access0: int = 1, n_access1: int = 1,
                   out_dtype: Optional[torch.dtype] = None, act: int = GS_ACT_NONE,
                   out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """compute dotProd (cartProd (access a0 n0) (access a1 n1)) -> tensor of shape S_A(a0) ++ S_A(a1)."""
-    if out is None:
-        if out_dtype is None:
-            out_dtype = torch.int32 if a0.dtype == torch.int8 else torch.float32
-        out = torch.empty(tuple(a0.shape[:n_access0]) + tuple(a1.shape[:n_access1]), dtype=out_dtype,
-                          device=a0.device)
-    _check(lib().glenside_cartesian_dot(ctypes.byref(make_ap(a0, n_access0)),
-                                        ctypes.byref(make_ap(a1, n_access1)),
-                                        ctypes.byref(make_ap(out, out.dim())), act, None, 0,
-                                        _stream(a0)), "cartesian_dot")
-    return out
-
-
-def _conv(fn_name: str, ws_name: str, x, w, stride, pad, residual, act, out_dtype, out, workspace):
-    L = lib()
-    xa, wa = make_ap(x, 1), make_ap(w, 1)
-    st, pd = _i64(stride), _i64(pad)
-    need = getattr(L, ws_name)(ctypes.byref(xa), ctypes.byref(wa), st, pd)
-    if out is None:
-        if out_dtype is None:
-            out_dtype = torch.int32 if x.dtype == torch.int8 else torch.float32
-        # H', W' from the library's shape rule of `windows` (window (C,Kh,Kw), strides (1,Sh,Sw))
-        shape, _ = windows_out_shape(x.shape, 1, (x.shape[1], w.shape[2], w.shape[3]), (1, stride[0], stride[1]),
-                                     (0, pad[0], pad[1]), (0, pad[0], pad[1]))
-        out = torch.empty((x.shape[0], w.shape[0], shape[2], shape[3]), dtype=out_dtype, device=x.device)
-    if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
-    res = ctypes.byref(make_ap(residual, residual.dim())) if residual is not None else None
-    _check(getattr(L, fn_name)(ctypes.byref(xa), ctypes.byref(wa), st, pd, res, act,
-                               ctypes.byref(make_ap(out, 4)), workspace.data_ptr(),
-                               workspace.numel(), _stream(x)), fn_name)
-    return out
+    return _m().cartesian_dot(a0, a1, n_access0, n_access1, out_dtype, act, out)
 
 
 def conv2d_workspace(x: torch.Tensor, w: torch.Tensor, stride, pad, form: str = "direct",
@@ -227,21 +209,12 @@ def conv2d_workspace(x: torch.Tensor, w: torch.Tensor, stride, pad, form: str = 
 def conv2d_direct(x, w, stride=(1, 1), pad=(0, 0), residual=None, act=GS_ACT_NONE, out_dtype=None,
                   out=None, workspace=None) -> torch.Tensor:
     """Fig. 2a with the windows formed on chip; x (N,C,H,W), w (O,C,Kh,Kw) -> (N,O,H',W')."""
-    return _conv("glenside_conv2d_direct", "glenside_conv2d_direct_workspace", x, w, stride, pad,
-                 residual, act, out_dtype, out, workspace)
+    return _m().conv(0, x, w, stride, pad, residual, act, out_dtype, out, workspace)
 
 
 def depthwise_conv2d(x, w, stride=(1, 1), pad=(0, 0), act=GS_ACT_NONE, out_dtype=None, out=None) -> torch.Tensor:
     """Every channel convolved with its own filter: x (N,C,H,W), w (C,Kh,Kw) -> (N,C,H',W')."""
-    if out is None:
-        if out_dtype is None:
-            out_dtype = torch.int32 if x.dtype == torch.int8 else torch.float32
-        shape, _ = windows_out_shape(x.shape, 2, (w.shape[1], w.shape[2]), tuple(stride), tuple(pad), tuple(pad))
-        out = torch.empty(tuple(shape[:4]), dtype=out_dtype, device=x.device)
-    _check(lib().glenside_depthwise_conv2d(ctypes.byref(make_ap(x, 1)), ctypes.byref(make_ap(w, 1)),
-                                           _i64(stride), _i64(pad), act, ctypes.byref(make_ap(out, 4)),
-                                           _stream(x)), "depthwise_conv2d")
-    return out
+    return _m().depthwise_conv2d(x, w, stride, pad, act, out_dtype, out)
 
 
 def conv2d_direct_static(x, w, stride=(1, 1), pad=(0, 0), residual=None, act=GS_ACT_NONE, out_dtype=None,
@@ -293,69 +266,38 @@ def conv2d_pack_weights(w: torch.Tensor, packed: Optional[torch.Tensor] = None,
 def conv2d_direct_packed(x, w, packed, stride=(1, 1), pad=(0, 0), residual=None, act=GS_ACT_NONE,
                          out_dtype=None, out=None) -> torch.Tensor:
     """Fig. 2a reading weights from `conv2d_pack_weights(w)`; `w` supplies shape and dtype only."""
-    return _conv("glenside_conv2d_direct_packed", "glenside_conv2d_direct_workspace", x, w, stride, pad,
-                 residual, act, out_dtype, out, packed)
+    return _m().conv(1, x, w, stride, pad, residual, act, out_dtype, out, packed)
 
 
 def conv2d_im2col(x, w, stride=(1, 1), pad=(0, 0), residual=None, act=GS_ACT_NONE, out_dtype=None,
                   out=None, workspace=None) -> torch.Tensor:
     """Fig. 5: explicit flatten(windows) in the workspace, then the dense contraction."""
-    return _conv("glenside_conv2d_im2col", "glenside_conv2d_im2col_workspace", x, w, stride, pad,
-                 residual, act, out_dtype, out, workspace)
-
-
-def _reduce_out_dtype(x: torch.Tensor, op: int, out_dtype):
-    if out_dtype is not None:
-        return out_dtype
-    if x.dtype == torch.int8:
-        return torch.int32 if op == GS_SUM else torch.int8
-    return x.dtype
+    return _m().conv(2, x, w, stride, pad, residual, act, out_dtype, out, workspace)
 
 
 def reduce(x: torch.Tensor, n_access: int, op: int, scale: float = 1.0, out_dtype=None,
            out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """compute reduceSum|reduceMax (access x n_access) -> tensor of shape S_A."""
-    if out is None:
-        out = torch.empty(tuple(x.shape[:n_access]), dtype=_reduce_out_dtype(x, op, out_dtype),
-                          device=x.device)
-    _check(lib().glenside_reduce(ctypes.byref(make_ap(x, n_access)), op, scale,
-                                 ctypes.byref(make_ap(out, out.dim())), _stream(x)), "reduce")
-    return out
+    return _m().reduce(x, n_access, op, scale, out_dtype, out)
 
 
 def windows_reduce(x: torch.Tensor, n_access: int, window, stride, pad_lo=None, pad_hi=None,
                    op: int = GS_MAX, scale: float = 1.0, out_dtype=None,
                    out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """compute reduce (windows (access x n_access) window stride) without materialising the windows."""
-    if out is None:
-        shape, na = windows_out_shape(x.shape, n_access, window, stride, pad_lo, pad_hi)
-        out = torch.empty(shape[:na], dtype=_reduce_out_dtype(x, op, out_dtype), device=x.device)
-    _check(lib().glenside_windows_reduce(ctypes.byref(make_ap(x, n_access)), _i64(window), _i64(stride),
-                                         _i64(pad_lo), _i64(pad_hi), op, scale,
-                                         ctypes.byref(make_ap(out, out.dim())), _stream(x)),
-           "windows_reduce")
-    return out
+    return _m().windows_reduce(x, n_access, window, stride, pad_lo, pad_hi, op, scale, out_dtype, out)
 
 
 def pair_reduce(a: torch.Tensor, b: torch.Tensor, op: int = GS_SUM, act: int = GS_ACT_NONE,
                 out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """compute reduceSum|reduceMax (pair a b) for patterns with empty compute shape: element-wise."""
-    if out is None:
-        out = torch.empty_like(a)
-    _check(lib().glenside_pair_reduce(ctypes.byref(make_ap(a, a.dim())), ctypes.byref(make_ap(b, b.dim())),
-                                      op, act, ctypes.byref(make_ap(out, out.dim())), _stream(a)),
-           "pair_reduce")
-    return out
+    return _m().pair_reduce(a, b, op, act, out)
 
 
 def transpose(x: torch.Tensor, n_access: int, perm: Sequence[int],
               out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """transpose (access x n_access) perm, materialised: output dimension t is input dimension perm[t]."""
-    if out is None:
-        out = torch.empty([x.shape[p] for p in perm], dtype=x.dtype, device=x.device)
-    _check(lib().glenside_transpose(ctypes.byref(make_ap(x, n_access)), _i64(perm),
-                                    ctypes.byref(make_ap(out, n_access)), _stream(x)), "transpose")
-    return out
+    return _m().transpose(x, n_access, perm, out)
 
 
 def slice_(x: torch.Tensor, n_access: int, dim: int, lo: int, hi: int,

@@ -1,15 +1,17 @@
-"""Build the HIP library in-tree: `python -m paper_2105_09377_amd.build`."""
+"""Build the HIP library and the binding's extension module in-tree: `python -m paper_2105_09377_amd.build`."""
 
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libglenside.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -39,11 +41,29 @@ def _compile(unit) -> str:
     return obj
 
 
+def _compile_marshal() -> None:
+    """The binding's extension module: host C++ against torch's and HIP's headers."""
+    import torch
+    base = os.path.dirname(torch.__file__)
+    libs = os.path.join(base, "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
+           "-L" + libs, "-Wl,-rpath," + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed on marshal.cpp")
+
+
 def build(verbose: bool = True) -> str:
-    """Compile every kernel source for gfx950 and link libglenside.so next to this file."""
+    """Compile every kernel source for gfx950 and link libglenside.so and _marshal.so next to this file."""
     workers = min(len(UNITS), max(1, len(os.sched_getaffinity(0))))
     with ThreadPoolExecutor(max_workers=workers) as pool:
+        marshal = pool.submit(_compile_marshal)
         objs = list(pool.map(_compile, UNITS))
+        marshal.result()
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     if verbose:
         print("built", LIB)
