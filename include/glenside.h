@@ -255,13 +255,16 @@ int glenside_program_shape(const char* text, const gs_named_ap* tensors, int n_t
  * dtype the same, or GS_BF16 where the root is a bfloat16 contraction).  Node by node:
  *   (compute dotProd (cartProd a0 a1))   one MFMA contraction; the Cartesian product is never
  *                                        formed (the pattern Fig. 3 maps to hardware);
- *   the whole listing of Fig. 2a         the direct convolution (windows formed on chip);
+ *   the whole listing of Fig. 2a, or of
+ *   Fig. 5 (what Fig. 4 makes of it)     the direct convolution (windows formed on chip); symmetric
+ *                                        zero padding in front of the windows becomes its own;
  *   (compute reduceX (windows ...))      the fused pooling kernel (Fig. 2c);
  *   (compute reduceX (pair a b))         the element-wise kernel (Sec. 5.4);
  *   access squeeze flatten reshape,
  *   a slice of the outermost dimension   descriptor changes, no data moves;
  *   transpose slice concat pair pad
- *   windows                              the data-moving kernels, into the workspace;
+ *   windows                              the data-moving kernels, into the workspace (pad in front of
+ *                                        windows, or of a reduceSum over them, becomes their padding);
  *   cartProd anywhere else               GS_ERR_UNSUPPORTED.
  * Identical sub-programs are evaluated once.  `workspace`: device memory of at least
  * glenside_program_workspace bytes (0 = invalid program), 16-byte aligned, caller-owned.       */

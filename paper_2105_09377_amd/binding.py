@@ -402,19 +402,7 @@ def program_shape(text: str, tensors, ints=None):
 def program_eval(text: str, tensors, ints=None, out_dtype=None, out: Optional[torch.Tensor] = None,
                  workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Evaluate an access-pattern program (the paper's s-expression text) on the GPU."""
-    ints = ints or {}
-    ta, nt, ia, ni, _keep = _named(tensors, ints)
-    L = lib()
-    shape, na, dtype = program_shape(text, tensors, ints)
-    first = next(iter(tensors.values()))
-    if out is None:
-        out = torch.empty(shape, dtype=out_dtype or dtype, device=first.device)
-    if workspace is None:
-        need = L.glenside_program_workspace(text.encode(), ta, nt, ia, ni)
-        workspace = torch.empty(max(int(need), 16), dtype=torch.uint8, device=first.device)
-    _check(L.glenside_program_eval(text.encode(), ta, nt, ia, ni, ctypes.byref(make_ap(out, na, shape=shape)),
-                                   workspace.data_ptr(), workspace.numel(), _stream(first)), "program_eval")
-    return out
+    return _m().program_eval(text, tensors, ints or {}, out_dtype, out, workspace)
 
 
 def program_rewrite(text: str, strategy: str, tensors, ints=None, params: Sequence[int] = ()) -> str:

@@ -11,6 +11,8 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <vector>
+
 #include "../../include/glenside.h"
 
 namespace {
@@ -28,6 +30,9 @@ struct Api {
   decltype(&glenside_pair_reduce) pair_reduce;
   decltype(&glenside_depthwise_conv2d) depthwise_conv2d;
   decltype(&glenside_transpose) transpose;
+  decltype(&glenside_program_shape) program_shape;
+  decltype(&glenside_program_workspace) program_workspace;
+  decltype(&glenside_program_eval) program_eval;
 } api;
 PyObject* error_class;
 
@@ -375,6 +380,59 @@ PyObject* py_transpose(PyObject*, PyObject* const* p, Py_ssize_t n) {
   });
 }
 
+// program_eval(text, tensors by name, integers by name, out_dtype, out, workspace)
+PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
+  return guarded(n, 6, [&](PyObject*& r) {
+    const char* text = PyUnicode_AsUTF8(p[0]);
+    if (!text) throw Failed{};
+    if (!PyDict_Check(p[1]) || !PyDict_Check(p[2])) {
+      PyErr_SetString(PyExc_TypeError, "tensors and integers are given as dicts by name");
+      throw Failed{};
+    }
+    // the name strings are owned by the dicts, which the caller keeps alive
+    auto name_of = [](PyObject* key) {
+      const char* s = PyUnicode_AsUTF8(key);
+      if (!s) throw Failed{};
+      return s;
+    };
+    std::vector<gs_named_ap> tensors;
+    std::vector<gs_named_int> ints;
+    const at::Tensor* first = nullptr;
+    PyObject *key, *value;
+    for (Py_ssize_t pos = 0; PyDict_Next(p[1], &pos, &key, &value);) {
+      const at::Tensor& t = tensor(value);
+      if (!first) first = &t;
+      tensors.push_back({name_of(key), describe(t, 0)});
+    }
+    for (Py_ssize_t pos = 0; PyDict_Next(p[2], &pos, &key, &value);) ints.push_back({name_of(key), integer(value)});
+    if (!first) {
+      PyErr_SetString(PyExc_StopIteration, "a program needs a tensor");
+      throw Failed{};
+    }
+    const int nt = int(tensors.size()), ni = int(ints.size());
+    gs_ap want{};
+    call("program_shape", [&] { return api.program_shape(text, tensors.data(), nt, ints.data(), ni, &want); });
+    constexpr at::ScalarType types[5] = {at::kChar, at::kInt, at::kBFloat16, at::kFloat, at::kFloat8_e4m3fn};   // by gs_dtype
+    Result out(p[4], p[3], types[want.dtype], want.shape, want.rank, *first);
+    r = out.object;
+    at::Tensor ws;
+    if (p[5] != Py_None) {
+      ws = tensor(p[5]);
+    } else {
+      const size_t need = api.program_workspace(text, tensors.data(), nt, ints.data(), ni);
+      ws = at::empty({int64_t(need > 16 ? need : 16)}, at::TensorOptions().dtype(at::kByte).device(first->device()));
+    }
+    // the result as the program's access pattern, whatever shape its tensor has
+    gs_ap oa = describe(out.value, 0);
+    oa.rank = want.rank;
+    oa.n_access = want.n_access;
+    for (int i = 0; i < want.rank; ++i) oa.shape[i] = want.shape[i];
+    void *wsp = ws.data_ptr(), *s = stream_of(*first);
+    const size_t bytes = size_t(ws.numel());
+    call("program_eval", [&] { return api.program_eval(text, tensors.data(), nt, ints.data(), ni, &oa, wsp, bytes, s); });
+  });
+}
+
 // bind(addresses by entry point name, GlensideError)
 PyObject* py_bind(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 2, [&](PyObject*& r) {
@@ -403,6 +461,9 @@ PyObject* py_bind(PyObject*, PyObject* const* p, Py_ssize_t n) {
     get("glenside_pair_reduce", api.pair_reduce);
     get("glenside_depthwise_conv2d", api.depthwise_conv2d);
     get("glenside_transpose", api.transpose);
+    get("glenside_program_shape", api.program_shape);
+    get("glenside_program_workspace", api.program_workspace);
+    get("glenside_program_eval", api.program_eval);
     Py_INCREF(p[1]);
     Py_XDECREF(error_class);
     error_class = p[1];
@@ -416,6 +477,7 @@ PyMethodDef methods[] = {
     GS_FN("bind", py_bind), GS_FN("cartesian_dot", py_cartesian_dot), GS_FN("conv", py_conv), GS_FN("reduce", py_reduce),
     GS_FN("windows_reduce", py_windows_reduce), GS_FN("access_windows", py_access_windows),
     GS_FN("depthwise_conv2d", py_depthwise), GS_FN("pair_reduce", py_pair_reduce), GS_FN("transpose", py_transpose),
+    GS_FN("program_eval", py_program_eval),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -7,10 +7,12 @@
 //   * evaluates a program by dispatching its nodes to the library's kernels: the pattern the
 //     paper maps to hardware, (compute dotProd (cartProd ?a0 ?a1)) (Fig. 3, Sec. 5.2), becomes one
 //     MFMA contraction without the Cartesian product ever existing in memory; the whole listing
-//     of Fig. 2a becomes the direct convolution; (compute reduceX (windows ...)) becomes the fused
+//     of Fig. 2a, and the whole of Fig. 5 that Fig. 4's rules derive from it, becomes the direct
+//     convolution; (compute reduceX (windows ...)) becomes the fused
 //     pooling kernel; (compute reduceX (pair a b)) the element-wise kernel; every other
 //     transformer is a descriptor change (access, squeeze, flatten, reshape, outermost slice) or
-//     one of the data-moving kernels (transpose, slice, concat, pair, pad, windows).  Identical
+//     one of the data-moving kernels (transpose, slice, concat, pair, pad, windows); zero padding
+//     in front of windows becomes the padding of the kernel that forms them.  Identical
 //     sub-programs are evaluated once.
 //   * applies the rewrites: the three rules of Fig. 4 that turn the convolution of Fig. 2a into
 //     its im2col form (Fig. 5), the systolic-array rule of Fig. 3, and the blocking rules of
@@ -22,7 +24,7 @@
 
 #include <string.h>
 
-#include <map>
+#include <atomic>
 #include <memory>
 #include <string>
 #include <vector>
@@ -36,6 +38,24 @@ using gs::round_up;
 // ---------------------------------------------------------------------------------------------
 // Text <-> tree
 // ---------------------------------------------------------------------------------------------
+struct Shape {           // an access pattern's shape and element type
+  std::vector<int64_t> d;
+  int na = 0;
+  int dtype = GS_F32;
+  int nc() const { return int(d.size()) - na; }
+  int64_t numel() const {
+    int64_t n = 1;
+    for (int64_t x : d) n *= x;
+    return n;
+  }
+  int64_t access_numel() const {
+    int64_t n = 1;
+    for (int i = 0; i < na; ++i) n *= d[i];
+    return n;
+  }
+  int64_t compute_numel() const { return numel() / (access_numel() ? access_numel() : 1); }
+};
+
 struct Tree;
 using TreeP = std::shared_ptr<const Tree>;
 struct Tree {
@@ -43,24 +63,44 @@ struct Tree {
   std::string sym;
   int64_t value = 0;
   std::vector<TreeP> items;
+  uint64_t hash = 0;            // of the text the node stands for
+  // Shape inferred for the environment of this number (0: none yet).  A tree is used by one thread.
+  mutable uint64_t shaped_for = 0;
+  mutable int shape_status = 0;
+  mutable Shape shape;
 };
+
+uint64_t mix(uint64_t h, uint64_t v) { return (h ^ v) * 0x9e3779b97f4a7c15ull + (h >> 29); }
+bool same_text(const TreeP& a, const TreeP& b) {
+  if (a == b) return true;
+  if (a->hash != b->hash || a->kind != b->kind || a->value != b->value || a->sym != b->sym || a->items.size() != b->items.size())
+    return false;
+  for (size_t i = 0; i < a->items.size(); ++i)
+    if (!same_text(a->items[i], b->items[i])) return false;
+  return true;
+}
 
 TreeP mk_int(int64_t v) {
   auto t = std::make_shared<Tree>();
   t->kind = Tree::kInt;
   t->value = v;
+  t->hash = mix(1, uint64_t(v));
   return t;
 }
 TreeP mk_sym(const std::string& s) {
   auto t = std::make_shared<Tree>();
   t->kind = Tree::kSymbol;
   t->sym = s;
+  t->hash = 2;
+  for (char c : s) t->hash = mix(t->hash, uint8_t(c));
   return t;
 }
 TreeP mk_list(std::vector<TreeP> items) {
   auto t = std::make_shared<Tree>();
   t->kind = Tree::kList;
   t->items = std::move(items);
+  t->hash = 3;
+  for (const TreeP& i : t->items) t->hash = mix(t->hash, i->hash);
   return t;
 }
 TreeP call(const std::string& head, std::vector<TreeP> args) {
@@ -132,13 +172,21 @@ struct Parser {
   }
 };
 
+// The tree of a program.  Each thread keeps the one it read last: an evaluation asks for the
+// program's shape, its workspace and its result in turn, and programs are evaluated over and over.
 TreeP parse(const char* text) {
   if (!text) return nullptr;
+  thread_local std::string last_text;
+  thread_local TreeP last;
+  if (last && last_text == text) return last;
   Parser ps{text};
   TreeP t = ps.read(0);
   if (!ps.ok) return nullptr;
   ps.skip();
-  return *ps.p ? nullptr : t;
+  if (*ps.p) return nullptr;
+  last = t;
+  last_text = text;
+  return t;
 }
 
 bool is_call(const TreeP& t, const char* head, size_t nargs) {
@@ -150,11 +198,16 @@ const TreeP& arg(const TreeP& t, size_t i) { return t->items[i + 1]; }
 // ---------------------------------------------------------------------------------------------
 // Environment, shapes (Table 1, Table 2)
 // ---------------------------------------------------------------------------------------------
+uint64_t next_env() {
+  static std::atomic<uint64_t> n{0};
+  return ++n;
+}
 struct Env {
   const gs_named_ap* tensors;
   int n_tensors;
   const gs_named_int* ints;
   int n_ints;
+  uint64_t number = next_env();   // names the environment a node's remembered shape belongs to
   const gs_ap* tensor(const std::string& name) const {
     for (int i = 0; i < n_tensors; ++i)
       if (tensors[i].name && name == tensors[i].name) return &tensors[i].tensor;
@@ -188,28 +241,20 @@ struct Env {
   }
 };
 
-struct Shape {           // an access pattern's shape and element type
-  std::vector<int64_t> d;
-  int na = 0;
-  int dtype = GS_F32;
-  int nc() const { return int(d.size()) - na; }
-  int64_t numel() const {
-    int64_t n = 1;
-    for (int64_t x : d) n *= x;
-    return n;
-  }
-  int64_t access_numel() const {
-    int64_t n = 1;
-    for (int i = 0; i < na; ++i) n *= d[i];
-    return n;
-  }
-  int64_t compute_numel() const { return numel() / (access_numel() ? access_numel() : 1); }
-};
-
 int dot_out_dtype(int in) { return in == GS_I8 ? GS_I32 : (in == GS_BF16 || in == GS_F8) ? GS_F32 : -1; }
 
 // Shape of a node; GS_OK or the status that evaluation would return.
-int infer(const TreeP& t, const Env& env, Shape* out);
+int infer_node(const TreeP& t, const Env& env, Shape* out);
+int infer(const TreeP& t, const Env& env, Shape* out) {
+  if (!t) return GS_ERR_NULL;
+  if (t->shaped_for != env.number) {
+    t->shape = Shape();
+    t->shape_status = infer_node(t, env, &t->shape);
+    t->shaped_for = env.number;
+  }
+  if (t->shape_status == GS_OK) *out = t->shape;
+  return t->shape_status;
+}
 
 int infer_compute(const TreeP& t, const Env& env, Shape* out) {
   const TreeP& op = arg(t, 0);
@@ -246,8 +291,7 @@ int infer_compute(const TreeP& t, const Env& env, Shape* out) {
   return GS_ERR_UNSUPPORTED;
 }
 
-int infer(const TreeP& t, const Env& env, Shape* out) {
-  if (!t) return GS_ERR_NULL;
+int infer_node(const TreeP& t, const Env& env, Shape* out) {
   if (t->kind == Tree::kSymbol) {
     const gs_ap* a = env.tensor(t->sym);
     if (!a) return GS_ERR_NULL;
@@ -436,10 +480,31 @@ struct Value {
   void* data = nullptr;
 };
 
-// The listing of Fig. 2a, with the sizes of its shape literals.
+// x with the (pad ...)s in front of it taken off; lo / hi receive what they add to each dimension.
+// False if a padding touches a dimension below `first`, which the consumer cannot pad itself.
+bool strip_pads(const TreeP& x, const Env& env, int64_t first, TreeP* inner, int64_t* lo, int64_t* hi) {
+  for (int i = 0; i < GS_MAX_RANK; ++i) lo[i] = hi[i] = 0;
+  TreeP t = x;
+  Shape s;
+  while (is_call(t, "pad", 4)) {
+    int64_t dim, l, h;
+    if (infer(t, env, &s) || !env.integer(arg(t, 1), &dim) || !env.integer(arg(t, 2), &l) || !env.integer(arg(t, 3), &h)) return false;
+    if (dim < first || dim >= GS_MAX_RANK) return false;
+    lo[dim] += l;
+    hi[dim] += h;
+    t = arg(t, 0);
+  }
+  *inner = t;
+  return true;
+}
+
+// The listing of Fig. 2a, or the form of it that the rules of Fig. 4 derive (Fig. 5: windows and
+// weights flattened, the product reshaped back), with the sizes of its shape literals.  The two are
+// the same convolution, and forming the windows on chip is the faster way to it.
 struct ConvMatch {
   TreeP act, weights;
   std::vector<int64_t> window, stride;
+  int64_t pad[2] = {0, 0};
 };
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
@@ -448,12 +513,14 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   if (perm != std::vector<int64_t>({0, 3, 1, 2})) return false;
   const TreeP& sq = arg(t, 0);
   if (!is_call(sq, "squeeze", 2) || !env.integer(arg(sq, 1), &one) || one != 1) return false;
-  const TreeP& cp = arg(sq, 0);
+  const bool flat = is_call(arg(sq, 0), "reshape", 3);
+  const TreeP& cp = flat ? arg(arg(sq, 0), 0) : arg(sq, 0);
   if (!is_call(cp, "compute", 2) || arg(cp, 0)->kind != Tree::kSymbol || arg(cp, 0)->sym != "dotProd") return false;
   const TreeP& c = arg(cp, 1);
   if (!is_call(c, "cartProd", 2)) return false;
-  const TreeP& w = arg(c, 0);
-  const TreeP& f = arg(c, 1);
+  if (flat && (!is_call(arg(c, 0), "flatten", 1) || !is_call(arg(c, 1), "flatten", 1))) return false;
+  const TreeP& w = flat ? arg(arg(c, 0), 0) : arg(c, 0);
+  const TreeP& f = flat ? arg(arg(c, 1), 0) : arg(c, 1);
   int64_t i;
   if (!is_call(w, "windows", 3) || !is_call(arg(w, 0), "access", 2) || !env.integer(arg(arg(w, 0), 1), &i) || i != 1)
     return false;
@@ -461,12 +528,24 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   if (!env.tuple(arg(w, 1), "shape", &m->window) || !env.tuple(arg(w, 2), "shape", &m->stride)) return false;
   m->act = arg(arg(w, 0), 0);
   m->weights = arg(f, 0);
-  Shape a, b;
-  if (infer(m->act, env, &a) || infer(m->weights, env, &b)) return false;
+  Shape a, b, all, win;
+  if (infer(t, env, &all) || infer(w, env, &win) || infer(m->act, env, &a) || infer(m->weights, env, &b)) return false;
   if (a.d.size() != 4 || b.d.size() != 4 || m->window.size() != 3 || m->stride.size() != 3) return false;
   // window = the weights' (C, Kh, Kw), covering every channel; stride 1 over the channels
-  return m->window[0] == a.d[1] && m->window[0] == b.d[1] && m->window[1] == b.d[2] && m->window[2] == b.d[3] &&
-         m->stride[0] == 1 && (a.dtype == GS_I8 || a.dtype == GS_BF16) && a.dtype == b.dtype;
+  if (!(m->window[0] == a.d[1] && m->window[0] == b.d[1] && m->window[1] == b.d[2] && m->window[2] == b.d[3] &&
+        m->stride[0] == 1 && (a.dtype == GS_I8 || a.dtype == GS_BF16) && a.dtype == b.dtype))
+    return false;
+  // (N, O, H', W'): what the reshape of the flat form must restore
+  if (all.d.size() != 4 || all.d[0] != a.d[0] || all.d[1] != b.d[0] || all.d[2] != win.d[2] || all.d[3] != win.d[3]) return false;
+  // symmetric zero padding of H and W is the convolution's own
+  TreeP inner;
+  int64_t lo[GS_MAX_RANK], hi[GS_MAX_RANK];
+  if (strip_pads(m->act, env, 2, &inner, lo, hi) && lo[2] == hi[2] && lo[3] == hi[3] && lo[2] <= 64 && lo[3] <= 64) {
+    m->act = inner;
+    m->pad[0] = lo[2];
+    m->pad[1] = lo[3];
+  }
+  return true;
 }
 
 struct Evaluator {
@@ -475,7 +554,12 @@ struct Evaluator {
   uint8_t* ws;
   size_t ws_bytes, used = 0;
   void* stream;
-  std::map<std::string, Value> memo;     // identical sub-programs are evaluated once
+  struct Done {
+    TreeP t;
+    int want;
+    Value value;
+  };
+  std::vector<Done> memo;                // identical sub-programs are evaluated once
 
   void* alloc(int64_t bytes, int* st) {
     const size_t need = size_t(round_up(bytes > 0 ? bytes : 1, 256));
@@ -496,16 +580,14 @@ struct Evaluator {
   // bfloat16 contraction may store narrower than it accumulates, and the transformers between it
   // and the root pass the request down (they keep the element type).
   int eval(const TreeP& t, void* dst, Value* out, int want = -1) {
-    const std::string key = dst ? std::string() : to_text(t) + (want >= 0 ? "#" + std::to_string(want) : std::string());
-    if (!dst) {
-      auto it = memo.find(key);
-      if (it != memo.end()) {
-        *out = it->second;
-        return GS_OK;
-      }
-    }
+    if (!dst)
+      for (const Done& d : memo)
+        if (d.want == want && same_text(d.t, t)) {
+          *out = d.value;
+          return GS_OK;
+        }
     int st = eval_node(t, dst, out, want);
-    if (st == GS_OK && !dst) memo[key] = *out;
+    if (st == GS_OK && !dst) memo.push_back(Done{t, want, *out});
     return st;
   }
 
@@ -603,11 +685,12 @@ struct Evaluator {
       env.tuple(arg(t, 1), "shape", &w);
       env.tuple(arg(t, 2), "shape", &sd);
       Value in;
-      if ((st = eval(arg(t, 0), nullptr, &in))) return st;
+      int64_t lo[GS_MAX_RANK], hi[GS_MAX_RANK];
+      if ((st = eval_padded(arg(t, 0), &in, lo, hi))) return st;
       if ((st = materialize(s, dst, out))) return st;
       if (dry) return GS_OK;
       gs_ap ia = make_ap(in.data, in.s), oa = make_ap(out->data, s);
-      return glenside_access_windows(&ia, w.data(), sd.data(), nullptr, nullptr, GS_PAD_ZERO, &oa, stream);
+      return glenside_access_windows(&ia, w.data(), sd.data(), lo + in.s.na, hi + in.s.na, GS_PAD_ZERO, &oa, stream);
     }
     if (h == "pair" || h == "concat") {
       Value a, b;
@@ -685,11 +768,13 @@ struct Evaluator {
         env.tuple(arg(x, 1), "shape", &w);
         env.tuple(arg(x, 2), "shape", &sd);
         Value in;
-        if ((st = eval(arg(x, 0), nullptr, &in))) return st;
+        int64_t lo[GS_MAX_RANK] = {}, hi[GS_MAX_RANK] = {};
+        // padded zeros count in a sum as the kernel's own padding does, in a maximum they do not
+        if ((st = rop == GS_SUM ? eval_padded(arg(x, 0), &in, lo, hi) : eval(arg(x, 0), nullptr, &in))) return st;
         if ((st = materialize(s, dst, out))) return st;
         if (dry) return GS_OK;
         gs_ap ia = make_ap(in.data, in.s), oa = make_ap(out->data, s);
-        return glenside_windows_reduce(&ia, w.data(), sd.data(), nullptr, nullptr, rop, 1.0f, &oa, stream);
+        return glenside_windows_reduce(&ia, w.data(), sd.data(), lo + in.s.na, hi + in.s.na, rop, 1.0f, &oa, stream);
       }
       if (is_call(x, "pair", 2) && xs.nc() == 1 && xs.dtype != GS_I8) {   // Sec. 5.4: element-wise sum / max
         Value a, b;
@@ -710,6 +795,21 @@ struct Evaluator {
     return GS_ERR_UNSUPPORTED;
   }
 
+  // The operand of a windows node: (access X n) with zero padding of compute dimensions left to the
+  // consumer (lo, hi by dimension).
+  int eval_padded(const TreeP& t, Value* in, int64_t* lo, int64_t* hi) {
+    TreeP inner;
+    int64_t na;
+    if (is_call(t, "access", 2) && env.integer(arg(t, 1), &na) && is_call(arg(t, 0), "pad", 4) &&
+        strip_pads(arg(t, 0), env, na, &inner, lo, hi)) {
+      const int st = eval(inner, nullptr, in);
+      in->s.na = int(na);
+      return st;
+    }
+    for (int i = 0; i < GS_MAX_RANK; ++i) lo[i] = hi[i] = 0;
+    return eval(t, nullptr, in);
+  }
+
   int eval_conv2d(const ConvMatch& m, const Shape& s, void* dst, Value* out) {
     Value a, w;
     int st;
@@ -718,7 +818,7 @@ struct Evaluator {
     a.s.na = 1;
     w.s.na = 1;
     gs_ap aa = make_ap(a.data, a.s), wa = make_ap(w.data, w.s);
-    const int64_t stride[2] = {m.stride[1], m.stride[2]}, pad[2] = {0, 0};
+    const int64_t stride[2] = {m.stride[1], m.stride[2]}, *pad = m.pad;
     const size_t cws = glenside_conv2d_direct_workspace(&aa, &wa, stride, pad);
     if (cws == 0) return GS_ERR_UNSUPPORTED;
     void* scratch = alloc(int64_t(cws), &st);

@@ -50,6 +50,33 @@ def test_conv2d_listing_on_padded_tensor():
     assert torch.equal(got, gs.conv2d_direct(cfg["x"].to(DEV), cfg["w"].to(DEV), (1, 1), (1, 1)))
 
 
+# Zero padding that a consumer can take over (convolution, windows, sums of windows), padding that it
+# cannot (one side only, other dimensions, a maximum), and the flat form of the convolution listing.
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("pads", [((2, 1, 1), (3, 2, 2)), ((2, 1, 0), (3, 0, 2)), ((1, 0, 2), (2, 1, 1)), ((0, 1, 0), (3, 1, 1))])
+def test_padding_in_front_of_windows(pads, dtype):
+    x = {"i8": synth.uniform_int8, "bf16": lambda s, lo, hi, st: synth.normal_bf16(s, 1.0, st)}[dtype]((2, 6, 9, 8), -9, 9, 9450)
+    grown = [2, 6, 9, 8]
+    act = "activations"
+    for dim, lo, hi in pads:
+        act = f"(pad {act} {dim} {lo} {hi})"
+        grown[dim] += lo + hi
+    c = grown[1]
+    w = {"i8": synth.uniform_int8, "bf16": lambda s, lo, hi, st: synth.normal_bf16(s, 0.2, st)}[dtype]((5, c, 3, 2), -9, 9, 9451)
+    ints = dict(C=c, Kh=3, Kw=2, Sh=1, Sw=2)
+    tensors = {"activations": x, "weights": w}
+    conv = listings.CONV2D.replace("activations", act, 1)
+    meta = {k: (tuple(v.shape), v.dtype) for k, v in tensors.items()}
+    for text in (conv, gs.program_rewrite(conv, "im2col", meta, ints)):
+        got, want = run_both(text, tensors, ints)
+        assert_parity(got, want.materialize(), what=text)
+    for text in (f"(windows (access {act} 2) (shape Kh Kw) (shape Sh Sw))",
+                 f"(compute reduceSum (windows (access {act} 2) (shape Kh Kw) (shape Sh Sw)))",
+                 f"(compute reduceMax (windows (access {act} 2) (shape Kh Kw) (shape Sh Sw)))"):
+        got, want = run_both(text, {"activations": x}, ints)
+        assert_parity(got, want.materialize(), what=text)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "fp8"])
 @pytest.mark.parametrize("dims", [(32, 32, 32), (70, 96, 200)])
 def test_matmul_listing_and_its_rewrites(dtype, dims):
