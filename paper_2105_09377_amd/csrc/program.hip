@@ -481,7 +481,8 @@ struct Value {
 };
 
 // x with the (pad ...)s in front of it taken off; lo / hi receive what they add to each dimension.
-// False if a padding touches a dimension below `first`, which the consumer cannot pad itself.
+// False if a padding touches a dimension below `first`, which the consumer cannot pad itself, or if
+// nothing is padded but zeros (an empty operand: the kernels take rows of at least one element).
 bool strip_pads(const TreeP& x, const Env& env, int64_t first, TreeP* inner, int64_t* lo, int64_t* hi) {
   for (int i = 0; i < GS_MAX_RANK; ++i) lo[i] = hi[i] = 0;
   TreeP t = x;
@@ -495,7 +496,7 @@ bool strip_pads(const TreeP& x, const Env& env, int64_t first, TreeP* inner, int
     t = arg(t, 0);
   }
   *inner = t;
-  return true;
+  return infer(t, env, &s) == GS_OK && s.numel() > 0;
 }
 
 // The listing of Fig. 2a, or the form of it that the rules of Fig. 4 derive (Fig. 5: windows and
@@ -506,6 +507,17 @@ struct ConvMatch {
   std::vector<int64_t> window, stride;
   int64_t pad[2] = {0, 0};
 };
+bool flat_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result) {
+  Shape act;
+  if (infer(m.act, env, &act)) return false;
+  act.na = 1;
+  Shape weights = w;
+  weights.na = 1;
+  const gs_ap aa = make_ap(nullptr, act), wa = make_ap(nullptr, weights);
+  const int64_t stride[2] = {m.stride[1], m.stride[2]};
+  return act.numel() > 0 && glenside_conv2d_direct_workspace(&aa, &wa, stride, m.pad) != 0 &&
+         gs::conv_direct_fits(act.d[0], act.d[3], w.d[2], w.d[3], stride[0], m.pad[1], result.d[2], result.d[3]);
+}
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
   int64_t one;
@@ -545,7 +557,9 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
     m->pad[0] = lo[2];
     m->pad[1] = lo[3];
   }
-  return true;
+  // What no direct kernel is sure to take (strides, windows and rows too large for the LDS, more images
+  // in a tile than it counts) the flat form still evaluates node by node.
+  return !flat || flat_fits(*m, env, b, all);
 }
 
 struct Evaluator {

@@ -77,6 +77,19 @@ def test_padding_in_front_of_windows(pads, dtype):
         assert_parity(got, want.materialize(), what=text)
 
 
+# Convolutions that the direct kernels refuse (a stride above 64, rows or windows too large for the LDS, many
+# images in one tile), and the next ones that they take: the flat form evaluates all of them.
+@pytest.mark.parametrize("shape", [(1, 2, 70, 9, 3, 3, 1, 65, 1), (1, 16, 4, 1300, 8, 3, 3, 1, 1), (1, 16, 4, 900, 8, 3, 3, 1, 1),
+                                   (40, 32, 3, 3, 8, 3, 3, 1, 1), (16, 32, 3, 3, 8, 3, 3, 1, 1), (1, 32, 12, 12, 4, 11, 11, 1, 1)])
+def test_flat_form_where_no_direct_kernel_fits(shape):
+    n, c, h, w, o, kh, kw, sh, sw = shape
+    tensors = {"activations": synth.uniform_int8((n, c, h, w), -9, 9, 9470), "weights": synth.uniform_int8((o, c, kh, kw), -9, 9, 9471)}
+    ints = dict(C=c, Kh=kh, Kw=kw, Sh=sh, Sw=sw)
+    meta = {k: (tuple(v.shape), v.dtype) for k, v in tensors.items()}
+    got, want = run_both(gs.program_rewrite(listings.CONV2D, "im2col", meta, ints), tensors, ints)
+    assert_parity(got, want.materialize(), what=str(shape))
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "fp8"])
 @pytest.mark.parametrize("dims", [(32, 32, 32), (70, 96, 200)])
 def test_matmul_listing_and_its_rewrites(dtype, dims):
