@@ -55,12 +55,14 @@ template <> struct DwElem<int8_t> {
 
 struct DwTask {
   int64_t plane0;
-  int gcount, ho0, nho, R;   // planes, first output row, output rows, gcount * nho
+  int gcount, ho0, nho, R;   // planes, first output row, output rows, rows of strips
+  int ih1;           // end of the input rows copied
   int64_t ebase;     // first element (16-byte aligned) of the copy
   int nvec;          // 16-byte vectors in the copy
   int shift;         // LDS element index of (g, ih, iw) is (g*H + ih)*W + iw - shift
 };
 
+template <int VY>
 __device__ __forceinline__ DwTask dw_task(const DwArgs& a, int64_t task, int epv) {
   DwTask t;
   const int64_t grp = task / a.bands;
@@ -70,12 +72,13 @@ __device__ __forceinline__ DwTask dw_task(const DwArgs& a, int64_t task, int epv
   t.gcount = left < a.G ? int(left) : a.G;
   t.ho0 = band * a.HB;
   t.nho = a.Ho - t.ho0 < a.HB ? a.Ho - t.ho0 : a.HB;
-  t.R = t.gcount * t.nho;
+  t.R = t.gcount * ((t.nho + VY - 1) / VY);
   int ih0 = t.ho0 * a.Sh - a.Ph;
   ih0 = ih0 < 0 ? 0 : ih0;
   int ih1 = (t.ho0 + t.nho - 1) * a.Sh - a.Ph + a.Kh;
   ih1 = ih1 > a.H ? a.H : ih1;
   ih1 = ih1 < ih0 ? ih0 : ih1;
+  t.ih1 = ih1;
   const int64_t e0 = (t.plane0 * a.H + ih0) * a.W;
   const int64_t e1 = ((t.plane0 + t.gcount - 1) * a.H + ih1) * a.W;
   t.ebase = e0 / epv * epv;
@@ -84,9 +87,23 @@ __device__ __forceinline__ DwTask dw_task(const DwArgs& a, int64_t task, int epv
   return t;
 }
 
+// Streaming where neighbouring lines are written together; strips of several rows leave a line's halves to
+// different instructions, which the cache joins.
+template <int VY, typename V>
+__device__ __forceinline__ void dw_store(V v, V* p) {
+  if constexpr (VY > 1) *p = v;
+  else __builtin_nontemporal_store(v, p);
+}
+
 // KH, KW, SW > 0: window and horizontal stride fixed at compile time; 0: run-time loops.
-template <typename T, int KH, int KW, int SW>
-__global__ void __launch_bounds__(256)
+// VY > 1 (vertical stride 1): a thread produces strips of VY output rows, one below the other, from
+// VY + KH - 1 input rows, each read, converted and cut at the border once.  The kernel is bound by the
+// instructions it issues, and with one row per strip two thirds of a 3x3 window's conversions repeat
+// what the rows above and below do.
+// EDGE: stride 1, "same" padding, rows of a multiple of eight: a strip's own eight columns are one
+// aligned vector of LDS and always inside the image, only its KW - 1 neighbours can be outside.
+template <typename T, int KH, int KW, int SW, int VY, bool EDGE>
+__global__ void __launch_bounds__(256, VY > 1 ? 3 : 1)
 depthwise_kernel(DwArgs a) {
   using A = typename DwElem<T>::acc;
   constexpr int ESZ = int(sizeof(T));
@@ -123,7 +140,7 @@ depthwise_kernel(DwArgs a) {
 
   int64_t task = blockIdx.x;
   if (task >= a.tasks) return;
-  DwTask cur = dw_task(a, task, EPV);
+  DwTask cur = dw_task<VY>(a, task, EPV);
   issue_loads(cur);
   for (; task < a.tasks; task += gridDim.x) {
     __syncthreads();                                   // the previous task has been computed
@@ -141,7 +158,7 @@ depthwise_kernel(DwArgs a) {
     __syncthreads();
     const DwTask t = cur;
     if (task + gridDim.x < a.tasks) {
-      cur = dw_task(a, task + gridDim.x, EPV);
+      cur = dw_task<VY>(a, task + gridDim.x, EPV);
       issue_loads(cur);
     }
 
@@ -158,14 +175,16 @@ depthwise_kernel(DwArgs a) {
         ++r;
       }
       uint32_t g = 0, yl = r;
-      if (a.G > 1) a.dHo.divmod(r, &g, &yl);           // G > 1: whole planes, nho == Ho
-      const int y = t.ho0 + int(yl);
+      if (a.G > 1) a.dHo.divmod(r, &g, &yl);           // G > 1: whole planes
+      const int y = t.ho0 + int(yl) * VY;
       const int x0 = int(xs) * kVX;
       const int iw0 = x0 * sw - a.Pw;                   // column of the first element of the span
       const A* wg = wl + __mul24(int(g), a.KKP);
-      A acc[kVX];
+      A accs[VY][kVX];
 #pragma unroll
-      for (int v = 0; v < kVX; ++v) acc[v] = 0;
+      for (int vy = 0; vy < VY; ++vy)
+#pragma unroll
+        for (int v = 0; v < kVX; ++v) accs[vy][v] = 0;
       if constexpr (FIXED) {
         constexpr int SPAN = (kVX - 1) * SW + KW;
         constexpr int KKP = (KH * KW + 3) / 4 * 4;
@@ -182,33 +201,53 @@ depthwise_kernel(DwArgs a) {
         const int ih_first = __mul24(y, a.Sh) - a.Ph;
         // 24-bit multiplies: LDS indices are far below 2^23
         const T* row0 = stage + (__mul24(__mul24(int(g), a.H) + ih_first, a.W) + iw0 - t.shift);
-        T raw[KH][SPAN];
+        constexpr int RIN = VY - 1 + KH;                // input rows of the strip
+        T raw[RIN][SPAN];
 #pragma unroll
-        for (int ky = 0; ky < KH; ++ky) {
+        for (int ky = 0; ky < RIN; ++ky) {
 #pragma unroll
           for (int j = 0; j < SPAN; ++j) raw[ky][j] = 0;
-          if (ih_first + ky >= 0 && ih_first + ky < a.H) {
+          // rows past the copy belong to output rows past the task's, which are not written
+          if (ih_first + ky >= 0 && ih_first + ky < t.ih1) {
             const T* row = row0 + ky * a.W;
+            if constexpr (EDGE) {
+              typedef T own_t __attribute__((ext_vector_type(kVX)));
+              constexpr int P = KW / 2;
+              const own_t own = *reinterpret_cast<const own_t*>(row + P);
 #pragma unroll
-            for (int j = 0; j < SPAN; ++j) raw[ky][j] = row[j];
+              for (int j = 0; j < P; ++j) {
+                raw[ky][j] = row[j];
+                raw[ky][P + kVX + j] = row[P + kVX + j];
+              }
+#pragma unroll
+              for (int j = 0; j < kVX; ++j) raw[ky][P + j] = own[j];
+            } else {
+#pragma unroll
+              for (int j = 0; j < SPAN; ++j) raw[ky][j] = row[j];
+            }
           }
         }
         // Element j of a span sits in column iw0 + j: columns left of the image (only the first
         // KW - 1 elements can be) and right of it hold a neighbouring row's data and count as zero.
         const int lo_bad = -iw0, hi_ok = a.W - iw0;
 #pragma unroll
-        for (int ky = 0; ky < KH; ++ky) {
+        for (int r_in = 0; r_in < RIN; ++r_in) {
           A e[SPAN];
 #pragma unroll
           for (int j = 0; j < SPAN; ++j) {
-            e[j] = DwElem<T>::cvt(raw[ky][j]);
-            if (j < KW - 1) e[j] = j >= lo_bad ? e[j] : A(0);
-            e[j] = j < hi_ok ? e[j] : A(0);
+            e[j] = DwElem<T>::cvt(raw[r_in][j]);
+            if (EDGE ? j < KW / 2 : j < KW - 1) e[j] = j >= lo_bad ? e[j] : A(0);
+            if (!EDGE || j >= KW / 2 + kVX) e[j] = j < hi_ok ? e[j] : A(0);
           }
 #pragma unroll
-          for (int v = 0; v < kVX; ++v)
+          for (int vy = 0; vy < VY; ++vy) {
+            const int ky = r_in - vy;
+            if (ky < 0 || ky >= KH) continue;
 #pragma unroll
-            for (int kx = 0; kx < KW; ++kx) acc[v] += e[v * SW + kx] * wr[ky * KW + kx];
+            for (int v = 0; v < kVX; ++v)
+#pragma unroll
+              for (int kx = 0; kx < KW; ++kx) accs[vy][v] += e[v * SW + kx] * wr[ky * KW + kx];
+          }
         }
       } else {
         for (int ky = 0; ky < kh; ++ky) {
@@ -220,51 +259,56 @@ depthwise_kernel(DwArgs a) {
 #pragma unroll
             for (int v = 0; v < kVX; ++v) {
               const int iw = iw0 + v * sw + kx;
-              if (iw >= 0 && iw < a.W && x0 + v < a.Wo) acc[v] += DwElem<T>::cvt(row[iw]) * wv;
+              if (iw >= 0 && iw < a.W && x0 + v < a.Wo) accs[0][v] += DwElem<T>::cvt(row[iw]) * wv;
             }
           }
         }
       }
-      if (a.relu) {
 #pragma unroll
-        for (int v = 0; v < kVX; ++v) acc[v] = acc[v] > A(0) ? acc[v] : A(0);
-      }
-      // within a task the results are fewer than 2^23 rows of fewer than 2^23 values
-      const int64_t o = obase + (int64_t(__mul24(__mul24(int(g), a.Ho) + y, a.Wo)) + x0);
-      if (a.vec_out && x0 + kVX <= a.Wo) {
-        if (a.out_dtype == GS_BF16) {
-          if constexpr (__is_same(A, float)) {
-            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-            u4 p;
+      for (int vy = 0; vy < VY; ++vy) {
+        if (vy > 0 && y + vy >= t.ho0 + t.nho) break;
+        A* const acc = accs[vy];
+        if (a.relu) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) p[q] = pack_bf16x2(acc[2 * q], acc[2 * q + 1]);
-            __builtin_nontemporal_store(p, reinterpret_cast<u4*>(static_cast<uint16_t*>(a.out) + o));
-          }
-        } else {                                        // 32-bit results: two 16-byte stores
-          typedef A a4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const a4 p = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-            __builtin_nontemporal_store(p, reinterpret_cast<a4*>(static_cast<A*>(a.out) + o) + q);
-          }
+          for (int v = 0; v < kVX; ++v) acc[v] = acc[v] > A(0) ? acc[v] : A(0);
         }
-      } else if (__is_same(A, float) && a.out_dtype == GS_BF16 && a.pair_out) {
-        // rows of an even number of results: pairs never straddle the end of a row
-        if constexpr (__is_same(A, float)) {
-#pragma unroll
-          for (int q = 0; q < kVX / 2; ++q)
-            if (x0 + 2 * q < a.Wo)
-              reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) + o)[q] = pack_bf16x2(acc[2 * q], acc[2 * q + 1]);
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < kVX; ++v) {
-          if (x0 + v < a.Wo) {
+        // within a task the results are fewer than 2^23 rows of fewer than 2^23 values
+        const int64_t o = obase + (int64_t(__mul24(__mul24(int(g), a.Ho) + y + vy, a.Wo)) + x0);
+        if (a.vec_out && x0 + kVX <= a.Wo) {
+          if (a.out_dtype == GS_BF16) {
             if constexpr (__is_same(A, float)) {
-              if (a.out_dtype == GS_BF16) static_cast<uint16_t*>(a.out)[o + v] = float_to_bf16_bits(acc[v]);
-              else static_cast<float*>(a.out)[o + v] = acc[v];
-            } else {
-              static_cast<int32_t*>(a.out)[o + v] = acc[v];
+              typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+              u4 p;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) p[q] = pack_bf16x2(acc[2 * q], acc[2 * q + 1]);
+              dw_store<VY>(p, reinterpret_cast<u4*>(static_cast<uint16_t*>(a.out) + o));
+            }
+          } else {                                        // 32-bit results: two 16-byte stores
+            typedef A a4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              const a4 p = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+              dw_store<VY>(p, reinterpret_cast<a4*>(static_cast<A*>(a.out) + o) + q);
+            }
+          }
+        } else if (__is_same(A, float) && a.out_dtype == GS_BF16 && a.pair_out) {
+          // rows of an even number of results: pairs never straddle the end of a row
+          if constexpr (__is_same(A, float)) {
+#pragma unroll
+            for (int q = 0; q < kVX / 2; ++q)
+              if (x0 + 2 * q < a.Wo)
+                reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) + o)[q] = pack_bf16x2(acc[2 * q], acc[2 * q + 1]);
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < kVX; ++v) {
+            if (x0 + v < a.Wo) {
+              if constexpr (__is_same(A, float)) {
+                if (a.out_dtype == GS_BF16) static_cast<uint16_t*>(a.out)[o + v] = float_to_bf16_bits(acc[v]);
+                else static_cast<float*>(a.out)[o + v] = acc[v];
+              } else {
+                static_cast<int32_t*>(a.out)[o + v] = acc[v];
+              }
             }
           }
         }
@@ -284,10 +328,16 @@ int dw_num_cus() {
   return n;
 }
 
-template <typename T>
-hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
+// What the EDGE kernels take.
+bool dw_edge(const DepthwiseArgs& d) {
+  return d.Sw == 1 && d.W % kVX == 0 && d.Wo == d.W && d.Pw == d.Kw / 2;
+}
+
+template <typename T, int VY>
+hipError_t launch_depthwise_rows(const DepthwiseArgs& d, hipStream_t s) {
   constexpr int ESZ = int(sizeof(T));
   constexpr int EPV = 16 / ESZ;
+  constexpr int kResident = VY > 1 ? 3 : 4;   // workgroups per compute unit that the registers allow
   using A = typename DwElem<T>::acc;
   DwArgs a;
   memset(&a, 0, sizeof(a));
@@ -308,8 +358,8 @@ hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
     // `slots` tasks at once; take the G with the fewest (rounds + one round of fixed cost) x passes.
     int gmax = int(cap / plane);
     gmax = gmax > 64 ? 64 : gmax;
-    const int64_t slots = int64_t(dw_num_cus()) * 4;
-    const int64_t strips = ceil_div(d.Wo, kVX) * d.Ho;
+    const int64_t slots = int64_t(dw_num_cus()) * kResident;
+    const int64_t strips = ceil_div(d.Wo, kVX) * ceil_div(d.Ho, VY);
     int64_t best = -1;
     a.G = 1;
     for (int g = 1; g <= gmax; ++g) {
@@ -337,7 +387,7 @@ hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
   a.dXS = FastDiv::make(uint32_t(a.XS));
   a.step_r = 256 / a.XS;
   a.step_xs = 256 % a.XS;
-  a.dHo = FastDiv::make(uint32_t(d.Ho));
+  a.dHo = FastDiv::make(uint32_t(ceil_div(d.Ho, VY)));
   a.dKK = FastDiv::make(uint32_t(d.Kh * d.Kw));
   a.vec_in = reinterpret_cast<uintptr_t>(d.in) % 16 == 0;
   a.vec_out = d.Wo % kVX == 0 && reinterpret_cast<uintptr_t>(d.out) % 16 == 0;
@@ -349,20 +399,47 @@ hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
   const size_t lds = a.lds_w + size_t(a.G) * a.KKP * sizeof(A);
   if (d.Pw * ESZ > kGuard || lds > 64 * 1024) return hipErrorInvalidValue;
   int per_cu = int((160 * 1024) / (lds + 512));
-  per_cu = per_cu < 1 ? 1 : per_cu > 4 ? 4 : per_cu;
+  per_cu = per_cu < 1 ? 1 : per_cu > kResident ? kResident : per_cu;
   int64_t grid = int64_t(dw_num_cus()) * per_cu;
   if (grid > a.tasks) grid = a.tasks;
   grid = ceil_div(a.tasks, ceil_div(a.tasks, grid));     // the same number of tasks for everyone
   const dim3 g{unsigned(grid)}, b{256};
-  if (d.Kh == 3 && d.Kw == 3 && d.Sw == 1)
-    hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 1>), g, b, lds, s, a);
-  else if (d.Kh == 3 && d.Kw == 3 && d.Sw == 2)
-    hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 2>), g, b, lds, s, a);
-  else if (d.Kh == 5 && d.Kw == 5 && d.Sw == 1)
-    hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 1>), g, b, lds, s, a);
-  else
-    hipLaunchKernelGGL((depthwise_kernel<T, 0, 0, 0>), g, b, lds, s, a);
+  if constexpr (VY == 4) {
+    hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 1, 4, true>), g, b, lds, s, a);
+  } else if constexpr (VY == 2) {
+    if (dw_edge(d)) hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 1, 2, true>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 1, 2, false>), g, b, lds, s, a);
+  } else if (d.Kh == 3 && d.Kw == 3 && d.Sw == 1) {
+    hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 1, 1, false>), g, b, lds, s, a);
+  } else if (d.Kh == 3 && d.Kw == 3 && d.Sw == 2) {
+    hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 2, 1, false>), g, b, lds, s, a);
+  } else if (d.Kh == 5 && d.Kw == 5 && d.Sw == 1) {
+    hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 1, 1, false>), g, b, lds, s, a);
+  } else {
+    hipLaunchKernelGGL((depthwise_kernel<T, 0, 0, 0, 1, false>), g, b, lds, s, a);
+  }
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
+  // Several rows per strip (four for 3x3; two for 5x5, whose twenty-five filter taps leave registers for no
+  // more) where every compute unit still has 256 strips, few of the rows are past the end, and it was the
+  // faster way over 32 images (us, one row per strip against several):
+  //   3x3 bfloat16 to bfloat16, aligned columns: 128 planes of 112x112 67.1 / 52.4, 56x56 20.9 / 17.6; but not
+  //   with unaligned columns (512 of 14x14 9.8 / 11.7, 128 of 57x61 to f32 44.1 / 48.9) or int8 (56x56 21.0 / 22.0);
+  //   5x5 to bfloat16: 128 of 112x112 139.5 / 97.4, 57x61 53.1 / 47.0, 256 of 14x14 11.1 / 9.2; to 32 bits only
+  //   with aligned columns (int8, 56x56 36.1 / 34.0, 55x55 44.8 / 47.6).
+  if (d.Sw == 1 && d.Sh == 1 && d.Ho >= 6) {
+    const bool edge = dw_edge(d), narrow = d.out_dtype == GS_BF16;
+    const int64_t row_strips = int64_t(d.N) * d.C * ceil_div(d.Wo, kVX), fill = int64_t(dw_num_cus()) * 256;
+    if constexpr (__is_same(T, uint16_t))
+      if (d.Kh == 3 && d.Kw == 3 && edge && narrow && row_strips * ceil_div(d.Ho, 4) >= fill)
+        return launch_depthwise_rows<T, 4>(d, s);
+    if (d.Kh == 5 && d.Kw == 5 && (edge || narrow) && row_strips * ceil_div(d.Ho, 2) >= fill)
+      return launch_depthwise_rows<T, 2>(d, s);
+  }
+  return launch_depthwise_rows<T, 1>(d, s);
 }
 
 }  // namespace

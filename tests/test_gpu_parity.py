@@ -808,6 +808,33 @@ def test_depthwise_conv2d(case):
     assert_parity(got, want, what=str(case))
 
 
+# Enough planes for strips of several output rows: heights that leave each remainder, bands, columns read as
+# aligned vectors (widths of a multiple of eight, "same" padding) and not; rows of NaN next to the border stay theirs.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("k,pad", [(3, 1), (3, 0), (5, 2)])
+@pytest.mark.parametrize("n,c,h,w_", [(64, 520, 8, 16), (61, 560, 7, 24), (64, 523, 9, 9), (16, 509, 30, 17), (16, 130, 54, 104), (2, 100, 203, 240)])
+def test_depthwise_strips_of_several_rows(n, c, h, w_, k, pad, dtype, odt):
+    x = gen(dtype, (n, c, h, w_), 3400 + c + h)
+    w = gen(dtype, (c, k, k), 3500 + c + k, 1.0 / k if dtype == "bf16" else 1.0)
+    if dtype == "bf16":
+        x[0, 0, 0] = float("nan")
+        x[-1, -1, -1] = float("inf")
+    got = gs.depthwise_conv2d(x.to(DEV), w.to(DEV), (1, 1), (pad, pad), gs.GS_ACT_NONE, odt).cpu()
+    wide = torch.float64
+    xp = torch.nn.functional.pad(x.to(wide), (pad, pad, pad, pad))
+    ho, wo = h + 2 * pad - k + 1, w_ + 2 * pad - k + 1
+    want = sum(xp[:, :, i:i + ho, j:j + wo] * w.to(wide)[None, :, i, j, None, None] for i in range(k) for j in range(k))
+    if dtype == "i8":
+        assert torch.equal(got, want.to(torch.int32))
+        return
+    finite = torch.isfinite(want)
+    assert torch.equal(finite, torch.isfinite(got)) and torch.equal(torch.isnan(want), torch.isnan(got))
+    # one rounding to the result's type, and k * k products summed in 32 bits
+    mag = sum(xp[:, :, i:i + ho, j:j + wo].abs() * w.to(wide).abs()[None, :, i, j, None, None] for i in range(k) for j in range(k))
+    bound = mag * (k * k * 2.0 ** -23) + (want.abs() * 2.0 ** -8 if odt == torch.bfloat16 else 0.0) + 1e-30
+    assert bool(((got.to(wide) - want).abs() <= bound)[finite].all())
+
+
 def test_depthwise_extremes_and_empty():
     x = torch.full((2, 3, 10, 10), -128, dtype=torch.int8)
     w = torch.full((3, 3, 3), -128, dtype=torch.int8)
