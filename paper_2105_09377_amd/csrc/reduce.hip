@@ -39,6 +39,15 @@ template <typename A> __device__ inline A ident(int op);
 template <> __device__ inline int32_t ident<int32_t>(int op) { return op == GS_MAX ? INT_MIN : 0; }
 template <> __device__ inline float ident<float>(int op) { return op == GS_MAX ? -INFINITY : 0.0f; }
 
+// What a padded cell holds: the identity among the values of the element type.  A window that lies
+// wholly in padding yields it, so folds over windows start here and not at ident<A>, which an 8-bit
+// result cannot hold.
+template <typename T> __device__ inline T ident_elem(int op);
+template <> __device__ inline int8_t ident_elem<int8_t>(int op) { return op == GS_MAX ? int8_t(-128) : int8_t(0); }
+template <> __device__ inline int32_t ident_elem<int32_t>(int op) { return op == GS_MAX ? INT_MIN : 0; }
+template <> __device__ inline float ident_elem<float>(int op) { return op == GS_MAX ? -INFINITY : 0.0f; }
+template <> __device__ inline uint16_t ident_elem<uint16_t>(int op) { return op == GS_MAX ? uint16_t(0xff80) : uint16_t(0); }
+
 template <typename A> __device__ inline A combine(A a, A b, int op) {
   if (op == GS_MAX) return a > b ? a : b;
   return a + b;
@@ -244,7 +253,7 @@ windows_reduce_kernel(const T* __restrict__ in, void* __restrict__ out, WindowsR
     int64_t plane = 1;
     for (int d = 0; d < a.n_compute; ++d) plane *= a.in_dim[d];
     const T* src = in + o * plane;
-    A acc = ident<A>(a.op);   // padded cells read the identity: lowest for max, zero for sum
+    A acc = Elem<T>::cvt(ident_elem<T>(a.op));   // padded cells: lowest for max, zero for sum
     const int64_t w0 = a.n_compute > 2 ? a.win[a.n_compute - 3] : 1;
     const int64_t w1 = a.n_compute > 1 ? a.win[a.n_compute - 2] : 1;
     const int64_t w2 = a.win[a.n_compute - 1];
@@ -302,12 +311,6 @@ struct Pool2dArgs {
 };
 
 constexpr int kPoolLdsBudget = 32 * 1024;
-
-template <typename T> __device__ inline T ident_elem(int op);
-template <> __device__ inline int8_t ident_elem<int8_t>(int op) { return op == GS_MAX ? int8_t(-128) : int8_t(0); }
-template <> __device__ inline int32_t ident_elem<int32_t>(int op) { return op == GS_MAX ? INT_MIN : 0; }
-template <> __device__ inline float ident_elem<float>(int op) { return op == GS_MAX ? -INFINITY : 0.0f; }
-template <> __device__ inline uint16_t ident_elem<uint16_t>(int op) { return op == GS_MAX ? uint16_t(0xff80) : uint16_t(0); }
 
 // Copies the input rows of one band into LDS; cells outside the image hold the identity.
 template <typename T>
@@ -439,7 +442,7 @@ pool2d_planes_kernel(Pool2dArgs a) {
     const int dx0 = ih < 0 ? -ih : 0, dx1 = a.H - ih < a.Kh ? a.H - ih : a.Kh;
     const int dy0 = iw < 0 ? -iw : 0, dy1 = a.W - iw < a.Kw ? a.W - iw : a.Kw;
     const T* w0 = stage + shift + int(g) * hw + ih * a.W + iw;
-    A acc = ident<A>(a.op);       // padded cells hold the identity
+    A acc = Elem<T>::cvt(ident_elem<T>(a.op));   // padded cells: lowest for max, zero for sum
     if constexpr (KH > 0) {
       A cell[KH * KW];
 #pragma unroll

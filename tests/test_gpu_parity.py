@@ -558,6 +558,28 @@ def test_pool_of_whole_planes(shape, win, stride, pad, dtype):
             assert_parity(got, want, what=f"{shape} {op}")
 
 
+# Padding of at least the window: some windows hold no element at all.  One case per kernel and window form:
+# planes pooled several to a workgroup, vectors, bands, and windows of one and three dimensions.
+@pytest.mark.parametrize("dtype", ["bf16", "i8", "i32", "f32"])
+@pytest.mark.parametrize("shape,window,stride,pad", [
+    ((3, 5, 4, 6), (1, 1), (1, 1), (1, 1)), ((3, 5, 4, 6), (2, 2), (1, 2), (2, 3)), ((2, 3, 7, 5), (3, 3), (1, 1), (4, 3)),
+    ((2, 3, 7, 5), (5, 4), (2, 1), (6, 5)), ((1, 2, 96, 112), (3, 3), (1, 1), (4, 1)), ((1, 1, 220, 300), (4, 4), (2, 2), (5, 6)),
+    ((3, 10), (2,), (1,), (3,)), ((2, 3, 4, 5), (1, 2, 2), (1, 1, 1), (1, 2, 2))])
+def test_windows_wholly_in_padding(shape, window, stride, pad, dtype):
+    x = gen(dtype, shape, 2400 + shape[-1])
+    if dtype == "i8":
+        x = x.clamp(max=-100)           # nothing above what padding holds by much
+    n_access = len(shape) - len(window)
+    got = gs.windows_reduce(x.to(DEV), n_access, window, stride, pad, pad, gs.GS_MAX)
+    want = ap.compute(ap.reduceMax, oracle_windows(x, n_access, window, stride, pad, pad, LOWEST[dtype])).materialize()
+    np.testing.assert_array_equal(to_oracle(got), want)
+    unfused = gs.reduce(gs.access_windows(x.to(DEV), n_access, window, stride, pad, pad, gs.GS_PAD_LOWEST), len(shape), gs.GS_MAX)
+    assert torch.equal(got, unfused)
+    total = gs.windows_reduce(x.to(DEV), n_access, window, stride, pad, pad, gs.GS_SUM)
+    want = ap.compute(ap.reduceSum, oracle_windows(x, n_access, window, stride, pad, pad, 0)).materialize()
+    assert_parity(total, want, what=f"{shape} {window}")
+
+
 def test_sum_pool_and_1d_windows_reduce():
     x = gen("f32", (3, 40), 1950)
     got = gs.windows_reduce(x.to(DEV), 1, (5,), (3,), (2,), (2,), gs.GS_SUM, scale=0.2)
