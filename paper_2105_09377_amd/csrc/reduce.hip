@@ -311,6 +311,10 @@ struct Pool2dArgs {
 };
 
 constexpr int kPoolLdsBudget = 32 * 1024;
+// Results of one workgroup of pool2d_planes_kernel at most.  Padding can make a plane's results many times
+// its elements: without a bound they would be counted past 32 bits, and done by one workgroup.  48 KB
+// of bytes with a result for each stay below it.
+constexpr int64_t kPlanesResults = 1 << 16;
 
 // Copies the input rows of one band into LDS; cells outside the image hold the identity.
 template <typename T>
@@ -618,10 +622,12 @@ static hipError_t launch_pool2d_t(const WindowsReduceArgs& w, hipStream_t s) {
   const bool known = (a.Kh == 3 && a.Kw == 3 && ((a.Sh == 2 && a.Sw == 2) || (a.Sh == 1 && a.Sw == 1)) && a.Pw == 1) ||
                      (a.Kh == 2 && a.Kw == 2 && a.Sh == 2 && a.Sw == 2 && a.Pw == 0);
   if (reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && plane_bytes <= 48 * 1024 && plane_bytes > 0 && w.outer > 0 &&
-      int64_t(a.Ho) * a.Wo < (1 << 20) && (plane_bytes < 8192 || !(vec_rows && known && EPV % a.Sw == 0))) {
+      int64_t(a.Ho) * a.Wo <= kPlanesResults && (plane_bytes < 8192 || !(vec_rows && known && EPV % a.Sw == 0))) {
     int64_t want = w.outer * plane_bytes / 2048;
     want = want < 4096 ? 4096 : want > 16384 ? 16384 : want;
-    const int64_t g = want / plane_bytes > 1 ? want / plane_bytes : 1;
+    int64_t g = want / plane_bytes > 1 ? want / plane_bytes : 1;
+    const int64_t most = kPlanesResults / (int64_t(a.Ho) * a.Wo);
+    if (g > most) g = most;
     const int64_t blocks = ceil_div(w.outer, g);
     if (blocks <= 0x7fffffff) {
       a.G = int(g);

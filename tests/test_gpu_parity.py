@@ -580,6 +580,22 @@ def test_windows_wholly_in_padding(shape, window, stride, pad, dtype):
     assert_parity(total, want, what=f"{shape} {window}")
 
 
+# Padding that makes many results of few elements: small planes whose workgroup's results would pass 2^31 if
+# planes were counted by their elements only (the first), and ones that leave a workgroup a few planes.
+@pytest.mark.parametrize("planes,size,pad", [(4100, 1, 363), (300, 2, 60), (33, 3, 130)])
+def test_pool_of_small_planes_under_wide_padding(planes, size, pad):
+    x = torch.randint(-127, 0, (planes, size, size), dtype=torch.int8)
+    got = gs.windows_reduce(x.to(DEV), 1, (size, size), (1, 1), (pad, pad), (pad, pad), gs.GS_MAX)
+    out = 2 * pad + 1
+    assert tuple(got.shape) == (planes, out, out)
+    # only the windows within size - 1 of the middle one hold an element
+    lo, hi = pad - size + 1, pad + size
+    want = torch.nn.functional.max_pool2d(torch.nn.functional.pad(x.float(), (size - 1,) * 4, value=-128.0)[:, None], size, 1)[:, 0]
+    assert torch.equal(got[:, lo:hi, lo:hi].cpu(), want.to(torch.int8))
+    got[:, lo:hi, lo:hi] = -128
+    assert int(got.max()) == -128 and int(got.min()) == -128
+
+
 def test_sum_pool_and_1d_windows_reduce():
     x = gen("f32", (3, 40), 1950)
     got = gs.windows_reduce(x.to(DEV), 1, (5,), (3,), (2,), (2,), gs.GS_SUM, scale=0.2)
