@@ -614,24 +614,45 @@ static hipError_t launch_pool2d_t(const WindowsReduceArgs& w, hipStream_t s) {
   a.Ph = int(w.pad_lo[0]); a.Pw = int(w.pad_lo[1]);
   a.planes = w.outer;
   a.dWo = FastDiv::make(uint32_t(a.Wo));
-  // Planes that the vector kernel below does not take, or that would leave most of its workgroup
-  // idle, and that fit the LDS: several planes per workgroup, 4 KB (one vector per thread) of small
-  // inputs, up to 16 KB of those that fill the chip anyway.
-  const int64_t plane_bytes = int64_t(a.H) * a.W * ESZ;
-  const bool vec_rows = (a.W * ESZ) % 16 == 0 && reinterpret_cast<uintptr_t>(a.in) % 16 == 0;
+  // Whole planes to a workgroup, or bands of one plane below?  Measured both ways over 1212 cases (device
+  // time in us, whole planes / bands):
+  //   rows and windows that the vector kernel takes: whole planes up to 1 KB of results, where its
+  //   workgroup would be mostly idle (2x2: 4096 planes of 40x40 bfloat16 9.0 / 9.3, of 56x56 13.1 / 8.7;
+  //   3x3 stride 1: 16384 of 16x16 8.6 / 10.4, 4096 of 56x56 46.2 / 15.4);
+  //   other rows or windows: whole planes while a workgroup has at most one result per thread, or the
+  //   planes are enough to give every compute unit one (half of them where the windows do not overlap
+  //   much), since only bands can use the rest of the chip (16 of 75x77, 3x3 stride 1: 17.5 / 4.4;
+  //   1024 of them 18.3 / 20.6); not where every element is folded more than 16 times, which
+  //   the cut at the plane's edges makes dear (4096 of 24x8 bytes, 5x5 stride 1: 24.8 / 12.1); and up
+  //   to 24 KB, beyond which the LDS holds too few workgroups to hide the copy (1024 of 100x100 f32, 5x5
+  //   stride 1: 82.6 / 67.6), or 48 KB of windows that overlap little (512 of 150x150 bfloat16, 2x2: 17.1 /
+  //   24.7), unless they are few and the bands read 16 bytes at a time (512 of 100x100 f32, 7x7: 9.1 / 6.7).
+  const int64_t plane_bytes = int64_t(a.H) * a.W * ESZ, results = int64_t(a.Ho) * a.Wo, folds = results * a.Kh * a.Kw;
+  const bool aligned = reinterpret_cast<uintptr_t>(a.in) % 16 == 0;
   const bool known = (a.Kh == 3 && a.Kw == 3 && ((a.Sh == 2 && a.Sw == 2) || (a.Sh == 1 && a.Sw == 1)) && a.Pw == 1) ||
                      (a.Kh == 2 && a.Kw == 2 && a.Sh == 2 && a.Sw == 2 && a.Pw == 0);
-  if (reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && plane_bytes <= 48 * 1024 && plane_bytes > 0 && w.outer > 0 &&
-      int64_t(a.Ho) * a.Wo <= kPlanesResults && (plane_bytes < 8192 || !(vec_rows && known && EPV % a.Sw == 0))) {
-    int64_t want = w.outer * plane_bytes / 2048;
-    want = want < 4096 ? 4096 : want > 16384 ? 16384 : want;
+  const bool vec_rows = aligned && (a.W * ESZ) % 16 == 0, vec = vec_rows && known && EPV % a.Sw == 0;
+  const int64_t elems = int64_t(a.H) * a.W;
+  const bool light = folds <= 3 * elems;          // windows overlap little
+  const bool enough = w.outer >= (light ? reduce_num_cus() / 2 : reduce_num_cus());
+  const bool whole = vec ? results * ESZ <= 1024 : results <= 256 || (enough && folds <= 16 * elems);
+  if (aligned && whole && plane_bytes <= (light && (results > 256 || !vec_rows) ? 48 : 24) * 1024 && plane_bytes > 0 && w.outer > 0 && results <= kPlanesResults) {
+    // Planes per workgroup: four workgroups to a compute unit of up to 8 KB (every 1024 workgroups more cost
+    // 0.6 us; 1024 planes of 14x14 bfloat16, 5x5 stride 1: 4.7 us, 15.2 in workgroups of 4 KB), then
+    // eight of up to 16 KB (65536 planes of 16x16 bytes, 3x3 stride 1: 40.1 us in four of 16 KB, 35.1), and
+    // 32 results, or the launch is the longest part (2048 planes of 7x7, 7x7: 7.1 us with two each, 5.2).
+    const int64_t bytes = w.outer * plane_bytes, cus = reduce_num_cus();
+    int64_t want = bytes / (8 * cus) > 8192 ? bytes / (8 * cus) : 8192;
+    if (want > bytes / (4 * cus)) want = bytes / (4 * cus);
+    if (want < 32 * plane_bytes / results) want = 32 * plane_bytes / results;
+    if (want > 16384) want = 16384;
     int64_t g = want / plane_bytes > 1 ? want / plane_bytes : 1;
-    const int64_t most = kPlanesResults / (int64_t(a.Ho) * a.Wo);
+    const int64_t most = kPlanesResults / results;
     if (g > most) g = most;
     const int64_t blocks = ceil_div(w.outer, g);
     if (blocks <= 0x7fffffff) {
       a.G = int(g);
-      a.dplane = FastDiv::make(uint32_t(a.Ho * a.Wo));
+      a.dplane = FastDiv::make(uint32_t(results));
       const dim3 grid{unsigned(blocks)}, block{256};
       const size_t lds = size_t(round_up(g * plane_bytes, 16) + 32);
       if (a.Kh == 2 && a.Kw == 2) hipLaunchKernelGGL((pool2d_planes_kernel<T, 2, 2>), grid, block, lds, s, a);

@@ -580,6 +580,20 @@ def test_windows_wholly_in_padding(shape, window, stride, pad, dtype):
     assert_parity(total, want, what=f"{shape} {window}")
 
 
+# Both sides of the lines between whole planes and bands: results per plane (a workgroup's threads, 1 KB where rows
+# are vectors), planes per compute unit, folds per element, bytes per plane.
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("planes,h,w,win,stride,pad", [
+    (5, 16, 16, 3, 1, 1), (5, 17, 16, 3, 1, 1), (5, 16, 17, 3, 1, 1), (3, 47, 32, 3, 1, 1), (3, 63, 64, 2, 2, 0), (2, 65, 64, 2, 2, 0),
+    (127, 35, 33, 2, 2, 0), (128, 35, 33, 2, 2, 0), (255, 35, 33, 3, 1, 1), (256, 35, 33, 3, 1, 1), (256, 35, 33, 5, 1, 2),
+    (256, 35, 33, 4, 1, 1), (256, 111, 111, 3, 2, 1), (257, 156, 157, 3, 2, 1), (130, 156, 157, 2, 2, 0), (1, 220, 223, 2, 2, 0)])
+def test_pool_whole_planes_or_bands(planes, h, w, win, stride, pad, dtype):
+    x = gen(dtype, (planes, h, w), 2500 + planes + h)
+    got = gs.windows_reduce(x.to(DEV), 1, (win, win), (stride, stride), (pad, pad), (pad, pad), gs.GS_MAX)
+    want = torch.nn.functional.max_pool2d(torch.nn.functional.pad(x.float()[:, None], (pad,) * 4, value=-float("inf")), win, stride)
+    assert torch.equal(got.cpu().float(), want[:, 0])
+
+
 # Padding that makes many results of few elements: small planes whose workgroup's results would pass 2^31 if
 # planes were counted by their elements only (the first), and ones that leave a workgroup a few planes.
 @pytest.mark.parametrize("planes,size,pad", [(4100, 1, 363), (300, 2, 60), (33, 3, 130)])
