@@ -277,14 +277,15 @@ __device__ __forceinline__ i32x4 row_piece_fix(i32x4 v, int64_t over) {
   }
   return i32x4{int32_t(uint32_t(lo)), int32_t(uint32_t(lo >> 32)), int32_t(uint32_t(hi)), int32_t(uint32_t(hi >> 32))};
 }
-// Rows shorter than 16 bytes: every byte requested at once, the ones past the end replaced by zero.
-__device__ __forceinline__ i32x4 short_row_piece(const uint8_t* row, int64_t kb, int64_t Kb) {
+// A row of Kb < 16 bytes as one piece: every byte requested at once, the ones past the end replaced by zero.
+__device__ __forceinline__ i32x4 short_row(const uint8_t* row, int64_t Kb) {
+  if (Kb <= 0) return i32x4{0, 0, 0, 0};
   uint32_t byte[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) byte[t] = row[t < Kb ? t : 0];
   uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int t = 0; t < 16; ++t) w[t >> 2] |= (kb + t < Kb ? byte[t] : 0u) << (8 * (t & 3));
+  for (int t = 0; t < 16; ++t) w[t >> 2] |= (t < Kb ? byte[t] : 0u) << (8 * (t & 3));
   return i32x4{int32_t(w[0]), int32_t(w[1]), int32_t(w[2]), int32_t(w[3])};
 }
 
@@ -293,7 +294,9 @@ __device__ __forceinline__ i32x4 short_row_piece(const uint8_t* row, int64_t kb,
 // buffer.  Bound by LDS traffic (a slab of a 128x128 tile is written once, 436 cycles at 75 bytes per
 // cycle, and read as 98 KB of fragments, 610 at 160, against 256-512 of MFMAs).  2047 x 1531 x 1001:
 // e4m3 85 -> 13.8 us, bf16 18.7, int8 15.6 (before: 16-byte pieces gathered byte by byte).
-template <typename TR, int BM, int BN, int WGM, int WGN>
+// SHORT: rows of fewer than 16 bytes (empty ones included): one piece per row, one MFMA step, and the
+// result is what takes the time.
+template <typename TR, int BM, int BN, int WGM, int WGN, bool SHORT>
 __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a) {
   constexpr int NT = WGM * WGN * 64, D = 2;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
@@ -334,6 +337,18 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a)
     });
   });
 
+  constexpr int KST = TR::kStep, P = KST / 32;           // bytes of K per MFMA step; 16-byte pieces per lane
+  if constexpr (SHORT) {
+    for (int r = tid; r < BM + BN; r += NT) {
+      const int64_t i = r < BM ? i0 + r : j0 + r - BM, lim = r < BM ? box.ilim : box.jlim;
+      const uint8_t* row = static_cast<const uint8_t*>(r < BM ? a.x : a.y) +
+                           (i < lim ? i : lim - 1) * (r < BM ? a.ldx : a.ldy) * TR::kEsz;
+      i32x4* dst = reinterpret_cast<i32x4*>(lds + r * kRowBytes);
+      dst[0] = short_row(row, Kb);
+#pragma unroll
+      for (int f = 1; f < KST / 16; ++f) dst[f] = i32x4{0, 0, 0, 0};
+    }
+  }
   i32x4 piece[D][XCH + YCH];
   auto load = [&](int slab, auto slot_) {
     constexpr int slot = decltype(slot_)::value;
@@ -359,13 +374,12 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a)
     for (int r = 0; r < YCH; ++r)
       *reinterpret_cast<i32x4*>(dst + kXBytes + r * (NT / 8) * kRowBytes) = piece[slot][XCH + r];
   };
-  constexpr int KST = TR::kStep, P = KST / 32;           // bytes of K per MFMA step; 16-byte pieces per lane
   const uint8_t* const frag = lds + (lane & 31) * kRowBytes + (lane >> 5) * (KST / 2);
   auto multiply = [&](int buf) {
     const uint8_t* xs = frag + buf * kBuf + wm * WM * kRowBytes;
     const uint8_t* ys = frag + buf * kBuf + kXBytes + wn * WN * kRowBytes;
 #pragma unroll
-    for (int ks = 0; ks < kSlabBytes / KST; ++ks) {
+    for (int ks = 0; ks < (SHORT ? 1 : kSlabBytes / KST); ++ks) {
       i32x4 xf[MI * P], yf[NJ * P];
 #pragma unroll
       for (int m = 0; m < MI; ++m)
@@ -384,24 +398,30 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a)
     }
   };
 
-  static_for<D>([&](auto d_) { load(decltype(d_)::value, d_); });
-  store(0, std::integral_constant<int, 0>{}, 0);
-  load(D, std::integral_constant<int, 0>{});
-  lds_barrier();
-  for (int s0 = 0; s0 < nslab; s0 += D) {
-    static_for<D>([&](auto i_) {
-      constexpr int i = decltype(i_)::value;
-      using Next = std::integral_constant<int, (i + 1) % D>;
-      const int s = s0 + i;
-      if (s < nslab) {                                   // uniform
-        if (s + 1 < nslab) {
-          store(s + 1, Next{}, (i + 1) & 1);
-          load(s + 1 + D, Next{});
+  if constexpr (SHORT) {
+    lds_barrier();
+    multiply(0);
+    lds_barrier();
+  } else {
+    static_for<D>([&](auto d_) { load(decltype(d_)::value, d_); });
+    store(0, std::integral_constant<int, 0>{}, 0);
+    load(D, std::integral_constant<int, 0>{});
+    lds_barrier();
+    for (int s0 = 0; s0 < nslab; s0 += D) {
+      static_for<D>([&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        using Next = std::integral_constant<int, (i + 1) % D>;
+        const int s = s0 + i;
+        if (s < nslab) {                                   // uniform
+          if (s + 1 < nslab) {
+            store(s + 1, Next{}, (i + 1) & 1);
+            load(s + 1 + D, Next{});
+          }
+          multiply(i & 1);
+          lds_barrier();
         }
-        multiply(i & 1);
-        lds_barrier();
-      }
-    });
+      });
+    }
   }
   write_tile<TR, MI, NJ>(a, box, acc, i0 + wm * WM, j0 + wn * WN, lds + wave * (32 * (WN * 4 + 16)), lane);
 }
@@ -411,10 +431,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a)
 // moves and multiplies its own slabs in LDS of its own, two at a time, without any barrier; the
 // NW partial tiles are added pairwise at the end.  Bound by one memory latency, the launch and
 // the final exchange: with up to 2 NW slabs all of K is requested at once.  kDirect: aligned rows of whole MFMA steps,
-// transferred global -> LDS; kStaged: any alignment, through registers; kShortRows: rows of fewer
-// than 16 bytes (empty ones included).
+// transferred global -> LDS; kStaged: any alignment, rows of at least 16 bytes, through registers.
 // ---------------------------------------------------------------------------------------------
-enum KsplitLoad { kDirect, kStaged, kShortRows };   // see gemm_nt_ksplit_kernel
+enum KsplitLoad { kDirect, kStaged };   // see gemm_nt_ksplit_kernel
 template <typename TR, int NW, KsplitLoad LOAD>
 __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
   constexpr int KST = TR::kStep, P = KST / 32, KS = kSlabBytes / KST;
@@ -464,19 +483,11 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
       }
     } else {
       const int64_t kb = k0 + col * 16;
-      if constexpr (LOAD == kStaged) {
-        const int64_t at = kb < Kb - 16 ? kb : Kb - 16;
+      const int64_t at = kb < Kb - 16 ? kb : Kb - 16;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          piece[slot][q] = *reinterpret_cast<const i32x4_any*>(xp[q] + at);
-          piece[slot][4 + q] = *reinterpret_cast<const i32x4_any*>(yp[q] + at);
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          piece[slot][q] = short_row_piece(xp[q], kb, Kb);
-          piece[slot][4 + q] = short_row_piece(yp[q], kb, Kb);
-        }
+      for (int q = 0; q < 4; ++q) {
+        piece[slot][q] = *reinterpret_cast<const i32x4_any*>(xp[q] + at);
+        piece[slot][4 + q] = *reinterpret_cast<const i32x4_any*>(yp[q] + at);
       }
     }
   };
@@ -499,7 +510,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
           if (t + 1 < cnt) wait_vmem<8>();               // the next slab's transfers stay in flight
           else wait_vmem<0>();
         } else {
-          if (LOAD == kStaged && slab == nslab - 1) {
+          if (slab == nslab - 1) {
             const int64_t over = int64_t(slab) * kSlabBytes + col * 16 - (Kb - 16);
 #pragma unroll
             for (int q = 0; q < 8; ++q) piece[i][q] = row_piece_fix(piece[i][q], over);
@@ -825,9 +836,9 @@ static hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
   return launch_tiles<gemm_nt_dma_kernel<TR, BM, BN, WGM, WGN, SB, NS>>(a, BM, BN, WGM * WGN * 64, lds_bytes, s);
 }
-template <typename TR, int BM, int BN, int WGM, int WGN>
+template <typename TR, int BM, int BN, int WGM, int WGN, bool SHORT>
 static hipError_t launch_any(const GemmArgs& a, hipStream_t s) {
-  return launch_tiles<gemm_nt_any_kernel<TR, BM, BN, WGM, WGN>>(a, BM, BN, WGM * WGN * 64, 2 * (BM + BN) * kRowBytes, s);
+  return launch_tiles<gemm_nt_any_kernel<TR, BM, BN, WGM, WGN, SHORT>>(a, BM, BN, WGM * WGN * 64, 2 * (BM + BN) * kRowBytes, s);
 }
 template <typename TR, int NW, KsplitLoad LOAD>
 static hipError_t launch_ksplit(const GemmArgs& a, hipStream_t s) {
@@ -894,16 +905,19 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
       v.vj = cand;
   }
   if (v.vj == 1 && a.jp >= a.J) v.vj = 2;    // plain rows
-  if (a.K * TR::kEsz < 16) return launch_ksplit<TR, 4, kShortRows>(v, s);
+  // Rows of fewer than 16 bytes: one MFMA step per tile, in tiles as large as the others at any size (8192 x
+  // 8192 x 7 bf16 to f32 51.8 us, 133 with 64x64 tiles gathered byte by byte, 980 in 32x32 tiles dealt to
+  // waves; 64 x 64 x 7 3.2, 7.9 and 5.1).
+  const bool is_short = a.K * TR::kEsz < 16;
   if (dma) return launch_dma_tiles<TR>(v, s);
   bool eight;
-  if (few_tiles<TR>(v, &eight))
+  if (!is_short && few_tiles<TR>(v, &eight))
     return eight ? launch_ksplit<TR, 8, kStaged>(v, s) : launch_ksplit<TR, 4, kStaged>(v, s);
   // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.8 us
   // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6
   const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
-  if (t128 >= 160) return launch_any<TR, 128, 128, 2, 4>(v, s);
-  return launch_any<TR, 64, 64, 2, 2>(v, s);
+  if (t128 >= 160) return is_short ? launch_any<TR, 128, 128, 2, 4, true>(v, s) : launch_any<TR, 128, 128, 2, 4, false>(v, s);
+  return is_short ? launch_any<TR, 64, 64, 2, 2, true>(v, s) : launch_any<TR, 64, 64, 2, 2, false>(v, s);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {

@@ -165,6 +165,33 @@ def test_cartesian_dot_tile_edges(mnk, dtype, odt):
     assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
 
 
+# Rows of fewer than 16 bytes (and of none) at any size: one tile, cut tiles, 64x64 and 128x128 ones, narrow results.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32), ("fp8", torch.bfloat16)])
+@pytest.mark.parametrize("mnk", [(1, 1, 0), (130, 70, 0), (33, 65, 1), (129, 64, 7), (700, 333, 3), (1281, 2047, 5), (1664, 1280, 7), (30000, 3, 2),
+                                 (2, 30001, 7)])
+def test_cartesian_dot_short_rows(mnk, dtype, odt):
+    m, n, k = mnk
+    if dtype in ("i8", "fp8"):
+        k = 2 * k + (1 if k > 1 else 0)
+    a0, a1 = gen(dtype, (m, k), 1420 + m), gen(dtype, (n, k), 1520 + n)
+    buf = torch.full((m * n + 512,), 77, dtype=odt, device=DEV)
+    got = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), act=gs.GS_ACT_RELU, out=buf[256:256 + m * n].view(m, n))
+    x, y = to_oracle(a0), to_oracle(a1)
+    assert_parity(got, np.maximum(brute.matmul(x, y.T), 0), what=str(mnk), slack=fp8_slack(x, y) if dtype == "fp8" else None)
+    assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8", "fp8"])
+def test_blocked_dot_of_short_slices(dtype):
+    """K slices of fewer than 16 bytes at every alignment, each added to the result of those in front."""
+    m, n, k = 150, 139, 17
+    a0, a1 = gen(dtype, (m, k), 1440), gen(dtype, (n, k), 1540)
+    x, y = to_oracle(a0), to_oracle(a1)
+    for tile_k in (3, 5, 7):
+        got = gs.cartesian_dot_blocked(a0.to(DEV), a1.to(DEV), 70, 65, tile_k)
+        assert_parity(got, brute.matmul(x, y.T), what=str(tile_k), slack=fp8_slack(x, y) if dtype == "fp8" else None)
+
+
 def test_cartesian_dot_extreme_int8_values():
     """-128 * -128 * K stays exact in int32."""
     a0 = torch.full((40, 512), -128, dtype=torch.int8)
