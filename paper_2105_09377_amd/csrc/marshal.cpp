@@ -55,7 +55,7 @@ int dtype_code(at::ScalarType t) {
   }
 }
 
-// Descriptor of a contiguous tensor with n_access access dimensions (-1 = all of them).
+// Descriptor of a contiguous tensor with n_access access dimensions (the library refuses impossible ones).
 gs_ap describe(const at::Tensor& t, int64_t n_access) {
   gs_ap a{};
   if (!t.is_contiguous()) {
@@ -70,10 +70,12 @@ gs_ap describe(const at::Tensor& t, int64_t n_access) {
   a.data = t.data_ptr();
   a.dtype = dtype_code(t.scalar_type());
   a.rank = int32_t(sizes.size());
-  a.n_access = int32_t(n_access < 0 ? a.rank : n_access);
+  a.n_access = int32_t(n_access);
   for (size_t i = 0; i < sizes.size(); ++i) a.shape[i] = sizes[i];
   return a;
 }
+// Every dimension an access dimension: results and element-wise operands.
+gs_ap describe_all(const at::Tensor& t) { return describe(t, t.dim()); }
 
 int64_t integer(PyObject* o) {
   if (PyLong_CheckExact(o)) {
@@ -195,7 +197,7 @@ PyObject* py_cartesian_dot(PyObject*, PyObject* const* p, Py_ssize_t n) {
     }
     Result out(p[6], p[4], sum_type(a0), shape, rank, a0);
     r = out.object;
-    gs_ap x = describe(a0, n0), y = describe(a1, n1), o = describe(out.value, -1);
+    gs_ap x = describe(a0, n0), y = describe(a1, n1), o = describe_all(out.value);
     void* s = stream_of(a0);
     call("cartesian_dot", [&] { return api.cartesian_dot(&x, &y, &o, act, nullptr, 0, s); });
   });
@@ -239,7 +241,7 @@ PyObject* py_conv(PyObject*, PyObject* const* p, Py_ssize_t n) {
       ws = at::empty({int64_t(need > 16 ? need : 16)}, at::TensorOptions().dtype(at::kByte).device(x.device()));
     }
     gs_ap oa = describe(out.value, 4), ra{};
-    if (p[5] != Py_None) ra = describe(tensor(p[5]), -1);
+    if (p[5] != Py_None) ra = describe_all(tensor(p[5]));
     const gs_ap* res = p[5] != Py_None ? &ra : nullptr;
     void *wsp = ws.data_ptr(), *s = stream_of(x);
     const size_t bytes = size_t(ws.numel());
@@ -267,7 +269,7 @@ PyObject* py_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
     const int64_t dims = x.dim(), lead = na < 0 ? (na + dims > 0 ? na + dims : 0) : na < dims ? na : dims;
     Result out(p[5], p[4], reduce_type(x, op), sizes.data(), int(lead), x);
     r = out.object;
-    gs_ap xa = describe(x, 0), oa = describe(out.value, -1);
+    gs_ap xa = describe(x, 0), oa = describe_all(out.value);
     xa.n_access = int32_t(na);
     void* s = stream_of(x);
     call("reduce", [&] { return api.reduce(&xa, op, float(scale), &oa, s); });
@@ -289,7 +291,7 @@ PyObject* py_windows_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
       call("windows_out_shape", [&] { return api.windows_out_shape(&xa, window.get(), stride.get(), lo.get(), hi.get(), &want); });
     Result out(p[9], p[8], reduce_type(x, op), want.shape, want.n_access, x);
     r = out.object;
-    gs_ap oa = describe(out.value, -1);
+    gs_ap oa = describe_all(out.value);
     void* s = stream_of(x);
     call("windows_reduce", [&] {
       return api.windows_reduce(&xa, window.get(), stride.get(), lo.get(), hi.get(), op, float(scale), &oa, s);
@@ -349,7 +351,7 @@ PyObject* py_pair_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
     const int op = int(integer(p[2])), act = int(integer(p[3]));
     Result out(p[4], Py_None, a.scalar_type(), a.sizes().data(), int(a.dim()), a);
     r = out.object;
-    gs_ap xa = describe(a, -1), ya = describe(b, -1), oa = describe(out.value, -1);
+    gs_ap xa = describe_all(a), ya = describe_all(b), oa = describe_all(out.value);
     void* s = stream_of(a);
     call("pair_reduce", [&] { return api.pair_reduce(&xa, &ya, op, act, &oa, s); });
   });
