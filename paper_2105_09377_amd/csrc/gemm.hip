@@ -914,9 +914,13 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   if (!is_short && few_tiles<TR>(v, &eight))
     return eight ? launch_ksplit<TR, 8, kStaged>(v, s) : launch_ksplit<TR, 4, kStaged>(v, s);
   // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.8 us
-  // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6
+  // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6.  Results (or
+  // blocks) of up to 64 rows or columns would leave half of every tile empty (100000 x 10 x 65 bf16 to
+  // bf16: 17.4 against 12.0; 64 x 40000 x 1001 bf16 to f32: 30.4 against 24.0).
   const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
-  if (t128 >= 160) return is_short ? launch_any<TR, 128, 128, 2, 4, true>(v, s) : launch_any<TR, 128, 128, 2, 4, false>(v, s);
+  const int64_t fi = a.bm > 0 && a.bm < a.I ? a.bm : a.I, fj = a.bn > 0 && a.bn < a.J ? a.bn : a.J;
+  if (t128 >= 160 && fi > 64 && fj > 64)
+    return is_short ? launch_any<TR, 128, 128, 2, 4, true>(v, s) : launch_any<TR, 128, 128, 2, 4, false>(v, s);
   return is_short ? launch_any<TR, 64, 64, 2, 2, true>(v, s) : launch_any<TR, 64, 64, 2, 2, false>(v, s);
 }
 

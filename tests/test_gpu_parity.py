@@ -165,6 +165,23 @@ def test_cartesian_dot_tile_edges(mnk, dtype, odt):
     assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
 
 
+# Many 128x128 tiles that a narrow result would leave half empty, and the first width at which it does not.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("i8", torch.int32)])
+@pytest.mark.parametrize("mnk", [(20600, 64, 65), (64, 20600, 33), (20600, 65, 33), (65, 20600, 65), (1, 20600, 129), (20600, 1, 129)])
+def test_cartesian_dot_narrow_results(mnk, dtype, odt):
+    m, n, k = mnk
+    a0, a1 = gen(dtype, (m, k), 1450 + m), gen(dtype, (n, k), 1550 + n)
+    got = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), out_dtype=odt)
+    assert_parity(got, brute.matmul(to_oracle(a0), to_oracle(a1).T), what=str(mnk))
+
+
+def test_blocked_dot_of_narrow_blocks():
+    a0, a1 = gen("bf16", (1300, 77), 1460), gen("bf16", (900, 77), 1560)
+    for tile in ((40, 50), (64, 300), (300, 64), (65, 65)):
+        got = gs.cartesian_dot_blocked(a0.to(DEV), a1.to(DEV), *tile, 77)
+        assert_parity(got, brute.matmul(to_oracle(a0), to_oracle(a1).T), what=str(tile))
+
+
 # Rows of fewer than 16 bytes (and of none) at any size: one tile, cut tiles, 64x64 and 128x128 ones, narrow results.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32), ("fp8", torch.bfloat16)])
 @pytest.mark.parametrize("mnk", [(1, 1, 0), (130, 70, 0), (33, 65, 1), (129, 64, 7), (700, 333, 3), (1281, 2047, 5), (1664, 1280, 7), (30000, 3, 2),
