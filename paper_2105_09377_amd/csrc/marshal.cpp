@@ -91,6 +91,16 @@ int64_t integer(PyObject* o) {
   return v;
 }
 
+// A new reference, held until the end of the scope.
+struct Owned {
+  PyObject* object;
+  explicit Owned(PyObject* o) : object(o) {
+    if (!o) throw Failed{};
+  }
+  ~Owned() { Py_DECREF(object); }
+  Owned(const Owned&) = delete;
+};
+
 // A sequence of integers; None = absent (a null pointer at the C boundary).
 struct Ints {
   int64_t v[2 * GS_MAX_RANK] = {};
@@ -391,7 +401,9 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
       PyErr_SetString(PyExc_TypeError, "tensors and integers are given as dicts by name");
       throw Failed{};
     }
-    // the name strings are owned by the dicts, which the caller keeps alive
+    // Names and tensors are borrowed from copies of the dicts: the caller's may change meanwhile, from another
+    // thread while the interpreter lock is released, or from the conversion of an integer.
+    const Owned named(PyDict_Copy(p[1])), numbers(PyDict_Copy(p[2]));
     auto name_of = [](PyObject* key) {
       const char* s = PyUnicode_AsUTF8(key);
       if (!s) throw Failed{};
@@ -401,12 +413,12 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
     std::vector<gs_named_int> ints;
     const at::Tensor* first = nullptr;
     PyObject *key, *value;
-    for (Py_ssize_t pos = 0; PyDict_Next(p[1], &pos, &key, &value);) {
+    for (Py_ssize_t pos = 0; PyDict_Next(named.object, &pos, &key, &value);) {
       const at::Tensor& t = tensor(value);
       if (!first) first = &t;
       tensors.push_back({name_of(key), describe(t, 0)});
     }
-    for (Py_ssize_t pos = 0; PyDict_Next(p[2], &pos, &key, &value);) ints.push_back({name_of(key), integer(value)});
+    for (Py_ssize_t pos = 0; PyDict_Next(numbers.object, &pos, &key, &value);) ints.push_back({name_of(key), integer(value)});
     if (!first) {
       PyErr_SetString(PyExc_StopIteration, "a program needs a tensor");
       throw Failed{};

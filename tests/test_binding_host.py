@@ -20,3 +20,29 @@ def test_cartesian_dot_access_splits_that_do_not_exist(n0, n1):
     out = torch.zeros(lead[n0] + lead[n1], dtype=torch.float32)
     refused(gs.GS_ERR_RANK, gs.cartesian_dot, a, a, n0, n1, out=out)
     refused(gs.GS_ERR_RANK, gs.cartesian_dot, a, a, n0, n1)
+
+
+def long_name():
+    """A name that no constant of this module holds."""
+    return "".join(["activations", "_of_a_name", "_that_nothing_else_holds"])
+
+
+class Changing:
+    """An integer whose conversion empties the dict of tensors, as another thread might."""
+
+    def __init__(self, tensors):
+        self.tensors = tensors
+
+    def __int__(self):
+        self.tensors.clear()
+        self.held = ["y" * len(long_name()) for _ in range(1000)]     # where the freed name was
+        return 3
+
+
+def test_program_eval_holds_what_it_was_given():
+    tensors = {long_name(): torch.zeros((5, 4), dtype=torch.int8)}
+    text = f"(pad {long_name()} 0 A A)"
+    out = torch.zeros((11, 4), dtype=torch.int32)
+    # the name is found and the result's shape follows from the tensor: only its type is wrong
+    refused(gs.GS_ERR_DTYPE, gs.program_eval, text, tensors, {"A": Changing(tensors)}, out=out)
+    assert tensors == {}
