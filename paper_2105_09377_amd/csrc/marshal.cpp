@@ -132,6 +132,15 @@ void* stream_of(const at::Tensor& t) {
   return t.is_cuda() ? static_cast<void*>(c10::hip::getCurrentHIPStream(t.get_device()).stream()) : nullptr;
 }
 
+[[noreturn]] void refuse(int status, const char* where) {
+  PyObject* args = Py_BuildValue("(is)", status, where);
+  if (args) {
+    PyErr_SetObject(error_class, args);
+    Py_DECREF(args);
+  }
+  throw Failed{};
+}
+
 // Runs an entry point without the interpreter lock; a status other than GS_OK becomes GlensideError.
 template <typename F>
 void call(const char* where, F&& f) {
@@ -139,13 +148,7 @@ void call(const char* where, F&& f) {
   Py_BEGIN_ALLOW_THREADS
   status = f();
   Py_END_ALLOW_THREADS
-  if (status == GS_OK) return;
-  PyObject* args = Py_BuildValue("(is)", status, where);
-  if (args) {
-    PyErr_SetObject(error_class, args);
-    Py_DECREF(args);
-  }
-  throw Failed{};
+  if (status != GS_OK) refuse(status, where);
 }
 
 // The result: `out` as given, or a new tensor of this shape, of `dtype` (a torch dtype, None = `otherwise`).
@@ -436,8 +439,11 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
       const size_t need = api.program_workspace(text, tensors.data(), nt, ints.data(), ni);
       ws = at::empty({int64_t(need > 16 ? need : 16)}, at::TensorOptions().dtype(at::kByte).device(first->device()));
     }
-    // the result as the program's access pattern, whatever shape its tensor has
+    // the result as the program's access pattern, whatever shape its tensor has: as many elements, at least
     gs_ap oa = describe(out.value, 0);
+    int64_t elements = 1;
+    for (int i = 0; i < want.rank; ++i) elements *= want.shape[i];
+    if (out.value.numel() < elements) refuse(GS_ERR_SHAPE, "program_eval");
     oa.rank = want.rank;
     oa.n_access = want.n_access;
     for (int i = 0; i < want.rank; ++i) oa.shape[i] = want.shape[i];

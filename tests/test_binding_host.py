@@ -46,3 +46,15 @@ def test_program_eval_holds_what_it_was_given():
     # the name is found and the result's shape follows from the tensor: only its type is wrong
     refused(gs.GS_ERR_DTYPE, gs.program_eval, text, tensors, {"A": Changing(tensors)}, out=out)
     assert tensors == {}
+
+
+@pytest.mark.parametrize("shape", [(10, 4), (11, 3), (0,), ()])
+def test_program_eval_into_a_result_that_is_too_short(shape):
+    x = torch.zeros((5, 4), dtype=torch.int8)
+    refused(gs.GS_ERR_SHAPE, gs.program_eval, "(pad x 0 A A)", {"x": x}, {"A": 3}, out=torch.zeros(shape, dtype=torch.int8))
+
+
+def test_program_eval_into_a_result_of_another_shape():
+    """The same elements in another shape pass that check (the type is what is refused here)."""
+    x = torch.zeros((5, 4), dtype=torch.int8)
+    refused(gs.GS_ERR_DTYPE, gs.program_eval, "(pad x 0 A A)", {"x": x}, {"A": 3}, out=torch.zeros((44,), dtype=torch.int32))
