@@ -400,13 +400,10 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 6, [&](PyObject*& r) {
     const char* text = PyUnicode_AsUTF8(p[0]);
     if (!text) throw Failed{};
-    if (!PyDict_Check(p[1]) || !PyDict_Check(p[2])) {
-      PyErr_SetString(PyExc_TypeError, "tensors and integers are given as dicts by name");
-      throw Failed{};
-    }
-    // Names and tensors are borrowed from copies of the dicts: the caller's may change meanwhile, from another
-    // thread while the interpreter lock is released, or from the conversion of an integer.
-    const Owned named(PyDict_Copy(p[1])), numbers(PyDict_Copy(p[2]));
+    // Names and tensors are borrowed from copies of the mappings: the caller's may change meanwhile, from
+    // another thread while the interpreter lock is released, or from the conversion of an integer.
+    const Owned named(PyDict_New()), numbers(PyDict_New());
+    if (PyDict_Update(named.object, p[1]) || PyDict_Update(numbers.object, p[2])) throw Failed{};
     auto name_of = [](PyObject* key) {
       const char* s = PyUnicode_AsUTF8(key);
       if (!s) throw Failed{};

@@ -1,5 +1,7 @@
 """The binding's argument marshalling without a GPU: every call here is refused before anything is launched."""
 
+import types
+
 import pytest
 import torch
 
@@ -58,3 +60,15 @@ def test_program_eval_into_a_result_of_another_shape():
     """The same elements in another shape pass that check (the type is what is refused here)."""
     x = torch.zeros((5, 4), dtype=torch.int8)
     refused(gs.GS_ERR_DTYPE, gs.program_eval, "(pad x 0 A A)", {"x": x}, {"A": 3}, out=torch.zeros((44,), dtype=torch.int32))
+
+
+@pytest.mark.parametrize("mapping", [dict, types.MappingProxyType])
+def test_program_eval_takes_any_mapping(mapping):
+    x = torch.zeros((5, 4), dtype=torch.int8)
+    refused(gs.GS_ERR_DTYPE, gs.program_eval, "(pad x 0 A A)", mapping({"x": x}), mapping({"A": 3}), out=torch.zeros((11, 4), dtype=torch.int32))
+
+
+@pytest.mark.parametrize("not_a_mapping", [[("x", 1)], ["x"], 5])
+def test_program_eval_takes_nothing_else(not_a_mapping):
+    with pytest.raises((TypeError, AttributeError)):
+        gs.program_eval("(pad x 0 1 1)", not_a_mapping, {})
