@@ -91,6 +91,15 @@ int64_t integer(PyObject* o) {
   return v;
 }
 
+// An operator or activation code: integers only, a float is no code.
+int code(PyObject* o) {
+  PyObject* l = PyNumber_Index(o);
+  if (!l) throw Failed{};
+  const int v = int(PyLong_AsUnsignedLongMask(l));
+  Py_DECREF(l);
+  return v;
+}
+
 // A new reference, held until the end of the scope.
 struct Owned {
   PyObject* object;
@@ -109,21 +118,16 @@ struct Ints {
   explicit Ints(PyObject* o) {
     if (o == Py_None) return;
     present = true;
-    PyObject* seq = PySequence_Fast(o, "a sequence of integers is wanted");
-    if (!seq) throw Failed{};
-    const Py_ssize_t len = PySequence_Fast_GET_SIZE(seq);
-    try {
-      if (len > 2 * GS_MAX_RANK) {
-        PyErr_SetString(PyExc_ValueError, "too many integers");
-        throw Failed{};
-      }
-      for (Py_ssize_t i = 0; i < len; ++i) v[i] = integer(PySequence_Fast_GET_ITEM(seq, i));
-    } catch (...) {
-      Py_DECREF(seq);
-      throw;
+    // sized, as a generator is not; a tuple of its own, for the conversions may run any code
+    if (PyObject_Size(o) < 0) throw Failed{};
+    const Owned seq(PySequence_Tuple(o));
+    const Py_ssize_t len = PyTuple_GET_SIZE(seq.object);
+    if (len > 2 * GS_MAX_RANK) {
+      PyErr_SetString(PyExc_ValueError, "too many integers");
+      throw Failed{};
     }
+    for (Py_ssize_t i = 0; i < len; ++i) v[i] = integer(PyTuple_GET_ITEM(seq.object, i));
     n = int(len);
-    Py_DECREF(seq);
   }
   const int64_t* get() const { return present ? v : nullptr; }
 };
@@ -201,7 +205,7 @@ PyObject* py_cartesian_dot(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 7, [&](PyObject*& r) {
     const at::Tensor &a0 = tensor(p[0]), &a1 = tensor(p[1]);
     const int64_t n0 = integer(p[2]), n1 = integer(p[3]);
-    const int act = int(integer(p[5]));
+    const int act = code(p[5]);
     int64_t shape[2 * GS_MAX_RANK];
     int rank = 0;
     if (p[6] == Py_None) {
@@ -222,7 +226,7 @@ PyObject* py_conv(PyObject*, PyObject* const* p, Py_ssize_t n) {
     const int64_t form = integer(p[0]);
     const at::Tensor &x = tensor(p[1]), &w = tensor(p[2]);
     const Ints stride(p[3]), pad(p[4]);
-    const int act = int(integer(p[6]));
+    const int act = code(p[6]);
     gs_ap xa = describe(x, 1), wa = describe(w, 1);
     int64_t shape[4] = {0, 0, 0, 0};
     if (p[8] == Py_None) {
@@ -274,7 +278,7 @@ PyObject* py_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 6, [&](PyObject*& r) {
     const at::Tensor& x = tensor(p[0]);
     const int64_t na = integer(p[1]);
-    const int op = int(integer(p[2]));
+    const int op = code(p[2]);
     const double scale = PyFloat_AsDouble(p[3]);
     if (scale == -1.0 && PyErr_Occurred()) throw Failed{};
     const auto sizes = x.sizes();
@@ -295,7 +299,7 @@ PyObject* py_windows_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
     const at::Tensor& x = tensor(p[0]);
     const int64_t na = integer(p[1]);
     const Ints window(p[2]), stride(p[3]), lo(p[4]), hi(p[5]);
-    const int op = int(integer(p[6]));
+    const int op = code(p[6]);
     const double scale = PyFloat_AsDouble(p[7]);
     if (scale == -1.0 && PyErr_Occurred()) throw Failed{};
     gs_ap xa = describe(x, 0), want{};
@@ -318,7 +322,7 @@ PyObject* py_access_windows(PyObject*, PyObject* const* p, Py_ssize_t n) {
     const at::Tensor& x = tensor(p[0]);
     const int64_t na = integer(p[1]);
     const Ints window(p[2]), stride(p[3]), lo(p[4]), hi(p[5]);
-    const int mode = int(integer(p[6]));
+    const int mode = code(p[6]);
     gs_ap xa = describe(x, 0), want{};
     xa.n_access = int32_t(na);
     call("windows_out_shape", [&] { return api.windows_out_shape(&xa, window.get(), stride.get(), lo.get(), hi.get(), &want); });
@@ -337,7 +341,7 @@ PyObject* py_depthwise(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 7, [&](PyObject*& r) {
     const at::Tensor &x = tensor(p[0]), &w = tensor(p[1]);
     const Ints stride(p[2]), pad(p[3]);
-    const int act = int(integer(p[4]));
+    const int act = code(p[4]);
     gs_ap xa = describe(x, 1), wa = describe(w, 1), want{};
     if (p[6] == Py_None) {
       if (w.dim() < 3) {
@@ -361,7 +365,7 @@ PyObject* py_depthwise(PyObject*, PyObject* const* p, Py_ssize_t n) {
 PyObject* py_pair_reduce(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 5, [&](PyObject*& r) {
     const at::Tensor &a = tensor(p[0]), &b = tensor(p[1]);
-    const int op = int(integer(p[2])), act = int(integer(p[3]));
+    const int op = code(p[2]), act = code(p[3]);
     Result out(p[4], Py_None, a.scalar_type(), a.sizes().data(), int(a.dim()), a);
     r = out.object;
     gs_ap xa = describe_all(a), ya = describe_all(b), oa = describe_all(out.value);

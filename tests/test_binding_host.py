@@ -2,6 +2,7 @@
 
 import types
 
+import numpy as np
 import pytest
 import torch
 
@@ -72,3 +73,25 @@ def test_program_eval_takes_any_mapping(mapping):
 def test_program_eval_takes_nothing_else(not_a_mapping):
     with pytest.raises((TypeError, AttributeError)):
         gs.program_eval("(pad x 0 1 1)", not_a_mapping, {})
+
+
+def test_operators_and_activations_are_integers():
+    x = torch.zeros((4, 8), dtype=torch.bfloat16)
+    y = torch.zeros((1, 2, 6, 6), dtype=torch.bfloat16)
+    w = torch.zeros((2, 2, 3, 3), dtype=torch.bfloat16)
+    for call in (lambda c: gs.cartesian_dot(x, x, act=c), lambda c: gs.reduce(x, 1, c), lambda c: gs.conv2d_direct(y, w, act=c),
+                 lambda c: gs.pair_reduce(x, x, c), lambda c: gs.windows_reduce(y, 2, (2, 2), (2, 2), op=c),
+                 lambda c: gs.access_windows(y, 2, (2, 2), (2, 2), pad_mode=c), lambda c: gs.depthwise_conv2d(y, w[0], act=c)):
+        for wrong in (1.0, "1", None):
+            with pytest.raises(TypeError):
+                call(wrong)
+        refused(gs.GS_ERR_UNSUPPORTED, call, np.int64(77))
+
+
+def test_sequences_of_integers_are_sized():
+    y = torch.zeros((1, 2, 6, 6), dtype=torch.bfloat16)
+    with pytest.raises(TypeError):
+        gs.windows_reduce(y, 2, (i for i in (2, 2)), (2, 2))
+    # what is sized is taken: the operator is what is refused
+    for window in ([2, 2], torch.Size((2, 2)), np.array([2, 2]), torch.tensor([2, 2]), range(2, 4)):
+        refused(gs.GS_ERR_UNSUPPORTED, gs.windows_reduce, y, 2, window, (2, 2), op=77)
