@@ -9,6 +9,7 @@
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <vector>
@@ -145,13 +146,20 @@ void* stream_of(const at::Tensor& t) {
   throw Failed{};
 }
 
+// The interpreter lock released until the end of the scope, also where that is left by an exception.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // Runs an entry point without the interpreter lock; a status other than GS_OK becomes GlensideError.
 template <typename F>
 void call(const char* where, F&& f) {
   int status;
-  Py_BEGIN_ALLOW_THREADS
-  status = f();
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    status = f();
+  }
   if (status != GS_OK) refuse(status, where);
 }
 
@@ -191,8 +199,8 @@ PyObject* guarded(Py_ssize_t got, Py_ssize_t want, F&& f) {
     f(r);
     return r;
   } catch (const Failed&) {
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {       // torch's own classes: torch.OutOfMemoryError stays what it is
+    torch::translate_exception_to_python(std::current_exception());
   }
   Py_XDECREF(r);
   return nullptr;

@@ -209,6 +209,14 @@ def test_blocked_dot_of_short_slices(dtype):
         assert_parity(got, brute.matmul(x, y.T), what=str(tile_k), slack=fp8_slack(x, y) if dtype == "fp8" else None)
 
 
+def test_results_that_do_not_fit_the_memory():
+    """4 TB of result: torch's own exception, as from any allocation."""
+    a = torch.zeros((1 << 20, 16), dtype=torch.int8, device=DEV)
+    with pytest.raises(torch.OutOfMemoryError):
+        gs.cartesian_dot(a, a)
+    assert gs.cartesian_dot(a[:1], a[:1]).item() == 0
+
+
 def test_cartesian_dot_extreme_int8_values():
     """-128 * -128 * K stays exact in int32."""
     a0 = torch.full((40, 512), -128, dtype=torch.int8)
