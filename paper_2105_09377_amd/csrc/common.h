@@ -295,6 +295,7 @@ size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 hipError_t launch_conv_smallc_pack(const void* w, void* wn, int in_dtype, int O, int C, int Kh, int Kw,
                                    hipStream_t s);
 hipError_t launch_conv_smallc(const ConvArgs& a, hipStream_t s);   // reads a.wr = natural-order copy
+bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo);   // does the kernel take the layer?
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
                               hipStream_t s);
 // Returns hipErrorInvalidValue if no tile configuration fits the LDS for this shape.  With
@@ -303,8 +304,9 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 // Split the channel sum of this shape?  Returns 1, 2 or 4 (host heuristic: few tiles, many chunks).
 int conv_pick_ksplit(int in_dtype, int N, int C, int O, int Ho, int Wo);
-// True where some direct kernel is sure to take the layer (its patch fits the LDS, a tile spans few images).
-bool conv_direct_fits(int64_t N, int64_t W, int64_t Kh, int64_t Kw, int64_t Sh, int64_t Pw, int64_t Ho, int64_t Wo);
+// True where some direct kernel is sure to take the layer (its patch fits the LDS, a tile spans few images);
+// only the shape is read.
+bool conv_direct_fits(const ConvArgs& a);
 
 struct ReduceArgs {       // out[r] = reduce over `cols` contiguous values
   const void* in;

@@ -200,17 +200,20 @@ static hipError_t launch_conv_tile(const ConvArgs& a, ConvGeom g, hipStream_t s)
   return hipErrorInvalidValue;
 }
 
-// What launch_conv_tile<64, 64> in its smallest chunk (32 bytes of channels, which every padded channel
-// count is a multiple of) needs at most: 64 consecutive positions touch at most ceil(63 / Wo) + 1 output rows
-// of ceil(63 / HWo) + 1 images, and n images with R output rows between them (R - n) Sh + n Kh patch rows.
-bool conv_direct_fits(int64_t N, int64_t W, int64_t Kh, int64_t Kw, int64_t Sh, int64_t Pw, int64_t Ho, int64_t Wo) {
-  if (N * Ho * Wo == 0) return true;
+// The few-channel kernel, or launch_conv_tile<64, 64> in its smallest chunk (32 bytes of channels, which every
+// padded channel count is a multiple of).  The latter needs at most: 64 consecutive positions touch at most
+// ceil(63 / Wo) + 1 output rows of ceil(63 / HWo) + 1 images (64 / HWo where that divides), and n images with R
+// output rows between them (R - n) Sh + n Kh patch rows.
+bool conv_direct_fits(const ConvArgs& a) {
+  const int64_t N = a.N, Wo = a.Wo, HWo = int64_t(a.Ho) * Wo, Kh = a.Kh, Kw = a.Kw;
+  if (N * HWo == 0 || a.O == 0) return true;
+  if (conv_smallc_fits(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sw, a.Pw, a.Wo)) return true;
   if (Kh > 512 || Kw > 512) return false;
-  const int64_t images = ceil_div(63, Ho * Wo) + 1, n = images < N ? images : N;
-  const int64_t spanned = ceil_div(63, Wo) + 1, R = spanned < N * Ho ? spanned : N * Ho;
+  const int64_t images = 64 % HWo == 0 ? 64 / HWo : ceil_div(63, HWo) + 1, n = images < N ? images : N;
+  const int64_t spanned = ceil_div(63, Wo) + 1, R = spanned < N * a.Ho ? spanned : N * a.Ho;
   if (n > kMaxSeg) return false;
-  const int64_t one = (R - 1) * Sh + Kh, all = (R > n ? R - n : 0) * Sh + n * Kh;
-  const int64_t PW = round_up(round_up(Pw, 2) + W + Pw, 2);
+  const int64_t one = (R - 1) * a.Sh + Kh, all = (R > n ? R - n : 0) * a.Sh + n * Kh;
+  const int64_t PW = round_up(round_up(a.Pw, 2) + int64_t(a.W) + a.Pw, 2);
   return 256 + 64 * (Kh * Kw * 32 + 16) + (one > all ? one : all) * PW * (32 + 16) <= kLdsLimit;
 }
 

@@ -394,20 +394,59 @@ static int smallc_num_cus() {
   return cus;
 }
 
+// LDS of a workgroup: weights, staged input rows, and tiles or staging of the results.
+struct SmallCLayout {
+  bool dr;                       // row-window form
+  int Kp, wpb, XO, pitch;        // see SmallCArgs
+  int64_t tile_bytes, stage_bytes, lds_bytes;
+  bool fits;
+};
+static SmallCLayout smallc_layout(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo) {
+  const int esz = int(dtype_size(in_dtype)), epd = 4 / esz;
+  SmallCLayout l;
+  // Row-window form: windows a whole number of dwords apart, a window row within 16 bytes.
+  l.dr = smallc_has_rows_copy(in_dtype, Kw) && (Sw * esz) % 4 == 0;
+  l.Kp = l.dr ? int(round_up(C * Kh, 2)) * (16 / esz) : smallc_kp(in_dtype, C, Kh, Kw);
+  l.wpb = l.Kp * esz + 16;
+  // First data column of a staged row.  Row-window form: exactly Pw, so that window y starts
+  // y*Sw elements into the row, on a dword boundary (the staged data itself may then sit off one).
+  l.XO = l.dr ? Pw : int(round_up(Pw, epd));
+  const int64_t reach = int64_t(l.XO) - Pw + int64_t(Wo - 1) * Sw + Kw;
+  const int64_t width = reach > l.XO + W ? reach : l.XO + W;
+  l.pitch = int(round_up(width, epd));
+  if ((l.pitch / epd) % 2 == 0) l.pitch += epd;        // an odd number of dwords spreads the gather over banks
+  const int64_t staged = (int64_t(C) * Kh + 1) * l.pitch * esz;
+  l.stage_bytes = round_up(staged, 16);
+  constexpr int kStaging = (kSmallCThreads / 64) * 32 * (32 * 4 + 16);   // one staging area per wave
+  l.tile_bytes = (!l.dr && 128 * int64_t(l.wpb) > kStaging) ? 128 * int64_t(l.wpb) : kStaging;
+  l.lds_bytes = 64 * int64_t(l.wpb) + l.tile_bytes + l.stage_bytes + int64_t(l.Kp) * 4;
+  l.fits = l.lds_bytes <= 96 * 1024 && staged <= (1 << 20);
+  return l;
+}
+
+bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo) {
+  return conv_is_smallc(in_dtype, C) && smallc_layout(in_dtype, C, W, Kh, Kw, Sw, Pw, Wo).fits;
+}
+
 // `a.wr` must point at the natural-order weight copy.  Returns hipErrorInvalidValue when the
 // shape does not fit (LDS), so that the caller can fall back.
 template <typename TR>
 static hipError_t launch_smallc_t(const ConvArgs& a, hipStream_t s) {
   constexpr int ESZ = TR::kEsz;
   constexpr int EPV = 16 / ESZ, EPD = 4 / ESZ;
+  const SmallCLayout l = smallc_layout(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sw, a.Pw, a.Wo);
+  if (!l.fits) return hipErrorInvalidValue;
+  const bool dr = l.dr;
+  const int64_t lds_bytes = l.lds_bytes;
   SmallCArgs p;
   p.c = a;
   p.K = a.C * a.Kh * a.Kw;
-  p.Kp = smallc_kp(a.in_dtype, a.C, a.Kh, a.Kw);
-  // Row-window form: windows a whole number of dwords apart, a window row within 16 bytes.
-  const bool dr = smallc_has_rows_copy(a.in_dtype, a.Kw) && (a.Sw * ESZ) % 4 == 0;
+  p.Kp = l.Kp;
+  p.wpb = l.wpb;
+  p.XO = l.XO;
+  p.pitch = l.pitch;
+  p.tile_bytes = int(l.tile_bytes);
   if (dr) {
-    p.Kp = int(round_up(a.C * a.Kh, 2)) * EPV;
     p.c.wr = static_cast<const uint8_t*>(a.wr) + smallc_rows_offset(a.in_dtype, a.O, a.C, a.Kh, a.Kw);
     for (int d = 0; d < 4; ++d) {
       uint32_t m = 0;
@@ -416,22 +455,8 @@ static hipError_t launch_smallc_t(const ConvArgs& a, hipStream_t s) {
       p.dr_mask[d] = m;
     }
   }
-  p.wpb = p.Kp * ESZ + 16;
-  // First data column of a staged row.  Row-window form: exactly Pw, so that window y starts
-  // y*Sw elements into the row, on a dword boundary (the staged data itself may then sit off one).
-  p.XO = dr ? a.Pw : int(round_up(a.Pw, EPD));
-  const int64_t reach = int64_t(p.XO) - a.Pw + int64_t(a.Wo - 1) * a.Sw + a.Kw;
-  const int64_t width = reach > p.XO + a.W ? reach : p.XO + a.W;
-  p.pitch = int(round_up(width, EPD));
-  if ((p.pitch / EPD) % 2 == 0) p.pitch += EPD;        // an odd number of dwords spreads the gather over banks
-  const int nrows = a.C * a.Kh;
   p.vec_ok = ((a.W * ESZ) % 16 == 0 && reinterpret_cast<uintptr_t>(a.act) % 16 == 0 &&
-              int64_t(nrows) * (a.W * ESZ / 16) <= kSmallCThreads * kSmallCBatch) ? 1 : 0;
-  const int64_t stage_bytes = round_up(int64_t(nrows + 1) * p.pitch * ESZ, 16);
-  constexpr int kStaging = (kSmallCThreads / 64) * 32 * (32 * 4 + 16);   // one staging area per wave
-  p.tile_bytes = (!dr && 128 * p.wpb > kStaging) ? 128 * p.wpb : kStaging;
-  const int64_t lds_bytes = 64 * int64_t(p.wpb) + p.tile_bytes + stage_bytes + int64_t(p.Kp) * 4;
-  if (lds_bytes > 96 * 1024 || (int64_t(nrows) + 1) * p.pitch * ESZ > (1 << 20)) return hipErrorInvalidValue;
+              int64_t(a.C) * a.Kh * (a.W * ESZ / 16) <= kSmallCThreads * kSmallCBatch) ? 1 : 0;
   p.xtiles = int(ceil_div(a.Wo, 128));
   p.otiles = int(ceil_div(a.O, 64));
   p.tasks = int64_t(a.N) * a.Ho * p.xtiles * p.otiles;

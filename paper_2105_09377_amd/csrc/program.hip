@@ -507,7 +507,8 @@ struct ConvMatch {
   std::vector<int64_t> window, stride;
   int64_t pad[2] = {0, 0};
 };
-bool flat_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result) {
+// Is some direct kernel sure to take the convolution?
+bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result) {
   Shape act;
   if (infer(m.act, env, &act)) return false;
   act.na = 1;
@@ -515,8 +516,15 @@ bool flat_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& 
   weights.na = 1;
   const gs_ap aa = make_ap(nullptr, act), wa = make_ap(nullptr, weights);
   const int64_t stride[2] = {m.stride[1], m.stride[2]};
-  return act.numel() > 0 && glenside_conv2d_direct_workspace(&aa, &wa, stride, m.pad) != 0 &&
-         gs::conv_direct_fits(act.d[0], act.d[3], w.d[2], w.d[3], stride[0], m.pad[1], result.d[2], result.d[3]);
+  if (act.numel() == 0 || glenside_conv2d_direct_workspace(&aa, &wa, stride, m.pad) == 0) return false;
+  gs::ConvArgs a;
+  memset(&a, 0, sizeof(a));
+  a.in_dtype = act.dtype;
+  a.N = int(act.d[0]); a.C = int(act.d[1]); a.H = int(act.d[2]); a.W = int(act.d[3]);
+  a.O = int(w.d[0]); a.Kh = int(w.d[2]); a.Kw = int(w.d[3]);
+  a.Sh = int(stride[0]); a.Sw = int(stride[1]); a.Ph = int(m.pad[0]); a.Pw = int(m.pad[1]);
+  a.Ho = int(result.d[2]); a.Wo = int(result.d[3]);
+  return gs::conv_direct_fits(a);
 }
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
@@ -549,17 +557,24 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
     return false;
   // (N, O, H', W'): what the reshape of the flat form must restore
   if (all.d.size() != 4 || all.d[0] != a.d[0] || all.d[1] != b.d[0] || all.d[2] != win.d[2] || all.d[3] != win.d[3]) return false;
-  // symmetric zero padding of H and W is the convolution's own
+  // Symmetric zero padding of H and W is the convolution's own where a kernel is sure to take it so: a patch
+  // row with odd padding is up to two pixels longer than a row of the padded tensor, and may be the one
+  // that no longer fits.
   TreeP inner;
   int64_t lo[GS_MAX_RANK], hi[GS_MAX_RANK];
   if (strip_pads(m->act, env, 2, &inner, lo, hi) && lo[2] == hi[2] && lo[3] == hi[3] && lo[2] <= 64 && lo[3] <= 64) {
-    m->act = inner;
-    m->pad[0] = lo[2];
-    m->pad[1] = lo[3];
+    ConvMatch folded = *m;
+    folded.act = inner;
+    folded.pad[0] = lo[2];
+    folded.pad[1] = lo[3];
+    if (direct_fits(folded, env, b, all)) {
+      *m = folded;
+      return true;
+    }
   }
   // What no direct kernel is sure to take (strides, windows and rows too large for the LDS, more images
   // in a tile than it counts) the flat form still evaluates node by node.
-  return !flat || flat_fits(*m, env, b, all);
+  return !flat || direct_fits(*m, env, b, all);
 }
 
 struct Evaluator {

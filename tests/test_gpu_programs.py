@@ -90,6 +90,22 @@ def test_flat_form_where_no_direct_kernel_fits(shape):
     assert_parity(got, want.materialize(), what=str(shape))
 
 
+# Padded rows around the LDS limit of the direct kernels: with padding of its own a patch row is two pixels longer
+# than a row of the padded tensor, so at 748 columns the padding is materialised; and a few-channel image that
+# only the few-channel kernel takes.
+@pytest.mark.parametrize("shape", [(1, 40, 3, 746, 8, 3, 1), (1, 40, 3, 747, 8, 3, 1), (1, 40, 3, 748, 8, 3, 1), (1, 3, 9, 1100, 8, 7, 3)])
+def test_padded_rows_at_the_lds_limit(shape):
+    n, c, h, w, o, k, p = shape
+    tensors = {"activations": synth.uniform_int8((n, c, h, w), -9, 9, 9480), "weights": synth.uniform_int8((o, c, k, k), -9, 9, 9481)}
+    ints = dict(C=c, Kh=k, Kw=k, Sh=1, Sw=1, Ph=p, Pw=p)
+    meta = {name: (tuple(v.shape), v.dtype) for name, v in tensors.items()}
+    xp = torch.nn.functional.pad(tensors["activations"].double(), (p, p, p, p))
+    want = torch.nn.functional.conv2d(xp, tensors["weights"].double()).to(torch.int32)
+    for text in (listings.CONV2D_PADDED, gs.program_rewrite(listings.CONV2D_PADDED, "im2col", meta, ints)):
+        got = gs.program_eval(text, {name: v.to(DEV) for name, v in tensors.items()}, ints)
+        assert torch.equal(got.cpu(), want)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "fp8"])
 @pytest.mark.parametrize("dims", [(32, 32, 32), (70, 96, 200)])
 def test_matmul_listing_and_its_rewrites(dtype, dims):

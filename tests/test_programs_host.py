@@ -206,3 +206,20 @@ def test_rewrites_on_random_shapes():
         want = brute.conv2d(A, W, (sh, sw), (0, 0))
         np.testing.assert_array_equal(sexpr.evaluate(text, tensors, ints).materialize(), want, err_msg=str(ints))
         np.testing.assert_array_equal(sexpr.evaluate(listings.CONV2D, tensors, ints).materialize(), want)
+
+
+def program_workspace(text, tensors, ints):
+    ta, nt, ia, ni, _keep = gs._named(tensors, ints)
+    return gs.lib().glenside_program_workspace(text.encode(), ta, nt, ia, ni)
+
+
+def test_padding_is_the_convolutions_own_where_its_rows_fit():
+    """One pixel of padding makes rows of an even width two pixels longer than the padded tensor's: where that
+    passes the LDS of the direct kernels the padded tensor is materialised, in both forms of the listing."""
+    for w, folded in ((746, True), (748, False)):
+        tensors = {"activations": ((1, 40, 3, w), torch.int8), "weights": ((8, 40, 3, 3), torch.int8)}
+        ints = dict(C=40, Kh=3, Kw=3, Sh=1, Sw=1, Ph=1, Pw=1)
+        padded_bytes = 40 * 5 * (w + 2)
+        for text in (listings.CONV2D_PADDED, gs.program_rewrite(listings.CONV2D_PADDED, "im2col", tensors, ints)):
+            need = program_workspace(text, tensors, ints)
+            assert 0 < need < padded_bytes if folded else padded_bytes < need < 3 * padded_bytes
