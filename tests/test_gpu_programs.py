@@ -106,6 +106,27 @@ def test_padded_rows_at_the_lds_limit(shape):
         assert torch.equal(got.cpu(), want)
 
 
+# Padding of at least the window in front of convolutions that the pipelined kernels take (whole chunks of
+# channels; rows of whole vectors and not; several images in a tile): whole patch rows are padding.
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 64, 12, 16, 70, 3, 3, 1), (3, 64, 12, 16, 64, 3, 7, 1), (2, 128, 9, 13, 40, 3, 5, 2), (9, 64, 4, 4, 64, 3, 4, 1),
+                                   (2, 64, 10, 10, 32, 1, 3, 1), (2, 64, 8, 8, 33, 5, 9, 1), (1, 64, 6, 40, 32, 3, 64, 1)])
+def test_padding_wider_than_the_window(shape, dtype):
+    n, c, h, w, o, k, p, s = shape
+    x = gen_small(dtype, (n, c, h, w), 9490)
+    wt = gen_small(dtype, (o, c, k, k), 9491)
+    ints = dict(C=c, Kh=k, Kw=k, Sh=s, Sw=s, Ph=p, Pw=p)
+    want = torch.nn.functional.conv2d(torch.nn.functional.pad(x.double(), (p, p, p, p)), wt.double(), stride=s).numpy()
+    want = want.astype(np.int64) if dtype == "i8" else want
+    got = gs.program_eval(listings.CONV2D_PADDED, {"activations": x.to(DEV), "weights": wt.to(DEV)}, ints)
+    assert_parity(got, want, what=str(shape))
+    assert torch.equal(got, gs.conv2d_direct(x.to(DEV), wt.to(DEV), (s, s), (p, p)))
+
+
+def gen_small(dtype, shape, stream):
+    return synth.uniform_int8(shape, -9, 9, stream) if dtype == "i8" else synth.normal_bf16(shape, 0.3, stream)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "fp8"])
 @pytest.mark.parametrize("dims", [(32, 32, 32), (70, 96, 200)])
 def test_matmul_listing_and_its_rewrites(dtype, dims):
