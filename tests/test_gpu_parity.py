@@ -113,7 +113,7 @@ DOT_CASES = [
     ("i8", (64, 128), 1, (72, 128), 1, torch.int32, True),
     ("bf16", (40, 64), 1, (76, 64), 1, torch.bfloat16, False),
     ("bf16", (200, 256), 1, (264, 256), 1, torch.float32, False),
-    # 8-bit floats: 64-byte K steps; K not a multiple of 64 takes the checked kernel
+    # 8-bit floats: 64-byte K steps; K not a multiple of 64 takes the loader for rows of any alignment
     ("fp8", (300, 328), 1, (200, 328), 1, torch.float32, False),
     ("fp8", (130, 1000), 1, (70, 1000), 1, torch.bfloat16, True),
     ("fp8", (64, 128), 1, (72, 128), 1, torch.float32, True),
@@ -298,6 +298,37 @@ def test_conv2d_im2col_large_tiles_residual_relu(dtype, odt, o, n):
     idx = torch.tensor([0, n // 2, n - 1])
     want = brute.conv2d(to_oracle(cfg["x"][idx]), to_oracle(cfg["w"]), (1, 1), (0, 0)) + to_oracle(res[idx])
     assert_parity(got[idx.to(DEV)], np.maximum(want, 0), what=f"{dtype} O={o} N={n}")
+
+
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("c,k,o,h,w", [(32, 3, 300, 93, 95), (32, 1, 200, 211, 213), (16, 3, 64, 181, 183), (3, 1, 130, 121, 123)])
+def test_conv2d_im2col_of_one_image_with_residual(c, k, o, h, w, dtype, odt):
+    """One image of an odd plane: rows of the product are as long as the plane, of any alignment, and the residual
+    is read eight values at a time wherever they lie (more than 512 tiles of 32x32, all loaders)."""
+    cfg = synth.conv_layer(1, c, h, w, o, k, 1, k // 2, dtype, 8300 + o + h, gain=1.0)
+    shape = (1, o, h, w)
+    res = gen("i32" if dtype == "i8" else ("bf16" if odt == torch.bfloat16 else "f32"), shape, 8400 + o)
+    got = gs.conv2d_im2col(cfg["x"].to(DEV), cfg["w"].to(DEV), (1, 1), (k // 2, k // 2), residual=res.to(DEV), act=gs.GS_ACT_RELU, out_dtype=odt)
+    want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), padding=k // 2) + res.double()
+    want = want.clamp_min(0).numpy()
+    assert_parity(got, want.astype(np.int64) if dtype == "i8" else want, what=f"{dtype} {c} {k} {o}")
+
+
+@pytest.mark.parametrize("mnk,dtype,odt", [((8191, 8201, 33), "bf16", torch.bfloat16), ((6001, 7003, 7), "bf16", torch.float32),
+                                           ((7003, 6001, 64), "i8", torch.int32), ((6007, 6009, 65), "fp8", torch.bfloat16)])
+def test_cartesian_dot_streams_odd_rows(mnk, dtype, odt):
+    """Results above 128 MB in 32-bit values, whose stores pass the cache by, with rows of odd length."""
+    m, n, k = mnk
+    a0, a1 = gen(dtype, (m, k), 1470 + m), gen(dtype, (n, k), 1570 + n, k ** -0.5 if dtype != "i8" else 1.0)
+    buf = torch.full((m * n + 512,), 77, dtype=odt, device=DEV)
+    got = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), out=buf[256:256 + m * n].view(m, n))
+    rows = torch.tensor(sorted({0, 1, 2, 127, 128, m // 2, m - 129, m - 2, m - 1}))
+    x, y = to_oracle(a0[rows]), to_oracle(a1)
+    assert_parity(got[rows.to(DEV)], brute.matmul(x, y.T), what=str(mnk), slack=fp8_slack(x, y) if dtype == "fp8" else None)
+    assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
+    # every row was written: a second product into the same buffer, cleared, is the same
+    again = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), out=torch.zeros((m, n), dtype=odt, device=DEV))
+    assert torch.equal(got, again)
 
 
 
