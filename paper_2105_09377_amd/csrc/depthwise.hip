@@ -427,7 +427,9 @@ hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
   // more) where every compute unit still has 256 strips, few of the rows are past the end, and it was the
   // faster way over 32 images (us, one row per strip against several):
   //   3x3 bfloat16 to bfloat16, aligned columns: 128 planes of 112x112 67.1 / 52.4, 56x56 20.9 / 17.6; but not
-  //   with unaligned columns (512 of 14x14 9.8 / 11.7, 128 of 57x61 to f32 44.1 / 48.9) or int8 (56x56 21.0 / 22.0);
+  //   with unaligned columns (512 of 14x14 9.8 / 11.7, 128 of 57x61 to f32 44.1 / 48.9) or int8 (56x56 21.0 / 22.0),
+  //   nor to f32 with aligned ones, where it depends on the size (128 of 112x112 70.4 / 64.6, 56x56 19.0 / 20.5,
+  //   48x64 18.1 / 18.8);
   //   5x5 to bfloat16: 128 of 112x112 139.5 / 97.4, 57x61 53.1 / 47.0, 256 of 14x14 11.1 / 9.2; to 32 bits only
   //   with aligned columns (int8, 56x56 36.1 / 34.0, 55x55 44.8 / 47.6).
   if (d.Sw == 1 && d.Sh == 1 && d.Ho >= 6) {

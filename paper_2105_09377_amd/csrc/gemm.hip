@@ -4,7 +4,7 @@
 // element), which is exactly the operand order the MFMA wants, so tiles are copied global -> LDS
 // with 16-byte loads and no transposition.  A workgroup of 4 or 8 waves owns a BM x BN output tile
 // (the concat-on-access-dimensions blocking of Sec. 5.4); the K loop walks 128-byte slabs (the
-// pair/reduceSum blocking on the compute dimension), double-buffered in LDS with the next slab's
+// pair/reduceSum blocking on the compute dimension) through two to four LDS buffers, the next slabs'
 // global loads in flight while the current one feeds the MFMAs; fragment reads run one K step
 // ahead of the MFMAs and the per-slab barrier sits under the slab's last MFMAs.  The kernels are
 // written in bytes: a slab row is 128 bytes = 64 bf16 or 128 int8, one MFMA eats 32 bytes of K
@@ -17,9 +17,10 @@
 //                            because such a load writes 64 x 16 contiguous bytes, rows cannot be
 //                            padded, so bank conflicts are avoided by an XOR swizzle of the
 //                            16-byte columns instead.
-//   gemm_nt_any_kernel     : ragged K, unaligned rows: 16-byte loads at any address, register-staged.
-//   gemm_nt_ksplit_kernel  : few result tiles, any alignment: the K slabs of a small tile are dealt to
-//                            the waves of its workgroup.
+//   gemm_nt_any_kernel     : ragged K, unaligned rows: 16-byte loads at any address, register-staged; rows
+//                            of fewer than 16 bytes as one piece.
+//   gemm_nt_ksplit_kernel  : few result tiles, any alignment, rows of at least 16 bytes: the K slabs of a
+//                            small tile are dealt to the waves of its workgroup.
 //
 // Result element (i, j) is stored at (j / jp) * (I * jp) + i * jp + (j % jp): jp = J gives the
 // plain row-major ((I, J), ()) result; jp = H'*W' with j = flattened (n, h', w') and i = o gives
@@ -293,7 +294,7 @@ __device__ __forceinline__ i32x4 short_row(const uint8_t* row, int64_t Kb) {
 // two slabs are in flight in registers while one is multiplied and the next sits in the other LDS
 // buffer.  Bound by LDS traffic (a slab of a 128x128 tile is written once, 436 cycles at 75 bytes per
 // cycle, and read as 98 KB of fragments, 610 at 160, against 256-512 of MFMAs).  2047 x 1531 x 1001:
-// e4m3 85 -> 13.8 us, bf16 18.7, int8 15.6 (before: 16-byte pieces gathered byte by byte).
+// e4m3 70.6 -> 13.2 us, int8 74.7 -> 15.1, bf16 155.8 -> 18.1 (before: 16-byte pieces gathered byte by byte).
 // SHORT: rows of fewer than 16 bytes (empty ones included): one piece per row, one MFMA step, and the
 // result is what takes the time.
 template <typename TR, int BM, int BN, int WGM, int WGN, bool SHORT>
@@ -847,8 +848,12 @@ static hipError_t launch_ksplit(const GemmArgs& a, hipStream_t s) {
 
 // Few tiles: what a workgroup of the 64x64 kernels waits for is one slab after the other, so up to
 // 512 tiles of 32x32 the K slabs are dealt to waves instead (256 x 512 x 784 bf16: 4.2 us against
-// 6.4 in 32 tiles of 64x64; 512 x 1024 x 1024: 6.3 against 7.2; with twice the tiles 10.6 against
-// 7.4).  Eight waves need the LDS of a compute unit for themselves and pay from the ninth slab on
+// 6.4 in 32 tiles of 64x64; 512 x 1024 x 1024: 6.0 against 7.4; with twice the tiles 10.6 against
+// 7.4).  That holds at any K up to 256 tiles.  Between 257 and 512, where K is long, it holds while the tiles
+// of a row are a multiple of the 8 XCDs, whose L2 then keeps its columns (512 x 1024 x 8192: 24.5 against
+// 32.2), and not otherwise (384 x 1300 x 8192: 50.2 against 32.4; 1024 x 288 x 8192: 37.4 against 31.9), where
+// it is still faster than 64x64 tiles with two slab buffers were (64.1 and 63.4).
+// Eight waves need the LDS of a compute unit for themselves and pay from the ninth slab on
 // (300 x 300 x 8192 int8: 9.2 against 9.6 us; 512 tiles of eight slabs: 8.5 against 6.3).
 template <typename TR>
 static bool few_tiles(const GemmArgs& a, bool* eight) {
@@ -866,8 +871,8 @@ static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
   // extent a tile can fill: the block when the result is cut into blocks
   const int64_t fi = a.bm > 0 && a.bm < a.I ? a.bm : a.I, fj = a.bn > 0 && a.bn < a.J ? a.bn : a.J;
   if (t256 >= 256 && fi >= 256 && fj >= 256) return launch_dma<TR, 256, 256, 2, 4, 128, 2>(a, s);
-  // few rows (a convolution's output channels against many positions) or few columns (the im2col
-  // listing: 100352 x 64 x 576 takes 32.2 against 36.2 in half-empty 128x128 tiles)
+  // few rows (a convolution's output channels against many positions) or few columns (100352 x 64 x 576
+  // takes 32.2 against 36.2 in half-empty 128x128 tiles)
   if (a.I <= 64 && ceil_div(fj, 256) * ceil_div(a.J, fj) >= 192) return launch_dma<TR, 64, 256, 1, 4, 128, 2>(a, s);
   if (a.J <= 64 && ceil_div(fi, 256) * ceil_div(a.I, fi) >= 192) return launch_dma<TR, 256, 64, 4, 1, 128, 2>(a, s);
   bool eight;
@@ -913,7 +918,7 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   bool eight;
   if (!is_short && few_tiles<TR>(v, &eight))
     return eight ? launch_ksplit<TR, 8, kStaged>(v, s) : launch_ksplit<TR, 4, kStaged>(v, s);
-  // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.8 us
+  // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.2 us
   // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6.  Results (or
   // blocks) of up to 64 rows or columns would leave half of every tile empty (100000 x 10 x 65 bf16 to
   // bf16: 17.4 against 12.0; 64 x 40000 x 1001 bf16 to f32: 30.4 against 24.0).
