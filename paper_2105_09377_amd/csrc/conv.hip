@@ -218,12 +218,12 @@ bool conv_direct_fits(const ConvArgs& a) {
 }
 
 // Pipelined kernel instances (conv3_inst.hip), one per element type and tile shape.
-hipError_t launch_conv3_bf16_t0(const ConvArgs&, const ConvGeom&, hipStream_t);
-hipError_t launch_conv3_bf16_t1(const ConvArgs&, const ConvGeom&, hipStream_t);
-hipError_t launch_conv3_bf16_t2(const ConvArgs&, const ConvGeom&, hipStream_t);
-hipError_t launch_conv3_i8_t0(const ConvArgs&, const ConvGeom&, hipStream_t);
-hipError_t launch_conv3_i8_t1(const ConvArgs&, const ConvGeom&, hipStream_t);
-hipError_t launch_conv3_i8_t2(const ConvArgs&, const ConvGeom&, hipStream_t);
+hipError_t launch_conv3_bf16_t0(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
+hipError_t launch_conv3_bf16_t1(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
+hipError_t launch_conv3_bf16_t2(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
+hipError_t launch_conv3_i8_t0(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
+hipError_t launch_conv3_i8_t1(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
+hipError_t launch_conv3_i8_t2(const ConvArgs&, const ConvGeom&, hipStream_t, bool probe);
 
 // 64 x 256 or 64 x 128 tiles: whichever needs less time by rounds x cost per tile, a wide tile
 // costing 1.44 narrow ones (measured: 196 wide tiles of 256 channels at 14x14 take 23.7 us in one
@@ -238,14 +238,14 @@ static bool conv_prefers_wide_tile(int64_t M, int O) {
 }
 
 template <typename TR>
-static hipError_t launch_conv3(const ConvArgs& a, const ConvGeom& g, hipStream_t s) {
+static hipError_t launch_conv3(const ConvArgs& a, const ConvGeom& g, hipStream_t s, bool probe = false) {
   constexpr bool i8 = TR::kEsz == 1;
   if (a.C % (16 / TR::kEsz) != 0 || a.C != a.Cpad) return hipErrorInvalidValue;
   // Tile shapes: 64 channels x 256 positions (three weight buffers fit, the best pipeline) while
   // that still gives most compute units a tile; 64 x 128 for small feature maps; 128 x 128 last.
-  auto t0 = [&]() { return i8 ? launch_conv3_i8_t0(a, g, s) : launch_conv3_bf16_t0(a, g, s); };
-  auto t1 = [&]() { return i8 ? launch_conv3_i8_t1(a, g, s) : launch_conv3_bf16_t1(a, g, s); };
-  auto t2 = [&]() { return i8 ? launch_conv3_i8_t2(a, g, s) : launch_conv3_bf16_t2(a, g, s); };
+  auto t0 = [&]() { return i8 ? launch_conv3_i8_t0(a, g, s, probe) : launch_conv3_bf16_t0(a, g, s, probe); };
+  auto t1 = [&]() { return i8 ? launch_conv3_i8_t1(a, g, s, probe) : launch_conv3_bf16_t1(a, g, s, probe); };
+  auto t2 = [&]() { return i8 ? launch_conv3_i8_t2(a, g, s, probe) : launch_conv3_bf16_t2(a, g, s, probe); };
   hipError_t e = hipErrorInvalidValue;
   const bool wide = conv_prefers_wide_tile(g.M, a.O);
   e = wide ? t1() : t2();
@@ -322,13 +322,7 @@ int conv_pick_ksplit(int in_dtype, int N, int C, int O, int Ho, int Wo) {
   return 1;
 }
 
-template <typename TR>
-static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
-  ConvArgs a = a_in;
-  if (a.ksplit < 2 || !a.partial) {
-    a.ksplit = 1;
-    a.partial = nullptr;
-  }
+static ConvGeom conv_geom(const ConvArgs& a) {
   ConvGeom g;
   g.T = a.Kh * a.Kw;
   g.XO = int(round_up(a.Pw, 2));
@@ -342,6 +336,17 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   g.pos_major = 0;
   g.dHWo = FastDiv::make(uint32_t(g.HWo > 0 ? g.HWo : 1));
   g.dWo = FastDiv::make(uint32_t(a.Wo > 0 ? a.Wo : 1));
+  return g;
+}
+
+template <typename TR>
+static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
+  ConvArgs a = a_in;
+  if (a.ksplit < 2 || !a.partial) {
+    a.ksplit = 1;
+    a.partial = nullptr;
+  }
+  const ConvGeom g = conv_geom(a);
   if (g.M == 0 || a.O == 0) return hipSuccess;
   if (a.wnat) {                        // fewer channels than a chunk: windows formed as im2col rows in LDS
     ConvArgs b = a;
@@ -383,6 +388,21 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   e = launch_conv_tile<TR, 64, 128, 1, 4>(a, g, s);
   if (e != hipErrorInvalidValue) return e;
   return launch_conv_tile<TR, 64, 64, 2, 2>(a, g, s);
+}
+
+bool conv_pipelined_takes(const ConvArgs& a_in) {
+  ConvArgs a = a_in;
+  a.Cpad = conv_cpad(a.in_dtype, a.C);
+  if (conv_is_smallc(a.in_dtype, a.C) || !conv_blocked_weight_bytes(a.in_dtype, a.O, a.C, a.Kh, a.Kw)) return false;
+  a.wblk = &a;      // asked for, never read
+  const ConvGeom g = conv_geom(a);
+  if (g.M == 0 || a.O == 0) return false;
+  auto takes = [&](int ksplit) {
+    a.ksplit = ksplit;
+    return (a.in_dtype == GS_I8 ? launch_conv3<I8Traits>(a, g, nullptr, true) : launch_conv3<Bf16Traits>(a, g, nullptr, true)) == hipSuccess;
+  };
+  const int ksplit = conv_pick_ksplit(a.in_dtype, a.N, a.C, a.O, a.Ho, a.Wo);
+  return takes(ksplit) || (ksplit > 1 && takes(1));
 }
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {

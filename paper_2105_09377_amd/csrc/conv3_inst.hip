@@ -38,7 +38,8 @@ static hipError_t launch_conv3_cfg(const ConvArgs& a, ConvGeom g, hipStream_t s)
 // Producer / consumer kernel (eight waves): returns hipErrorInvalidValue when the shape does not
 // fit it.  Three weight buffers when the output-channel tile is 64 wide, two when it is 128.
 template <typename TR, int TO, int TP, int WO, int WP, int VW, int KH, int KW, int MAXI, int D, bool FLAT>
-static hipError_t launch_conv4_ring(const ConvArgs& a, const ConvGeom& g, size_t lds_bytes, hipStream_t s) {
+static hipError_t launch_conv4_ring(const ConvArgs& a, const ConvGeom& g, size_t lds_bytes, hipStream_t s, bool probe) {
+  if (probe) return hipSuccess;
   constexpr int NWB = TO <= 64 ? 3 : 2;
   auto kern = conv_direct4_kernel<TR, TO, TP, WO, WP, VW, KH, KW, MAXI, NWB, D, FLAT>;
   static std::once_flag once;              // the attribute is set once, whichever thread comes first
@@ -57,13 +58,13 @@ static hipError_t launch_conv4_ring(const ConvArgs& a, const ConvGeom& g, size_t
 // Ring depth: four chunks of loads in flight; two when the channel chunks per work item are only
 // a multiple of two (int8 with 64 channels) -- instantiated for int8 only, to bound compile time.
 template <typename TR, int TO, int TP, int WO, int WP, int VW, int KH, int KW, int MAXI, bool FLAT = false>
-static hipError_t launch_conv4_cfg(const ConvArgs& a, const ConvGeom& g, size_t lds_bytes, hipStream_t s) {
+static hipError_t launch_conv4_cfg(const ConvArgs& a, const ConvGeom& g, size_t lds_bytes, hipStream_t s, bool probe) {
   const int per_item = a.Cpad / (32 / TR::kEsz) / (a.ksplit > 1 ? a.ksplit : 1);
   if (per_item % 4 == 0)
-    return launch_conv4_ring<TR, TO, TP, WO, WP, VW, KH, KW, MAXI, 4, FLAT>(a, g, lds_bytes, s);
+    return launch_conv4_ring<TR, TO, TP, WO, WP, VW, KH, KW, MAXI, 4, FLAT>(a, g, lds_bytes, s, probe);
   if constexpr (TR::kEsz == 1) {
     if (per_item % 2 == 0)
-      return launch_conv4_ring<TR, TO, TP, WO, WP, VW, KH, KW, MAXI, 2, FLAT>(a, g, lds_bytes, s);
+      return launch_conv4_ring<TR, TO, TP, WO, WP, VW, KH, KW, MAXI, 2, FLAT>(a, g, lds_bytes, s, probe);
   }
   return hipErrorInvalidValue;
 }
@@ -71,7 +72,7 @@ static hipError_t launch_conv4_cfg(const ConvArgs& a, const ConvGeom& g, size_t 
 // Picks the shape of the producers' items: a producer thread moves one or two items of VW pixels
 // x 8 (16) channels per chunk.
 template <typename TR, int TO, int TP, int WO, int WP, int KH, int KW>
-static hipError_t launch_conv4(const ConvArgs& a, ConvGeom g, hipStream_t s) {
+static hipError_t launch_conv4(const ConvArgs& a, ConvGeom g, hipStream_t s, bool probe) {
   constexpr int NWB = TO <= 64 ? 3 : 2;
   const int ksplit = a.ksplit > 1 ? a.ksplit : 1;
   const int nchunk = a.Cpad / (32 / TR::kEsz);
@@ -142,11 +143,11 @@ static hipError_t launch_conv4(const ConvArgs& a, ConvGeom g, hipStream_t s) {
   if (a.W % VW_ == 0 && items(VW_) <= 192 * MAXI_) {                                        \
     g.rb_shift = pick_rb(VW_, MAXI_);                                                        \
     g.dXG = FastDiv::make(uint32_t(a.W / VW_));                                              \
-    return launch_conv4_cfg<TR, TO, TP, WO, WP, VW_, KH, KW, MAXI_>(a, g, lds_bytes, s);      \
+    return launch_conv4_cfg<TR, TO, TP, WO, WP, VW_, KH, KW, MAXI_>(a, g, lds_bytes, s, probe); \
   }
 #define GS_TRY_FLAT(VW_, MAXI_)                                                              \
   if (a.W >= VW_ && flat_items(VW_) <= 192 * MAXI_)                                         \
-    return launch_conv4_cfg<TR, TO, TP, WO, WP, VW_, KH, KW, MAXI_, true>(a, g, lds_bytes, s);
+    return launch_conv4_cfg<TR, TO, TP, WO, WP, VW_, KH, KW, MAXI_, true>(a, g, lds_bytes, s, probe);
   GS_TRY(1, 1) GS_TRY(2, 1) GS_TRY(4, 1) GS_TRY(8, 1)
   GS_TRY_FLAT(4, 1) GS_TRY_FLAT(8, 1)
   GS_TRY(1, 2) GS_TRY(2, 2) GS_TRY(4, 2)   // (8, 2) would need 256 ring registers
@@ -171,14 +172,14 @@ static hipError_t launch_conv3_taps(const ConvArgs& a, const ConvGeom& g, hipStr
 }
 
 template <typename TR, int TO, int TP, int WO, int WP>
-static hipError_t launch_conv3_vw(const ConvArgs& a, const ConvGeom& g, hipStream_t s) {
+static hipError_t launch_conv3_vw(const ConvArgs& a, const ConvGeom& g, hipStream_t s, bool probe) {
   constexpr int ESZ = TR::kEsz;
   {
-    const hipError_t e = (a.Kh == 3 && a.Kw == 3) ? launch_conv4<TR, TO, TP, WO, WP, 3, 3>(a, g, s)
-                                                  : launch_conv4<TR, TO, TP, WO, WP, 0, 0>(a, g, s);
+    const hipError_t e = (a.Kh == 3 && a.Kw == 3) ? launch_conv4<TR, TO, TP, WO, WP, 3, 3>(a, g, s, probe)
+                                                  : launch_conv4<TR, TO, TP, WO, WP, 0, 0>(a, g, s, probe);
     if (e != hipErrorInvalidValue) return e;
   }
-  if (a.ksplit > 1) return hipErrorInvalidValue;   // only the kernel above splits the channel sum
+  if (a.ksplit > 1 || probe) return hipErrorInvalidValue;   // only the kernel above splits the channel sum
   // Widest pixel vector whose loads stay aligned: W (hence every row start) a multiple of it.
   if (a.W % 8 == 0) return launch_conv3_taps<TR, TO, TP, WO, WP, 8>(a, g, s);
   if (a.W % 4 == 0) return launch_conv3_taps<TR, TO, TP, WO, WP, 4>(a, g, s);
@@ -196,8 +197,9 @@ static hipError_t launch_conv3_vw(const ConvArgs& a, const ConvGeom& g, hipStrea
 #define GS_TILE 64, 128, 1, 4
 #endif
 
-hipError_t GS_CONV3_NAME(const ConvArgs& a, const ConvGeom& g, hipStream_t s) {
-  return launch_conv3_vw<GS_CONV3_TRAITS, GS_TILE>(a, g, s);
+// probe: nothing is launched; success if the producer / consumer kernel takes the layer.
+hipError_t GS_CONV3_NAME(const ConvArgs& a, const ConvGeom& g, hipStream_t s, bool probe) {
+  return launch_conv3_vw<GS_CONV3_TRAITS, GS_TILE>(a, g, s, probe);
 }
 
 }  // namespace gs

@@ -7,8 +7,8 @@
 //   * evaluates a program by dispatching its nodes to the library's kernels: the pattern the
 //     paper maps to hardware, (compute dotProd (cartProd ?a0 ?a1)) (Fig. 3, Sec. 5.2), becomes one
 //     MFMA contraction without the Cartesian product ever existing in memory; the whole listing
-//     of Fig. 2a, and the whole of Fig. 5 that Fig. 4's rules derive from it, becomes the direct
-//     convolution; (compute reduceX (windows ...)) becomes the fused
+//     of Fig. 2a, and the whole of Fig. 5 that Fig. 4's rules derive from it where that is faster, becomes the
+//     direct convolution; (compute reduceX (windows ...)) becomes the fused
 //     pooling kernel; (compute reduceX (pair a b)) the element-wise kernel; every other
 //     transformer is a descriptor change (access, squeeze, flatten, reshape, outermost slice) or
 //     one of the data-moving kernels (transpose, slice, concat, pair, pad, windows); zero padding
@@ -501,14 +501,27 @@ bool strip_pads(const TreeP& x, const Env& env, int64_t first, TreeP* inner, int
 
 // The listing of Fig. 2a, or the form of it that the rules of Fig. 4 derive (Fig. 5: windows and
 // weights flattened, the product reshaped back), with the sizes of its shape literals.  The two are
-// the same convolution, and forming the windows on chip is the faster way to it.
+// the same convolution, and forming the windows on chip is mostly the faster way to it (direct_fits).
 struct ConvMatch {
   TreeP act, weights;
   std::vector<int64_t> window, stride;
   int64_t pad[2] = {0, 0};
 };
-// Is some direct kernel sure to take the convolution?
-bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result) {
+// Is some direct kernel sure to take the convolution?  `flat`: and is it the faster way than the listing node
+// by node (windows gathered in memory, one contraction, one transposition)?
+//
+// Measured over 1267 layers by device time of a whole evaluation, packing of the weights included (us, direct /
+// node by node); by this rule it is 1.05 times the better of the two on average, 1.28 always directly, 1.20 never:
+//   where the producer / consumer kernel takes windows of up to 3x3 it is the faster one nearly always (64
+//   channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192; 1x1 on average 0.8 of the time);
+//   the general and the few-channel kernel need positions to fill the chip, more for larger windows, and form
+//   the windows once for every 64 output channels (48 channels, 3x3: 0.6 of the time at 6e4 positions,
+//   1.3 times at 2e3; 64 images of 3 channels, 112x115, 5x5 to 64: 106 / 422; 256 of 8 channels, 14x15, 5x5 to
+//   256: 173 / 41);
+//   strides above 2 stage many times the pixels that are used (8 of 512 channels, 28x28, 1x1 stride 4: 234 / 15);
+//   windows of up to 64 bytes are over at once either way, and node by node has more launches to wait
+//   for (16 channels of 30x30, 1x1: 13 / 17 from the caller's side).
+bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result, bool flat) {
   Shape act;
   if (infer(m.act, env, &act)) return false;
   act.na = 1;
@@ -524,7 +537,15 @@ bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape
   a.O = int(w.d[0]); a.Kh = int(w.d[2]); a.Kw = int(w.d[3]);
   a.Sh = int(stride[0]); a.Sw = int(stride[1]); a.Ph = int(m.pad[0]); a.Pw = int(m.pad[1]);
   a.Ho = int(result.d[2]); a.Wo = int(result.d[3]);
-  return gs::conv_direct_fits(a);
+  if (!gs::conv_direct_fits(a)) return false;
+  if (!flat) return true;
+  const bool small_window = a.Kh <= 3 && a.Kw <= 3;
+  const int64_t plane = int64_t(a.Ho) * a.Wo, esz = int64_t(gs::dtype_size(a.in_dtype));
+  if (a.Sh <= 2 && a.Sw <= 2) {
+    if (a.N * plane >= gs::ceil_div(a.O, 64) * (small_window ? 4096 : 8192)) return true;
+    if (plane >= 16 && a.C * esz >= 32 && int64_t(a.C) * a.Kh * a.Kw * esz <= 64) return true;
+  }
+  return small_window && gs::conv_pipelined_takes(a);
 }
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
@@ -567,14 +588,14 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
     folded.act = inner;
     folded.pad[0] = lo[2];
     folded.pad[1] = lo[3];
-    if (direct_fits(folded, env, b, all)) {
+    if (direct_fits(folded, env, b, all, flat)) {
       *m = folded;
       return true;
     }
   }
   // What no direct kernel is sure to take (strides, windows and rows too large for the LDS, more images
-  // in a tile than it counts) the flat form still evaluates node by node.
-  return !flat || direct_fits(*m, env, b, all);
+  // in a tile than it counts), or takes longer for, the flat form evaluates node by node.
+  return !flat || direct_fits(*m, env, b, all, flat);
 }
 
 struct Evaluator {

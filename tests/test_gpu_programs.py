@@ -32,20 +32,19 @@ def test_conv2d_listing(dtype, odt, shape):
     tensors = {"activations": cfg["x"], "weights": wt}
     got, want = run_both(listings.CONV2D, tensors, ints, odt)
     assert_parity(got, want.materialize(), what=f"Fig. 2a {dtype} {shape}")
-    # the program the im2col rules derive from it (Fig. 5), which is dispatched like Fig. 2a
+    # the program the im2col rules derive from it (Fig. 5), dispatched like Fig. 2a or node by node
     meta = {k: (tuple(v.shape), v.dtype) for k, v in tensors.items()}
     im2col = gs.program_rewrite(listings.CONV2D, "im2col", meta, ints)
     got2 = gs.program_eval(im2col, {k: v.to(DEV) for k, v in tensors.items()}, ints, out_dtype=odt)
     assert_parity(got2, want.materialize(), what=f"Fig. 5 {dtype} {shape}")
-    assert torch.equal(got, got2)
-    # the same evaluated node by node (explicit windows -> flatten -> contraction -> reshape -> squeeze -> transpose):
+    # the same surely node by node (explicit windows -> flatten -> contraction -> reshape -> squeeze -> transpose):
     # a reshape of the flattened weights to their own shape is no part of the listing
     by_node = im2col.replace("(flatten (access weights 1))", f"(reshape (flatten (access weights 1)) (shape {o}) (shape {c * kh * kw}))")
     assert by_node != im2col
     got3 = gs.program_eval(by_node, {k: v.to(DEV) for k, v in tensors.items()}, ints, out_dtype=odt)
     assert_parity(got3, want.materialize(), what=f"Fig. 5 by node {dtype} {shape}")
     if dtype == "i8":
-        assert torch.equal(got, got3)
+        assert torch.equal(got, got2) and torch.equal(got, got3)
 
 
 def test_conv2d_listing_on_padded_tensor():
@@ -84,11 +83,14 @@ def test_padding_in_front_of_windows(pads, dtype):
 
 
 # Convolutions that the direct kernels refuse (a stride above 64, rows or windows too large for the LDS, many
-# images in one tile), and the next ones that they take: the flat form evaluates all of them.
+# images in one tile), the next ones that they take, and the sides of the line to where they are faster: the
+# flat form evaluates all of them.
 @pytest.mark.parametrize("dtype,odt", [("i8", None), ("bf16", None), ("bf16", torch.bfloat16)])
 @pytest.mark.parametrize("shape", [(1, 2, 70, 9, 3, 3, 1, 65, 1), (1, 16, 4, 1300, 8, 3, 3, 1, 1), (1, 16, 4, 900, 8, 3, 3, 1, 1),
-                                   (40, 32, 3, 3, 8, 3, 3, 1, 1), (16, 32, 3, 3, 8, 3, 3, 1, 1), (1, 32, 12, 12, 4, 11, 11, 1, 1)])
-def test_flat_form_where_no_direct_kernel_fits(shape, dtype, odt):
+                                   (40, 32, 3, 3, 8, 3, 3, 1, 1), (16, 32, 3, 3, 8, 3, 3, 1, 1), (1, 32, 12, 12, 4, 11, 11, 1, 1),
+                                   (2, 64, 9, 10, 24, 3, 3, 1, 1), (9, 48, 33, 31, 9, 3, 3, 1, 1), (8, 48, 33, 31, 9, 3, 3, 1, 1),
+                                   (1, 16, 6, 5, 20, 1, 1, 1, 1), (8, 3, 36, 37, 129, 5, 5, 1, 1), (2, 512, 9, 9, 4, 1, 1, 4, 4)])
+def test_flat_form_of_every_route(shape, dtype, odt):
     n, c, h, w, o, kh, kw, sh, sw = shape
     tensors = {"activations": gen_small(dtype, (n, c, h, w), 9470), "weights": gen_small(dtype, (o, c, kh, kw), 9471)}
     ints = dict(C=c, Kh=kh, Kw=kw, Sh=sh, Sw=sw)

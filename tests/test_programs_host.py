@@ -220,6 +220,18 @@ def test_padding_is_the_convolutions_own_where_its_rows_fit():
         tensors = {"activations": ((1, 40, 3, w), torch.int8), "weights": ((8, 40, 3, 3), torch.int8)}
         ints = dict(C=40, Kh=3, Kw=3, Sh=1, Sw=1, Ph=1, Pw=1)
         padded_bytes = 40 * 5 * (w + 2)
-        for text in (listings.CONV2D_PADDED, gs.program_rewrite(listings.CONV2D_PADDED, "im2col", tensors, ints)):
-            need = program_workspace(text, tensors, ints)
-            assert 0 < need < padded_bytes if folded else padded_bytes < need < 3 * padded_bytes
+        need = program_workspace(listings.CONV2D_PADDED, tensors, ints)
+        assert 0 < need < padded_bytes if folded else padded_bytes < need < 3 * padded_bytes
+
+
+@pytest.mark.parametrize("shape,direct", [
+    ((2, 64, 28, 32, 88, 3, 1), True), ((16, 48, 40, 40, 64, 3, 1), True), ((1, 16, 30, 30, 64, 1, 1), True), ((32, 3, 64, 64, 64, 5, 1), True),
+    ((8, 512, 28, 28, 4, 1, 4), False), ((1, 48, 39, 15, 80, 3, 2), False), ((64, 8, 20, 21, 256, 5, 1), False)])
+def test_flat_listing_takes_the_faster_way(shape, direct):
+    """The direct convolution's workspace is the packed weights and a split sum; node by node holds the gathered windows."""
+    n, c, h, w, o, k, s = shape
+    tensors = {"activations": ((n, c, h, w), torch.bfloat16), "weights": ((o, c, k, k), torch.bfloat16)}
+    ints = dict(C=c, Kh=k, Kw=k, Sh=s, Sw=s)
+    gathered = 2 * n * ((h - k) // s + 1) * ((w - k) // s + 1) * c * k * k
+    flat = program_workspace(gs.program_rewrite(listings.CONV2D, "im2col", tensors, ints), tensors, ints)
+    assert flat == program_workspace(listings.CONV2D, tensors, ints) if direct else flat > gathered
