@@ -255,9 +255,11 @@ int glenside_program_shape(const char* text, const gs_named_ap* tensors, int n_t
  * dtype the same, or GS_BF16 where the root is a bfloat16 contraction).  Node by node:
  *   (compute dotProd (cartProd a0 a1))   one MFMA contraction; the Cartesian product is never
  *                                        formed (the pattern Fig. 3 maps to hardware);
- *   the whole listing of Fig. 2a, or of
+ *   the whole listing of Fig. 2a, or,
+ *   where that is the faster way, of
  *   Fig. 5 (what Fig. 4 makes of it)     the direct convolution (windows formed on chip); symmetric
- *                                        zero padding in front of the windows becomes its own;
+ *                                        zero padding in front of the windows becomes its own where
+ *                                        its kernels are sure to take it so;
  *   (compute reduceX (windows ...))      the fused pooling kernel (Fig. 2c);
  *   (compute reduceX (pair a b))         the element-wise kernel (Sec. 5.4);
  *   access squeeze flatten reshape,

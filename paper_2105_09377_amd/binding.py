@@ -401,7 +401,9 @@ def program_shape(text: str, tensors, ints=None):
 
 def program_eval(text: str, tensors, ints=None, out_dtype=None, out: Optional[torch.Tensor] = None,
                  workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """Evaluate an access-pattern program (the paper's s-expression text) on the GPU."""
+    """Evaluate an access-pattern program (the paper's s-expression text) on the GPU.
+
+    `tensors` and `ints` are mappings by name; `out` has at least as many elements as the result."""
     return _m().program_eval(text, tensors, ints or {}, out_dtype, out, workspace)
 
 
