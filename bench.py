@@ -49,20 +49,20 @@ KERNEL_SOURCES = {
 # workload -> (fetch + write bytes per launch of its dominant kernel, source group, digest of the
 # sources the counters were taken with)
 TRAFFIC = {
-    "resnet18": (26.75e6 + 25.69e6, "conv", "f4748cc2caa3c2531990a0702814e011d54d0b5a9e9a12edc92d73cba98f0991"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
-    "conv3x3": (13.90e6 + 12.85e6, "conv", "f4748cc2caa3c2531990a0702814e011d54d0b5a9e9a12edc92d73cba98f0991"),
-    "conv3x3_b64": (26.75e6 + 25.69e6, "conv", "f4748cc2caa3c2531990a0702814e011d54d0b5a9e9a12edc92d73cba98f0991"),
-    "im2col_gather": (12.97e6 + 115.65e6, "windows", "28be54f8a8d040349c57db5f9820cda36bffe90e20b1b9dee462b12e92a66d8b"),
-    "maxpool": (103.00e6 + 25.69e6, "reduce", "b45ea8b2d26f14f5a55128314b01ed29d77f86f18a0cd19592276c47d9523874"),
-    "reduce": (268.44e6 + 0.52e6, "reduce", "b45ea8b2d26f14f5a55128314b01ed29d77f86f18a0cd19592276c47d9523874"),
-    "transpose": (25.82e6 + 25.70e6, "move", "3f71ed284b450b94c97176cd729f28061f8fef2f40f28ca8a27bfbf72e4a3d62"),
-    "dense_blocked": (50.63e6 + 16.78e6, "gemm", "26fb4e7e86e567072c495a5931bb5d3a671db0d4bbb0683e7d6380e858d29ee1"),
-    "dense": (1611.42e6 + 281.85e6, "gemm", "26fb4e7e86e567072c495a5931bb5d3a671db0d4bbb0683e7d6380e858d29ee1"),
-    "mlp_scaled": (28.91e6 + 16.78e6, "gemm", "26fb4e7e86e567072c495a5931bb5d3a671db0d4bbb0683e7d6380e858d29ee1"),
-    "conv3x3_i8": (7.15e6 + 25.69e6, "conv", "f4748cc2caa3c2531990a0702814e011d54d0b5a9e9a12edc92d73cba98f0991"),
-    "dense_i8": (805.93e6 + 287.46e6, "gemm", "26fb4e7e86e567072c495a5931bb5d3a671db0d4bbb0683e7d6380e858d29ee1"),
-    "dense_fp8": (806.21e6 + 134.22e6, "gemm", "26fb4e7e86e567072c495a5931bb5d3a671db0d4bbb0683e7d6380e858d29ee1"),
-    "depthwise": (103.03e6 + 102.76e6, "depthwise", "c9515252f603786f310d6a9178342e1244cdadaa9101f1a1d8b67c2f26904071"),
+    "resnet18": (26.75e6 + 25.69e6, "conv", "a55bb70d7643ade91cf9c4d1fadcb3a062d07d221ac4fca3c17c8752707c6498"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
+    "conv3x3": (13.90e6 + 12.85e6, "conv", "a55bb70d7643ade91cf9c4d1fadcb3a062d07d221ac4fca3c17c8752707c6498"),
+    "conv3x3_b64": (26.75e6 + 25.69e6, "conv", "a55bb70d7643ade91cf9c4d1fadcb3a062d07d221ac4fca3c17c8752707c6498"),
+    "im2col_gather": (12.97e6 + 115.64e6, "windows", "318b6463be6a633f366fdc08bf2255485ed7d57ef668acf91f41aa9d620d6a9c"),
+    "maxpool": (102.99e6 + 25.69e6, "reduce", "812d2a7516084d7007ca4433dfaee485a12f0de713989060d23fce143cf4a23a"),
+    "reduce": (268.44e6 + 0.52e6, "reduce", "812d2a7516084d7007ca4433dfaee485a12f0de713989060d23fce143cf4a23a"),
+    "transpose": (25.82e6 + 25.70e6, "move", "2a14f75ad84753296671fad4671c23a85d975f9ba434a4e46387230e36df2ff7"),
+    "dense_blocked": (50.62e6 + 16.78e6, "gemm", "56b6bc23dc3b4249a9628adc4a6061306b72d6615391069c59b8c1aa8e1e50d2"),
+    "dense": (1611.22e6 + 281.05e6, "gemm", "56b6bc23dc3b4249a9628adc4a6061306b72d6615391069c59b8c1aa8e1e50d2"),
+    "mlp_scaled": (28.92e6 + 16.78e6, "gemm", "56b6bc23dc3b4249a9628adc4a6061306b72d6615391069c59b8c1aa8e1e50d2"),
+    "conv3x3_i8": (7.15e6 + 25.69e6, "conv", "a55bb70d7643ade91cf9c4d1fadcb3a062d07d221ac4fca3c17c8752707c6498"),
+    "dense_i8": (805.88e6 + 282.67e6, "gemm", "56b6bc23dc3b4249a9628adc4a6061306b72d6615391069c59b8c1aa8e1e50d2"),
+    "dense_fp8": (806.23e6 + 134.22e6, "gemm", "56b6bc23dc3b4249a9628adc4a6061306b72d6615391069c59b8c1aa8e1e50d2"),
+    "depthwise": (103.11e6 + 102.78e6, "depthwise", "6109573ca7c7ac488588de7054e08cf70827baec79f69af2c654e35aae99799a"),
 }
 
 
