@@ -24,6 +24,7 @@
 
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <memory>
 #include <string>
@@ -510,17 +511,19 @@ struct ConvMatch {
 // Is some direct kernel sure to take the convolution?  `flat`: and is it the faster way than the listing node
 // by node (windows gathered in memory, one contraction, one transposition)?
 //
-// Measured over 1267 layers by device time of a whole evaluation, packing of the weights included (us, direct /
-// node by node); by this rule it is 1.05 times the better of the two on average, 1.28 always directly, 1.20 never:
+// Measured over 1267 layers, a whole evaluation with the packing of the weights (us, direct / node by node).  As
+// a caller meets it, passes among others, this rule is 1.03 times the better of the two on average
+// (at worst 1.65), 1.18 always directly, 1.21 never; by device time alone 1.08, 1.28 and 1.20:
 //   where the producer / consumer kernel takes windows of up to 3x3 it is the faster one nearly always (64
 //   channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192; 1x1 on average 0.8 of the time);
-//   the general and the few-channel kernel need positions to fill the chip, more for larger windows, and form
-//   the windows once for every 64 output channels (48 channels, 3x3: 0.6 of the time at 6e4 positions,
-//   1.3 times at 2e3; 64 images of 3 channels, 112x115, 5x5 to 64: 106 / 422; 256 of 8 channels, 14x15, 5x5 to
-//   256: 173 / 41);
-//   strides above 2 stage many times the pixels that are used (8 of 512 channels, 28x28, 1x1 stride 4: 234 / 15);
-//   windows of up to 64 bytes are over at once either way, and node by node has more launches to wait
-//   for (16 channels of 30x30, 1x1: 13 / 17 from the caller's side).
+//   the general and the few-channel kernel need positions to fill the chip, more for large windows of two-byte
+//   values, and form the windows once for every 64 output channels (48 channels, 3x3: 0.6 of the time at 6e4
+//   positions, 1.3 times at 2e3; 64 images of 3 channels, 112x115, 5x5 to 64: 106 / 422; 256 of 8 channels,
+//   14x15, 5x5 to 256: 173 / 41; 16 of 96, 57x58, 5x5 stride 2 to 128: 60 / 78 in bytes, 100 / 65 in bf16);
+//   short windows (in bytes, times the stride and 2 for odd rows, which are read pixel by pixel) are over before
+//   the launches of the other way are issued, 17 us: 2 images of 16 channels, 25x38, 3x3 stride 2 13.3 / 17.1
+//   from the caller's side, 11.8 / 10.7 on the device; with more bytes, 2 of 32, 51x47, padded, 3x3 stride 2: 29.9 / 18.1;
+//   strides above 2 stage many times the pixels that are used (8 of 512 channels, 28x28, 1x1 stride 4: 234 / 15).
 bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result, bool flat) {
   Shape act;
   if (infer(m.act, env, &act)) return false;
@@ -542,8 +545,9 @@ bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape
   const bool small_window = a.Kh <= 3 && a.Kw <= 3;
   const int64_t plane = int64_t(a.Ho) * a.Wo, esz = int64_t(gs::dtype_size(a.in_dtype));
   if (a.Sh <= 2 && a.Sw <= 2) {
-    if (a.N * plane >= gs::ceil_div(a.O, 64) * (small_window ? 4096 : 8192)) return true;
-    if (plane >= 16 && a.C * esz >= 32 && int64_t(a.C) * a.Kh * a.Kw * esz <= 64) return true;
+    if (a.N * plane >= gs::ceil_div(a.O, 64) * (small_window ? 4096 : 4096 * esz)) return true;
+    const int64_t window_bytes = int64_t(a.C) * a.Kh * a.Kw * esz;
+    if (small_window && a.C * esz >= 32 && window_bytes * std::max(a.Sh, a.Sw) * (1 + a.W % 2) <= 1152) return true;
   }
   return small_window && gs::conv_pipelined_takes(a);
 }

@@ -89,7 +89,8 @@ def test_padding_in_front_of_windows(pads, dtype):
 @pytest.mark.parametrize("shape", [(1, 2, 70, 9, 3, 3, 1, 65, 1), (1, 16, 4, 1300, 8, 3, 3, 1, 1), (1, 16, 4, 900, 8, 3, 3, 1, 1),
                                    (40, 32, 3, 3, 8, 3, 3, 1, 1), (16, 32, 3, 3, 8, 3, 3, 1, 1), (1, 32, 12, 12, 4, 11, 11, 1, 1),
                                    (2, 64, 9, 10, 24, 3, 3, 1, 1), (9, 48, 33, 31, 9, 3, 3, 1, 1), (8, 48, 33, 31, 9, 3, 3, 1, 1),
-                                   (1, 16, 6, 5, 20, 1, 1, 1, 1), (8, 3, 36, 37, 129, 5, 5, 1, 1), (2, 512, 9, 9, 4, 1, 1, 4, 4)])
+                                   (1, 16, 6, 5, 20, 1, 1, 1, 1), (8, 3, 36, 37, 129, 5, 5, 1, 1), (2, 512, 9, 9, 4, 1, 1, 4, 4),
+                                   (2, 16, 9, 11, 5, 3, 3, 2, 2), (2, 17, 9, 11, 5, 3, 3, 2, 2), (2, 32, 9, 10, 5, 3, 3, 2, 2)])
 def test_flat_form_of_every_route(shape, dtype, odt):
     n, c, h, w, o, kh, kw, sh, sw = shape
     tensors = {"activations": gen_small(dtype, (n, c, h, w), 9470), "weights": gen_small(dtype, (o, c, kh, kw), 9471)}

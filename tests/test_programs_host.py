@@ -225,8 +225,10 @@ def test_padding_is_the_convolutions_own_where_its_rows_fit():
 
 
 @pytest.mark.parametrize("shape,direct", [
-    ((2, 64, 28, 32, 88, 3, 1), True), ((16, 48, 40, 40, 64, 3, 1), True), ((1, 16, 30, 30, 64, 1, 1), True), ((32, 3, 64, 64, 64, 5, 1), True),
-    ((8, 512, 28, 28, 4, 1, 4), False), ((1, 48, 39, 15, 80, 3, 2), False), ((64, 8, 20, 21, 256, 5, 1), False)])
+    ((2, 64, 28, 32, 88, 3, 1), True), ((16, 48, 40, 40, 64, 3, 1), True), ((1, 16, 30, 30, 64, 1, 1), True),
+    ((2, 32, 25, 38, 24, 3, 2), True), ((2, 16, 25, 39, 24, 3, 2), True), ((32, 3, 64, 64, 64, 5, 1), True),
+    ((8, 512, 28, 28, 4, 1, 4), False), ((1, 48, 39, 15, 80, 3, 2), False), ((2, 33, 25, 38, 24, 3, 2), False),
+    ((2, 17, 25, 39, 24, 3, 2), False), ((64, 8, 20, 21, 256, 5, 1), False)])
 def test_flat_listing_takes_the_faster_way(shape, direct):
     """The direct convolution's workspace is the packed weights and a split sum; node by node holds the gathered windows."""
     n, c, h, w, o, k, s = shape
