@@ -12,6 +12,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <utility>
 #include <vector>
 
 #include "../../include/glenside.h"
@@ -109,6 +110,39 @@ struct Owned {
   }
   ~Owned() { Py_DECREF(object); }
   Owned(const Owned&) = delete;
+};
+
+// The items of a mapping, held until the end of the scope: all of them are taken before any is converted, which
+// may run any code.  Twice cheaper than a copy of the dict, which only other mappings need.
+struct Items {
+  std::vector<std::pair<PyObject*, PyObject*>> items;
+  explicit Items(PyObject* mapping) {
+    if (PyDict_CheckExact(mapping)) {
+      take(mapping);
+      return;
+    }
+    const Owned copy(PyDict_New());
+    if (PyDict_Update(copy.object, mapping)) throw Failed{};
+    take(copy.object);
+  }
+  ~Items() {
+    for (const auto& i : items) {
+      Py_DECREF(i.first);
+      Py_DECREF(i.second);
+    }
+  }
+  Items(const Items&) = delete;
+
+ private:
+  void take(PyObject* dict) {
+    items.reserve(size_t(PyDict_GET_SIZE(dict)));
+    PyObject *key, *value;
+    for (Py_ssize_t pos = 0; PyDict_Next(dict, &pos, &key, &value);) {
+      Py_INCREF(key);
+      Py_INCREF(value);
+      items.push_back({key, value});
+    }
+  }
 };
 
 // A sequence of integers; None = absent (a null pointer at the C boundary).
@@ -412,10 +446,9 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
   return guarded(n, 6, [&](PyObject*& r) {
     const char* text = PyUnicode_AsUTF8(p[0]);
     if (!text) throw Failed{};
-    // Names and tensors are borrowed from copies of the mappings: the caller's may change meanwhile, from
-    // another thread while the interpreter lock is released, or from the conversion of an integer.
-    const Owned named(PyDict_New()), numbers(PyDict_New());
-    if (PyDict_Update(named.object, p[1]) || PyDict_Update(numbers.object, p[2])) throw Failed{};
+    // Names and tensors are held: the caller's mappings may change meanwhile, from another thread while the
+    // interpreter lock is released, or from the conversion of an integer.
+    const Items named(p[1]), numbers(p[2]);
     auto name_of = [](PyObject* key) {
       const char* s = PyUnicode_AsUTF8(key);
       if (!s) throw Failed{};
@@ -424,13 +457,12 @@ PyObject* py_program_eval(PyObject*, PyObject* const* p, Py_ssize_t n) {
     std::vector<gs_named_ap> tensors;
     std::vector<gs_named_int> ints;
     const at::Tensor* first = nullptr;
-    PyObject *key, *value;
-    for (Py_ssize_t pos = 0; PyDict_Next(named.object, &pos, &key, &value);) {
+    for (const auto& [key, value] : named.items) {
       const at::Tensor& t = tensor(value);
       if (!first) first = &t;
       tensors.push_back({name_of(key), describe(t, 0)});
     }
-    for (Py_ssize_t pos = 0; PyDict_Next(numbers.object, &pos, &key, &value);) ints.push_back({name_of(key), integer(value)});
+    for (const auto& [key, value] : numbers.items) ints.push_back({name_of(key), integer(value)});
     if (!first) {
       PyErr_SetString(PyExc_StopIteration, "a program needs a tensor");
       throw Failed{};
