@@ -95,7 +95,8 @@ __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return ceil_
 // division is a ~40-instruction routine on this hardware).  With l = ceil(log2 d) and
 // m = floor(2^(31+l) / d) + 1, floor(x / d) = (x * m) >> (31 + l) for every x < 2^31.
 struct FastDiv {
-  uint32_t d, mul, shift;   // shift = l - 1 applied to the high word; d == 1 is special-cased
+  uint32_t d, mul, shift;   // shift = l - 1 applied to the high word
+  uint32_t one;             // d == 1, where the product is zero: all ones, so that no branch is needed
   __host__ __device__ static FastDiv make(uint32_t d) {
     FastDiv f;
     f.d = d;
@@ -103,10 +104,11 @@ struct FastDiv {
     while ((uint64_t(1) << l) < d) ++l;
     f.mul = d > 1 ? uint32_t(((uint64_t(1) << (31 + l)) / d) + 1) : 0;
     f.shift = l > 0 ? l - 1 : 0;
+    f.one = d > 1 ? 0u : ~0u;
     return f;
   }
   __device__ __forceinline__ uint32_t div(uint32_t x) const {
-    return d == 1 ? x : (__umulhi(x, mul) >> shift);
+    return (__umulhi(x, mul) >> shift) | (x & one);
   }
   __device__ __forceinline__ void divmod(uint32_t x, uint32_t* q, uint32_t* r) const {
     *q = div(x);

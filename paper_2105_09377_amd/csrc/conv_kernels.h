@@ -41,6 +41,7 @@ struct ConvGeom {
   int pos_major;    // producer/consumer kernel: tiles numbered position tile first (all channel tiles of a
                     // position tile are neighbours) instead of channel tile first
   FastDiv dHWo, dWo;  // division by Ho*Wo and by Wo
+  int php, rowp, halfb, bufb;   // conv_tile_kernel: LDS bytes of a patch row's phase, a row, a half, a buffer
   FastDiv dTiles, dXG, dW;   // producer/consumer kernel: by position tiles (channel tiles if pos_major), pixel groups per row, W
 };
 
@@ -77,6 +78,23 @@ constexpr int kLdsLimit = 160 * 1024;
 // span more images than the segment table holds.  Defined in conv.hip.
 int conv_max_rows(const ConvArgs& a, int64_t M, int HWo, int TP);
 int conv_num_cus();
+
+// Workgroup shapes of conv_tile_kernel (conv_tile_kernel.h): position blocks per wave, channel
+// waves, position waves, channel-sum groups.
+struct TileShape {
+  int nj, wo, wp, ks;
+};
+constexpr TileShape kTileShapes[] = {{4, 2, 2, 1}, {2, 2, 2, 1}, {2, 4, 1, 1}, {2, 1, 1, 4}, {1, 1, 1, 4}};
+constexpr int kNumTileShapes = 5;
+constexpr int kTileItem = 4;    // pixels of a patch item
+// How a layer runs on it.
+struct TilePlan {
+  int shape;                // index into kTileShapes, or -1: the kernel does not take the layer
+  int il, maxi;             // interleaved blocks, patch items per thread
+  bool one;                 // a single chunk per group
+  int tiles, lds_bytes;
+  ConvGeom g;
+};
 
 // CB = channel-chunk bytes per pixel (32, 64 or 128); WO x WP waves over (channels, positions).
 template <typename TR, int TO, int TP, int WO, int WP, int CB>

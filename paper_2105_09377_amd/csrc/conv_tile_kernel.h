@@ -1,0 +1,476 @@
+// Direct convolution (Fig. 2a) in small independent workgroups, several of which share a compute
+// unit, so that one multiplies while another waits for memory or writes its results back.
+//
+// A workgroup has KS x WO x WP waves.  The KS groups split the channel chunks (Fig. 6's last
+// blocking rule inside a workgroup: the partial sums meet in LDS at the end); within a group wave
+// (wo, wp) owns 32 output channels x NJ blocks of 32 positions, and the group's waves share one
+// patch: the input rows that the tile's positions need, one chunk of 32 bytes of channels at a
+// time, in three LDS buffers.  All waves do everything: request the patch of the chunk after next
+// (registers), multiply, pack the next chunk's patch into LDS, one barrier per chunk.
+//
+// Weights never touch the LDS.  A wave needs a 1 KB fragment per tap and chunk, and the blocked
+// copy of the weights holds exactly these fragments: they are loaded from L2 into a ring of KH * KW
+// register sets, each refilled with the next chunk's tap as soon as its MFMAs have been issued.
+//
+// Patch layout [half][row][phase][slot] in 16-byte cells (half: which 16 bytes of the 32-byte
+// channel chunk).  Column p of a patch row (p = input column + Pw) lies at phase p % PH, slot
+// p / PH with PH = IL * S.  The IL blocks of a block group interleave their positions -- lane n of
+// block j is position IL * n + j of the group -- so that the cell of (block j, tap column kw) is
+// column PH * n' + j * S + kw: lanes read consecutive slots of one phase (no bank conflicts, any
+// stride), and equal j * S + kw share one read.  IL = 4: 6 reads for 12 MFMAs of a 3x3 kernel row
+// instead of 12, which matters because with one read per MFMA the LDS would be as busy as the
+// matrix units.  IL positions must lie in one output row (Wo % IL == 0).
+//
+// What bounds it: a wave issues in order, so what is not an MFMA has to be issued under one (see the
+// loop); a chunk of 36 MFMAs (1152 cycles) takes 1800 cycles with one workgroup per compute unit,
+// 2450 before its loads and LDS stores were dealt out between the MFMAs.  On top come 1.9 us from
+// the launch to the first MFMA and 2 us of write-back, which only other workgroups can cover.
+// Against the kernels that these layers took before, by themselves: 64 channels at 56x56, batch 32,
+// 16.5 -> 14.4 us (int8 15.2 -> 13.0); one image of 56x56 x 64 6.6 -> 4.5, 28x28 x 128 9.1 -> 5.3,
+// 14x14 x 256 10.0 -> 6.1 (two launches before); 8 images of 14x14 x 256 12.9 -> 7.8; 16 of
+// 7x7 x 512 17.8 -> 12.0; chunk counts that are no multiple of four (80 channels, 30x12 -> 112, 6
+// images) 29.9 -> 4.8.  Over 620 layers of all sizes 2.2 times faster.
+#pragma once
+#include "conv4_kernel.h"
+
+namespace gs {
+
+typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
+
+template <typename TR, int KH, int KW, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE>
+__global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArgs a, ConvGeom g) {
+  static_assert(NJ % IL == 0, "whole groups of interleaved blocks");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  constexpr int ESZ = TR::kEsz;
+  constexpr int G = 16 / ESZ;             // channels per 16-byte cell
+  constexpr int CCH = 32 / ESZ;           // channels per chunk
+  constexpr int VW = kTileItem, LD = VW * ESZ / 4;        // pixels and dwords of a patch load
+  constexpr int T = KH * KW, PH = IL * S, NQ = (IL - 1) * S + KW;
+  constexpr int GP = IL == 1 && NJ > 1 ? 2 : 1;           // block groups that take turns within a step
+  constexpr int NG = NJ / IL, NSG = NG / GP, STEPS = KH * NSG, SLOTS = NQ * GP;
+  constexpr int NBUF = ONE ? 1 : 3;       // patch buffers (ONE: a group has a single chunk)
+  constexpr int NW = WO * WP, NT = 64 * NW;
+  constexpr bool INT = __is_same(typename TR::acc_t, int32_t);
+  using acc_t = typename TR::acc_t;
+  typedef int32_t ld2_t __attribute__((ext_vector_type(2), aligned(1)));
+  typedef int32_t ld1_t __attribute__((aligned(1)));
+  struct Piece { int32_t w[LD]; };        // one load: VW pixels of a channel
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave / NW, w = wave % NW, wo = w / WP, wp = w % WP;
+  const int gt = tid - kg * NT;           // thread within the group
+
+  // Every argument is requested at once: one latency instead of one per use.
+  asm volatile("" ::"s"(a.act), "s"(a.wblk), "s"(a.out), "s"(a.residual), "s"(a.C), "s"(a.H), "s"(a.W), "s"(a.O),
+               "s"(a.Ph), "s"(a.Pw), "s"(a.Wo), "s"(a.Cpad), "s"(a.relu), "s"(a.out_dtype), "s"(g.HWo), "s"(g.M), "s"(g.tps),
+               "s"(g.pos_major));
+  asm volatile("" ::"s"(g.dHWo.mul), "s"(g.dHWo.shift), "s"(g.dHWo.one), "s"(g.dWo.mul), "s"(g.dWo.shift), "s"(g.dWo.one),
+               "s"(g.dW.mul), "s"(g.dW.shift), "s"(g.dW.one), "s"(g.dTiles.d), "s"(g.dTiles.mul), "s"(g.dTiles.shift),
+               "s"(g.dTiles.one), "s"(g.php), "s"(g.rowp), "s"(g.halfb), "s"(g.bufb));
+
+  // Tile: renumbered so that an XCD owns a contiguous range (see conv4_kernel.h).
+  int m0, mend, o0;
+  {
+    const int n_tiles = int(gridDim.x), x = int(blockIdx.x) & 7;
+    const int per = n_tiles >> 3, rem = n_tiles & 7;
+    const int tile = x * per + (x < rem ? x : rem) + (int(blockIdx.x) >> 3);
+    const int q = int(g.dTiles.div(uint32_t(tile))), r = tile - q * int(g.dTiles.d);
+    const int mt = g.pos_major ? q : r;
+    o0 = (g.pos_major ? r : q) * (32 * WO);
+    m0 = mt * g.tps;
+    mend = m0 + g.tps < int(g.M) ? m0 + g.tps : int(g.M);
+  }
+  const TileSegs ts = tile_segs(m0, mend, g);
+  // Chunks of a group, and of this one: the last groups have fewer or none where KS does not divide them.
+  const int n_chunks = a.Cpad / CCH, most = (n_chunks + KS - 1) / KS, left = n_chunks - kg * most;
+  const int cnt = KS == 1 ? most : left < 0 ? 0 : left < most ? left : most;
+  const int first = cnt > 0 ? kg * most : 0;              // (a group without chunks loads the first one and leaves it)
+
+  // ---- weights: fragments of (32 channels, chunk, tap), 1 KB each -------------------------------
+  const uint8_t* wsrc;
+  {
+    const int n_oblk = (a.O + 31) / 32;
+    int ob = o0 / 32 + wo;
+    ob = ob < n_oblk ? ob : n_oblk - 1;   // blocks past O are never stored
+    wsrc = static_cast<const uint8_t*>(a.wblk) + (int64_t(ob) * n_chunks + first) * (T * 1024);
+  }
+  // lane's 16 bytes of a fragment: row lane % 32, half lane / 32, in the block's order (conv_repack_kernel)
+  const uint32_t wlane = uint32_t((lane & 31) * 32 + (((lane >> 5) ^ ((((lane & 31) >> 2) ^ ((lane & 31) >> 3)) & 1)) << 4));
+  i32x4 ring[T];
+  auto load_tap = [&](int ch, auto tap_) {
+    constexpr int tap = decltype(tap_)::value;
+    ring[tap] = *reinterpret_cast<const i32x4*>(wsrc + int64_t(ch) * (T * 1024) + tap * 1024 + wlane);
+  };
+
+  // ---- patch items: VW pixels, consecutive in the rows a segment needs, x one half of a chunk ----
+  const int64_t plane = int64_t(a.H) * a.W * ESZ;
+  const uint8_t* asrc = static_cast<const uint8_t*>(a.act) + int64_t(first) * CCH * plane;
+  // The extents of the first two segments are scalars; a tile that touches more than two images
+  // (small planes) walks them.
+  int ihlo0, rows0, ihlo1 = 0, rows1 = 0;
+  seg_extent(ts, 0, g, S, a.Ph, KH, &ihlo0, &rows0);
+  if (ts.nseg > 1) seg_extent(ts, 1, g, S, a.Ph, KH, &ihlo1, &rows1);
+  uint32_t src[MAXI];
+  int dst[MAXI][VW];
+  bool item_ok[MAXI];
+  {
+    auto valid = [&](int ihlo, int rows, int* vlo, int* items, int* len) {
+      *vlo = ihlo > 0 ? ihlo : 0;
+      const int vhi = ihlo + rows < a.H ? ihlo + rows : a.H;
+      *len = vhi > *vlo ? (vhi - *vlo) * a.W : 0;
+      *items = (*len + VW - 1) / VW;
+    };
+    int vlo0, it0, len0, vlo1 = 0, it1 = 0, len1 = 0;
+    valid(ihlo0, rows0, &vlo0, &it0, &len0);
+    if (ts.nseg > 1) valid(ihlo1, rows1, &vlo1, &it1, &len1);
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i) {
+      int rem = gt + NT * i, seg = 0, base = 0, ihlo = ihlo0, vlo = vlo0, items = it0, len = len0;
+      if (ts.nseg == 2) {                   // uniform
+        if (rem >= 2 * it0) {
+          rem -= 2 * it0;
+          seg = 1; base = rows0; ihlo = ihlo1; vlo = vlo1; items = it1; len = len1;
+        }
+      } else if (ts.nseg > 2) {
+        int rows = rows0;
+        while (rem >= 2 * items && seg + 1 < ts.nseg) {
+          rem -= 2 * items;
+          base += rows;
+          ++seg;
+          seg_extent(ts, seg, g, S, a.Ph, KH, &ihlo, &rows);
+          valid(ihlo, rows, &vlo, &items, &len);
+        }
+      }
+      item_ok[i] = rem < 2 * items;
+      const int half = rem >= items ? 1 : 0, k = item_ok[i] ? rem - half * items : 0;
+      int f = k * VW < len - VW ? k * VW : len - VW;      // the last item ends with the range
+      f = f > 0 ? f + vlo * a.W : vlo * a.W;
+      int row = int(g.dW.div(uint32_t(f))), col = f - row * a.W;
+      // byte offsets from the tensor's start fit 32 bits (fewer than 2^31 elements)
+      src[i] = item_ok[i] ? uint32_t((ts.n_first + seg) * a.C + half * G) * uint32_t(plane) + uint32_t(f) * uint32_t(ESZ) : 0u;
+      int cell = half * g.halfb + (base + row - ihlo) * g.rowp;
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        const uint32_t c = uint32_t(col + a.Pw);
+        dst[i][e] = cell + int(c % PH) * g.php + int(c / PH) * 16;
+        if (++col == a.W) {                               // rows are at least VW long: at most one wrap
+          col = 0;
+          cell += g.rowp;
+        }
+      }
+    }
+  }
+  Piece preg0[MAXI][G], preg[MAXI][G];
+  auto load_piece = [&](const uint8_t* b, Piece (&preg)[MAXI][G], auto i_, auto t_) {
+    constexpr int i = decltype(i_)::value, t = decltype(t_)::value;
+    const uint8_t* at = b + int64_t(t) * plane + src[i];
+    if constexpr (LD == 2) {
+      const i32x2 v = *reinterpret_cast<const ld2_t*>(at);
+      preg[i][t].w[0] = v[0]; preg[i][t].w[1] = v[1];
+    } else {
+      preg[i][t].w[0] = *reinterpret_cast<const ld1_t*>(at);
+    }
+  };
+  auto load_patch = [&](int ch, Piece (&preg)[MAXI][G]) {
+    static_for<MAXI>([&](auto i_) {
+      static_for<G>([&](auto t_) { load_piece(asrc + int64_t(ch) * CCH * plane, preg, i_, t_); });
+    });
+  };
+  uint8_t* const patch = lds + kg * NBUF * g.bufb;
+  // Pixel p of item i: element t of the cell is channel t of the half; one byte permute per two sources.
+  auto store_cell = [&](uint8_t* pb, const Piece (&preg)[MAXI][G], auto i_, auto p_) {
+    constexpr int i = decltype(i_)::value, p = decltype(p_)::value;
+    i32x4 cell;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      if constexpr (ESZ == 2) {
+        cell[d] = int32_t(__builtin_amdgcn_perm(preg[i][2 * d + 1].w[p / 2], preg[i][2 * d].w[p / 2],
+                                                p % 2 ? 0x07060302u : 0x05040100u));
+      } else {
+        const uint32_t sel = uint32_t((4 + p % 4) << 8 | p % 4);
+        const uint32_t lo = __builtin_amdgcn_perm(preg[i][4 * d + 1].w[p / 4], preg[i][4 * d].w[p / 4], sel);
+        const uint32_t hi = __builtin_amdgcn_perm(preg[i][4 * d + 3].w[p / 4], preg[i][4 * d + 2].w[p / 4], sel);
+        cell[d] = int32_t(__builtin_amdgcn_perm(hi, lo, 0x05040100u));
+      }
+    }
+    asm volatile("" : "+v"(cell));        // outside the branch: only the store is masked
+    if (item_ok[i]) *reinterpret_cast<i32x4*>(pb + dst[i][p]) = cell;
+  };
+  // Vector loads that go with slot `slot` of a chunk (see the loop below): pieces of the patch at
+  // `next_patch`, and taps of chunk `ch`.
+  constexpr int WORK = (VW + G) * MAXI;                        // cells, then loads
+  constexpr int QUOTA = (WORK + STEPS * SLOTS - 2) / (STEPS * SLOTS - 1);
+  static_assert(ONE || VW * MAXI <= QUOTA * (SLOTS * (STEPS - 1) - 1), "the cells are written before the barrier");
+  auto slot_loads = [&](const uint8_t* next_patch, Piece (&preg)[MAXI][G], int ch, auto slot_) {
+    constexpr int slot = decltype(slot_)::value, step = slot / SLOTS, s = slot % SLOTS;
+    if constexpr (slot > 0 && !ONE)
+      static_for<QUOTA>([&](auto k_) {
+        constexpr int wk = (slot - 1) * QUOTA + decltype(k_)::value - VW * MAXI;
+        if constexpr (wk >= 0 && wk < G * MAXI)
+          load_piece(next_patch, preg, std::integral_constant<int, wk / G>{}, std::integral_constant<int, wk % G>{});
+      });
+    constexpr int kw = s / GP - (IL - 1) * S, gi = step % NSG * GP + s % GP;   // the last use of tap kw in its row
+    if constexpr (gi == NG - 1 && kw >= 0) load_tap(ch, std::integral_constant<int, step / NSG * KW + kw>{});
+  };
+  // The first loads, in the order in which the loop issues them, so that its waits (loads complete
+  // in order) are exact from the first chunk on.
+  load_patch(0, preg0);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<STEPS * SLOTS>([&](auto slot_) {
+    slot_loads(asrc + int64_t(cnt > 1 ? 1 : 0) * CCH * plane, preg, 0, slot_);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+
+  // Padding cells (halo columns, rows outside the image) are written once: the buffers start as zeros.
+  {
+    const i32x4 z = {0, 0, 0, 0};
+    const int bytes = NBUF * g.bufb;
+    for (int off = gt * 16; off < bytes; off += NT * 16) *reinterpret_cast<i32x4*>(patch + off) = z;
+  }
+
+  // ---- fragment addresses: window origin of the first block's position of each block group -------
+  const int wpos = wp * 32 * NJ;          // first position of this wave, relative to m0
+  int fb[NG];                             // by block group
+#pragma unroll
+  for (int gi = 0; gi < NG; ++gi) {
+    int m = m0 + wpos + gi * 32 * IL + IL * (lane & 31);
+    m = m < mend ? m : mend - IL;         // a valid stand-in; its results are dropped (tiles hold whole groups of IL)
+    int img = ts.n_first;
+    if (ts.nseg > 1) img = int(g.dHWo.div(uint32_t(m)));
+    const int p = m - img * g.HWo;
+    const int ho = int(g.dWo.div(uint32_t(p))), wo_ = p - ho * a.Wo;
+    const int si = img - ts.n_first;
+    int base = si ? rows0 : 0, ihlo = si ? ihlo1 : ihlo0;
+    if (ts.nseg > 2) {
+      int rows = 0;
+      base = 0;
+      for (int s_ = 0; s_ <= si; ++s_) {
+        base += rows;
+        seg_extent(ts, s_, g, S, a.Ph, KH, &ihlo, &rows);
+      }
+    }
+    fb[gi] = (lane >> 5) * g.halfb + (base + ho * S - a.Ph - ihlo) * g.rowp + (wo_ / IL) * 16;
+  }
+
+  typename TR::accv_t acc[NJ];
+  static_for<NJ>([&](auto j_) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[decltype(j_)::value][v] = 0;
+  });
+
+  lds_barrier();                          // zeros are in place
+  static_for<MAXI>([&](auto i_) { static_for<VW>([&](auto p_) { store_cell(patch, preg0, i_, p_); }); });
+  lds_barrier();
+
+  // ---- chunks --------------------------------------------------------------------------------------
+  // A wave issues in order, and a global load holds it for some 40 cycles, so everything else is
+  // dealt out between the MFMAs (32 cycles each, two in a row never on the same accumulators): a
+  // slot is one fragment, the MFMAs that need it, the request of the fragment that takes its
+  // register in the next step, and one piece of other work -- first the cells of the next chunk's
+  // patch (LDS), then the loads of the chunk after it, and each tap's refill behind its last use.
+  // The chunk's one barrier stands in front of its last step, whose slots request the first
+  // fragments of the next chunk.  With three buffers that is enough: a wave writes the buffer that
+  // was read two chunks ago, and who has passed the last barrier is done with that one.
+  i32x4 fr[SLOTS];
+  auto request = [&](const uint8_t* pb, auto step_, auto s_) {
+    constexpr int step = decltype(step_)::value, q = decltype(s_)::value / GP, gi = step % NSG * GP + decltype(s_)::value % GP;
+    fr[decltype(s_)::value] = *reinterpret_cast<const i32x4*>(pb + fb[gi] + step / NSG * g.rowp + (q % PH) * g.php + (q / PH) * 16);
+  };
+  constexpr int kReads = SLOTS * (STEPS - 1) - (VW * MAXI + QUOTA - 1) / QUOTA;   // fragments requested behind the last cell
+  int cur = 0;                                                 // LDS offset of the chunk's buffer
+  auto chunk = [&](auto last_, int ch) {
+    constexpr bool LAST = decltype(last_)::value;
+    const uint8_t* const pb = patch + cur;
+    const int nxt = cur + g.bufb < NBUF * g.bufb ? cur + g.bufb : 0;
+    uint8_t* const nb = patch + nxt;
+    const uint8_t* const asrc2 = asrc + int64_t(ch + 2 < cnt ? ch + 2 : ch) * CCH * plane;   // surplus at the end: no branch
+    static_for<STEPS>([&](auto step_) {
+      constexpr int step = decltype(step_)::value, kh = step / NSG;
+      static_for<SLOTS>([&](auto s_) {
+        constexpr int s = decltype(s_)::value, q = s / GP, gi = step % NSG * GP + s % GP, slot = step * SLOTS + s;
+        static_for<IL>([&](auto j_) {
+          constexpr int j = IL - 1 - decltype(j_)::value, kw = q - j * S;
+          if constexpr (kw >= 0 && kw < KW)
+            acc[gi * IL + j] = TR::mfma(fr[s], ring[kh * KW + kw], acc[gi * IL + j]);
+        });
+        if constexpr (step + 1 < STEPS) request(pb, std::integral_constant<int, step + 1>{}, s_);
+        else if constexpr (!LAST) request(nb, std::integral_constant<int, 0>{}, s_);
+        if constexpr (!LAST) {
+          if constexpr (slot > 0)
+            static_for<QUOTA>([&](auto k_) {
+              constexpr int wk = (slot - 1) * QUOTA + decltype(k_)::value;
+              if constexpr (wk < VW * MAXI)
+                store_cell(nb, preg, std::integral_constant<int, wk / VW>{}, std::integral_constant<int, wk % VW>{});
+            });
+          slot_loads(asrc2, preg, ch + 1, std::integral_constant<int, slot>{});
+          // the cells are in LDS when at most the fragments requested behind them are outstanding
+          if constexpr (step == STEPS - 2 && s == SLOTS - 1)
+            asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(kReads < 15 ? kReads : 15) : "memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+    cur = nxt;
+  };
+  static_for<SLOTS>([&](auto s_) { request(patch, std::integral_constant<int, 0>{}, s_); });
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!ONE)
+    for (int ch = 0; ch + 1 < cnt; ++ch) chunk(std::false_type{}, ch);
+  if (KS == 1 || cnt > 0) chunk(std::true_type{}, cnt - 1);
+  if constexpr (KS > 1 && !ONE)
+    for (int i = cnt > 0 ? cnt : 1; i < most; ++i) lds_barrier();   // the barriers of the chunks that this group does not have
+  lds_barrier();                          // every wave is done with the patches
+
+  // ---- write-back: out[(img*O + o)*HWo + p] -----------------------------------------------------
+  // SP positions at a time: staged in LDS of the wave's own as [channel][position] rows of 32-bit
+  // values (16-byte stores), read back along the rows and written PG positions per lane.
+  constexpr int SP = 32 * (NJ < 4 ? NJ : 4), RS = SP * 4 + 16;
+  constexpr int kRed = KS > 1 ? KS * NW * NJ * 4096 : 0;
+  uint8_t* const stage = lds + kRed + w * (32 * RS);
+  if constexpr (KS > 1) {
+    // The groups' partial sums meet in LDS; quads of registers are dealt to the groups' waves, added
+    // pairwise (fewer roundings than a chain) and staged.
+    static_assert(IL == 1 && SP == 32 * NJ, "a quad is four consecutive positions of the one pass");
+    typedef acc_t acc4_t __attribute__((ext_vector_type(4)));
+    uint8_t* const red = lds + w * (NJ * 4096) + lane * 16;
+    static_for<NJ * 4>([&](auto u_) {
+      constexpr int j = decltype(u_)::value / 4, q = decltype(u_)::value % 4;
+      const auto v = __builtin_shufflevector(acc[j], acc[j], 4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3);
+      *reinterpret_cast<i32x4*>(red + kg * (NW * NJ * 4096) + (j * 4 + q) * 1024) = __builtin_bit_cast(i32x4, v);
+    });
+    lds_barrier();
+#pragma unroll 1
+    for (int u = kg; u < NJ * 4; u += KS) {
+      acc4_t t[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) t[k] = *reinterpret_cast<const acc4_t*>(red + k * (NW * NJ * 4096) + u * 1024);
+#pragma unroll
+      for (int st = 1; st < KS; st *= 2)
+#pragma unroll
+        for (int k = 0; k < KS; k += 2 * st) t[k] += t[k + st];
+      *reinterpret_cast<i32x4*>(stage + (lane & 31) * RS + (u / 4 * 32 + 8 * (u % 4) + 4 * (lane >> 5)) * 4) =
+          __builtin_bit_cast(i32x4, t[0]);
+    }
+    lds_barrier();
+  }
+  const int ow = o0 + wo * 32;
+  const bool has_res = a.residual != nullptr;
+  // ReLU as one maximum with a run-time operand: zero, or a NaN, which fmaxf ignores.
+  const float lo_f = a.relu ? 0.0f : __builtin_nanf("");
+  const int lo_i = a.relu ? 0 : INT_MIN;
+  auto stage_pass = [&](auto ps_) {       // positions ps * SP .. of this wave
+    constexpr int ps = decltype(ps_)::value;
+    uint8_t* const row = stage + (lane & 31) * RS;
+    static_for<SP / 32 / IL>([&](auto gi_) {
+      constexpr int gi = decltype(gi_)::value, b = ps * (SP / 32) + gi * IL;
+      static_for<16 * IL / 4>([&](auto u_) {              // four consecutive positions: IL blocks x 4 / IL registers
+        constexpr int v = decltype(u_)::value * (4 / IL);
+        const int n = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        i32x4 t;
+        static_for<4>([&](auto e_) {
+          constexpr int e = decltype(e_)::value;
+          t[e] = __builtin_bit_cast(int32_t, acc_t(acc[b + e % IL][v + e / IL]));
+        });
+        *reinterpret_cast<i32x4*>(row + (gi * 32 * IL + n * IL) * 4) = t;
+      });
+    });
+  };
+  // A group of PG consecutive positions (16 bytes) that lies within one image and the tile goes out
+  // with one store per lane, aligned to the element only; the groups that an image's end or the
+  // tile's cuts follow value by value, all lanes on one group's 32 x PG values.
+  auto write_rows = [&](auto ps_, auto kind_) {
+    constexpr int ps = decltype(ps_)::value;
+    constexpr int kind = decltype(kind_)::value;           // 0: int32, 1: f32, 2: bf16
+    constexpr int PG = kind == 2 ? 8 : 4, LPR = SP / PG, RPI = 64 / LPR, NIT = 32 / RPI;
+    const int start = m0 + wpos + ps * SP;                 // first position of the pass
+    if (start >= mend) return;
+    auto mine = [&](int it) { return KS == 1 || it % KS == kg; };   // steps are dealt to the groups' waves
+    const int gq = lane % LPR, rsub = lane / LPR;
+    const int m = start + gq * PG;
+    const int img = int(g.dHWo.div(uint32_t(m < mend ? m : start))), p = (m < mend ? m : start) - img * g.HWo;
+    const bool whole = m + PG <= mend && p + PG <= g.HWo;
+    const uint32_t base = whole ? uint32_t(img) * uint32_t(a.O) * uint32_t(g.HWo) + uint32_t(p) : 0u;
+    auto addr_of = [&](int it) {
+      const int o = ow + it * RPI + rsub;
+      return whole && o < a.O ? base + uint32_t(o) * uint32_t(g.HWo) : 0u;
+    };
+    i32x4 res[NIT];
+    if (has_res && int64_t(a.O) * g.M >= PG) {             // (a lane without a group reads the first values)
+#pragma unroll
+      for (int it = 0; it < NIT; ++it)
+        if (mine(it))
+          res[it] = *reinterpret_cast<const i32x4_bytes*>(static_cast<const uint8_t*>(a.residual) +
+                                                          int64_t(addr_of(it)) * (kind == 2 ? 2 : 4));
+    }
+    i32x4 raw[NIT][PG / 4];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+#pragma unroll
+      for (int h = 0; h < PG / 4; ++h)
+        if (mine(it)) raw[it][h] = *reinterpret_cast<const i32x4*>(stage + (it * RPI + rsub) * RS + (gq * PG + h * 4) * 4);
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      if (!mine(it)) continue;
+      const bool ok = whole && ow + it * RPI + rsub < a.O;
+      i32x4_bytes* const dst =
+          reinterpret_cast<i32x4_bytes*>(static_cast<uint8_t*>(a.out) + int64_t(addr_of(it)) * (kind == 2 ? 2 : 4));
+      i32x4 r;
+      if constexpr (kind == 0) {
+        r = raw[it][0];
+        if (has_res) r += res[it];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = r[e] > lo_i ? r[e] : lo_i;
+      } else {
+        float f[PG];
+#pragma unroll
+        for (int e = 0; e < PG; ++e) f[e] = __int_as_float(raw[it][e / 4][e % 4]);
+        if (has_res) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (kind == 1) {
+              f[e] += __int_as_float(res[it][e]);
+            } else {
+              f[2 * e] += __uint_as_float(uint32_t(res[it][e]) << 16);
+              f[2 * e + 1] += __uint_as_float(uint32_t(res[it][e]) & 0xffff0000u);
+            }
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < PG; ++e) f[e] = fmaxf(f[e], lo_f);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          r[e] = kind == 1 ? __float_as_int(f[e]) : int32_t(pack_bf16x2(f[2 * e % PG], f[(2 * e + 1) % PG]));
+      }
+      if (ok) *dst = r;
+    }
+    // cut groups: where an image or the tile ends inside a group
+    if (((g.HWo | g.tps) & (PG - 1)) == 0) return;         // uniform
+    const int len = mend - start < SP ? mend - start : SP;
+    const int img0 = int(g.dHWo.div(uint32_t(start)));
+    for (int end = (img0 + 1) * g.HWo - start;; end += g.HWo) {      // uniform
+      const int cut = end < len ? end : len;
+      if (cut % PG != 0) {
+        const int gpos = cut / PG * PG, e = lane % PG, mm = start + gpos + e;
+        const int im = int(g.dHWo.div(uint32_t(mm < mend ? mm : start)));
+        const uint32_t at = uint32_t(im) * uint32_t(a.O) * uint32_t(g.HWo) + uint32_t(mm - im * g.HWo);
+#pragma unroll
+        for (int it = 0; it < PG / 2; ++it) {
+          const int row = it * (64 / PG) + lane / PG;
+          if (mine(it) && mm < mend && ow + row < a.O)
+            store_result<acc_t>(a.out, a.residual, a.out_dtype, at + uint32_t(ow + row) * uint32_t(g.HWo),
+                                *reinterpret_cast<const acc_t*>(stage + row * RS + (gpos + e) * 4), a.relu);
+        }
+      }
+      if (end >= len) break;
+    }
+  };
+  static_for<32 * NJ / SP>([&](auto ps_) {
+    if constexpr (KS == 1) stage_pass(ps_);
+    if constexpr (INT) write_rows(ps_, std::integral_constant<int, 0>{});
+    else if (a.out_dtype == GS_BF16) write_rows(ps_, std::integral_constant<int, 2>{});
+    else write_rows(ps_, std::integral_constant<int, 1>{});
+  });
+}
+
+}  // namespace gs
