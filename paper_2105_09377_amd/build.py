@@ -24,10 +24,11 @@ for _tr, _tag in (("Bf16Traits", "bf16"), ("I8Traits", "i8")):
         UNITS.append(("conv3_inst.hip", f"conv3_{_tag}_t{_tile}.o",
                       [f"-DGS_CONV3_TRAITS={_tr}", f"-DGS_CONV3_TILE={_tile}",
                        f"-DGS_CONV3_NAME=launch_conv3_{_tag}_t{_tile}"]))
-    for _shape in range(5):
-        UNITS.append(("conv_tile_inst.hip", f"conv_tile_{_tag}_s{_shape}.o",
-                      [f"-DGS_TILE_TRAITS={_tr}", f"-DGS_TILE_SHAPE={_shape}",
-                       f"-DGS_TILE_NAME=launch_conv_tile_{_tag}_s{_shape}"]))
+    for _k in (1, 3, 5):
+        for _shape in range(5):
+            UNITS.append(("conv_tile_inst.hip", f"conv_tile_{_tag}_k{_k}s{_shape}.o",
+                          [f"-DGS_TILE_TRAITS={_tr}", f"-DGS_TILE_SHAPE={_shape}", f"-DGS_TILE_K={_k}",
+                           f"-DGS_TILE_NAME=launch_conv_tile_{_tag}_k{_k}s{_shape}"]))
 
 
 def _compile(unit) -> str:

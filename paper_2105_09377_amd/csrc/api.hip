@@ -504,6 +504,23 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   uint8_t* cols = static_cast<uint8_t*>(workspace);
   uint8_t* wpad = cols + round_up(M * ld * esz, 256);
 
+  // A window of one pixel: the rows of the matrix are the pixels themselves, read where they lie.
+  if (cs.Kh == 1 && cs.Kw == 1 && cs.Ph == 0 && cs.Pw == 0) {
+    ConvArgs a;
+    memset(&a, 0, sizeof(a));
+    a.act = act->data;
+    a.wr = w->data;
+    a.out = out->data;
+    a.residual = residual ? residual->data : nullptr;
+    a.in_dtype = act->dtype;
+    a.out_dtype = out->dtype;
+    a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = 1; a.Kw = 1;
+    a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ho = cs.Ho; a.Wo = cs.Wo;
+    a.relu = actfn == GS_ACT_RELU;
+    const hipError_t e = launch_conv_point(a, s);
+    if (e != hipErrorInvalidValue) return launch_status(e);
+  }
+
   // flatten (windows (access activations 1) (C Kh Kw) (1 Sh Sw)), rows padded to 16 bytes.
   WindowsArgs wa;
   memset(&wa, 0, sizeof(wa));

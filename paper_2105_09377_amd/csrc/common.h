@@ -304,6 +304,8 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
 // a.ksplit > 1 and a.partial set, kernels that support it split the channel sum (Fig. 6's last
 // blocking rule: partial dot products combined by reduceSum over a pair); others ignore it.
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
+// 1x1 windows without padding on unpacked weights (a.wr), where a kernel takes them: hipErrorInvalidValue otherwise.
+hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s);
 // Split the channel sum of this shape?  Returns 1, 2 or 4 (host heuristic: few tiles, many chunks).
 int conv_pick_ksplit(int in_dtype, int N, int C, int O, int Ho, int Wo);
 // True where some direct kernel is sure to take the layer (its patch fits the LDS, a tile spans few images);

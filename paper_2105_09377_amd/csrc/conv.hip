@@ -5,10 +5,11 @@
 //
 // Kernels, in the order they are tried:
 //   * conv_smallc_kernel  (conv_smallc.hip)  fewer input channels than one 32-byte chunk;
-//   * conv_tile_kernel    (conv_tile_kernel.h)  3x3, strides 1 and 2: small independent workgroups,
-//                                            weights from L2 into registers; in the workgroup shape
-//                                            that a cost model picks, unless it expects the next one
-//                                            to be faster;
+//   * conv_tile_kernel    (conv_tile_kernel.h)  3x3, 5x5 and (whole groups of channel chunks, no
+//                                            padding) 1x1 windows of strides 1 and 2: small
+//                                            independent workgroups, weights from L2 into registers;
+//                                            in the workgroup shape that a cost model picks, unless it
+//                                            expects the next one to be faster;
 //   * conv_direct4_kernel (conv4_kernel.h)   eight waves, producers and consumers; may split the
 //                                            channel sum among workgroups;
 //   * conv_direct3_kernel (conv_kernels.h)   four waves doing everything, same LDS layout;
@@ -347,29 +348,53 @@ static ConvGeom conv_geom(const ConvArgs& a) {
 
 // conv_tile_kernel instances (conv_tile_inst.hip), one per element type and workgroup shape.
 using TileLaunch = hipError_t (*)(const ConvArgs&, const TilePlan&, hipStream_t);
-#define GS_TILE_DECL(i)                                                              \
-  hipError_t launch_conv_tile_bf16_s##i(const ConvArgs&, const TilePlan&, hipStream_t); \
-  hipError_t launch_conv_tile_i8_s##i(const ConvArgs&, const TilePlan&, hipStream_t);
-GS_TILE_DECL(0) GS_TILE_DECL(1) GS_TILE_DECL(2) GS_TILE_DECL(3) GS_TILE_DECL(4)
+#define GS_TILE_DECL(k, i)                                                                 \
+  hipError_t launch_conv_tile_bf16_k##k##s##i(const ConvArgs&, const TilePlan&, hipStream_t); \
+  hipError_t launch_conv_tile_i8_k##k##s##i(const ConvArgs&, const TilePlan&, hipStream_t);
+#define GS_TILE_DECLS(k) GS_TILE_DECL(k, 0) GS_TILE_DECL(k, 1) GS_TILE_DECL(k, 2) GS_TILE_DECL(k, 3) GS_TILE_DECL(k, 4)
+GS_TILE_DECLS(1) GS_TILE_DECLS(3) GS_TILE_DECLS(5)
+#undef GS_TILE_DECLS
 #undef GS_TILE_DECL
 
-// Time of a layer in each workgroup shape, in microseconds, fitted to measured times of 620 layers
-// of 1 to 128 images, 16 to 512 channels on either side, planes of 7x7 to 112x112, strides 1 and 2,
-// both element types (mean error 13 %; the shape it picks is 2.3 % slower than the fastest one on
-// average, and 2.2 times faster than without this kernel).  A workgroup alone takes
-// wg + store + cnt * alone; a compute unit that is given one after the other takes 0.6 store +
-// cnt * busy for each.  `store` grows by `cut` for planes that are no multiple of a 16-byte
-// store's positions, the chunks by `item` for each patch item of a thread beyond the first and by
-// `strided` for stride 2.  `at_once`: workgroups that fit a compute unit together.
+template <typename TR>
+static hipError_t launch_tiles(const ConvArgs& a, const TilePlan& plan, hipStream_t s) {
+#define GS_TILE_ROW(t, k)                                                                              \
+  {launch_conv_tile_##t##_k##k##s0, launch_conv_tile_##t##_k##k##s1, launch_conv_tile_##t##_k##k##s2, \
+   launch_conv_tile_##t##_k##k##s3, launch_conv_tile_##t##_k##k##s4}
+  static constexpr TileLaunch bf16[3][kNumTileShapes] = {GS_TILE_ROW(bf16, 1), GS_TILE_ROW(bf16, 3), GS_TILE_ROW(bf16, 5)};
+  static constexpr TileLaunch i8[3][kNumTileShapes] = {GS_TILE_ROW(i8, 1), GS_TILE_ROW(i8, 3), GS_TILE_ROW(i8, 5)};
+#undef GS_TILE_ROW
+  return (TR::kEsz == 1 ? i8 : bf16)[a.Kh / 2][plan.shape](a, plan, s);
+}
+
+// Time of a layer in each workgroup shape, in microseconds, fitted by window size to measured times of
+// 240 (1x1), 620 (3x3) and 200 (5x5) layers of 1 to 128 images, 16 to 512 channels on either side,
+// planes of 7x7 to 112x112, strides 1 and 2, both element types (mean error 13 %; the shape it picks
+// is 1 to 3 % slower than the fastest one on average, and 1.5, 2.2 and 4.8 times faster than the
+// kernels without this one).  A workgroup alone takes wg + store + cnt * alone; a compute unit that
+// is given one after the other takes 0.6 store + cnt * busy for each.  `store` grows by `cut` for
+// planes that are no multiple of a 16-byte store's positions, the chunks by `item` for each patch
+// item of a thread beyond the first and by `strided` for stride 2.  `at_once`: workgroups that fit a
+// compute unit together.
 struct TileCost {
   float base, wg, alone, busy, store, cut, item, at_once, strided;
 };
-constexpr TileCost kTileCost[kNumTileShapes] = {
-    {0.22f, 5.32f, 0.854f, 1.488f, 1.02f, 1.02f, 0.0f, 2, 0.32f},   // 64 channels x 256 positions
-    {0.98f, 3.08f, 0.622f, 0.750f, 1.02f, 0.66f, 0.88f, 3, 0.32f},  // 64 x 128
-    {2.35f, 1.32f, 0.637f, 0.706f, 1.02f, 0.68f, 1.58f, 3, 0.23f},  // 128 x 64
-    {1.73f, 2.19f, 0.919f, 1.230f, 0.07f, 5.87f, 0.90f, 3, 0.0f},   // 32 x 64, four channel groups
-    {0.91f, 2.83f, 0.714f, 0.865f, 0.02f, 0.20f, 1.36f, 4, 0.0f},   // 32 x 32, four channel groups
+constexpr TileCost kTileCost[3][kNumTileShapes] = {   // shapes as in kTileShapes
+    {{1.00f, 4.40f, 0.59f, 3.79f, 1.00f, 1.00f, 0.57f, 2, 0.57f},
+     {1.01f, 2.92f, 0.26f, 0.55f, 1.00f, 0.99f, 4.87f, 3, 0.0f},
+     {1.00f, 2.66f, 0.44f, 0.62f, 1.00f, 0.99f, 4.15f, 3, 0.0f},
+     {1.38f, 0.47f, 0.93f, 0.39f, 1.12f, 0.55f, 1.01f, 3, 0.21f},
+     {1.77f, 1.54f, 0.65f, 0.53f, 0.37f, 0.78f, 0.99f, 4, 0.30f}},
+    {{0.22f, 5.32f, 0.854f, 1.488f, 1.02f, 1.02f, 0.0f, 2, 0.32f},
+     {0.98f, 3.08f, 0.622f, 0.750f, 1.02f, 0.66f, 0.88f, 3, 0.32f},
+     {2.35f, 1.32f, 0.637f, 0.706f, 1.02f, 0.68f, 1.58f, 3, 0.23f},
+     {1.73f, 2.19f, 0.919f, 1.230f, 0.07f, 5.87f, 0.90f, 3, 0.0f},
+     {0.91f, 2.83f, 0.714f, 0.865f, 0.02f, 0.20f, 1.36f, 4, 0.0f}},
+    {{0, 0, 0, 0, 0, 0, 0, 1, 0},                     // not taken (tile_geometry)
+     {0.99f, 3.53f, 1.15f, 2.35f, 1.00f, 1.06f, 1.30f, 3, 0.01f},
+     {1.07f, 3.38f, 1.15f, 2.06f, 0.97f, 0.97f, 0.79f, 3, 0.0f},
+     {1.05f, 0.89f, 2.37f, 1.72f, 1.00f, 1.01f, 0.69f, 3, 0.0f},
+     {1.02f, 2.72f, 1.18f, 1.35f, 0.03f, 17.0f, 0.99f, 4, 0.18f}},
 };
 
 // Positions per tile of at most `tp`: fewest rounds over the compute units, then whole output rows
@@ -388,6 +413,8 @@ static int tile_positions(int64_t M, int n_ot, int Wo, int tp) {
 static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, TilePlan* p, float* cost) {
   const TileShape sh = kTileShapes[shape];
   const int tp = 32 * sh.nj * sh.wp, to = 32 * sh.wo, S = a.Sh, threads = 64 * sh.wo * sh.wp;
+  const bool point = a.Kh == 1;        // patch rows are output rows, several chunks at a time
+  const int cm = point ? kTileChunks : 1;
   p->shape = shape;
   p->g = g0;
   ConvGeom& g = p->g;
@@ -396,17 +423,21 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, Tile
   else if (sh.ks == 1 && sh.nj >= 2 && a.Wo % 2 == 0) p->il = 2;
   const int n_ot = int(ceil_div(a.O, to));
   g.tps = tile_positions(g.M, n_ot, a.Wo, tp);
-  const int max_rows = conv_max_rows(a, g.M, g.HWo, g.tps);
+  ConvArgs r = a;
+  if (point) r.Sh = 1;
+  const int max_rows = conv_max_rows(r, g.M, g.HWo, g.tps);
   if (max_rows < 0) return false;
   const int64_t segs = (g.tps + g.HWo - 2) / g.HWo + 1;
-  const int64_t items = 2 * (ceil_div(int64_t(max_rows) * a.W, kTileItem) + segs);
+  const int64_t items = point ? 2 * cm * max_rows * ceil_div(a.W, kTileItem)
+                              : 2 * (ceil_div(int64_t(max_rows) * a.W, kTileItem) + segs);
+  if (a.Kh == 5 && sh.nj > 2) return false;              // a ring of 25 taps leaves no registers for it
   p->maxi = items <= threads ? 1 : items <= 2 * threads ? 2 : 4;
   if (items > 4 * threads || (sh.nj > 2 && p->maxi > 2)) return false;
-  const int nchunk = a.Cpad * int(dtype_size(a.in_dtype)) / 32, cnt = int(ceil_div(nchunk, sh.ks));
+  const int nchunk = a.Cpad * int(dtype_size(a.in_dtype)) / (32 * cm), cnt = int(ceil_div(nchunk, sh.ks));
   p->one = sh.ks > 1 && cnt == 1;
   const int PH = p->il * S;
   const int lastcol = a.W + a.Pw - 1 > (a.Wo - 1) * S + a.Kw - 1 ? a.W + a.Pw - 1 : (a.Wo - 1) * S + a.Kw - 1;
-  const int64_t php = (lastcol / PH + 1) * 16, bufb = 2 * max_rows * PH * php;
+  const int64_t php = (lastcol / PH + 1) * 16, bufb = 2 * cm * max_rows * PH * php;
   const int64_t patches = sh.ks * (p->one ? 1 : 3) * bufb;
   const int64_t results = (sh.ks > 1 ? int64_t(sh.ks) * sh.wo * sh.wp * sh.nj * 4096 : 0) +
                           int64_t(sh.wo) * sh.wp * 32 * (32 * (sh.nj < 4 ? sh.nj : 4) * 4 + 16);
@@ -427,9 +458,12 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, Tile
   g.pos_major = (n_ot > 1 && pos_first < ch_first) ? 1 : 0;
   g.dTiles = FastDiv::make(uint32_t(g.pos_major ? n_ot : tiles_m));
   g.dW = FastDiv::make(uint32_t(a.W));
-  const TileCost& c = kTileCost[shape];
+  g.dXG = FastDiv::make(uint32_t(ceil_div(a.W, kTileItem)));
+  const TileCost& c = kTileCost[a.Kh / 2][shape];
   const int group = a.in_dtype == GS_I8 || a.out_dtype == GS_F32 ? 4 : 8;     // positions of a 16-byte store
-  const float per_thread = float((g.tps + a.Wo - 1) / a.Wo * S + 3) * a.W / (2 * threads);
+  const int64_t rows = ceil_div(g.tps, a.Wo);
+  const float per_thread = point ? float(2 * cm * (rows + 1) * ceil_div(a.W, kTileItem)) / threads
+                                 : float((rows * S + a.Kh) * a.W) / (2 * threads);
   const float chunk = 1 + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
   const float store = c.store * (g.HWo % group ? 1 + c.cut : 1.0f);
   const float alone = c.wg + store + c.alone * cnt * chunk, busy = c.busy * cnt * chunk + 0.6f * store;
@@ -450,27 +484,38 @@ static float pipelined_cost(const ConvArgs& a, const ConvGeom& g) {
          (a.ksplit > 1 ? 3.59f : 0.0f);
 }
 
+// A 1x1 window's matrix gathered and multiplied by the dense kernels (246 layers, mean error 22 %; what
+// counts is that it is the faster way for large ones: 128 images of 28x28 x 512 -> 512 146 us against
+// 203).  In MB and MFLOP.
+static float gathered_cost(const ConvArgs& a, const ConvGeom& g) {
+  const float esz = float(dtype_size(a.in_dtype)), m = float(g.M) * 1e-6f;
+  return 7.7f + 0.27f * esz * a.C * (m + float(a.N) * a.H * a.W * 1e-6f) + 0.00072f * esz * a.C * a.O * m +
+         0.44f * float(dtype_size(a.out_dtype)) * a.O * m * (a.residual ? 2 : 1);
+}
+
 // How the layer runs on conv_tile_kernel, or shape -1.  A plan depends on the shape alone; each
 // thread keeps the last ones it made (64, by a hash of the shape), since making one costs a few
 // microseconds.
 template <typename TR>
-static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g) {
+static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g, bool natural = false) {
   struct Entry {
-    std::array<int, 17> key;
+    std::array<int, 18> key;
     TilePlan plan;
     bool set = false;
   };
   static thread_local Entry kept[64];
-  const std::array<int, 17> key = {a.in_dtype, a.out_dtype, a.N, a.C, a.H, a.W, a.O, a.Kh, a.Kw, a.Sh, a.Sw, a.Ph, a.Pw, a.ksplit,
-                                   a.Cpad, a.wblk != nullptr, conv_num_cus()};
+  const std::array<int, 18> key = {a.in_dtype, a.out_dtype, a.N, a.C, a.H, a.W, a.O, a.Kh, a.Kw, a.Sh, a.Sw, a.Ph, a.Pw, a.ksplit,
+                                   a.Cpad, a.wblk != nullptr, natural, a.residual != nullptr};
   uint32_t h = 2166136261u;
   for (int v : key) h = (h ^ uint32_t(v)) * 16777619u;
   Entry& e = kept[(h >> 16) & 63];
   if (e.set && e.key == key) return e.plan;
   TilePlan best;
   best.shape = -1;
-  if (a.wblk && a.Kh == 3 && a.Kw == 3 && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem && a.C == a.Cpad &&
-      round_up(a.O, 32) * 9 * a.Cpad * TR::kEsz < (int64_t(1) << 32)) {
+  const bool window = a.Kh == a.Kw && (a.Kh == 3 || a.Kh == 5 ||
+                                       (a.Kh == 1 && a.Ph + a.Pw == 0 && a.Cpad * TR::kEsz % (32 * kTileChunks) == 0));
+  if ((a.wblk || natural) && window && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem && a.C == a.Cpad &&
+      round_up(a.O, 32) * a.Kh * a.Kw * a.Cpad * TR::kEsz < (int64_t(1) << 32)) {
     float least = 0;
     for (int i = 0; i < kNumTileShapes; ++i) {
       TilePlan p;
@@ -480,8 +525,10 @@ static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g) {
         least = cost;
       }
     }
-    // the estimates err by 14 %: a tenth in favour of the older kernel keeps it where it is the faster one
-    if (best.shape >= 0 && launch_conv3<TR>(a, g, nullptr, true) == hipSuccess && 0.9f * pipelined_cost(a, g) < least)
+    // The estimates err by 14 %: a tenth in favour of the older way keeps it where it is the faster one.
+    if (best.shape >= 0 && (natural ? 0.9f * gathered_cost(a, g) < least
+                                    : a.Kh == 3 && launch_conv3<TR>(a, g, nullptr, true) == hipSuccess &&
+                                          0.9f * pipelined_cost(a, g) < least))
       best.shape = -1;
   }
   e.key = key;
@@ -506,13 +553,7 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
     if (es != hipErrorInvalidValue) return es;
   }
   const TilePlan& plan = plan_tiles<TR>(a, g);
-  if (plan.shape >= 0) {
-    static constexpr TileLaunch bf16[kNumTileShapes] = {launch_conv_tile_bf16_s0, launch_conv_tile_bf16_s1, launch_conv_tile_bf16_s2,
-                                                        launch_conv_tile_bf16_s3, launch_conv_tile_bf16_s4};
-    static constexpr TileLaunch i8[kNumTileShapes] = {launch_conv_tile_i8_s0, launch_conv_tile_i8_s1, launch_conv_tile_i8_s2,
-                                                      launch_conv_tile_i8_s3, launch_conv_tile_i8_s4};
-    return (TR::kEsz == 1 ? i8 : bf16)[plan.shape](a, plan, s);
-  }
+  if (plan.shape >= 0) return launch_tiles<TR>(a, plan, s);
   hipError_t e = launch_conv3<TR>(a, g, s);
   if (a.ksplit > 1) {
     if (e == hipSuccess) {
@@ -547,6 +588,24 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   e = launch_conv_tile<TR, 64, 128, 1, 4>(a, g, s);
   if (e != hipErrorInvalidValue) return e;
   return launch_conv_tile<TR, 64, 64, 2, 2>(a, g, s);
+}
+
+// 1x1 windows without padding on weights in the listing's order (a.wr = ((O),(C))): one launch, no
+// packing.  hipErrorInvalidValue where conv_tile_kernel does not take the layer.
+template <typename TR>
+static hipError_t launch_conv_point_t(const ConvArgs& a_in, hipStream_t s) {
+  ConvArgs a = a_in;
+  a.Cpad = conv_cpad(a.in_dtype, a.C);
+  a.ksplit = 1;
+  a.wblk = nullptr;
+  const ConvGeom g = conv_geom(a);
+  if (g.M == 0 || a.O == 0) return hipSuccess;
+  if (a.Kh != 1 || a.Kw != 1) return hipErrorInvalidValue;
+  const TilePlan& plan = plan_tiles<TR>(a, g, true);
+  return plan.shape >= 0 ? launch_tiles<TR>(a, plan, s) : hipErrorInvalidValue;
+}
+hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s) {
+  return a.in_dtype == GS_I8 ? launch_conv_point_t<I8Traits>(a, s) : launch_conv_point_t<Bf16Traits>(a, s);
 }
 
 bool conv_pipelined_takes(const ConvArgs& a_in) {

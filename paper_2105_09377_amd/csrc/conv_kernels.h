@@ -87,6 +87,7 @@ struct TileShape {
 constexpr TileShape kTileShapes[] = {{4, 2, 2, 1}, {2, 2, 2, 1}, {2, 4, 1, 1}, {2, 1, 1, 4}, {1, 1, 1, 4}};
 constexpr int kNumTileShapes = 5;
 constexpr int kTileItem = 4;    // pixels of a patch item
+constexpr int kTileChunks = 4;  // 32-byte channel chunks per step for 1x1 windows
 // How a layer runs on it.
 struct TilePlan {
   int shape;                // index into kTileShapes, or -1: the kernel does not take the layer

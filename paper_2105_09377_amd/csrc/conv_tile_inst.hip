@@ -1,6 +1,6 @@
-// One translation unit per (element type, workgroup shape) of conv_tile_kernel, so that the
+// One translation unit per (element type, workgroup shape, window size) of conv_tile_kernel, so that the
 // instances compile in parallel.  Built several times with different -DGS_TILE_TRAITS /
-// -DGS_TILE_SHAPE / -DGS_TILE_NAME (see build.py).
+// -DGS_TILE_SHAPE / -DGS_TILE_K / -DGS_TILE_NAME (see build.py).
 #include "conv_tile_kernel.h"
 
 #include <mutex>
@@ -9,9 +9,9 @@ namespace gs {
 
 constexpr TileShape kShape = kTileShapes[GS_TILE_SHAPE];
 
-template <int KH, int KW, int S, int IL, int MAXI, bool ONE>
+template <int K, int CM, bool NAT, int S, int IL, int MAXI, bool ONE>
 static hipError_t launch_tile_inst(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
-  auto kern = conv_tile_kernel<GS_TILE_TRAITS, KH, KW, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE>;
+  auto kern = conv_tile_kernel<GS_TILE_TRAITS, K, K, CM, NAT, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE>;
   static std::once_flag once;              // the attribute is set once, whichever thread comes first
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&]() {
@@ -23,32 +23,44 @@ static hipError_t launch_tile_inst(const ConvArgs& a, const TilePlan& p, hipStre
   return hipGetLastError();
 }
 
-template <int KH, int KW, int S, int IL>
+template <int K, int CM, bool NAT, int S, int IL>
 static hipError_t launch_tile_items(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
   if constexpr (kShape.ks > 1) {
-    if (p.one && p.maxi == 1) return launch_tile_inst<KH, KW, S, IL, 1, true>(a, p, s);
-    if (p.one && p.maxi == 2) return launch_tile_inst<KH, KW, S, IL, 2, true>(a, p, s);
-    if (p.one) return launch_tile_inst<KH, KW, S, IL, 4, true>(a, p, s);
+    if (p.one && p.maxi == 1) return launch_tile_inst<K, CM, NAT, S, IL, 1, true>(a, p, s);
+    if (p.one && p.maxi == 2) return launch_tile_inst<K, CM, NAT, S, IL, 2, true>(a, p, s);
+    if (p.one) return launch_tile_inst<K, CM, NAT, S, IL, 4, true>(a, p, s);
   }
-  if (p.maxi == 1) return launch_tile_inst<KH, KW, S, IL, 1, false>(a, p, s);
-  if (p.maxi == 2) return launch_tile_inst<KH, KW, S, IL, 2, false>(a, p, s);
-  if constexpr (kShape.nj <= 2) return launch_tile_inst<KH, KW, S, IL, 4, false>(a, p, s);
+  if (p.maxi == 1) return launch_tile_inst<K, CM, NAT, S, IL, 1, false>(a, p, s);
+  if (p.maxi == 2) return launch_tile_inst<K, CM, NAT, S, IL, 2, false>(a, p, s);
+  if constexpr (kShape.nj <= 2) return launch_tile_inst<K, CM, NAT, S, IL, 4, false>(a, p, s);
   return hipErrorInvalidValue;
+}
+
+template <int K, int CM, bool NAT>
+static hipError_t launch_tile_il(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
+  constexpr bool kMany = kShape.nj >= 2 && kShape.ks == 1;
+  if (a.Sh == 1) {
+    if constexpr (kShape.nj >= 4)
+      if (p.il == 4) return launch_tile_items<K, CM, NAT, 1, 4>(a, p, s);
+    if constexpr (kMany)
+      if (p.il == 2) return launch_tile_items<K, CM, NAT, 1, 2>(a, p, s);
+    return launch_tile_items<K, CM, NAT, 1, 1>(a, p, s);
+  }
+  if constexpr (kMany)
+    if (p.il == 2) return launch_tile_items<K, CM, NAT, 2, 2>(a, p, s);
+  return launch_tile_items<K, CM, NAT, 2, 1>(a, p, s);
 }
 
 // The plan's values are the ones that plan_tiles (conv.hip) chooses from.
 hipError_t GS_TILE_NAME(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
-  constexpr bool kMany = kShape.nj >= 2 && kShape.ks == 1;
-  if (a.Sh == 1) {
-    if constexpr (kShape.nj >= 4)
-      if (p.il == 4) return launch_tile_items<3, 3, 1, 4>(a, p, s);
-    if constexpr (kMany)
-      if (p.il == 2) return launch_tile_items<3, 3, 1, 2>(a, p, s);
-    return launch_tile_items<3, 3, 1, 1>(a, p, s);
-  }
-  if constexpr (kMany)
-    if (p.il == 2) return launch_tile_items<3, 3, 2, 2>(a, p, s);
-  return launch_tile_items<3, 3, 2, 1>(a, p, s);
+#if GS_TILE_K == 3
+  return launch_tile_il<3, 1, false>(a, p, s);
+#elif GS_TILE_K == 1
+  return a.wblk ? launch_tile_il<1, kTileChunks, false>(a, p, s) : launch_tile_il<1, kTileChunks, true>(a, p, s);
+#else
+  if constexpr (kShape.nj <= 2) return launch_tile_il<5, 1, false>(a, p, s);   // (a ring of 25 taps leaves no room for more)
+  return hipErrorInvalidValue;
+#endif
 }
 
 }  // namespace gs

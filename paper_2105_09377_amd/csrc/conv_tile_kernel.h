@@ -37,17 +37,23 @@ namespace gs {
 
 typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
 
-template <typename TR, int KH, int KW, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE>
+// CM: 32-byte channel chunks that a step of the chunk loop ("chunk" below) holds.  One, except for
+// 1x1 windows, whose single tap would leave too little between two barriers: there CM chunks take
+// the place of the taps, each with a patch of its own, and a patch row is the input row of an output
+// row (rows and columns in between are not read; no padding).  NAT: weights in the listing's order
+// ((O),(C)) instead of the blocked copy.
+template <typename TR, int KH, int KW, int CM, bool NAT, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE>
 __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArgs a, ConvGeom g) {
   static_assert(NJ % IL == 0, "whole groups of interleaved blocks");
+  static_assert(CM == 1 || KH * KW == 1, "chunks take the place of taps");
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int ESZ = TR::kEsz;
   constexpr int G = 16 / ESZ;             // channels per 16-byte cell
-  constexpr int CCH = 32 / ESZ;           // channels per chunk
+  constexpr int CCH = CM * 32 / ESZ;      // channels per chunk
   constexpr int VW = kTileItem, LD = VW * ESZ / 4;        // pixels and dwords of a patch load
-  constexpr int T = KH * KW, PH = IL * S, NQ = (IL - 1) * S + KW;
+  constexpr int KR = KH * CM, T = KR * KW, PH = IL * S, NQ = (IL - 1) * S + KW;
   constexpr int GP = IL == 1 && NJ > 1 ? 2 : 1;           // block groups that take turns within a step
-  constexpr int NG = NJ / IL, NSG = NG / GP, STEPS = KH * NSG, SLOTS = NQ * GP;
+  constexpr int NG = NJ / IL, NSG = NG / GP, STEPS = KR * NSG, SLOTS = NQ * GP;
   constexpr int NBUF = ONE ? 1 : 3;       // patch buffers (ONE: a group has a single chunk)
   constexpr int NW = WO * WP, NT = 64 * NW;
   constexpr bool INT = __is_same(typename TR::acc_t, int32_t);
@@ -88,19 +94,27 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   const int first = cnt > 0 ? kg * most : 0;              // (a group without chunks loads the first one and leaves it)
 
   // ---- weights: fragments of (32 channels, chunk, tap), 1 KB each -------------------------------
+  // (rows and blocks past O are never stored)
+  constexpr int kTap = NAT ? 32 : 1024;   // bytes from a tap to the next
   const uint8_t* wsrc;
-  {
+  if constexpr (NAT) {
+    wsrc = static_cast<const uint8_t*>(a.wr) + int64_t(first) * (T * kTap);
+  } else {
     const int n_oblk = (a.O + 31) / 32;
     int ob = o0 / 32 + wo;
-    ob = ob < n_oblk ? ob : n_oblk - 1;   // blocks past O are never stored
-    wsrc = static_cast<const uint8_t*>(a.wblk) + (int64_t(ob) * n_chunks + first) * (T * 1024);
+    ob = ob < n_oblk ? ob : n_oblk - 1;
+    wsrc = static_cast<const uint8_t*>(a.wblk) + (int64_t(ob) * n_chunks + first) * (T * kTap);
   }
   // lane's 16 bytes of a fragment: row lane % 32, half lane / 32, in the block's order (conv_repack_kernel)
-  const uint32_t wlane = uint32_t((lane & 31) * 32 + (((lane >> 5) ^ ((((lane & 31) >> 2) ^ ((lane & 31) >> 3)) & 1)) << 4));
+  uint32_t wlane = uint32_t((lane & 31) * 32 + (((lane >> 5) ^ ((((lane & 31) >> 2) ^ ((lane & 31) >> 3)) & 1)) << 4));
+  if constexpr (NAT) {
+    const int o = o0 + wo * 32 + (lane & 31);
+    wlane = uint32_t(o < a.O ? o : a.O - 1) * uint32_t(a.C * ESZ) + uint32_t(lane >> 5) * 16u;   // (fits: host check)
+  }
   i32x4 ring[T];
   auto load_tap = [&](int ch, auto tap_) {
     constexpr int tap = decltype(tap_)::value;
-    ring[tap] = *reinterpret_cast<const i32x4*>(wsrc + int64_t(ch) * (T * 1024) + tap * 1024 + wlane);
+    ring[tap] = *reinterpret_cast<const i32x4*>(wsrc + int64_t(ch) * (T * kTap) + tap * kTap + wlane);
   };
 
   // ---- patch items: VW pixels, consecutive in the rows a segment needs, x one half of a chunk ----
@@ -108,14 +122,24 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   const uint8_t* asrc = static_cast<const uint8_t*>(a.act) + int64_t(first) * CCH * plane;
   // The extents of the first two segments are scalars; a tile that touches more than two images
   // (small planes) walks them.
+  // (1x1 windows: in output rows)
+  constexpr bool PT = KH * KW == 1;
+  constexpr int SR = PT ? 1 : S;
+  const int Ph = PT ? 0 : a.Ph, Pw = PT ? 0 : a.Pw;
   int ihlo0, rows0, ihlo1 = 0, rows1 = 0;
-  seg_extent(ts, 0, g, S, a.Ph, KH, &ihlo0, &rows0);
-  if (ts.nseg > 1) seg_extent(ts, 1, g, S, a.Ph, KH, &ihlo1, &rows1);
+  seg_extent(ts, 0, g, SR, Ph, KH, &ihlo0, &rows0);
+  if (ts.nseg > 1) seg_extent(ts, 1, g, SR, Ph, KH, &ihlo1, &rows1);
   uint32_t src[MAXI];
   int dst[MAXI][VW];
   bool item_ok[MAXI];
   {
     auto valid = [&](int ihlo, int rows, int* vlo, int* items, int* len) {
+      if constexpr (PT) {                   // row by row: the rows between are not wanted
+        *vlo = ihlo;
+        *len = 0;
+        *items = rows * int(g.dXG.d);
+        return;
+      }
       *vlo = ihlo > 0 ? ihlo : 0;
       const int vhi = ihlo + rows < a.H ? ihlo + rows : a.H;
       *len = vhi > *vlo ? (vhi - *vlo) * a.W : 0;
@@ -128,31 +152,46 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     for (int i = 0; i < MAXI; ++i) {
       int rem = gt + NT * i, seg = 0, base = 0, ihlo = ihlo0, vlo = vlo0, items = it0, len = len0;
       if (ts.nseg == 2) {                   // uniform
-        if (rem >= 2 * it0) {
-          rem -= 2 * it0;
+        if (rem >= 2 * CM * it0) {
+          rem -= 2 * CM * it0;
           seg = 1; base = rows0; ihlo = ihlo1; vlo = vlo1; items = it1; len = len1;
         }
       } else if (ts.nseg > 2) {
         int rows = rows0;
-        while (rem >= 2 * items && seg + 1 < ts.nseg) {
-          rem -= 2 * items;
+        while (rem >= 2 * CM * items && seg + 1 < ts.nseg) {
+          rem -= 2 * CM * items;
           base += rows;
           ++seg;
-          seg_extent(ts, seg, g, S, a.Ph, KH, &ihlo, &rows);
+          seg_extent(ts, seg, g, SR, Ph, KH, &ihlo, &rows);
           valid(ihlo, rows, &vlo, &items, &len);
         }
       }
-      item_ok[i] = rem < 2 * items;
-      const int half = rem >= items ? 1 : 0, k = item_ok[i] ? rem - half * items : 0;
-      int f = k * VW < len - VW ? k * VW : len - VW;      // the last item ends with the range
-      f = f > 0 ? f + vlo * a.W : vlo * a.W;
-      int row = int(g.dW.div(uint32_t(f))), col = f - row * a.W;
+      item_ok[i] = rem < 2 * CM * items;
+      // half: which 16 bytes of the chunk's 32 CM
+      int half = rem >= items ? 1 : 0;
+      if constexpr (CM > 1) half = int((float(rem) + 0.5f) / float(items));   // (exact: both below 2^16)
+      const int k = item_ok[i] ? rem - half * items : 0;
+      half = item_ok[i] ? half : 0;
+      int row, col, cell;
+      if constexpr (PT) {
+        const int r = int(g.dXG.div(uint32_t(k)));
+        col = (k - r * int(g.dXG.d)) * VW;
+        col = col < a.W - VW ? col : a.W - VW;            // the last item ends with the row
+        row = (vlo + r) * S;
+        cell = base + r;
+      } else {
+        int f = k * VW < len - VW ? k * VW : len - VW;    // the last item ends with the range
+        f = f > 0 ? f + vlo * a.W : vlo * a.W;
+        row = int(g.dW.div(uint32_t(f)));
+        col = f - row * a.W;
+        cell = base + row - ihlo;
+      }
       // byte offsets from the tensor's start fit 32 bits (fewer than 2^31 elements)
-      src[i] = item_ok[i] ? uint32_t((ts.n_first + seg) * a.C + half * G) * uint32_t(plane) + uint32_t(f) * uint32_t(ESZ) : 0u;
-      int cell = half * g.halfb + (base + row - ihlo) * g.rowp;
+      src[i] = item_ok[i] ? uint32_t((ts.n_first + seg) * a.C + half * G) * uint32_t(plane) + uint32_t(row * a.W + col) * uint32_t(ESZ) : 0u;
+      cell = half * g.halfb + cell * g.rowp;
 #pragma unroll
       for (int e = 0; e < VW; ++e) {
-        const uint32_t c = uint32_t(col + a.Pw);
+        const uint32_t c = uint32_t(col + Pw);
         dst[i][e] = cell + int(c % PH) * g.php + int(c / PH) * 16;
         if (++col == a.W) {                               // rows are at least VW long: at most one wrap
           col = 0;
@@ -247,10 +286,10 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
       base = 0;
       for (int s_ = 0; s_ <= si; ++s_) {
         base += rows;
-        seg_extent(ts, s_, g, S, a.Ph, KH, &ihlo, &rows);
+        seg_extent(ts, s_, g, SR, Ph, KH, &ihlo, &rows);
       }
     }
-    fb[gi] = (lane >> 5) * g.halfb + (base + ho * S - a.Ph - ihlo) * g.rowp + (wo_ / IL) * 16;
+    fb[gi] = (lane >> 5) * g.halfb + (base + ho * SR - Ph - ihlo) * g.rowp + (wo_ / IL) * 16;
   }
 
   typename TR::accv_t acc[NJ];
@@ -275,7 +314,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   i32x4 fr[SLOTS];
   auto request = [&](const uint8_t* pb, auto step_, auto s_) {
     constexpr int step = decltype(step_)::value, q = decltype(s_)::value / GP, gi = step % NSG * GP + decltype(s_)::value % GP;
-    fr[decltype(s_)::value] = *reinterpret_cast<const i32x4*>(pb + fb[gi] + step / NSG * g.rowp + (q % PH) * g.php + (q / PH) * 16);
+    fr[decltype(s_)::value] = *reinterpret_cast<const i32x4*>(pb + fb[gi] + step / NSG * (CM > 1 ? 2 * g.halfb : g.rowp) + (q % PH) * g.php + (q / PH) * 16);
   };
   constexpr int kReads = SLOTS * (STEPS - 1) - (VW * MAXI + QUOTA - 1) / QUOTA;   // fragments requested behind the last cell
   int cur = 0;                                                 // LDS offset of the chunk's buffer
@@ -286,7 +325,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     uint8_t* const nb = patch + nxt;
     const uint8_t* const asrc2 = asrc + int64_t(ch + 2 < cnt ? ch + 2 : ch) * CCH * plane;   // surplus at the end: no branch
     static_for<STEPS>([&](auto step_) {
-      constexpr int step = decltype(step_)::value, kh = step / NSG;
+      constexpr int step = decltype(step_)::value, kh = step / NSG;   // kernel row, or chunk of CM
       static_for<SLOTS>([&](auto s_) {
         constexpr int s = decltype(s_)::value, q = s / GP, gi = step % NSG * GP + s % GP, slot = step * SLOTS + s;
         static_for<IL>([&](auto j_) {

@@ -5,8 +5,8 @@ Every layer is one access-pattern program of the paper evaluated by the HIP libr
 * 3x3 and 7x7 convolutions are Fig. 2a (`conv2d_direct_packed`, windows formed on chip; the
   3-channel stem takes the library's few-channel kernel, which forms im2col rows in LDS);
 * the 1x1 stride-2 shortcut projections have no window overlap to exploit, so they run in the
-  im2col-rewritten form of Fig. 5 (`conv2d_im2col`: explicit gather, then the dense contraction),
-  which is the faster of the two forms for them;
+  im2col-rewritten form of Fig. 5 (`conv2d_im2col`), whose matrix rows are then the pixels
+  themselves: the library reads them where they lie;
 * ReLU and the residual addition (the `reduceSum (pair a b)` idiom of Sec. 5.4) are fused into the
   convolution epilogues;
 * max pooling is Fig. 2c (`windows_reduce`), the global average is `compute reduceSum` with a

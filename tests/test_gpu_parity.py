@@ -554,32 +554,41 @@ def test_conv2d_few_channels_random_shapes(case):
 # planes of which a tile holds several or none, whose ends cut a 16-byte store; channel counts whose chunks
 # the groups of a channel sum divide, do not divide, or do not all get; channel tiles cut short.
 CONV_TILE_CASES = [
-    # n, c (32-byte chunks), h, w, o, stride, pad
-    (1, 1, 1, 4, 1, 1, 1), (3, 2, 4, 5, 31, 1, 1), (70, 3, 2, 4, 33, 1, 1), (1, 4, 56, 56, 64, 1, 1), (2, 5, 9, 11, 65, 2, 0),
-    (5, 9, 7, 7, 96, 1, 1), (1, 33, 7, 7, 40, 1, 1), (21, 8, 7, 7, 130, 1, 1), (2, 7, 14, 14, 64, 2, 1), (9, 4, 28, 28, 128, 1, 1),
-    (6, 4, 28, 28, 72, 2, 1), (33, 2, 31, 29, 17, 1, 0), (16, 4, 56, 56, 64, 1, 1), (13, 3, 41, 52, 100, 1, 1), (40, 2, 40, 44, 128, 2, 1),
-    (2, 6, 3, 112, 16, 1, 1), (1, 2, 112, 3, 48, 1, 1), (3, 2, 20, 18, 32, 1, 3), (2, 2, 60, 62, 200, 2, 2), (64, 1, 16, 16, 65, 1, 1),
+    # k, n, c (32-byte chunks), h, w, o, stride, pad
+    (3, 1, 1, 1, 4, 1, 1, 1), (3, 3, 2, 4, 5, 31, 1, 1), (3, 70, 3, 2, 4, 33, 1, 1), (3, 1, 4, 56, 56, 64, 1, 1), (3, 2, 5, 9, 11, 65, 2, 0),
+    (3, 5, 9, 7, 7, 96, 1, 1), (3, 1, 33, 7, 7, 40, 1, 1), (3, 21, 8, 7, 7, 130, 1, 1), (3, 2, 7, 14, 14, 64, 2, 1), (3, 9, 4, 28, 28, 128, 1, 1),
+    (3, 6, 4, 28, 28, 72, 2, 1), (3, 33, 2, 31, 29, 17, 1, 0), (3, 16, 4, 56, 56, 64, 1, 1), (3, 13, 3, 41, 52, 100, 1, 1), (3, 40, 2, 40, 44, 128, 2, 1),
+    (3, 2, 6, 3, 112, 16, 1, 1), (3, 1, 2, 112, 3, 48, 1, 1), (3, 3, 2, 20, 18, 32, 1, 3), (3, 2, 2, 60, 62, 200, 2, 2), (3, 64, 1, 16, 16, 65, 1, 1),
+    (5, 1, 1, 5, 5, 1, 1, 0), (5, 2, 3, 4, 6, 33, 1, 2), (5, 30, 2, 7, 7, 70, 1, 2), (5, 12, 4, 28, 30, 128, 1, 2), (5, 9, 2, 31, 33, 40, 2, 2),
+    (5, 1, 9, 14, 14, 65, 1, 2), (5, 3, 1, 112, 4, 16, 2, 1),
+    (1, 1, 4, 1, 4, 1, 1, 0), (1, 3, 4, 5, 5, 33, 2, 0), (1, 50, 8, 7, 7, 64, 1, 0), (1, 2, 12, 14, 15, 130, 2, 0), (1, 64, 4, 28, 28, 128, 2, 0),
+    (1, 8, 4, 56, 56, 64, 1, 0), (1, 5, 20, 29, 31, 31, 1, 0), (1, 32, 8, 28, 28, 256, 2, 0), (1, 1, 64, 7, 7, 512, 2, 0),
 ]
 
 
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
 @pytest.mark.parametrize("case", CONV_TILE_CASES)
-def test_conv2d_3x3_tiles(case, dtype, odt):
-    n, chunks, h, w, o, s, p = case
+def test_conv2d_tiles(case, dtype, odt):
+    k, n, chunks, h, w, o, s, p = case
     c = chunks * (32 if dtype == "i8" else 16)
-    cfg = synth.conv_layer(n, c, h, w, o, 3, s, p, dtype, 8500 + h + 3 * o)
+    cfg = synth.conv_layer(n, c, h, w, o, k, s, p, dtype, 8500 + h + 3 * o)
+    x, wt = cfg["x"].to(DEV), cfg["w"].to(DEV)
     want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p)
     res = gen("i32" if dtype == "i8" else ("bf16" if odt == torch.bfloat16 else "f32"), tuple(want.shape), 8600 + o)
-    packed = gs.conv2d_pack_weights(cfg["w"].to(DEV), for_input=(cfg["x"].to(DEV), (s, s), (p, p)))
+    packed = gs.conv2d_pack_weights(wt, for_input=(x, (s, s), (p, p)))
     # results sit between guard values: nothing outside them may be written
     buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
     out = buf[256:256 + want.numel()].view(want.shape)
     for residual, act in ((None, gs.GS_ACT_NONE), (res, gs.GS_ACT_RELU)):
-        gs.conv2d_direct_packed(cfg["x"].to(DEV), cfg["w"].to(DEV), packed, (s, s), (p, p), act=act, out=out,
-                                residual=None if residual is None else residual.to(DEV))
         ref = want if residual is None else (want + res.double()).clamp_min(0)
-        ref = ref.numpy()
-        assert_parity(out, ref.astype(np.int64) if dtype == "i8" else ref, what=f"{dtype} {case}")
+        ref = ref.numpy().astype(np.int64) if dtype == "i8" else ref.numpy()
+        how = dict(act=act, out=out, residual=None if residual is None else residual.to(DEV))
+        gs.conv2d_direct_packed(x, wt, packed, (s, s), (p, p), **how)
+        assert_parity(out, ref, what=f"{dtype} {case}")
+        if k == 1:      # the listing's own weights
+            out.fill_(55)
+            gs.conv2d_im2col(x, wt, (s, s), (p, p), **how)
+            assert_parity(out, ref, what=f"{dtype} {case} im2col")
         assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
