@@ -154,6 +154,33 @@ int conv_check_io(const gs_ap* act, const gs_ap* w, const gs_ap* residual, int a
   return GS_OK;
 }
 
+// Arguments of the direct convolution on the packed weights `packed`, with the scratch behind them if there is room.
+ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_ap* out, const ConvShape& cs, void* packed,
+                   bool split, size_t wneed) {
+  ConvArgs a;
+  memset(&a, 0, sizeof(a));
+  a.ksplit = 1;
+  if (split) {
+    a.ksplit = conv_pick_ksplit(act->dtype, cs.N, cs.C, cs.O, cs.Ho, cs.Wo);
+    a.partial = static_cast<uint8_t*>(packed) + wneed;
+  }
+  a.act = act->data;
+  a.wr = packed;
+  a.out = out->data;
+  a.residual = residual ? residual->data : nullptr;
+  a.in_dtype = act->dtype;
+  a.out_dtype = out->dtype;
+  a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = cs.Kh; a.Kw = cs.Kw;
+  a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ph = cs.Ph; a.Pw = cs.Pw; a.Ho = cs.Ho; a.Wo = cs.Wo;
+  a.Cpad = int(round_up(cs.C, act->dtype == GS_I8 ? 32 : 16));
+  if (conv_is_smallc(act->dtype, cs.C))
+    a.wnat = static_cast<const uint8_t*>(packed) + conv_smallc_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
+  if (conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw))
+    a.wblk = static_cast<const uint8_t*>(packed) + conv_blocked_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
+  a.relu = actfn == GS_ACT_RELU;
+  return a;
+}
+
 // Row stride of the im2col matrix (and of the padded weight matrix): K rounded up to the 32-byte
 // K step of the dense kernel.  Columns K..ld are zeros in both operands, so the contraction may
 // run over ld columns and take the direct-to-LDS path.
@@ -394,27 +421,7 @@ int glenside_conv2d_direct_packed(const gs_ap* act, const gs_ap* w, const int64_
   const size_t need = glenside_conv2d_direct_workspace(act, w, stride, pad);
   if (!packed || packed_bytes < wneed || reinterpret_cast<uintptr_t>(packed) % 16)
     return GS_ERR_WORKSPACE;
-  ConvArgs a;
-  memset(&a, 0, sizeof(a));
-  a.ksplit = 1;
-  if (need > wneed && packed_bytes >= need) {
-    a.ksplit = conv_pick_ksplit(act->dtype, cs.N, cs.C, cs.O, cs.Ho, cs.Wo);
-    a.partial = static_cast<uint8_t*>(packed) + wneed;
-  }
-  a.act = act->data;
-  a.wr = packed;
-  a.out = out->data;
-  a.residual = residual ? residual->data : nullptr;
-  a.in_dtype = act->dtype;
-  a.out_dtype = out->dtype;
-  a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = cs.Kh; a.Kw = cs.Kw;
-  a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ph = cs.Ph; a.Pw = cs.Pw; a.Ho = cs.Ho; a.Wo = cs.Wo;
-  a.Cpad = int(round_up(cs.C, act->dtype == GS_I8 ? 32 : 16));
-  if (conv_is_smallc(act->dtype, cs.C))
-    a.wnat = static_cast<const uint8_t*>(packed) + conv_smallc_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
-  if (conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw))
-    a.wblk = static_cast<const uint8_t*>(packed) + conv_blocked_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
-  a.relu = actfn == GS_ACT_RELU;
+  const ConvArgs a = conv_args(act, residual, actfn, out, cs, packed, need > wneed && packed_bytes >= need, wneed);
   return launch_status(launch_conv(a, static_cast<hipStream_t>(stream)));
 }
 
@@ -430,10 +437,20 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
   const size_t need = glenside_conv2d_direct_workspace(act, w, stride, pad);
   if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16)
     return GS_ERR_WORKSPACE;
-  st = glenside_conv2d_pack_weights(w, workspace, workspace_bytes, stream);
-  if (st) return st;
-  return glenside_conv2d_direct_packed(act, w, stride, pad, residual, actfn, out, workspace,
-                                       workspace_bytes, stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const size_t wneed = size_t(round_up(int64_t(conv_weight_workspace(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)), 256)) + 256;
+  ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, need > wneed, wneed);
+  // Few channels: the kernel takes the weights as they are.
+  if (conv_is_smallc(act->dtype, cs.C)) {
+    ConvArgs b = a;
+    b.wr = w->data;
+    const hipError_t e = launch_conv_smallc(b, true, s);
+    if (e != hipErrorInvalidValue) return launch_status(e);
+  }
+  // Only the copy that the layer's kernel reads is made.
+  const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, s, conv_reads_blocked(a));
+  if (e != hipSuccess) return launch_status(e);
+  return launch_status(launch_conv(a, s));
 }
 
 }  // extern "C"
@@ -541,8 +558,12 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   if (e != hipSuccess) return launch_status(e);
 
   // flatten (access weights 1): already ((O),(K)) in memory; copied only when rows need padding.
+  // Results of few tiles take rows of any alignment in the same kernel: two launches less.
   const void* wmat = w->data;
-  if (ld != K) {
+  int64_t kdot = ld, ldw = ld;
+  if (ld != K && gemm_few_tiles(cs.O, M) && K * esz >= 16) {
+    kdot = ldw = K;
+  } else if (ld != K) {
     WindowsArgs ww;
     memset(&ww, 0, sizeof(ww));
     ww.in = w->data;
@@ -567,8 +588,9 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   g.out_dtype = out->dtype;
   g.I = cs.O;
   g.J = M;
-  g.K = ld;   // the pad columns are zeros on both sides
-  g.ldx = g.ldy = ld;
+  g.K = kdot;   // ld: the pad columns are zeros on both sides
+  g.ldx = ldw;
+  g.ldy = ld;
   g.jp = int64_t(cs.Ho) * cs.Wo;
   if (g.jp < 1) g.jp = 1;
   g.relu = actfn == GS_ACT_RELU;

@@ -40,6 +40,7 @@ struct SmallCArgs {
   int otiles;       // 64-channel tiles
   int64_t tasks;    // N * Ho * xtiles * otiles
   int vec_ok;       // input rows are whole 16-byte vectors
+  int raw;          // a.wr is the listing's ((O),(C,Kh,Kw)) tensor itself, not one of the packed copies
   uint32_t dr_mask[4];   // row-window form: keeps the first Kw elements of a 16-byte window
   FastDiv dvpr, dW, dhalo, dKh, dT, dKw, dchunk;
 };
@@ -138,6 +139,16 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
     if (ot != cur_ot) {                                // weight tile: rows past O and columns past K are zero
       cur_ot = ot;
       const T* wsrc = static_cast<const T*>(a.wr);     // ((O rounded up to 64),(Kp)), zero padded
+      if (p.raw) {                                     // eight threads to a row, element by element
+        const int r = tid >> 3, o = ot * 64 + r;
+        const T* row = wsrc + int64_t(o < a.O ? o : 0) * p.K;
+        for (int k = tid & 7; k < p.Kp; k += 8) {
+          // row-window form: element dy of row k / EPV; otherwise the listing's order
+          const int at = DR ? k / EPV * a.Kw + k % EPV : k;
+          const bool in = o < a.O && (DR ? k / EPV < nrows && k % EPV < a.Kw : k < p.K);
+          *reinterpret_cast<T*>(wl + r * p.wpb + k * ESZ) = in ? row[at] : T(0);
+        }
+      } else
       for (int id = tid; id < 64 * (p.Kp / EPV); id += NT) {
         const int r = id / (p.Kp / EPV), v = id - r * (p.Kp / EPV);
         *reinterpret_cast<i32x4*>(wl + r * p.wpb + v * 16) =
@@ -428,10 +439,11 @@ bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw
   return conv_is_smallc(in_dtype, C) && smallc_layout(in_dtype, C, W, Kh, Kw, Sw, Pw, Wo).fits;
 }
 
-// `a.wr` must point at the natural-order weight copy.  Returns hipErrorInvalidValue when the
+// `a.wr` must point at the natural-order weight copy, or (raw) at the weights themselves: a call that
+// brings its weights then needs no packing launches, for a few microseconds at each workgroup's start.  Returns hipErrorInvalidValue when the
 // shape does not fit (LDS), so that the caller can fall back.
 template <typename TR>
-static hipError_t launch_smallc_t(const ConvArgs& a, hipStream_t s) {
+static hipError_t launch_smallc_t(const ConvArgs& a, bool raw, hipStream_t s) {
   constexpr int ESZ = TR::kEsz;
   constexpr int EPV = 16 / ESZ, EPD = 4 / ESZ;
   const SmallCLayout l = smallc_layout(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sw, a.Pw, a.Wo);
@@ -446,8 +458,10 @@ static hipError_t launch_smallc_t(const ConvArgs& a, hipStream_t s) {
   p.XO = l.XO;
   p.pitch = l.pitch;
   p.tile_bytes = int(l.tile_bytes);
-  if (dr) {
+  p.raw = raw;
+  if (dr && !raw)
     p.c.wr = static_cast<const uint8_t*>(a.wr) + smallc_rows_offset(a.in_dtype, a.O, a.C, a.Kh, a.Kw);
+  if (dr) {
     for (int d = 0; d < 4; ++d) {
       uint32_t m = 0;
       for (int e = 0; e < EPD; ++e)
@@ -486,9 +500,9 @@ static hipError_t launch_smallc_t(const ConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_conv_smallc(const ConvArgs& a, hipStream_t s) {
+hipError_t launch_conv_smallc(const ConvArgs& a, bool raw, hipStream_t s) {
   if (!conv_is_smallc(a.in_dtype, a.C)) return hipErrorInvalidValue;
-  return a.in_dtype == GS_I8 ? launch_smallc_t<I8Traits>(a, s) : launch_smallc_t<Bf16Traits>(a, s);
+  return a.in_dtype == GS_I8 ? launch_smallc_t<I8Traits>(a, raw, s) : launch_smallc_t<Bf16Traits>(a, raw, s);
 }
 
 }  // namespace gs

@@ -929,6 +929,8 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   return is_short ? launch_any<TR, 64, 64, 2, 2, true>(v, s) : launch_any<TR, 64, 64, 2, 2, false>(v, s);
 }
 
+bool gemm_few_tiles(int64_t I, int64_t J) { return ceil_div(I, 32) * ceil_div(J, 32) <= 512; }
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.I == 0 || a.J == 0) return hipSuccess;
   if (ceil_div(a.I, 32) * ceil_div(a.J, 32) > 0x7fffffff) return hipErrorInvalidValue;
