@@ -299,7 +299,7 @@ size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 hipError_t launch_conv_smallc_pack(const void* w, void* wn, int in_dtype, int O, int C, int Kh, int Kw,
                                    hipStream_t s);
 hipError_t launch_conv_smallc(const ConvArgs& a, bool raw, hipStream_t s);   // reads a.wr = natural-order copy; raw: the weights themselves
-bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo);   // does the kernel take the layer?
+bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo);   // does the kernel take the layer?
 // only_blocked: the other copies are left out (they must not be read afterwards)
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
                               hipStream_t s, bool only_blocked = false);

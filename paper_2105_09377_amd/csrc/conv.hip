@@ -219,7 +219,7 @@ static hipError_t launch_conv_tile(const ConvArgs& a, ConvGeom g, hipStream_t s)
 bool conv_direct_fits(const ConvArgs& a) {
   const int64_t N = a.N, Wo = a.Wo, HWo = int64_t(a.Ho) * Wo, Kh = a.Kh, Kw = a.Kw;
   if (N * HWo == 0 || a.O == 0) return true;
-  if (conv_smallc_fits(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sw, a.Pw, a.Wo)) return true;
+  if (conv_smallc_fits(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sh, a.Sw, a.Pw, a.Wo)) return true;
   if (Kh > 512 || Kw > 512) return false;
   const int64_t images = 64 % HWo == 0 ? 64 / HWo : ceil_div(63, HWo) + 1, n = images < N ? images : N;
   const int64_t spanned = ceil_div(63, Wo) + 1, R = spanned < N * a.Ho ? spanned : N * a.Ho;

@@ -21,7 +21,8 @@
 // staged row is Pw, which puts every window on a dword boundary (16-byte LDS reads off a dword
 // boundary are several times slower); the staged data may then sit off a dword boundary and is
 // written with stores aligned to the element only, which the hardware's unaligned mode allows
-// and which are few.  The weights get a second copy in that order, zero in the padding.
+// and which are few.  The weights get a second copy in that order, zero in the padding.  Where that
+// fills the chip, conv_rows_kernel makes tasks of two output rows.
 #include "common.h"
 
 #include <limits.h>
@@ -43,6 +44,7 @@ struct SmallCArgs {
   int raw;          // a.wr is the listing's ((O),(C,Kh,Kw)) tensor itself, not one of the packed copies
   uint32_t dr_mask[4];   // row-window form: keeps the first Kw elements of a 16-byte window
   FastDiv dvpr, dW, dhalo, dKh, dT, dKw, dchunk;
+  FastDiv dkh2, dxt, dpairs;   // conv_rows_kernel: Kh + Sh, position tiles, pairs of output rows
 };
 
 constexpr int kSmallCBatch = 4;   // 16-byte vectors a thread stages per task
@@ -310,6 +312,248 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
   }
 }
 
+// Row-window form for many rows: a task is two output rows (n, x), (n, x + 1) of up to 128 positions,
+// whose input rows are staged once (C (Kh + Sh) instead of 2 C Kh).  Wave w multiplies 32 positions of row w / 4
+// with all 64 channels of the tile, so that every window is read once, positions on the MFMA rows:
+// a lane then holds four consecutive positions of a channel, which reach the staging rows as 16-byte
+// LDS stores and memory as 16 bytes per lane.  Two workgroups per compute unit take turns between
+// LDS, matrix unit and memory.
+template <typename TR>
+__global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs p) {
+  constexpr int NT = kSmallCThreads;
+  using T = typename std::conditional<TR::kEsz == 1, uint8_t, uint16_t>::type;
+  constexpr int ESZ = TR::kEsz, EPV = 16 / ESZ;
+  constexpr bool INT = __is_same(typename TR::acc_t, int32_t);
+  constexpr int RS = 32 * 4 + 16;          // row stride of the results' staging
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const ConvArgs& a = p.c;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh2 = a.Kh + a.Sh, nrows = a.C * kh2;     // staged rows: row c * kh2 + i is image row x * Sh - Ph + i of channel c
+  const int row_bytes = p.pitch * ESZ;
+  // LDS: weights [64][wpb] | results' staging, one area per wave | input rows and a zero row
+  uint8_t* const wl = lds;
+  uint8_t* const st = lds + 64 * p.wpb + wave * (32 * RS);
+  T* const stage = reinterpret_cast<T*>(lds + 64 * p.wpb + p.tile_bytes);
+  const T* in = static_cast<const T*>(a.act);
+  const int vpr = a.W * ESZ / 16, nvec = nrows * vpr;
+  const int halo = p.pitch - a.W;
+
+  // Within each round of gridDim.x tasks an XCD takes a contiguous run of them (see conv_smallc_kernel).
+  int64_t task = blockIdx.x;
+  if (gridDim.x % 8 == 0) task = int64_t(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  if (task >= p.tasks) return;
+  const int64_t per_o = p.tasks / p.otiles;
+  const int pairs = (a.Ho + 1) / 2;
+  auto decode = [&](int64_t t, int* ot, int* n, int* ho, int* xt) {
+    *ot = int(t / per_o);
+    const uint32_t r = uint32_t(t - int64_t(*ot) * per_o), q = p.dxt.div(r);     // (tasks per channel tile fit 31 bits: host check)
+    *xt = int(r - q * uint32_t(p.xtiles));
+    *n = int(p.dpairs.div(q));
+    *ho = 2 * int(q - uint32_t(*n) * uint32_t(pairs));
+  };
+  // what is written once: padding cells and the zero row
+  for (int id = tid; id < nrows * halo; id += NT) {
+    uint32_t r, h;
+    p.dhalo.divmod(uint32_t(id), &r, &h);
+    stage[int(r) * p.pitch + (int(h) < p.XO ? int(h) : a.W + int(h))] = T(0);
+  }
+  for (int id = tid; id < p.pitch; id += NT) stage[nrows * p.pitch + id] = T(0);
+
+  i32x4 val[kSmallCBatch];
+  auto issue_loads = [&](int64_t t) {
+    int ot, n, ho, xt;
+    decode(t, &ot, &n, &ho, &xt);
+#pragma unroll
+    for (int u = 0; u < kSmallCBatch; ++u) {
+      val[u] = i32x4{0, 0, 0, 0};
+      if (u * NT < nvec) {                               // uniform: skip batches past the last vector
+        const int id = u * NT + tid;
+        uint32_t r, v, c, i;
+        p.dvpr.divmod(uint32_t(id), &r, &v);
+        p.dkh2.divmod(r, &c, &i);
+        const int ih = ho * a.Sh + int(i) - a.Ph;
+        if (id < nvec && ih >= 0 && ih < a.H)
+          val[u] = *reinterpret_cast<const i32x4*>(in + ((int64_t(n) * a.C + int(c)) * a.H + ih) * a.W + int(v) * EPV);
+      }
+    }
+  };
+  if (p.vec_ok) issue_loads(task);
+
+  const int pb = wave & 3, rr = wave >> 2;               // position block, row of the task
+  const int half = lane >> 5;
+  const i32x4 keep = {int(p.dr_mask[0]), int(p.dr_mask[1]), int(p.dr_mask[2]), int(p.dr_mask[3])};
+  const int ksteps = p.Kp * ESZ / 32;
+  int cur_ot = -1;
+  for (; task < p.tasks; task += gridDim.x) {
+    int ot, n, ho, xt;
+    decode(task, &ot, &n, &ho, &xt);
+    const int y0 = xt * 128;
+    const int npos = a.Wo - y0 < 128 ? a.Wo - y0 : 128;
+    lds_barrier();                                       // the previous task's rows have been read
+    if (ot != cur_ot) {                                  // weights: rows past O and columns past the window are zero
+      cur_ot = ot;
+      const T* wsrc = static_cast<const T*>(a.wr);       // ((O rounded up to 64),(Kp)), zero padded; raw: ((O),(C,Kh,Kw))
+      if (p.raw) {                                       // eight threads to a row, element by element
+        const int r = tid >> 3, o = ot * 64 + r;
+        const T* row = wsrc + int64_t(o < a.O ? o : 0) * p.K;
+        for (int k = tid & 7; k < p.Kp; k += 8) {
+          const bool ok = o < a.O && k / EPV < a.C * a.Kh && k % EPV < a.Kw;
+          *reinterpret_cast<T*>(wl + r * p.wpb + k * ESZ) = ok ? row[k / EPV * a.Kw + k % EPV] : T(0);
+        }
+      } else {
+        for (int id = tid; id < 64 * (p.Kp / EPV); id += NT) {
+          const int r = id / (p.Kp / EPV), v = id - r * (p.Kp / EPV);
+          *reinterpret_cast<i32x4*>(wl + r * p.wpb + v * 16) =
+              *reinterpret_cast<const i32x4*>(wsrc + (int64_t(ot) * 64 + r) * p.Kp + v * EPV);
+        }
+      }
+    }
+    if (p.vec_ok) {
+#pragma unroll
+      for (int u = 0; u < kSmallCBatch; ++u) {
+        const int id = u * NT + tid;
+        if (u * NT < nvec && id < nvec) {
+          uint32_t r, v;
+          p.dvpr.divmod(uint32_t(id), &r, &v);
+          typedef int32_t word_t __attribute__((aligned(1)));   // aligned to the element only
+          word_t* d = reinterpret_cast<word_t*>(reinterpret_cast<uint8_t*>(stage) + (int(r) * p.pitch + p.XO) * ESZ + int(v) * 16);
+          d[0] = val[u][0];
+          d[1] = val[u][1];
+          d[2] = val[u][2];
+          d[3] = val[u][3];
+        }
+      }
+    } else {
+      for (int id = tid; id < nrows * a.W; id += NT) {
+        uint32_t r, x, c, i;
+        p.dW.divmod(uint32_t(id), &r, &x);
+        p.dkh2.divmod(r, &c, &i);
+        const int ih = ho * a.Sh + int(i) - a.Ph;
+        stage[int(r) * p.pitch + p.XO + int(x)] =
+            (ih >= 0 && ih < a.H) ? in[((int64_t(n) * a.C + int(c)) * a.H + ih) * a.W + int(x)] : T(0);
+      }
+    }
+    lds_barrier();
+    if (p.vec_ok && task + gridDim.x < p.tasks) issue_loads(task + gridDim.x);
+    if (pb * 32 >= npos || ho + rr >= a.Ho) continue;    // uniform; the barriers are at the loop's head
+    // -- multiply: K step ks holds window rows 2 ks and 2 ks + 1 (c, dx); lanes past the last position
+    // read the last position's windows and are not stored
+    typename TR::accv_t acc[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0;
+    {
+      typedef i32x4 win_t __attribute__((aligned(4)));   // windows start on dword boundaries
+      const int pos = pb * 32 + (lane & 31);
+      const uint8_t* const b0 = reinterpret_cast<const uint8_t*>(stage) +
+                                (p.XO - a.Pw + (y0 + (pos < npos ? pos : npos - 1)) * a.Sw) * ESZ;
+      const uint8_t* ap = wl + (lane & 31) * p.wpb + half * 16;
+      // window row r, its row dx in the channel (a single one: never past it), its LDS offset
+      int r = half, dx = a.Kh == 1 ? INT_MIN / 2 : half;
+      int at = (rr * a.Sh + (a.Kh == 1 ? half * kh2 : half)) * row_bytes;
+      const int step = a.Kh == 1 ? 2 * kh2 * row_bytes : 2 * row_bytes, skip = (kh2 - a.Kh) * row_bytes;
+      const int last = a.C * a.Kh, zero = nrows * row_bytes;
+      auto window = [&]() { return *reinterpret_cast<const win_t*>(b0 + (r < last ? at : zero)); };
+      // the next step's fragments are requested in front of the MFMAs
+      i32x4 b = window(), w0 = *reinterpret_cast<const i32x4*>(ap), w1 = *reinterpret_cast<const i32x4*>(ap + 32 * p.wpb);
+      for (int ks = 1; ks < ksteps; ++ks) {
+        r += 2;
+        dx += 2;
+        const bool wrap = dx >= a.Kh;                    // into the next channel
+        at += wrap ? step + skip : step;
+        dx -= wrap ? a.Kh : 0;
+        ap += 32;
+        const i32x4 bn = window(), w0n = *reinterpret_cast<const i32x4*>(ap);
+        const i32x4 w1n = *reinterpret_cast<const i32x4*>(ap + 32 * p.wpb);
+        acc[0] = TR::mfma(b & keep, w0, acc[0]);
+        acc[1] = TR::mfma(b & keep, w1, acc[1]);
+        b = bn;
+        w0 = w0n;
+        w1 = w1n;
+      }
+      acc[0] = TR::mfma(b & keep, w0, acc[0]);
+      acc[1] = TR::mfma(b & keep, w1, acc[1]);
+    }
+    // -- write-back: out[((n*O + o)*Ho + ho + rr)*Wo + y], 32 channels at a time
+    const int m0 = y0 + pb * 32, mlim = y0 + npos;
+    const int64_t ostride = int64_t(a.Ho) * a.Wo;
+    const int64_t row0 = (int64_t(n) * a.O * a.Ho + ho + rr) * a.Wo;                    // o = 0, y = 0
+    const int esz_out = INT || a.out_dtype == GS_F32 ? 4 : 2;
+    typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
+    static_for<2>([&](auto m_) {
+      constexpr int m = decltype(m_)::value;
+      static_for<4>([&](auto q_) {
+        constexpr int q = decltype(q_)::value;
+        const auto t = __builtin_shufflevector(acc[m], acc[m], 4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3);
+        *reinterpret_cast<i32x4*>(st + (lane & 31) * RS + (8 * q + 4 * half) * 4) = __builtin_bit_cast(i32x4, t);
+      });
+      const int o0 = ot * 64 + m * 32;
+      // 16 bytes per lane, aligned to the element only; the group that the row's end cuts value by value
+      auto cut_group = [&](int r, int y, int count) {
+        for (int e = 0; e < count; ++e)
+          store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, row0 + int64_t(o0 + r) * ostride + y + e,
+                                           *reinterpret_cast<const typename TR::acc_t*>(st + r * RS + (y - m0 + e) * 4), a.relu);
+      };
+      if (esz_out == 2) {
+        const int g = lane & 3, rsub = lane >> 2, y = m0 + g * 8;
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int r = it * 16 + rsub;
+          const i32x4 lo = *reinterpret_cast<const i32x4*>(st + r * RS + g * 32);
+          const i32x4 hi = *reinterpret_cast<const i32x4*>(st + r * RS + g * 32 + 16);
+          if (y >= mlim || o0 + r >= a.O) continue;
+          if (y + 8 > mlim) {
+            cut_group(r, y, mlim - y);
+            continue;
+          }
+          const int64_t at = row0 + int64_t(o0 + r) * ostride + y;
+          float f[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) f[e] = __int_as_float(e < 4 ? lo[e & 3] : hi[e & 3]);
+          if (a.residual) {
+            const i32x4 q = *reinterpret_cast<const i32x4_bytes*>(static_cast<const uint16_t*>(a.residual) + at);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              f[2 * e] += __uint_as_float(uint32_t(q[e]) << 16);
+              f[2 * e + 1] += __uint_as_float(uint32_t(q[e]) & 0xffff0000u);
+            }
+          }
+          i32x4 w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            w[e] = int32_t(a.relu ? pack_bf16x2(fmaxf(f[2 * e], 0.0f), fmaxf(f[2 * e + 1], 0.0f)) : pack_bf16x2(f[2 * e], f[2 * e + 1]));
+          *reinterpret_cast<i32x4_bytes*>(static_cast<uint16_t*>(a.out) + at) = w;
+        }
+      } else {
+        const int g = lane & 7, rsub = lane >> 3, y = m0 + g * 4;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int r = it * 8 + rsub;
+          i32x4 w = *reinterpret_cast<const i32x4*>(st + r * RS + g * 16);
+          if (y >= mlim || o0 + r >= a.O) continue;
+          if (y + 4 > mlim) {
+            cut_group(r, y, mlim - y);
+            continue;
+          }
+          const int64_t at = row0 + int64_t(o0 + r) * ostride + y;
+          if (a.residual) {
+            const i32x4 q = *reinterpret_cast<const i32x4_bytes*>(static_cast<const int32_t*>(a.residual) + at);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              w[e] = INT ? w[e] + q[e] : __float_as_int(__int_as_float(w[e]) + __int_as_float(q[e]));
+          }
+          if (a.relu) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              w[e] = INT ? (w[e] > 0 ? w[e] : 0) : __float_as_int(fmaxf(__int_as_float(w[e]), 0.0f));
+          }
+          *reinterpret_cast<i32x4_bytes*>(static_cast<int32_t*>(a.out) + at) = w;
+        }
+      }
+    });
+  }
+}
+
 // Natural-order copy of the weights for the kernel above: ((O rounded up to 64),(Kp)), zeros in
 // the padding.  `w` is ((O),(C,Kh,Kw)) = ((O),(K)) already.
 template <typename T>
@@ -408,11 +652,12 @@ static int smallc_num_cus() {
 // LDS of a workgroup: weights, staged input rows, and tiles or staging of the results.
 struct SmallCLayout {
   bool dr;                       // row-window form
+  int R;                         // its output rows per task
   int Kp, wpb, XO, pitch;        // see SmallCArgs
   int64_t tile_bytes, stage_bytes, lds_bytes;
   bool fits;
 };
-static SmallCLayout smallc_layout(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo) {
+static SmallCLayout smallc_layout(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo, int rows = 1) {
   const int esz = int(dtype_size(in_dtype)), epd = 4 / esz;
   SmallCLayout l;
   // Row-window form: windows a whole number of dwords apart, a window row within 16 bytes.
@@ -426,17 +671,18 @@ static SmallCLayout smallc_layout(int in_dtype, int C, int W, int Kh, int Kw, in
   const int64_t width = reach > l.XO + W ? reach : l.XO + W;
   l.pitch = int(round_up(width, epd));
   if ((l.pitch / epd) % 2 == 0) l.pitch += epd;        // an odd number of dwords spreads the gather over banks
-  const int64_t staged = (int64_t(C) * Kh + 1) * l.pitch * esz;
-  l.stage_bytes = round_up(staged, 16);
   constexpr int kStaging = (kSmallCThreads / 64) * 32 * (32 * 4 + 16);   // one staging area per wave
   l.tile_bytes = (!l.dr && 128 * int64_t(l.wpb) > kStaging) ? 128 * int64_t(l.wpb) : kStaging;
-  l.lds_bytes = 64 * int64_t(l.wpb) + l.tile_bytes + l.stage_bytes + int64_t(l.Kp) * 4;
+  l.R = l.dr ? rows : 1;
+  const int64_t staged = (int64_t(C) * (Kh + (l.R - 1) * Sh) + 1) * l.pitch * esz;
+  l.stage_bytes = round_up(staged, 16);
+  l.lds_bytes = 64 * int64_t(l.wpb) + l.tile_bytes + l.stage_bytes + (l.R > 1 ? 0 : int64_t(l.Kp) * 4);
   l.fits = l.lds_bytes <= 96 * 1024 && staged <= (1 << 20);
   return l;
 }
 
-bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sw, int Pw, int Wo) {
-  return conv_is_smallc(in_dtype, C) && smallc_layout(in_dtype, C, W, Kh, Kw, Sw, Pw, Wo).fits;
+bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo) {
+  return conv_is_smallc(in_dtype, C) && smallc_layout(in_dtype, C, W, Kh, Kw, Sh, Sw, Pw, Wo).fits;
 }
 
 // `a.wr` must point at the natural-order weight copy, or (raw) at the weights themselves: a call that
@@ -446,8 +692,17 @@ template <typename TR>
 static hipError_t launch_smallc_t(const ConvArgs& a, bool raw, hipStream_t s) {
   constexpr int ESZ = TR::kEsz;
   constexpr int EPV = 16 / ESZ, EPD = 4 / ESZ;
-  const SmallCLayout l = smallc_layout(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sw, a.Pw, a.Wo);
+  SmallCLayout l = smallc_layout(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sh, a.Sw, a.Pw, a.Wo);
   if (!l.fits) return hipErrorInvalidValue;
+  // Pairs of rows where they fill the chip: a task of two costs 1.6 of one (64 x 3 x 224x224 -> 64, 7x7 at
+  // stride 2, on 512 workgroups: 3584 pairs 62 us, 7168 rows 75; one image 7.5 and 6.5, 16 of 150x150 25.1
+  // and 23.8).
+  if (l.dr) {
+    const int64_t slots = 2 * smallc_num_cus(), per_row = int64_t(a.N) * ceil_div(a.Wo, 128) * ceil_div(a.O, 64);
+    const SmallCLayout two = smallc_layout(a.in_dtype, a.C, a.W, a.Kh, a.Kw, a.Sh, a.Sw, a.Pw, a.Wo, 2);
+    const bool whole = (a.W * ESZ) % 16 != 0 || int64_t(a.C) * (a.Kh + a.Sh) * (a.W * ESZ / 16) <= kSmallCThreads * kSmallCBatch;
+    if (two.fits && whole && 1.6 * double(ceil_div(per_row * ((a.Ho + 1) / 2), slots)) < double(ceil_div(per_row * a.Ho, slots))) l = two;
+  }
   const bool dr = l.dr;
   const int64_t lds_bytes = l.lds_bytes;
   SmallCArgs p;
@@ -470,10 +725,14 @@ static hipError_t launch_smallc_t(const ConvArgs& a, bool raw, hipStream_t s) {
     }
   }
   p.vec_ok = ((a.W * ESZ) % 16 == 0 && reinterpret_cast<uintptr_t>(a.act) % 16 == 0 &&
-              int64_t(a.C) * a.Kh * (a.W * ESZ / 16) <= kSmallCThreads * kSmallCBatch) ? 1 : 0;
+              int64_t(a.C) * (a.Kh + (l.R - 1) * a.Sh) * (a.W * ESZ / 16) <= kSmallCThreads * kSmallCBatch) ? 1 : 0;
   p.xtiles = int(ceil_div(a.Wo, 128));
   p.otiles = int(ceil_div(a.O, 64));
-  p.tasks = int64_t(a.N) * a.Ho * p.xtiles * p.otiles;
+  const int per_image = int(ceil_div(a.Ho, l.R));      // (tensors have fewer than 2^31 elements: so do tasks per channel tile)
+  p.tasks = int64_t(a.N) * per_image * p.xtiles * p.otiles;
+  p.dkh2 = FastDiv::make(uint32_t(a.Kh + (l.R - 1) * a.Sh));
+  p.dxt = FastDiv::make(uint32_t(p.xtiles > 0 ? p.xtiles : 1));
+  p.dpairs = FastDiv::make(uint32_t(per_image > 0 ? per_image : 1));
   if (p.tasks == 0) return hipSuccess;
   if (p.tasks > (int64_t(1) << 40)) return hipErrorInvalidValue;
   p.dvpr = FastDiv::make(uint32_t(a.W * ESZ / 16 > 0 ? a.W * ESZ / 16 : 1));
@@ -483,14 +742,15 @@ static hipError_t launch_smallc_t(const ConvArgs& a, bool raw, hipStream_t s) {
   p.dT = FastDiv::make(uint32_t(a.Kh * a.Kw));
   p.dKw = FastDiv::make(uint32_t(a.Kw));
   p.dchunk = FastDiv::make(uint32_t(p.Kp / EPV));
-  auto kern = dr ? conv_smallc_kernel<TR, true> : conv_smallc_kernel<TR, false>;
-  static std::once_flag once[2];
-  static hipError_t attr_status[2] = {hipSuccess, hipSuccess};
-  std::call_once(once[dr], [&]() {
-    attr_status[dr] = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+  auto kern = l.R > 1 ? conv_rows_kernel<TR> : dr ? conv_smallc_kernel<TR, true> : conv_smallc_kernel<TR, false>;
+  const int which = l.R > 1 ? 2 : dr;
+  static std::once_flag once[3];
+  static hipError_t attr_status[3] = {hipSuccess, hipSuccess, hipSuccess};
+  std::call_once(once[which], [&]() {
+    attr_status[which] = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
   });
-  if (attr_status[dr] != hipSuccess) return attr_status[dr];
+  if (attr_status[which] != hipSuccess) return attr_status[which];
   int per_cu = int((160 * 1024) / (lds_bytes + 512));
   per_cu = per_cu < 1 ? 1 : per_cu > 4 ? 4 : per_cu;
   int64_t grid = int64_t(smallc_num_cus()) * per_cu;

@@ -592,6 +592,32 @@ def test_conv2d_tiles(case, dtype, odt):
         assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# Few channels and many output rows: tasks of two rows (conv_rows_kernel).  Odd row counts, rows cut inside a
+# 16-byte store, several position and channel tiles, windows of one row, 16-byte loads and element by element.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("n,c,h,w,o,kh,kw,pad", [(41, 3, 77, 80, 64, 7, 7, 3), (42, 3, 79, 83, 33, 7, 7, 3), (11, 1, 300, 300, 40, 3, 5, 1),
+                                                 (30, 9, 64, 64, 100, 3, 3, 1), (40, 5, 90, 48, 65, 1, 8, 0), (50, 2, 66, 66, 8, 2, 4, 1)])
+def test_conv2d_few_channels_many_rows(n, c, h, w, o, kh, kw, pad, dtype, odt):
+    s = 4 if dtype == "i8" else 2
+    if dtype == "i8":
+        n *= 4
+    x, wt = gen(dtype, (n, c, h, w), 8700 + h), gen(dtype, (o, c, kh, kw), 8800 + o, (c * kh * kw) ** -0.5)
+    want = torch.nn.functional.conv2d(x.double(), wt.double(), stride=s, padding=pad)
+    res = gen("i32" if dtype == "i8" else ("bf16" if odt == torch.bfloat16 else "f32"), tuple(want.shape), 8900 + o)
+    buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
+    out = buf[256:256 + want.numel()].view(want.shape)
+    packed = gs.conv2d_pack_weights(wt.to(DEV), for_input=(x.to(DEV), (s, s), (pad, pad)))
+    for residual, act in ((None, gs.GS_ACT_NONE), (res, gs.GS_ACT_RELU)):
+        ref = want if residual is None else (want + res.double()).clamp_min(0)
+        ref = ref.numpy().astype(np.int64) if dtype == "i8" else ref.numpy()
+        how = dict(act=act, residual=None if residual is None else residual.to(DEV))
+        gs.conv2d_direct_packed(x.to(DEV), wt.to(DEV), packed, (s, s), (pad, pad), out=out, **how)
+        assert_parity(out, ref, what=f"{dtype} packed")
+        assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
+        got = gs.conv2d_direct(x.to(DEV), wt.to(DEV), (s, s), (pad, pad), out_dtype=odt, **how)
+        assert_parity(got, ref, what=f"{dtype} weights as they are")
+
+
 def test_conv2d_minus_128_and_empty_batch():
     x = torch.full((1, 32, 6, 6), -128, dtype=torch.int8)
     w = torch.full((8, 32, 3, 3), -128, dtype=torch.int8)
