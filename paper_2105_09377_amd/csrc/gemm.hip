@@ -41,21 +41,40 @@ constexpr int kSlabBytes = 128;             // K bytes per slab row
 constexpr int kRowBytes = kSlabBytes + 16;  // LDS row stride: odd multiple of 16 B, conflict-free b128
 constexpr int kXcds = 8;
 
+// Every argument is requested at once: one latency instead of one per use.
+__device__ __forceinline__ void request_args(const GemmArgs& a) {
+  asm volatile("" ::"s"(a.x), "s"(a.y), "s"(a.out), "s"(a.residual), "s"(a.I), "s"(a.J), "s"(a.K), "s"(a.ldx), "s"(a.ldy), "s"(a.jp),
+               "s"(a.bm), "s"(a.bn), "s"(a.relu), "s"(a.vj), "s"(a.out_dtype));
+}
+
 // Map the hardware workgroup id to a tile so that an XCD's workgroups cover a compact region:
 // XCD x gets the contiguous range of "logical" ids [x*n/8, (x+1)*n/8), and logical ids walk the
 // grid in column bands of `band` tile rows.
-__device__ inline void tile_of_block(int64_t bid, int64_t nblocks, int64_t tiles_i, int64_t tiles_j,
+__device__ inline void tile_of_block(uint32_t bid, uint32_t nblocks, int64_t tiles_i, int64_t tiles_j,
                                      int64_t* ti, int64_t* tj) {
-  const int64_t per = nblocks / kXcds, rem = nblocks % kXcds;
-  const int64_t x = bid % kXcds, l = bid / kXcds;
+  const uint32_t per = nblocks / kXcds, rem = nblocks % kXcds;   // (fewer than 2^31 tiles: host check)
+  const uint32_t x = bid % kXcds, l = bid / kXcds;
   // XCDs 0..rem-1 own (per + 1) ids.
-  const int64_t logical = x * per + (x < rem ? x : rem) + l;
-  constexpr int64_t band = 8;
-  const int64_t band_size = band * tiles_j;
-  const int64_t b = logical / band_size, r = logical % band_size;
-  const int64_t rows_here = (b * band + band <= tiles_i) ? band : tiles_i - b * band;
-  *ti = b * band + r % rows_here;
-  *tj = r / rows_here;
+  const uint32_t logical = x * per + (x < rem ? x : rem) + l;
+  constexpr uint32_t band = 8;
+  const uint64_t band_size = band * uint64_t(tiles_j);           // (more than 32 bits: one band)
+  const uint32_t b = band_size > logical ? 0 : logical / uint32_t(band_size);
+  const uint32_t r = logical - b * uint32_t(band_size);
+  const uint32_t rows_here = (b * band + band <= uint32_t(tiles_i)) ? band : uint32_t(tiles_i) - b * band;
+  const uint32_t q = r / rows_here;
+  *ti = b * band + (r - q * rows_here);
+  *tj = q;
+}
+
+// Offset of column j in a row of the result (see the top).  64-bit divisions are routines of more than a
+// hundred instructions: plain rows need none, other results seldom more than 32 bits.
+__device__ __forceinline__ int64_t column_offset(const GemmArgs& a, int64_t j) {
+  if (a.jp >= a.J) return j;
+  if (a.J <= 0x7fffffff) {
+    const uint32_t q = uint32_t(j) / uint32_t(a.jp);
+    return int64_t(q) * (a.I * a.jp) + (uint32_t(j) - q * uint32_t(a.jp));
+  }
+  return (j / a.jp) * (a.I * a.jp) + (j % a.jp);
 }
 
 // The rows [i0, ilim) and columns [j0, jlim) a tile may touch.  Unblocked: tile (ti, tj) starts at
@@ -128,7 +147,7 @@ __device__ __forceinline__ void write_tile(const GemmArgs& a, const TileBox& box
       const int64_t jg = jw + cq * VJ;
       const bool j_ok = jg < box.jlim;
       const int64_t jq = j_ok ? jg : 0;
-      const int64_t jbase = (jq / a.jp) * (a.I * a.jp) + (jq % a.jp);
+      const int64_t jbase = column_offset(a, jq);
       static_for<MI>([&](auto m_) {
         constexpr int m = decltype(m_)::value;
         static_for<NJ>([&](auto n_) {
@@ -243,7 +262,7 @@ __device__ __forceinline__ void write_tile(const GemmArgs& a, const TileBox& box
     constexpr int n = decltype(n_)::value;
     const int64_t j = jw + n * 32 + (lane & 31);
     const bool j_ok = j < box.jlim;
-    const int64_t jbase = (j / a.jp) * (a.I * a.jp) + (j % a.jp);
+    const int64_t jbase = column_offset(a, j);
     static_for<MI>([&](auto m_) {
       constexpr int m = decltype(m_)::value;
       const int64_t ibase = iw + m * 32 + 4 * (lane >> 5);
@@ -299,6 +318,7 @@ __device__ __forceinline__ i32x4 short_row(const uint8_t* row, int64_t Kb) {
 // result is what takes the time.
 template <typename TR, int BM, int BN, int WGM, int WGN, bool SHORT>
 __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a) {
+  request_args(a);
   constexpr int NT = WGM * WGN * 64, D = 2;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
   constexpr int XCH = BM * 8 / NT, YCH = BN * 8 / NT;   // 16-byte pieces per thread per slab
@@ -437,6 +457,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_any_kernel(GemmArgs a)
 enum KsplitLoad { kDirect, kStaged };   // see gemm_nt_ksplit_kernel
 template <typename TR, int NW, KsplitLoad LOAD>
 __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
+  request_args(a);
   constexpr int KST = TR::kStep, P = KST / 32, KS = kSlabBytes / KST;
   constexpr int kOp = 32 * kSlabBytes;                   // bytes of one operand's slab
   constexpr int kWaveBytes = 4 * kOp;                         // two slabs of both operands
@@ -446,7 +467,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t tiles_j = tile_count(a.J, a.bn, 32);
-  const TileBox box = tile_box<32, 32>(a, blockIdx.x / tiles_j, blockIdx.x % tiles_j);
+  const uint32_t row = blockIdx.x / uint32_t(tiles_j);    // (tiles_j is the grid at most)
+  const TileBox box = tile_box<32, 32>(a, row, blockIdx.x - row * uint32_t(tiles_j));
   const int64_t i0 = uniform64(box.i0), j0 = uniform64(box.j0);
   if (i0 >= box.ilim || j0 >= box.jlim) return;          // past the end of a smaller last block
   const int64_t Kb = a.K * TR::kEsz, ldxb = a.ldx * TR::kEsz, ldyb = a.ldy * TR::kEsz;
@@ -566,7 +588,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
   const int64_t i = i0 + (tid >> 3), j = j0 + (tid & 7) * 4;
   if (i >= box.ilim || j >= box.jlim) return;
   if (a.vj >= 4) {
-    const int64_t addr = j / a.jp * (a.I * a.jp) + i * a.jp + j % a.jp;
+    const int64_t addr = column_offset(a, j) + i * a.jp;
     if constexpr (__is_same(typename TR::acc_t, float)) {
       if (a.out_dtype == GS_BF16) {
         if (a.residual) {
@@ -591,7 +613,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
 #pragma unroll
   for (int e = 0; e < 4; ++e)
     if (j + e < box.jlim)
-      store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, (j + e) / a.jp * (a.I * a.jp) + i * a.jp + (j + e) % a.jp,
+      store_result<typename TR::acc_t>(a.out, a.residual, a.out_dtype, column_offset(a, j + e) + i * a.jp,
                                        sum[e], a.relu);
 }
 
@@ -603,6 +625,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_nt_ksplit_kernel(GemmArgs a) {
 
 template <typename TR, int BM, int BN, int WGM, int WGN, int SB, int NS>
 __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_dma_kernel(GemmArgs a) {
+  request_args(a);
   constexpr int NW = WGM * WGN;                   // waves per workgroup
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   static_assert(SB == 64 || SB == 128, "K bytes per slab row");
