@@ -32,6 +32,7 @@
 // images) 29.9 -> 4.8.  Over 620 layers of all sizes 2.2 times faster.
 #pragma once
 #include "conv4_kernel.h"
+#include "conv_tile_schedule.h"
 
 namespace gs {
 
@@ -51,9 +52,10 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   constexpr int G = 16 / ESZ;             // channels per 16-byte cell
   constexpr int CCH = CM * 32 / ESZ;      // channels per chunk
   constexpr int VW = kTileItem, LD = VW * ESZ / 4;        // pixels and dwords of a patch load
-  constexpr int KR = KH * CM, T = KR * KW, PH = IL * S, NQ = (IL - 1) * S + KW;
-  constexpr int GP = IL == 1 && NJ > 1 ? 2 : 1;           // block groups that take turns within a step
-  constexpr int NG = NJ / IL, NSG = NG / GP, STEPS = KR * NSG, SLOTS = NQ * GP;
+  // (ONE: a group has a single chunk and writes no cells in a loop; its schedule is the shortest one)
+  using SC = TileSchedule<ESZ, KH, KW, CM, S, IL, NJ, VW, ONE ? 1 : MAXI>;
+  constexpr int KR = SC::KR, T = KR * KW, PH = IL * S, GP = SC::GP, NG = SC::NG, NSG = SC::NSG;
+  constexpr int STEPS = SC::STEPS, SLOTS = SC::SLOTS, QUOTA = SC::QUOTA;
   constexpr int NBUF = ONE ? 1 : 3;       // patch buffers (ONE: a group has a single chunk)
   constexpr int NW = WO * WP, NT = 64 * NW;
   constexpr bool INT = __is_same(typename TR::acc_t, int32_t);
@@ -238,14 +240,11 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   };
   // Vector loads that go with slot `slot` of a chunk (see the loop below): pieces of the patch at
   // `next_patch`, and taps of chunk `ch`.
-  constexpr int WORK = (VW + G) * MAXI;                        // cells, then loads
-  constexpr int QUOTA = (WORK + STEPS * SLOTS - 2) / (STEPS * SLOTS - 1);
-  static_assert(ONE || VW * MAXI <= QUOTA * (SLOTS * (STEPS - 1) - 1), "the cells are written before the barrier");
   auto slot_loads = [&](const uint8_t* next_patch, Piece (&preg)[MAXI][G], int ch, auto slot_) {
     constexpr int slot = decltype(slot_)::value, step = slot / SLOTS, s = slot % SLOTS;
-    if constexpr (slot > 0 && !ONE)
+    if constexpr (!ONE)
       static_for<QUOTA>([&](auto k_) {
-        constexpr int wk = (slot - 1) * QUOTA + decltype(k_)::value - VW * MAXI;
+        constexpr int wk = SC::piece(slot, decltype(k_)::value) - SC::CELLS;
         if constexpr (wk >= 0 && wk < G * MAXI)
           load_piece(next_patch, preg, std::integral_constant<int, wk / G>{}, std::integral_constant<int, wk % G>{});
       });
@@ -314,9 +313,9 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   i32x4 fr[SLOTS];
   auto request = [&](const uint8_t* pb, auto step_, auto s_) {
     constexpr int step = decltype(step_)::value, q = decltype(s_)::value / GP, gi = step % NSG * GP + decltype(s_)::value % GP;
-    fr[decltype(s_)::value] = *reinterpret_cast<const i32x4*>(pb + fb[gi] + step / NSG * (CM > 1 ? 2 * g.halfb : g.rowp) + (q % PH) * g.php + (q / PH) * 16);
+    if constexpr (SC::used(decltype(s_)::value))
+      fr[decltype(s_)::value] = *reinterpret_cast<const i32x4*>(pb + fb[gi] + step / NSG * (CM > 1 ? 2 * g.halfb : g.rowp) + (q % PH) * g.php + (q / PH) * 16);
   };
-  constexpr int kReads = SLOTS * (STEPS - 1) - (VW * MAXI + QUOTA - 1) / QUOTA;   // fragments requested behind the last cell
   int cur = 0;                                                 // LDS offset of the chunk's buffer
   auto chunk = [&](auto last_, int ch) {
     constexpr bool LAST = decltype(last_)::value;
@@ -336,16 +335,18 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
         if constexpr (step + 1 < STEPS) request(pb, std::integral_constant<int, step + 1>{}, s_);
         else if constexpr (!LAST) request(nb, std::integral_constant<int, 0>{}, s_);
         if constexpr (!LAST) {
-          if constexpr (slot > 0)
-            static_for<QUOTA>([&](auto k_) {
-              constexpr int wk = (slot - 1) * QUOTA + decltype(k_)::value;
-              if constexpr (wk < VW * MAXI)
-                store_cell(nb, preg, std::integral_constant<int, wk / VW>{}, std::integral_constant<int, wk % VW>{});
-            });
+          static_for<QUOTA>([&](auto k_) {
+            constexpr int wk = SC::piece(slot, decltype(k_)::value);
+            if constexpr (wk < SC::CELLS)
+              store_cell(nb, preg, std::integral_constant<int, wk / VW>{}, std::integral_constant<int, wk % VW>{});
+          });
           slot_loads(asrc2, preg, ch + 1, std::integral_constant<int, slot>{});
-          // the cells are in LDS when at most the fragments requested behind them are outstanding
-          if constexpr (step == STEPS - 2 && s == SLOTS - 1)
-            asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(kReads < 15 ? kReads : 15) : "memory");
+          // The cells are in LDS when at most the fragments requested behind them are outstanding (the
+          // counter ends at 15; a request moved in front of its slot's cells or behind them waits for more).
+          if constexpr (slot == SC::BARRIER) {
+            constexpr int reads = SC::reads_behind_cells();
+            asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(reads < 15 ? reads : 15) : "memory");
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
       });

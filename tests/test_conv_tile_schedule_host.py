@@ -1,0 +1,63 @@
+"""The chunk barrier of conv_tile_kernel without a GPU: the order of every built instance is replayed from the
+numbers that the kernel itself is compiled with, and no patch cell may be outstanding behind the barrier's wait."""
+
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+REPLAY = r"""
+#include <cstdio>
+#include "conv_tile_schedule.h"
+using namespace gs;
+// One line: the parameters, the wait's count, then the LDS operations up to the barrier: R a read, W a cell.
+template <int ESZ, int K, int CM, int S, int IL, int NJ, int MAXI> void replay() {
+  using SC = TileSchedule<ESZ, K, K, CM, S, IL, NJ, 4, MAXI>;
+  std::printf("%d %d %d %d %d %d %d ", ESZ, K, S, IL, NJ, MAXI, SC::reads_behind_cells());
+  for (int slot = 0; slot < SC::STEPS * SC::SLOTS; ++slot) {
+    if (SC::used(slot % SC::SLOTS)) std::printf("R");
+    for (int k = 0; k < SC::QUOTA; ++k)
+      if (SC::piece(slot, k) < SC::CELLS) std::printf("W");
+    if (slot == SC::BARRIER) std::printf("|");
+  }
+  std::printf("\n");
+}
+template <int ESZ, int K, int CM, int S, int IL, int NJ> void items() {
+  replay<ESZ, K, CM, S, IL, NJ, 1>();
+  replay<ESZ, K, CM, S, IL, NJ, 2>();
+  if constexpr (NJ <= 2) replay<ESZ, K, CM, S, IL, NJ, 4>();
+}
+template <int ESZ, int K, int CM, int NJ> void strides() {
+  items<ESZ, K, CM, 1, 1, NJ>();
+  items<ESZ, K, CM, 2, 1, NJ>();
+  if constexpr (NJ >= 2) { items<ESZ, K, CM, 1, 2, NJ>(); items<ESZ, K, CM, 2, 2, NJ>(); }
+  if constexpr (NJ >= 4) items<ESZ, K, CM, 1, 4, NJ>();
+}
+template <int ESZ> void all() {
+  strides<ESZ, 1, 4, 4>(); strides<ESZ, 1, 4, 2>(); strides<ESZ, 1, 4, 1>();
+  strides<ESZ, 3, 1, 4>(); strides<ESZ, 3, 1, 2>(); strides<ESZ, 3, 1, 1>();
+  strides<ESZ, 5, 1, 2>(); strides<ESZ, 5, 1, 1>();
+}
+int main() { all<1>(); all<2>(); }
+"""
+
+
+def test_every_cell_is_written_before_the_chunk_barrier(tmp_path):
+    src, exe = tmp_path / "replay.cpp", tmp_path / "replay"
+    src.write_text(REPLAY)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "paper_2105_09377_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+    assert len(lines) == 2 * (2 * (5 * 2 + 4 * 3 + 2 * 3) + 4 * 3 + 2 * 3)
+    for line in lines:
+        esz, k, stride, il, nj, maxi, reads, ops = line.split()
+        before, behind = ops.split("|")
+        assert before.count("W") == 4 * int(maxi) and "W" not in behind, line
+        # A wave's LDS operations complete in order, so a wait for n leaves at most the last n outstanding; the
+        # counter holds 15.  Waiting for fewer than are behind the last cell would only cost time.
+        assert int(reads) == len(before) - 1 - before.rindex("W"), line
+        assert "W" not in before[len(before) - min(int(reads), 15):], line
+        # 3x3 and 5x5 windows use every fragment; two blocks of 1x1 windows at stride 2 use two of three
+        per_step = (int(il) - 1) * int(stride) + int(k)
+        if k != "1" or stride == "1":
+            assert ops.count("R") % per_step == 0, line
