@@ -428,7 +428,8 @@ int glenside_conv2d_direct_packed(const gs_ap* act, const gs_ap* w, const int64_
 int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
                            const int64_t pad[2], const gs_ap* residual, int actfn, gs_ap* out,
                            void* workspace, size_t workspace_bytes, void* stream) {
-  // Validate everything first so that a bad call launches nothing, then run the two halves.
+  // Validate everything first so that a bad call launches nothing, then run the two halves, or one launch that
+  // does the work of both: either way the workspace holds the packed weights afterwards.
   ConvShape cs;
   int st = conv_shape(act, w, stride, pad, &cs);
   if (st) return st;
@@ -439,16 +440,15 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
     return GS_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t wneed = size_t(round_up(int64_t(conv_weight_workspace(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)), 256)) + 256;
-  ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, need > wneed, wneed);
-  // Few channels: the kernel takes the weights as they are.
-  if (conv_is_smallc(act->dtype, cs.C)) {
+  const ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, need > wneed, wneed);
+  // Few channels: the kernel takes the weights as they are and writes the copies on the side.
+  if (conv_is_smallc(act->dtype, cs.C) && int64_t(cs.N) * cs.Ho * cs.Wo > 0) {
     ConvArgs b = a;
     b.wr = w->data;
-    const hipError_t e = launch_conv_smallc(b, true, s);
+    const hipError_t e = launch_conv_smallc(b, workspace, s);
     if (e != hipErrorInvalidValue) return launch_status(e);
   }
-  // Only the copy that the layer's kernel reads is made.
-  const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, s, conv_reads_blocked(a));
+  const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, s);
   if (e != hipSuccess) return launch_status(e);
   return launch_status(launch_conv(a, s));
 }

@@ -296,15 +296,13 @@ size_t conv_smallc_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 // offset in the weight workspace.
 size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
-hipError_t launch_conv_smallc_pack(const void* w, void* wn, int in_dtype, int O, int C, int Kh, int Kw,
+hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, int O, int C, int Kh, int Kw,
                                    hipStream_t s);
-hipError_t launch_conv_smallc(const ConvArgs& a, bool raw, hipStream_t s);   // reads a.wr = natural-order copy; raw: the weights themselves
+// Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there.
+hipError_t launch_conv_smallc(const ConvArgs& a, void* packed, hipStream_t s);
 bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo);   // does the kernel take the layer?
-// only_blocked: the other copies are left out (they must not be read afterwards)
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
-                              hipStream_t s, bool only_blocked = false);
-// Does the kernel that launch_conv picks for the layer read the blocked weight copy alone?
-bool conv_reads_blocked(const ConvArgs& a);
+                              hipStream_t s);
 // Returns hipErrorInvalidValue if no tile configuration fits the LDS for this shape.  With
 // a.ksplit > 1 and a.partial set, kernels that support it split the channel sum (Fig. 6's last
 // blocking rule: partial dot products combined by reduceSum over a pair); others ignore it.

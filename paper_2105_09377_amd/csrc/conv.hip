@@ -34,40 +34,38 @@ static int conv_max_rows_scan(const ConvArgs& a, int64_t M, int HWo, int TP);
 // element e of 16-byte piece i of block (ob, chunk, tap) is
 // w[ob * 32 + i / 2][chunk * CCH + h * G + e][tap], G = elements in 16 bytes, CCH = 2 G,
 // h = (i % 2) ^ (((r >> 2) ^ (r >> 3)) & 1) with r = i / 2 -- the swizzle the consumers'
-// fragment reads undo; rows past O are zero.
+// fragment reads undo; rows past O are zero.  A thread gathers one 16-byte piece, its G elements T_ apart,
+// and writes it to both copies (packing and convolving 512 x 7x7 -> 512, 3x3: 18.3 us, 24.9 with an element per
+// thread and copy).
 template <typename T>
 __global__ void __launch_bounds__(256)
 conv_repack_kernel(const T* __restrict__ w, T* __restrict__ wr, T* __restrict__ wb, int O, int C, int T_,
                    int Cpad) {
-  const int64_t total = wr ? int64_t(O) * T_ * Cpad : 0;
-  for (int64_t f = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; f < total;
-       f += int64_t(gridDim.x) * blockDim.x) {
-    const int c = int(f % Cpad);
-    const int64_t ot = f / Cpad;
-    const int tap = int(ot % T_);
-    const int64_t o = ot / T_;
-    wr[f] = c < C ? w[(o * C + c) * T_ + tap] : T(0);
-  }
-  if (!wb) return;
-  constexpr int G = 16 / int(sizeof(T)), CCH = 2 * G;
-  const int nchunk = C / CCH;
-  // A thread writes one 16-byte piece, its G elements gathered T_ apart: 64 x 64 x 3x3 bf16 4.0 -> 2.6 us
-  // (with the other copy left out; an element per thread and both copies before).
+  constexpr int G = 16 / int(sizeof(T));
   typedef T piece_t __attribute__((ext_vector_type(G)));
-  const int64_t pieces = round_up(O, 32) * T_ * (C / G);
+  const int nchunk = Cpad / (2 * G);
+  const int64_t pieces = (wb ? round_up(O, 32) : int64_t(O)) * T_ * (Cpad / G);
   for (int64_t f = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; f < pieces; f += int64_t(gridDim.x) * blockDim.x) {
-    const int i = int(f % 64);
-    const int64_t blk = f / 64;
-    const int tap = int(blk % T_);
-    const int chunk = int((blk / T_) % nchunk);
-    const int64_t ob = blk / T_ / nchunk;
-    const int r = i >> 1, h = (i & 1) ^ (((r >> 2) ^ (r >> 3)) & 1);
-    const int64_t o = ob * 32 + r;
-    const T* src = w + ((o < O ? o : 0) * C + chunk * CCH + h * G) * T_ + tap;
+    int64_t o;
+    int tap, c0;
+    if (wb) {
+      const int i = int(f % 64), r = i >> 1, h = (i & 1) ^ (((r >> 2) ^ (r >> 3)) & 1);
+      const int64_t blk = f / 64, bt = blk / T_;
+      tap = int(blk - bt * T_);
+      o = bt / nchunk * 32 + r;
+      c0 = (int(bt % nchunk) * 2 + h) * G;
+    } else {
+      const int64_t ot = f / (Cpad / G);
+      c0 = int(f - ot * (Cpad / G)) * G;
+      o = ot / T_;
+      tap = int(ot - o * T_);
+    }
+    const T* src = w + (o < O ? o : 0) * C * T_ + tap;
     piece_t v;
 #pragma unroll
-    for (int e = 0; e < G; ++e) v[e] = o < O ? src[int64_t(e) * T_] : T(0);
-    *reinterpret_cast<piece_t*>(wb + f * G) = v;
+    for (int e = 0; e < G; ++e) v[e] = o < O && c0 + e < C ? src[int64_t(c0 + e) * T_] : T(0);
+    if (wb) *reinterpret_cast<piece_t*>(wb + f * G) = v;
+    if (o < O) *reinterpret_cast<piece_t*>(wr + (o * T_ + tap) * Cpad + c0) = v;
   }
 }
 
@@ -103,28 +101,23 @@ size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw) {
 }
 
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
-                              hipStream_t s, bool only_blocked) {
+                              hipStream_t s) {
   const int Cpad = conv_cpad(in_dtype, C);
   if (int64_t(O) * Kh * Kw * Cpad == 0) return hipSuccess;
-  only_blocked = only_blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw);
-  const int64_t total = round_up(O, 32) * Kh * Kw * Cpad;   // the longer of the kernel's two loops
-  const int64_t b = ceil_div(only_blocked ? total * int64_t(dtype_size(in_dtype)) / 16 : total, 256);
+  if (conv_is_smallc(in_dtype, C)) return launch_conv_smallc_pack(w, wr, in_dtype, O, C, Kh, Kw, s);
+  const int64_t b = ceil_div(round_up(O, 32) * Kh * Kw * Cpad * int64_t(dtype_size(in_dtype)) / 16, 256);
   const dim3 grid(unsigned(b < 65536 ? b : 65536));
   uint8_t* wb = conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
                     ? static_cast<uint8_t*>(wr) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw)
                     : nullptr;
   if (in_dtype == GS_I8)
     hipLaunchKernelGGL((conv_repack_kernel<uint8_t>), grid, dim3(256), 0, s,
-                       static_cast<const uint8_t*>(w), only_blocked ? nullptr : static_cast<uint8_t*>(wr), wb, O, C, Kh * Kw, Cpad);
+                       static_cast<const uint8_t*>(w), static_cast<uint8_t*>(wr), wb, O, C, Kh * Kw, Cpad);
   else
     hipLaunchKernelGGL((conv_repack_kernel<uint16_t>), grid, dim3(256), 0, s,
-                       static_cast<const uint16_t*>(w), only_blocked ? nullptr : static_cast<uint16_t*>(wr),
+                       static_cast<const uint16_t*>(w), static_cast<uint16_t*>(wr),
                        reinterpret_cast<uint16_t*>(wb), O, C, Kh * Kw, Cpad);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && !only_blocked && conv_is_smallc(in_dtype, C))
-    e = launch_conv_smallc_pack(w, static_cast<uint8_t*>(wr) + conv_smallc_weight_offset(in_dtype, O, C, Kh, Kw),
-                                in_dtype, O, C, Kh, Kw, s);
-  return e;
+  return hipGetLastError();
 }
 
 // Host: most patch rows any tile of TP positions needs, or -1 if a tile spans too many images.
@@ -554,7 +547,7 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   if (a.wnat) {                        // fewer channels than a chunk: windows formed as im2col rows in LDS
     ConvArgs b = a;
     b.wr = a.wnat;
-    const hipError_t es = launch_conv_smallc(b, false, s);
+    const hipError_t es = launch_conv_smallc(b, nullptr, s);
     if (es != hipErrorInvalidValue) return es;
   }
   const TilePlan& plan = plan_tiles<TR>(a, g);
@@ -611,15 +604,6 @@ static hipError_t launch_conv_point_t(const ConvArgs& a_in, hipStream_t s) {
 }
 hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s) {
   return a.in_dtype == GS_I8 ? launch_conv_point_t<I8Traits>(a, s) : launch_conv_point_t<Bf16Traits>(a, s);
-}
-
-bool conv_reads_blocked(const ConvArgs& a_in) {
-  ConvArgs a = a_in;
-  if (!a.wblk || conv_is_smallc(a.in_dtype, a.C)) return false;
-  a.ksplit = a.ksplit < 2 || !a.partial ? 1 : a.ksplit;
-  const ConvGeom g = conv_geom(a);
-  if (g.M == 0 || a.O == 0) return false;
-  return (a.in_dtype == GS_I8 ? plan_tiles<I8Traits>(a, g) : plan_tiles<Bf16Traits>(a, g)).shape >= 0;
 }
 
 bool conv_pipelined_takes(const ConvArgs& a_in) {

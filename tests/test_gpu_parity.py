@@ -618,6 +618,28 @@ def test_conv2d_few_channels_many_rows(n, c, h, w, o, kh, kw, pad, dtype, odt):
         assert_parity(got, ref, what=f"{dtype} weights as they are")
 
 
+# conv2d_direct(.., ws) == conv2d_pack_weights(w, ws), then conv2d_direct_packed(.., ws): the workspace holds the same
+# bytes afterwards and goes on serving other batches.  Few channels in both forms and with tasks of two rows, a chunk
+# filled in part, whole chunks, 1x1, output channels past a block of 32 and of 64, an empty batch.
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("n,c,h,w,o,k,s,p", [(1, 3, 8, 8, 4, 3, 1, 0), (2, 3, 40, 44, 70, 7, 2, 3), (41, 3, 77, 80, 64, 7, 4, 3), (3, 9, 12, 11, 130, 5, 1, 2),
+                                             (2, 1, 9, 9, 5, 1, 1, 0), (1, 40, 9, 10, 33, 3, 1, 1), (2, 64, 14, 14, 65, 3, 2, 1), (1, 32, 7, 9, 31, 5, 1, 2),
+                                             (2, 128, 7, 7, 40, 1, 1, 0), (0, 3, 8, 8, 4, 3, 1, 0), (0, 64, 8, 8, 4, 3, 1, 0)])
+def test_conv2d_direct_leaves_packed_weights(n, c, h, w, o, k, s, p, dtype):
+    x, wt = gen(dtype, (n, c, h, w), 8950 + h).to(DEV), gen(dtype, (o, c, k, k), 8960 + o, (c * k * k) ** -0.5).to(DEV)
+    x2 = gen(dtype, (n + 3, c, h, w), 8970 + h)
+    size = gs.conv2d_workspace(x2.to(DEV), wt, (s, s), (p, p))
+    size = max(size, gs.conv2d_workspace(x, wt, (s, s), (p, p)))
+    ws, packed = (torch.full((size,), 0x5a, dtype=torch.uint8, device=DEV) for _ in range(2))
+    gs.conv2d_direct(x, wt, (s, s), (p, p), workspace=ws)
+    gs.conv2d_pack_weights(wt, packed)
+    weights = gs.conv2d_pack_weights(wt).numel()          # without scratch for a split channel sum
+    assert torch.equal(ws[:weights], packed[:weights])
+    got = gs.conv2d_direct_packed(x2.to(DEV), wt, ws, (s, s), (p, p))
+    want = torch.nn.functional.conv2d(x2.double(), wt.cpu().double(), stride=s, padding=p).numpy()
+    assert_parity(got, want.astype(np.int64) if dtype == "i8" else want, what="packed by the call")
+
+
 def test_conv2d_minus_128_and_empty_batch():
     x = torch.full((1, 32, 6, 6), -128, dtype=torch.int8)
     w = torch.full((8, 32, 3, 3), -128, dtype=torch.int8)
