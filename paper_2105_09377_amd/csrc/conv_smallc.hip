@@ -725,7 +725,8 @@ bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw
 
 // `a.wr` must point at the natural-order weight copy, or, with `packed`, at the weights themselves: a call that
 // brings its weights then needs no packing launch in front, and its kernel writes the copies to `packed` on
-// the side.  Returns hipErrorInvalidValue when the shape does not fit (LDS), so that the caller can fall back.
+// the side.  Returns hipErrorInvalidValue when the shape does not fit (LDS), or where packing first is the
+// faster way, so that the caller can fall back.
 template <typename TR>
 static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s) {
   const bool raw = packed != nullptr;
@@ -799,7 +800,16 @@ static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s
   per_cu = per_cu < 1 ? 1 : per_cu > 4 ? 4 : per_cu;
   int64_t grid = int64_t(smallc_num_cus()) * per_cu;
   if (grid > p.tasks) grid = p.tasks;
-  grid = ceil_div(p.tasks, ceil_div(p.tasks, grid));
+  const int64_t per_group = ceil_div(p.tasks, grid);   // tasks of a workgroup
+  grid = ceil_div(p.tasks, per_group);
+  // Weights as they come save the packing launch (1.9 us), but a workgroup reads them element by element, some 13 ns
+  // for each of K at every change of its channel tile, the first time beside its input loads.  Measured over 85
+  // layers, packed first / as they are: 24 images of 6 x 49x71 -> 205, 7x7 (K = 294, four channel tiles, three
+  // tasks) 42.8 / 58.7 us, 2 of 8 x 78x152 -> 441, 5x5 45.8 / 53.1, 2 of 15 x 64x113 -> 13, 5x5 (K = 375) 14.7 /
+  // 15.9; 15 of 2 x 26x27 -> 264, 3x3 (K = 18, five tiles) 24.9 / 23.5, 64 of 3 x 224x224 -> 64, 7x7 stride 2
+  // (K = 147) 66 / 64, 3 x 8x8 -> 4, 3x3 7.2 / 5.8.
+  const int64_t tiles_each = p.otiles < per_group ? p.otiles : per_group;
+  if (raw && (2 * tiles_each - 1) * p.K > 256) return hipErrorInvalidValue;
   // The copies go to workgroups of their own while there is room for them: 3 x 8x8 -> 4, 3x3 5.6 us, 5.8 where
   // the others write them, 5.0 without copies.
   p.groups = unsigned(grid);
