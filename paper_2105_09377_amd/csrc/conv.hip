@@ -18,16 +18,14 @@
 // columns (lanes), which makes the (N,O,H',W') store of the listing coalesced, read weights from
 // the packed copy [o][tap][channel] and form windows out of an LDS patch [row][pixel][channel].
 #include "conv_kernels.h"
+#include "conv_scan.h"
 
 #include <stdint.h>
 
 #include <array>
-#include <map>
 #include <mutex>
 
 namespace gs {
-
-static int conv_max_rows_scan(const ConvArgs& a, int64_t M, int HWo, int TP);
 
 // wr[o][tap][c] = w[o][c][tap] for c < C, zero for C <= c < Cpad.  With `wb` (channel counts
 // that are whole chunks, C == Cpad) also the blocked copy (see conv_blocked_weight_offset):
@@ -121,32 +119,26 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
 }
 
 // Host: most patch rows any tile of TP positions needs, or -1 if a tile spans too many images.
-// The scan over tiles is remembered per shape so that repeated calls cost a map lookup.
+// A scan costs some 15 ns per tile that it looks at: 0.8 us for 64 images of 56x56 in tiles of 256, 46 for 111x113,
+// whose tiles do not repeat within them.  Each thread keeps the last ones (256, by a hash of the shape), which
+// kernels planned anew on every call look up.
 int conv_max_rows(const ConvArgs& a, int64_t M, int HWo, int TP) {
-  static std::mutex mu;
-  static std::map<std::array<int64_t, 7>, int> memo;
-  const std::array<int64_t, 7> key = {M, HWo, a.Wo, a.Sh, a.Ph, a.Kh, TP};
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = memo.find(key);
-    if (it != memo.end()) return it->second;
+  struct Entry {
+    std::array<int64_t, 6> key;
+    int rows;
+    bool set = false;
+  };
+  static thread_local Entry kept[256];
+  const std::array<int64_t, 6> key = {M, HWo, a.Wo, a.Sh, a.Kh, TP};
+  uint64_t h = 14695981039346656037u;
+  for (int64_t v : key) h = (h ^ uint64_t(v)) * 1099511628211u;
+  Entry& e = kept[(h >> 32) & 255];
+  if (!e.set || e.key != key) {
+    e.rows = scan_patch_rows(M, HWo, a.Wo, a.Sh, a.Kh, TP, kMaxSeg);
+    e.key = key;
+    e.set = true;
   }
-  const int r = conv_max_rows_scan(a, M, HWo, TP);
-  std::lock_guard<std::mutex> lock(mu);
-  memo[key] = r;
-  return r;
-}
-
-static int conv_max_rows_scan(const ConvArgs& a, int64_t M, int HWo, int TP) {
-  int best = 0;
-  SegTable t;
-  for (int64_t m0 = 0; m0 < M; m0 += TP) {
-    const int64_t mend = m0 + TP < M ? m0 + TP : M;
-    if ((mend - 1) / HWo - m0 / HWo + 1 > kMaxSeg) return -1;
-    build_segments(int(m0), int(mend), HWo, a.Wo, a.Sh, a.Ph, a.Kh, &t);
-    if (t.rowbase[t.nseg] > best) best = t.rowbase[t.nseg];
-  }
-  return best;
+  return e.rows;
 }
 
 int conv_num_cus() {
@@ -492,8 +484,8 @@ static float gathered_cost(const ConvArgs& a, const ConvGeom& g) {
 }
 
 // How the layer runs on conv_tile_kernel, or shape -1.  A plan depends on the shape alone; each
-// thread keeps the last ones it made (64, by a hash of the shape), since making one costs a few
-// microseconds.
+// thread keeps the last ones it made (64, by a hash of the shape), since making one takes a scan of the tiles
+// (conv_max_rows) in up to five workgroup shapes: 5 us for 56x56, up to 0.5 ms for large planes of odd sizes.
 template <typename TR>
 static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g, bool natural = false) {
   struct Entry {
