@@ -483,6 +483,15 @@ static float gathered_cost(const ConvArgs& a, const ConvGeom& g) {
          0.44f * float(dtype_size(a.out_dtype)) * a.O * m * (a.residual ? 2 : 1);
 }
 
+// Does conv_tile_kernel take the layer, in a workgroup shape that fits?
+template <typename TR>
+static bool tile_takes(const ConvArgs& a, bool natural) {
+  const bool window = a.Kh == a.Kw && (a.Kh == 3 || a.Kh == 5 ||
+                                       (a.Kh == 1 && a.Ph + a.Pw == 0 && a.Cpad * TR::kEsz % (32 * kTileChunks) == 0));
+  return (a.wblk || (natural && a.Kh == 1)) && window && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem && a.C == a.Cpad &&
+         round_up(a.O, 32) * a.Kh * a.Kw * a.Cpad * TR::kEsz < (int64_t(1) << 32);
+}
+
 // How the layer runs on conv_tile_kernel, or shape -1.  A plan depends on the shape alone; each
 // thread keeps the last ones it made (64, by a hash of the shape), since making one takes a scan of the tiles
 // (conv_max_rows) in up to five workgroup shapes: 5 us for 56x56, up to 0.5 ms for large planes of odd sizes.
@@ -502,10 +511,7 @@ static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g, bool nat
   if (e.set && e.key == key) return e.plan;
   TilePlan best;
   best.shape = -1;
-  const bool window = a.Kh == a.Kw && (a.Kh == 3 || a.Kh == 5 ||
-                                       (a.Kh == 1 && a.Ph + a.Pw == 0 && a.Cpad * TR::kEsz % (32 * kTileChunks) == 0));
-  if ((a.wblk || natural) && window && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem && a.C == a.Cpad &&
-      round_up(a.O, 32) * a.Kh * a.Kw * a.Cpad * TR::kEsz < (int64_t(1) << 32)) {
+  if (tile_takes<TR>(a, natural)) {
     float least = 0;
     for (int i = 0; i < kNumTileShapes; ++i) {
       TilePlan p;
@@ -596,6 +602,26 @@ static hipError_t launch_conv_point_t(const ConvArgs& a_in, hipStream_t s) {
 }
 hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s) {
   return a.in_dtype == GS_I8 ? launch_conv_point_t<I8Traits>(a, s) : launch_conv_point_t<Bf16Traits>(a, s);
+}
+
+template <typename TR>
+static hipError_t conv_tile_forced_t(const ConvArgs& a_in, int shape, bool launch, int* out, hipStream_t s) {
+  ConvArgs a = a_in;
+  a.ksplit = 1;
+  const bool natural = !a.wblk;
+  const ConvGeom g = conv_geom(a);
+  if (g.M == 0 || a.O == 0 || shape >= kNumTileShapes || !tile_takes<TR>(a, natural)) return hipErrorInvalidValue;
+  TilePlan p;
+  float cost;
+  if (shape < 0) p = plan_tiles<TR>(a, g, natural);
+  else if (!tile_geometry(a, g, shape, &p, &cost)) return hipErrorInvalidValue;
+  if (p.shape < 0) return hipErrorInvalidValue;
+  out[0] = p.shape; out[1] = p.il; out[2] = p.maxi; out[3] = p.one;
+  return launch ? launch_tiles<TR>(a, p, s) : hipSuccess;
+}
+hipError_t conv_tile_forced(const ConvArgs& a, int shape, bool launch, int* out, hipStream_t s) {
+  return a.in_dtype == GS_I8 ? conv_tile_forced_t<I8Traits>(a, shape, launch, out, s)
+                             : conv_tile_forced_t<Bf16Traits>(a, shape, launch, out, s);
 }
 
 bool conv_pipelined_takes(const ConvArgs& a_in) {

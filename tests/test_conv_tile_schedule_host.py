@@ -1,8 +1,15 @@
-"""The chunk barrier of conv_tile_kernel without a GPU: the order of every built instance is replayed from the
-numbers that the kernel itself is compiled with, and no patch cell may be outstanding behind the barrier's wait."""
+"""conv_tile_kernel without a GPU.  The chunk barrier: the order of every built instance is replayed from the
+numbers that the kernel itself is compiled with, and no patch cell may be outstanding behind the barrier's wait.
+The planner: every built instance is reached, and no other."""
 
 import os
+import random
 import subprocess
+
+import pytest
+
+import tile_instances
+from paper_2105_09377_amd import binding as gs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -61,3 +68,25 @@ def test_every_cell_is_written_before_the_chunk_barrier(tmp_path):
         per_step = (int(il) - 1) * int(stride) + int(k)
         if k != "1" or stride == "1":
             assert ops.count("R") % per_step == 0, line
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+def test_every_instance_has_a_layer(dtype):
+    for k, natural in ((1, False), (1, True), (3, False), (5, False)):
+        for shape in tile_instances.SHAPES:
+            assert set(tile_instances.layers(dtype, k, natural, shape)) == tile_instances.built(dtype, k, shape), (k, natural, shape)
+
+
+def test_the_planner_picks_built_instances():
+    rng, seen = random.Random(8), set()
+    for _ in range(1500):
+        dtype, k, s = rng.choice(["bf16", "i8"]), rng.choice([1, 3, 5]), rng.choice([1, 2])
+        code, unit = (gs.GS_I8, 32) if dtype == "i8" else (gs.GS_BF16, 16)
+        c = unit * (4 if k == 1 else 1) * rng.randint(1, 8)
+        x = tile_instances.ap((rng.choice([1, 2, 7, 32]), c, rng.randint(k, 112), rng.randint(k, 112)), 1, code)
+        w = tile_instances.ap((16 * rng.randint(1, 32), c, k, k), 1, code)
+        st, (shape, *instance) = tile_instances.call(x, w, s, k // 2, None, 0, None, 0x10000, -1, None)
+        if st == gs.GS_OK:
+            seen.add(shape)
+            assert (s, *instance) in tile_instances.built(dtype, k, shape)
+    assert seen == set(tile_instances.SHAPES)

@@ -14,6 +14,7 @@ from oracle import brute
 from oracle import programs as pg
 from paper_2105_09377_amd import binding as gs
 from paper_2105_09377_amd import synth
+import tile_instances
 from helpers import assert_parity, fp8_slack, to_oracle
 
 pytestmark = pytest.mark.gpu
@@ -550,9 +551,10 @@ def test_conv2d_few_channels_random_shapes(case):
     assert_parity(got, want, what=str(case))
 
 
-# Edges of conv_tile_kernel: every workgroup shape; widths that allow four, two and no interleaved blocks;
-# planes of which a tile holds several or none, whose ends cut a 16-byte store; channel counts whose chunks
-# the groups of a channel sum divide, do not divide, or do not all get; channel tiles cut short.
+# Edges of conv_tile_kernel in the instances that the cost model picks: planes of which a tile holds several or
+# none, whose ends cut a 16-byte store; channel counts whose chunks the groups of a channel sum divide, do not
+# divide, or do not all get; channel tiles cut short; rows too short for it, which take another kernel.
+# test_conv_tile_instances takes every instance.
 CONV_TILE_CASES = [
     # k, n, c (32-byte chunks), h, w, o, stride, pad
     (3, 1, 1, 1, 4, 1, 1, 1), (3, 3, 2, 4, 5, 31, 1, 1), (3, 70, 3, 2, 4, 33, 1, 1), (3, 1, 4, 56, 56, 64, 1, 1), (3, 2, 5, 9, 11, 65, 2, 0),
@@ -590,6 +592,34 @@ def test_conv2d_tiles(case, dtype, odt):
             gs.conv2d_im2col(x, wt, (s, s), (p, p), **how)
             assert_parity(out, ref, what=f"{dtype} {case} im2col")
         assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
+
+
+# Every built instance of conv_tile_kernel, on the smallest layer that the planner puts there: workgroup shape,
+# window, stride, interleaved blocks (widths that are multiples of four, two, or neither), patch items per thread (up
+# to rows of some 2000 pixels), one chunk per group or several, packed weights or the listing's own.
+@pytest.mark.parametrize("shape", tile_instances.SHAPES)
+@pytest.mark.parametrize("k,natural", [(1, False), (1, True), (3, False), (5, False)])
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+def test_conv_tile_instances(dtype, k, natural, shape):
+    layers = tile_instances.layers(dtype, k, natural, shape)
+    assert set(layers) == tile_instances.built(dtype, k, shape)
+    for (s, *instance), (n, c, h, w, o, p) in layers.items():
+        cfg = synth.conv_layer(n, c, h, w, o, k, s, p, dtype, 9100 + h + w)
+        x, wt = cfg["x"].to(DEV), cfg["w"].to(DEV)
+        want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p)
+        packed = gs.conv2d_pack_weights(wt, for_input=(x, (s, s), (p, p)))
+        for odt, with_res in ((torch.int32, False), (torch.int32, True)) if dtype == "i8" else ((torch.bfloat16, False), (torch.float32, True)):
+            res = gen("i32" if dtype == "i8" else "f32", tuple(want.shape), 9200 + w) if with_res else None
+            buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
+            out = buf[256:256 + want.numel()].view(want.shape)
+            rd = None if res is None else res.to(DEV)
+            st, plan = tile_instances.call(gs.make_ap(x, 1), gs.make_ap(wt, 1), s, p, None if rd is None else gs.make_ap(rd, 4),
+                                           gs.GS_ACT_RELU if with_res else gs.GS_ACT_NONE, gs.make_ap(out, 4),
+                                           None if natural else packed.data_ptr(), shape, gs._stream(x))
+            assert (st, plan) == (gs.GS_OK, (shape, *instance))
+            ref = want if res is None else (want + res.double()).clamp_min(0)
+            assert_parity(out, ref.numpy().astype(np.int64) if dtype == "i8" else ref.numpy(), what=f"{plan} {(n, c, h, w)} stride {s}")
+            assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
 # Few channels and many output rows: tasks of two rows (conv_rows_kernel).  Odd row counts, rows cut inside a
