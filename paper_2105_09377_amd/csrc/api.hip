@@ -456,7 +456,7 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
 // For tests, not part of the interface: one instance of conv_tile_kernel (conv_tile_forced).  `packed`: from
 // glenside_conv2d_pack_weights, or null for 1x1 weights in the listing's order.  `out` null: only planned, on the host.
 int gs_test_conv_tile(const gs_ap* act, const gs_ap* w, const int64_t stride[2], const int64_t pad[2], const gs_ap* residual,
-                      int actfn, gs_ap* out, void* packed, int shape, int plan[4], void* stream) {
+                      int actfn, gs_ap* out, void* packed, int way, int plan[5], void* stream) {
   ConvShape cs;
   int st = conv_shape(act, w, stride, pad, &cs);
   if (st) return st;
@@ -472,7 +472,7 @@ int gs_test_conv_tile(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
     a.wr = w->data;
     a.wblk = nullptr;
   }
-  return launch_status(conv_tile_forced(a, shape, out != nullptr, plan, static_cast<hipStream_t>(stream)));
+  return launch_status(conv_tile_forced(a, way, out != nullptr, plan, static_cast<hipStream_t>(stream)));
 }
 
 }  // extern "C"

@@ -307,10 +307,10 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
 // a.ksplit > 1 and a.partial set, kernels that support it split the channel sum (Fig. 6's last
 // blocking rule: partial dot products combined by reduceSum over a pair); others ignore it.
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
-// For tests: the layer on conv_tile_kernel in workgroup shape `shape` (below zero: the one that the cost model
-// picks), whether or not a call would go there; only planned unless `launch`.  a.wblk null: weights in the listing's
-// order (a.wr).  out: shape, interleaved blocks, patch items per thread, a single chunk per group.
-hipError_t conv_tile_forced(const ConvArgs& a, int shape, bool launch, int* out, hipStream_t s);
+// For tests: the layer on conv_tile_kernel cut in way `way` (tile_way in conv.hip; below zero: the one that the cost
+// model picks), whether or not a call would go there; only planned unless `launch`.  a.wblk null: weights in the listing's
+// order (a.wr).  out: shape, interleaved blocks, patch items per thread, a single chunk per group, positions of a tile.
+hipError_t conv_tile_forced(const ConvArgs& a, int way, bool launch, int* out, hipStream_t s);
 // 1x1 windows without padding on unpacked weights (a.wr), where a kernel takes them: hipErrorInvalidValue otherwise.
 hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s);
 // Split the channel sum of this shape?  Returns 1, 2 or 4 (host heuristic: few tiles, many chunks).

@@ -399,10 +399,11 @@ static int tile_positions(int64_t M, int n_ot, int Wo, int tp) {
   return tps;
 }
 
-// The layer in workgroup shape `shape`: false where it does not fit (LDS, patch items per thread).
-static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, TilePlan* p, float* cost) {
+// The layer in workgroup shape `shape` and tiles of `tps` positions, `whole`: whole output rows; false where it does
+// not fit (LDS, patch items per thread).
+static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, int tps, bool whole, TilePlan* p, float* cost) {
   const TileShape sh = kTileShapes[shape];
-  const int tp = 32 * sh.nj * sh.wp, to = 32 * sh.wo, S = a.Sh, threads = 64 * sh.wo * sh.wp;
+  const int to = 32 * sh.wo, S = a.Sh, threads = 64 * sh.wo * sh.wp;
   const bool point = a.Kh == 1;        // patch rows are output rows, several chunks at a time
   const int cm = point ? kTileChunks : 1;
   p->shape = shape;
@@ -412,7 +413,7 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, Tile
   if (sh.ks == 1 && sh.nj >= 4 && S == 1 && a.Wo % 4 == 0) p->il = 4;
   else if (sh.ks == 1 && sh.nj >= 2 && a.Wo % 2 == 0) p->il = 2;
   const int n_ot = int(ceil_div(a.O, to));
-  g.tps = tile_positions(g.M, n_ot, a.Wo, tp);
+  g.tps = tps;
   ConvArgs r = a;
   if (point) r.Sh = 1;
   const int max_rows = conv_max_rows(r, g.M, g.HWo, g.tps);
@@ -452,7 +453,7 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, Tile
   const TileCost& c = kTileCost[a.Kh / 2][shape];
   const int group = a.in_dtype == GS_I8 || a.out_dtype == GS_F32 ? 4 : 8;     // positions of a 16-byte store
   const int64_t rows = ceil_div(g.tps, a.Wo);
-  const float per_thread = point ? float(2 * cm * (rows + 1) * ceil_div(a.W, kTileItem)) / threads
+  const float per_thread = point ? float(2 * cm * (whole ? rows : rows + 1) * ceil_div(a.W, kTileItem)) / threads
                                  : float((rows * S + a.Kh) * a.W) / (2 * threads);
   const float chunk = 1 + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
   const float store = c.store * (g.HWo % group ? 1 + c.cut : 1.0f);
@@ -461,6 +462,21 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, Tile
   const float by_work = alone + busy * float(ceil_div(tiles, 256) - 1);
   *cost = c.base + (by_rounds > by_work ? by_rounds : by_work);
   return true;
+}
+
+// Ways to cut a layer: every workgroup shape with the positions of tile_positions, then, for 1x1 windows, with
+// whole output rows.  Those stage the whole rows that a tile touches and nothing around them, so that a tile
+// that ends with a row stages no pixel in vain: 40 images of 94x94 x 128 bytes -> 16 in tiles of 120 positions 77 us,
+// of 94 26 (31 in the producer / consumer kernel).  Over 211 layers of more than 8 us the cheaper cut is 1.33 times
+// faster than the first kind alone, 6 layers lose 3 to 15 %.
+constexpr int kTileWays = 2 * kNumTileShapes;
+static bool tile_way(const ConvArgs& a, const ConvGeom& g, int way, TilePlan* p, float* cost) {
+  const int shape = way % kNumTileShapes;
+  const TileShape sh = kTileShapes[shape];
+  const int tp = 32 * sh.nj * sh.wp, tps = tile_positions(g.M, int(ceil_div(a.O, 32 * sh.wo)), a.Wo, tp);
+  if (way == shape) return tile_geometry(a, g, shape, tps, false, p, cost);
+  const int whole = tp / a.Wo * a.Wo;
+  return a.Kh == 1 && whole > 0 && whole != tps && tile_geometry(a, g, shape, whole, true, p, cost);
 }
 
 // The same for the producer / consumer kernel (290 layers, mean error 14 %).
@@ -474,9 +490,10 @@ static float pipelined_cost(const ConvArgs& a, const ConvGeom& g) {
          (a.ksplit > 1 ? 3.59f : 0.0f);
 }
 
-// A 1x1 window's matrix gathered and multiplied by the dense kernels (246 layers, mean error 22 %; what
-// counts is that it is the faster way for large ones: 128 images of 28x28 x 512 -> 512 146 us against
-// 203).  In MB and MFLOP.
+// A 1x1 window's matrix gathered and multiplied by the dense kernels (fitted to 246 layers; mean error 28 % over 500
+// others).  What counts is that it is the faster way for large ones: 128 images of 28x28 x 512 -> 512 142 us
+// against 165.  Few channels and many results are where it errs most: 12 images of 103x72 x 64 -> 473 go to the
+// tiles, 61 us against 35.  In MB and MFLOP.
 static float gathered_cost(const ConvArgs& a, const ConvGeom& g) {
   const float esz = float(dtype_size(a.in_dtype)), m = float(g.M) * 1e-6f;
   return 7.7f + 0.27f * esz * a.C * (m + float(a.N) * a.H * a.W * 1e-6f) + 0.00072f * esz * a.C * a.O * m +
@@ -494,7 +511,7 @@ static bool tile_takes(const ConvArgs& a, bool natural) {
 
 // How the layer runs on conv_tile_kernel, or shape -1.  A plan depends on the shape alone; each
 // thread keeps the last ones it made (64, by a hash of the shape), since making one takes a scan of the tiles
-// (conv_max_rows) in up to five workgroup shapes: 5 us for 56x56, up to 0.5 ms for large planes of odd sizes.
+// (conv_max_rows) in up to five workgroup shapes: 5 us for 56x56, up to 0.5 ms for large planes of odd sizes (1x1: twice that).
 template <typename TR>
 static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g, bool natural = false) {
   struct Entry {
@@ -513,10 +530,10 @@ static const TilePlan& plan_tiles(const ConvArgs& a, const ConvGeom& g, bool nat
   best.shape = -1;
   if (tile_takes<TR>(a, natural)) {
     float least = 0;
-    for (int i = 0; i < kNumTileShapes; ++i) {
+    for (int i = 0; i < kTileWays; ++i) {
       TilePlan p;
       float cost;
-      if (tile_geometry(a, g, i, &p, &cost) && (best.shape < 0 || cost < least)) {
+      if (tile_way(a, g, i, &p, &cost) && (best.shape < 0 || cost < least)) {
         best = p;
         least = cost;
       }
@@ -605,23 +622,23 @@ hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s) {
 }
 
 template <typename TR>
-static hipError_t conv_tile_forced_t(const ConvArgs& a_in, int shape, bool launch, int* out, hipStream_t s) {
+static hipError_t conv_tile_forced_t(const ConvArgs& a_in, int way, bool launch, int* out, hipStream_t s) {
   ConvArgs a = a_in;
   a.ksplit = 1;
   const bool natural = !a.wblk;
   const ConvGeom g = conv_geom(a);
-  if (g.M == 0 || a.O == 0 || shape >= kNumTileShapes || !tile_takes<TR>(a, natural)) return hipErrorInvalidValue;
+  if (g.M == 0 || a.O == 0 || way >= kTileWays || !tile_takes<TR>(a, natural)) return hipErrorInvalidValue;
   TilePlan p;
   float cost;
-  if (shape < 0) p = plan_tiles<TR>(a, g, natural);
-  else if (!tile_geometry(a, g, shape, &p, &cost)) return hipErrorInvalidValue;
+  if (way < 0) p = plan_tiles<TR>(a, g, natural);
+  else if (!tile_way(a, g, way, &p, &cost)) return hipErrorInvalidValue;
   if (p.shape < 0) return hipErrorInvalidValue;
-  out[0] = p.shape; out[1] = p.il; out[2] = p.maxi; out[3] = p.one;
+  out[0] = p.shape; out[1] = p.il; out[2] = p.maxi; out[3] = p.one; out[4] = p.g.tps;
   return launch ? launch_tiles<TR>(a, p, s) : hipSuccess;
 }
-hipError_t conv_tile_forced(const ConvArgs& a, int shape, bool launch, int* out, hipStream_t s) {
-  return a.in_dtype == GS_I8 ? conv_tile_forced_t<I8Traits>(a, shape, launch, out, s)
-                             : conv_tile_forced_t<Bf16Traits>(a, shape, launch, out, s);
+hipError_t conv_tile_forced(const ConvArgs& a, int way, bool launch, int* out, hipStream_t s) {
+  return a.in_dtype == GS_I8 ? conv_tile_forced_t<I8Traits>(a, way, launch, out, s)
+                             : conv_tile_forced_t<Bf16Traits>(a, way, launch, out, s);
 }
 
 bool conv_pipelined_takes(const ConvArgs& a_in) {

@@ -85,8 +85,20 @@ def test_the_planner_picks_built_instances():
         c = unit * (4 if k == 1 else 1) * rng.randint(1, 8)
         x = tile_instances.ap((rng.choice([1, 2, 7, 32]), c, rng.randint(k, 112), rng.randint(k, 112)), 1, code)
         w = tile_instances.ap((16 * rng.randint(1, 32), c, k, k), 1, code)
-        st, (shape, *instance) = tile_instances.call(x, w, s, k // 2, None, 0, None, 0x10000, -1, None)
+        st, (shape, *instance, _positions) = tile_instances.call(x, w, s, k // 2, None, 0, None, 0x10000, -1, None)
         if st == gs.GS_OK:
             seen.add(shape)
             assert (s, *instance) in tile_instances.built(dtype, k, shape)
     assert seen == set(tile_instances.SHAPES)
+
+
+@pytest.mark.parametrize("natural", [False, True])
+@pytest.mark.parametrize("dtype,n,c,h,w,o,s", [("i8", 40, 128, 94, 94, 16, 1), ("bf16", 94, 64, 56, 98, 27, 1), ("bf16", 41, 64, 96, 104, 336, 2),
+                                               ("i8", 48, 128, 79, 79, 50, 1)])
+def test_wide_planes_of_1x1_windows_are_cut_at_row_ends(dtype, n, c, h, w, o, s, natural):
+    """Whole rows are staged: a tile that ends within one stages up to three times the pixels that it multiplies."""
+    code = gs.GS_I8 if dtype == "i8" else gs.GS_BF16
+    st, plan = tile_instances.call(tile_instances.ap((n, c, h, w), 1, code), tile_instances.ap((o, c, 1, 1), 1, code), s, 0, None, 0,
+                                   None, None if natural else 0x10000, -1, None)
+    assert natural or st == gs.GS_OK        # (in the listing's order the gathered matrix may be the faster way)
+    assert st != gs.GS_OK or plan[4] % ((w - 1) // s + 1) == 0

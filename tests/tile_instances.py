@@ -19,13 +19,13 @@ def ap(shape, n_access, dtype, data=0x10000):
     return a
 
 
-def call(x, w, stride, pad, residual, act, out, packed, shape, stream):
-    """(status, (shape, interleaved blocks, items per thread, a single chunk per group))."""
-    plan = (ctypes.c_int * 4)()
+def call(x, w, stride, pad, residual, act, out, packed, way, stream):
+    """(status, (shape, interleaved blocks, items per thread, a single chunk per group, positions of a tile))."""
+    plan = (ctypes.c_int * 5)()
     pair = lambda v: (ctypes.c_int64 * 2)(v, v)
     ref = lambda t: ctypes.byref(t) if t is not None else None
     st = gs.lib().gs_test_conv_tile(ref(x), ref(w), pair(stride), pair(pad), ref(residual), act, ref(out),
-                                    ctypes.c_void_p(packed), shape, plan, ctypes.c_void_p(stream))
+                                    ctypes.c_void_p(packed), way, plan, ctypes.c_void_p(stream))
     return st, tuple(plan)
 
 
@@ -43,7 +43,7 @@ def built(dtype, k, shape):
 
 @functools.lru_cache(maxsize=None)
 def layers(dtype, k, natural, shape):
-    """Instance -> the smallest layer (n, c, h, w, o, pad) among the candidates that the planner puts there."""
+    """Instance -> the way to cut it and the smallest layer (n, c, h, w, o, pad) among the candidates that lands there."""
     found = {}
     unit, code = (32, gs.GS_I8) if dtype == "i8" else (16, gs.GS_BF16)
     steps = 4 if k == 1 else 1          # chunks go to 1x1 windows four at a time
@@ -56,8 +56,9 @@ def layers(dtype, k, natural, shape):
                 for s in (1, 2):
                     size = n * h * w * chunks
                     x, wt = ap((n, steps * chunks * unit, h, w), 1, code), ap((40, steps * chunks * unit, k, k), 1, code)
-                    st, plan = call(x, wt, s, k // 2, None, 0, None, None if natural else 0x10000, shape, None)
-                    key = (s, *plan[1:])
-                    if st == gs.GS_OK and (key not in found or size < found[key][0]):
-                        found[key] = (size, (n, steps * chunks * unit, h, w, 40, k // 2))
-    return {key: layer for key, (_size, layer) in found.items()}
+                    for way in (shape, shape + len(SHAPES)):      # the second: tiles of whole output rows (1x1 windows)
+                        st, plan = call(x, wt, s, k // 2, None, 0, None, None if natural else 0x10000, way, None)
+                        key = (s, *plan[1:4])
+                        if st == gs.GS_OK and (key not in found or size < found[key][0]):
+                            found[key] = (size, way, (n, steps * chunks * unit, h, w, 40, k // 2))
+    return {key: (way, layer) for key, (_size, way, layer) in found.items()}
