@@ -52,7 +52,6 @@ struct SmallCArgs {
   int otiles;       // 64-channel tiles
   int64_t tasks;    // N * Ho * xtiles * otiles
   int vec_ok;       // input rows are whole 16-byte vectors
-  int raw;          // a.wr is the listing's ((O),(C,Kh,Kw)) tensor itself, not one of the packed copies
   uint32_t dr_mask[4];   // row-window form: keeps the first Kw elements of a 16-byte window
   FastDiv dvpr, dW, dhalo, dKh, dT, dKw, dchunk;
   FastDiv dkh2, dxt, dpairs;   // conv_rows_kernel: Kh + Sh, position tiles, pairs of output rows
@@ -62,8 +61,8 @@ constexpr int kSmallCBatch = 4;   // 16-byte vectors a thread stages per task
 constexpr int kSmallCThreads = 512;
 
 // Thread `first` of `step` writes its share of the 16-byte pieces, all copies in one loop: a thread has one
-// latency to wait for where there are threads enough (3 x 8x8 -> 4, 3x3 in bytes, the whole call: 5.0 us without
-// copies, 5.8 with this, 6.5 with one loop after the other).  I: an index type that holds all copies' element counts plus step.
+// latency to wait for where there are threads enough (3 x 8x8 -> 4, 3x3 in bytes, the whole call, all workgroups
+// writing: 5.0 us without copies, 5.8 with this, 6.5 with one loop after the other).  I: an index type that holds all copies' element counts plus step.
 template <typename T, typename I>
 __device__ __forceinline__ void write_copies(const T* __restrict__ w, const SmallCCopies& c, I first, I step) {
   constexpr int G = 16 / int(sizeof(T));
@@ -103,7 +102,9 @@ __device__ __forceinline__ void write_copies(const T* __restrict__ w, const Smal
   }
 }
 
-template <typename TR, bool DR>
+// RAW: a.wr is the listing's ((O),(C,Kh,Kw)) tensor itself, not one of the packed copies, which the kernel writes on
+// the side (a kernel of its own: with a run-time branch the other one took up to 0.3 us longer).
+template <typename TR, bool DR, bool RAW>
 __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs p) {
   constexpr int NT = kSmallCThreads;
   using T = typename std::conditional<TR::kEsz == 1, uint8_t, uint16_t>::type;
@@ -128,11 +129,12 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
   const int halo = p.pitch - a.W;
   const bool vec_ok = p.vec_ok != 0;
 
-  // Workgroup b runs on XCD b % 8.  Within each round of p.groups tasks an XCD takes a contiguous
+  // Workgroup b runs on XCD b % 8.  Within each round of `groups` tasks an XCD takes a contiguous
   // run of them, so that the input rows shared by neighbouring output rows meet in one L2.
+  const unsigned groups = RAW ? p.groups : gridDim.x;
   int64_t task = blockIdx.x;
-  if (p.groups % 8 == 0) task = int64_t(blockIdx.x % 8) * (p.groups / 8) + blockIdx.x / 8;
-  const bool aside = blockIdx.x >= p.groups;
+  if (groups % 8 == 0) task = int64_t(blockIdx.x % 8) * (groups / 8) + blockIdx.x / 8;
+  const bool aside = RAW && blockIdx.x >= groups;
   if (!aside && task >= p.tasks) return;
   // task -> (o tile, n, x, position tile): the channel tile changes slowest so that a workgroup
   // almost never reloads its weights
@@ -184,13 +186,15 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
     }
   };
   if (vec_ok && !aside) issue_loads(task);
-  if (aside || (p.raw && gridDim.x == p.groups))       // (the latter while the loads are on their way)
-    write_copies(static_cast<const T*>(a.wr), p.copies, (blockIdx.x - (aside ? p.groups : 0)) * unsigned(NT) + unsigned(tid),
-                 (aside ? gridDim.x - p.groups : p.groups) * unsigned(NT));
-  if (aside) return;
+  if constexpr (RAW) {
+    if (aside || gridDim.x == groups)                  // (the latter while the loads are on their way)
+      write_copies(static_cast<const T*>(a.wr), p.copies, (blockIdx.x - (aside ? groups : 0)) * unsigned(NT) + unsigned(tid),
+                   (aside ? gridDim.x - groups : groups) * unsigned(NT));
+    if (aside) return;
+  }
 
   int cur_ot = -1;
-  for (; task < p.tasks; task += p.groups) {
+  for (; task < p.tasks; task += groups) {
     int ot, n, ho, xt;
     decode(task, &ot, &n, &ho, &xt);
     const int y0 = xt * 128;
@@ -199,7 +203,7 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
     if (ot != cur_ot) {                                // weight tile: rows past O and columns past K are zero
       cur_ot = ot;
       const T* wsrc = static_cast<const T*>(a.wr);     // ((O rounded up to 64),(Kp)), zero padded
-      if (p.raw) {                                     // eight threads to a row, element by element
+      if constexpr (RAW) {                             // eight threads to a row, element by element
         const int r = tid >> 3, o = ot * 64 + r;
         const T* row = wsrc + int64_t(o < a.O ? o : 0) * p.K;
         for (int k = tid & 7; k < p.Kp; k += 8) {
@@ -208,11 +212,12 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
           const bool in = o < a.O && (DR ? k / EPV < nrows && k % EPV < a.Kw : k < p.K);
           *reinterpret_cast<T*>(wl + r * p.wpb + k * ESZ) = in ? row[at] : T(0);
         }
-      } else
-      for (int id = tid; id < 64 * (p.Kp / EPV); id += NT) {
-        const int r = id / (p.Kp / EPV), v = id - r * (p.Kp / EPV);
-        *reinterpret_cast<i32x4*>(wl + r * p.wpb + v * 16) =
-            *reinterpret_cast<const i32x4*>(wsrc + (int64_t(ot) * 64 + r) * p.Kp + v * EPV);
+      } else {
+        for (int id = tid; id < 64 * (p.Kp / EPV); id += NT) {
+          const int r = id / (p.Kp / EPV), v = id - r * (p.Kp / EPV);
+          *reinterpret_cast<i32x4*>(wl + r * p.wpb + v * 16) =
+              *reinterpret_cast<const i32x4*>(wsrc + (int64_t(ot) * 64 + r) * p.Kp + v * EPV);
+        }
       }
     }
     // -- stage the input rows (c, dx): image row ho*Sh + dx - Ph of channel c
@@ -244,7 +249,7 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
       }
     }
     __syncthreads();
-    if (vec_ok && task + p.groups < p.tasks) issue_loads(task + p.groups);
+    if (vec_ok && task + groups < p.tasks) issue_loads(task + groups);
     // -- gather the [position][k] tile: item = (position, 16-byte chunk of k)
     if constexpr (!DR) {
       const int nchunk = p.Kp / EPV;
@@ -376,7 +381,7 @@ __global__ void __launch_bounds__(kSmallCThreads) conv_smallc_kernel(SmallCArgs 
 // a lane then holds four consecutive positions of a channel, which reach the staging rows as 16-byte
 // LDS stores and memory as 16 bytes per lane.  Two workgroups per compute unit take turns between
 // LDS, matrix unit and memory.
-template <typename TR>
+template <typename TR, bool RAW>
 __global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs p) {
   constexpr int NT = kSmallCThreads;
   using T = typename std::conditional<TR::kEsz == 1, uint8_t, uint16_t>::type;
@@ -397,10 +402,11 @@ __global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs
   const int vpr = a.W * ESZ / 16, nvec = nrows * vpr;
   const int halo = p.pitch - a.W;
 
-  // Within each round of p.groups tasks an XCD takes a contiguous run of them (see conv_smallc_kernel).
+  // Within each round of `groups` tasks an XCD takes a contiguous run of them (see conv_smallc_kernel).
+  const unsigned groups = RAW ? p.groups : gridDim.x;
   int64_t task = blockIdx.x;
-  if (p.groups % 8 == 0) task = int64_t(blockIdx.x % 8) * (p.groups / 8) + blockIdx.x / 8;
-  const bool aside = blockIdx.x >= p.groups;
+  if (groups % 8 == 0) task = int64_t(blockIdx.x % 8) * (groups / 8) + blockIdx.x / 8;
+  const bool aside = RAW && blockIdx.x >= groups;
   if (!aside && task >= p.tasks) return;
   const int64_t per_o = p.tasks / p.otiles;
   const int pairs = (a.Ho + 1) / 2;
@@ -438,17 +444,19 @@ __global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs
     }
   };
   if (p.vec_ok && !aside) issue_loads(task);
-  if (aside || (p.raw && gridDim.x == p.groups))         // (the latter while the loads are on their way)
-    write_copies(static_cast<const T*>(a.wr), p.copies, (blockIdx.x - (aside ? p.groups : 0)) * unsigned(NT) + unsigned(tid),
-                 (aside ? gridDim.x - p.groups : p.groups) * unsigned(NT));
-  if (aside) return;
+  if constexpr (RAW) {
+    if (aside || gridDim.x == groups)                    // (the latter while the loads are on their way)
+      write_copies(static_cast<const T*>(a.wr), p.copies, (blockIdx.x - (aside ? groups : 0)) * unsigned(NT) + unsigned(tid),
+                   (aside ? gridDim.x - groups : groups) * unsigned(NT));
+    if (aside) return;
+  }
 
   const int pb = wave & 3, rr = wave >> 2;               // position block, row of the task
   const int half = lane >> 5;
   const i32x4 keep = {int(p.dr_mask[0]), int(p.dr_mask[1]), int(p.dr_mask[2]), int(p.dr_mask[3])};
   const int ksteps = p.Kp * ESZ / 32;
   int cur_ot = -1;
-  for (; task < p.tasks; task += p.groups) {
+  for (; task < p.tasks; task += groups) {
     int ot, n, ho, xt;
     decode(task, &ot, &n, &ho, &xt);
     const int y0 = xt * 128;
@@ -457,7 +465,7 @@ __global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs
     if (ot != cur_ot) {                                  // weights: rows past O and columns past the window are zero
       cur_ot = ot;
       const T* wsrc = static_cast<const T*>(a.wr);       // ((O rounded up to 64),(Kp)), zero padded; raw: ((O),(C,Kh,Kw))
-      if (p.raw) {                                       // eight threads to a row, element by element
+      if constexpr (RAW) {                               // eight threads to a row, element by element
         const int r = tid >> 3, o = ot * 64 + r;
         const T* row = wsrc + int64_t(o < a.O ? o : 0) * p.K;
         for (int k = tid & 7; k < p.Kp; k += 8) {
@@ -498,7 +506,7 @@ __global__ void __launch_bounds__(kSmallCThreads, 4) conv_rows_kernel(SmallCArgs
       }
     }
     lds_barrier();
-    if (p.vec_ok && task + p.groups < p.tasks) issue_loads(task + p.groups);
+    if (p.vec_ok && task + groups < p.tasks) issue_loads(task + groups);
     if (pb * 32 >= npos || ho + rr >= a.Ho) continue;    // uniform; the barriers are at the loop's head
     // -- multiply: K step ks holds window rows 2 ks and 2 ks + 1 (c, dx); lanes past the last position
     // read the last position's windows and are not stored
@@ -753,7 +761,6 @@ static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s
   p.XO = l.XO;
   p.pitch = l.pitch;
   p.tile_bytes = int(l.tile_bytes);
-  p.raw = raw;
   int64_t elements = 0;
   if (raw) {
     p.copies = smallc_copies(packed, a.in_dtype, a.O, a.C, a.Kh, a.Kw, &elements);
@@ -787,10 +794,13 @@ static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s
   p.dT = FastDiv::make(uint32_t(a.Kh * a.Kw));
   p.dKw = FastDiv::make(uint32_t(a.Kw));
   p.dchunk = FastDiv::make(uint32_t(p.Kp / EPV));
-  auto kern = l.R > 1 ? conv_rows_kernel<TR> : dr ? conv_smallc_kernel<TR, true> : conv_smallc_kernel<TR, false>;
-  const int which = l.R > 1 ? 2 : dr;
-  static std::once_flag once[3];
-  static hipError_t attr_status[3] = {hipSuccess, hipSuccess, hipSuccess};
+  constexpr decltype(&conv_rows_kernel<TR, false>) kernels[6] = {
+      conv_smallc_kernel<TR, false, false>, conv_smallc_kernel<TR, true, false>, conv_rows_kernel<TR, false>,
+      conv_smallc_kernel<TR, false, true>, conv_smallc_kernel<TR, true, true>, conv_rows_kernel<TR, true>};
+  const int which = (l.R > 1 ? 2 : dr) + 3 * raw;
+  const auto kern = kernels[which];
+  static std::once_flag once[6];
+  static hipError_t attr_status[6];        // (hipSuccess is zero)
   std::call_once(once[which], [&]() {
     attr_status[which] = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
@@ -807,11 +817,11 @@ static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s
   // layers, packed first / as they are: 24 images of 6 x 49x71 -> 205, 7x7 (K = 294, four channel tiles, three
   // tasks) 42.8 / 58.7 us, 2 of 8 x 78x152 -> 441, 5x5 45.8 / 53.1, 2 of 15 x 64x113 -> 13, 5x5 (K = 375) 14.7 /
   // 15.9; 15 of 2 x 26x27 -> 264, 3x3 (K = 18, five tiles) 24.9 / 23.5, 64 of 3 x 224x224 -> 64, 7x7 stride 2
-  // (K = 147) 66 / 64, 3 x 8x8 -> 4, 3x3 7.2 / 5.8.
+  // (K = 147) 66 / 64, 3 x 8x8 -> 4, 3x3 7.2 / 5.4.
   const int64_t tiles_each = p.otiles < per_group ? p.otiles : per_group;
   if (raw && (2 * tiles_each - 1) * p.K > 256) return hipErrorInvalidValue;
-  // The copies go to workgroups of their own while there is room for them: 3 x 8x8 -> 4, 3x3 5.6 us, 5.8 where
-  // the others write them, 5.0 without copies.
+  // The copies go to workgroups of their own while there is room for them: 3 x 8x8 -> 4, 3x3 5.4 us, some
+  // 0.2 more where the others write them, 5.0 without copies.
   p.groups = unsigned(grid);
   const int64_t room = int64_t(smallc_num_cus()) * per_cu - grid, wanted = ceil_div(elements / EPV, kSmallCThreads);
   grid += wanted < room ? wanted : room;
