@@ -39,7 +39,7 @@ DOM_BATCH = 20                # launches of the dominant kernel per timing graph
 # only counts for the kernel sources it was taken with: their hash is stored beside it and the
 # bench reports null once the sources differ.
 KERNEL_SOURCES = {
-    "conv": ("conv_tile_kernel.h", "conv_tile_inst.hip", "conv4_kernel.h", "conv_kernels.h", "conv3_inst.hip", "conv.hip", "common.h"),
+    "conv": ("conv_tile_kernel.h", "conv_tile_schedule.h", "conv_tile_inst.hip", "conv_scan.h", "conv4_kernel.h", "conv_kernels.h", "conv3_inst.hip", "conv.hip", "common.h"),
     "windows": ("windows.hip", "common.h"),
     "reduce": ("reduce.hip", "common.h"),
     "move": ("move.hip", "common.h"),

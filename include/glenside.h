@@ -121,7 +121,9 @@ int glenside_cartesian_dot_blocked(const gs_ap* a0, const gs_ap* a1, int64_t til
  * act applies ReLU last.  Types as for glenside_cartesian_dot.
  *   _direct : the windows are formed on chip (LDS-staged patches), never written to memory.
  *   _im2col : the rewritten program of Fig. 5: flatten(windows ...) is written to the workspace,
- *             then contracted with flatten(weights) by the same kernel as glenside_cartesian_dot.
+ *             then contracted with flatten(weights) by the same kernel as glenside_cartesian_dot
+ *             (for 1x1 windows without padding the matrix's rows are the pixels themselves, which a
+ *             kernel may read where they lie).
  * Both need a workspace of the size their *_workspace query returns (16-byte aligned).
  * The two forms give bit-identical integer results and float results equal up to summation
  * order.                                                                                       */

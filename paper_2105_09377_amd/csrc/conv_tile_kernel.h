@@ -16,20 +16,23 @@
 // channel chunk).  Column p of a patch row (p = input column + Pw) lies at phase p % PH, slot
 // p / PH with PH = IL * S.  The IL blocks of a block group interleave their positions -- lane n of
 // block j is position IL * n + j of the group -- so that the cell of (block j, tap column kw) is
-// column PH * n' + j * S + kw: lanes read consecutive slots of one phase (no bank conflicts, any
-// stride), and equal j * S + kw share one read.  IL = 4: 6 reads for 12 MFMAs of a 3x3 kernel row
-// instead of 12, which matters because with one read per MFMA the LDS would be as busy as the
-// matrix units.  IL positions must lie in one output row (Wo % IL == 0).
+// column PH * n' + j * S + kw: lanes read consecutive slots of one phase, at any stride, and equal
+// j * S + kw share one read.  IL = 4: 6 reads for 12 MFMAs of a 3x3 kernel row instead of 12, which
+// matters because with one read per MFMA the LDS would be as busy as the matrix units.  IL positions
+// must lie in one output row (Wo % IL == 0).  Consecutive slots do not meet in the banks; a wave whose
+// positions go on in the next patch row does, since a row's pitch does not continue the banks (56
+// columns, IL = 4: two of 16 lanes), and so does the write-back of bfloat16, whose lanes read 32 bytes
+// apart: 323 conflict cycles per wave on 64 channels at 56x56.
 //
 // What bounds it: a wave issues in order, so what is not an MFMA has to be issued under one (see the
 // loop); a chunk of 36 MFMAs (1152 cycles) takes 1800 cycles with one workgroup per compute unit,
 // 2450 before its loads and LDS stores were dealt out between the MFMAs.  On top come 1.9 us from
 // the launch to the first MFMA and 2 us of write-back, which only other workgroups can cover.
-// Against the kernels that these layers took before, by themselves: 64 channels at 56x56, batch 32,
-// 16.5 -> 14.4 us (int8 15.2 -> 13.0); one image of 56x56 x 64 6.6 -> 4.5, 28x28 x 128 9.1 -> 5.3,
-// 14x14 x 256 10.0 -> 6.1 (two launches before); 8 images of 14x14 x 256 12.9 -> 7.8; 16 of
-// 7x7 x 512 17.8 -> 12.0; chunk counts that are no multiple of four (80 channels, 30x12 -> 112, 6
-// images) 29.9 -> 4.8.  Over 620 layers of all sizes 2.2 times faster.
+// Against the kernels that these 3x3 layers took before, in turn on one card, launches among others: 64
+// channels at 56x56, batch 32, 17.4 -> 15.1 us (int8 15.3 -> 13.5); one image of 56x56 x 64 6.8 -> 4.7,
+// 28x28 x 128 9.1 -> 5.0 to 6.0, 14x14 x 256 10.2 -> 6.0 (two launches before); 8 images of 14x14 x 256
+// 13.2 -> 7.7; 16 of 7x7 x 512 18.0 -> 11.5; chunk counts that are no multiple of four (80 channels,
+// 30x12 -> 112, 6 images) 29.5 -> 5.5.  Random layers of all sizes: see kTileCost in conv.hip.
 #pragma once
 #include "conv4_kernel.h"
 #include "conv_tile_schedule.h"
@@ -41,7 +44,8 @@ typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   /
 // CM: 32-byte channel chunks that a step of the chunk loop ("chunk" below) holds.  One, except for
 // 1x1 windows, whose single tap would leave too little between two barriers: there CM chunks take
 // the place of the taps, each with a patch of its own, and a patch row is the input row of an output
-// row (rows and columns in between are not read; no padding).  NAT: weights in the listing's order
+// row (no padding; the rows between are not read, but at stride 2 the columns between are staged with
+// the others: half of the cells and of the patch buffer are never read).  NAT: weights in the listing's order
 // ((O),(C)) instead of the blocked copy.
 template <typename TR, int KH, int KW, int CM, bool NAT, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE>
 __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArgs a, ConvGeom g) {

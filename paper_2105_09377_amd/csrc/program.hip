@@ -511,9 +511,14 @@ struct ConvMatch {
 // Is some direct kernel sure to take the convolution?  `flat`: and is it the faster way than the listing node
 // by node (windows gathered in memory, one contraction, one transposition)?
 //
-// Measured over 1267 layers, a whole evaluation with the packing of the weights (us, direct / node by node).  As
-// a caller meets it, passes among others, this rule is 1.03 times the better of the two on average
-// (at worst 1.65), 1.18 always directly, 1.21 never; by device time alone 1.08, 1.28 and 1.20:
+// The lines were drawn over 1267 layers, a whole evaluation with the packing of the weights (us, direct / node by
+// node), before conv_tile_kernel took most layers of whole channel chunks from the kernels named here and packing
+// became one launch.  As a caller met it then, passes among others, the rule was 1.03 times the better of the two
+// on average (at worst 1.65), 1.18 always directly, 1.21 never.  Now, over 400 others: 1.28, 1.22 and 1.41.  No
+// layer is more than 6 % slower than it was, but all 153 that conv_tile_kernel takes are faster directly, by 1.27
+// to 5 times, and the rule still sends 75 of them node by node, 32 of 33 with 5x5 windows among them (3 of 160
+// channels in bytes, 43x21, 5x5 to 23: 11.8 / 43.4).
+//
 //   where the producer / consumer kernel takes windows of up to 3x3 it is the faster one nearly always (64
 //   channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192; 1x1 on average 0.8 of the time);
 //   the general and the few-channel kernel need positions to fill the chip, more for large windows of two-byte
