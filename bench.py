@@ -49,20 +49,20 @@ KERNEL_SOURCES = {
 # workload -> (fetch + write bytes per launch of its dominant kernel, source group, digest of the
 # sources the counters were taken with)
 TRAFFIC = {
-    "resnet18": (26.47e6 + 25.69e6, "conv", "be1e4f8105693da298045e95338888e8025fe8bd4a7b49d790768a7138d0e76a"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
-    "conv3x3": (13.70e6 + 12.85e6, "conv", "be1e4f8105693da298045e95338888e8025fe8bd4a7b49d790768a7138d0e76a"),
-    "conv3x3_b64": (26.47e6 + 25.69e6, "conv", "be1e4f8105693da298045e95338888e8025fe8bd4a7b49d790768a7138d0e76a"),
-    "im2col_gather": (12.98e6 + 115.66e6, "windows", "c21344c14f1504daa8055e2a4530315290fe4dde6ac3b3da1cbe1cf4ffb3b733"),
-    "maxpool": (102.99e6 + 25.69e6, "reduce", "025a77d71d3d2c8ef1d10bb80c03577c7ffc692f00195123f95591fbf1b37b65"),
-    "reduce": (268.47e6 + 0.52e6, "reduce", "025a77d71d3d2c8ef1d10bb80c03577c7ffc692f00195123f95591fbf1b37b65"),
-    "transpose": (25.82e6 + 25.69e6, "move", "ec8c64401b48951140900e64e6c3382927b723df7726d4f03811cf8f5b5e0be4"),
-    "dense_blocked": (50.62e6 + 16.78e6, "gemm", "f729acde06a340a590a660ecf2c20f29683fbe4e198c1e4c649664210b304336"),
-    "dense": (1611.51e6 + 279.85e6, "gemm", "f729acde06a340a590a660ecf2c20f29683fbe4e198c1e4c649664210b304336"),
-    "mlp_scaled": (29.76e6 + 16.78e6, "gemm", "f729acde06a340a590a660ecf2c20f29683fbe4e198c1e4c649664210b304336"),
-    "conv3x3_i8": (6.96e6 + 25.69e6, "conv", "be1e4f8105693da298045e95338888e8025fe8bd4a7b49d790768a7138d0e76a"),
-    "dense_i8": (805.95e6 + 282.89e6, "gemm", "f729acde06a340a590a660ecf2c20f29683fbe4e198c1e4c649664210b304336"),
-    "dense_fp8": (806.18e6 + 134.22e6, "gemm", "f729acde06a340a590a660ecf2c20f29683fbe4e198c1e4c649664210b304336"),
-    "depthwise": (103.12e6 + 102.78e6, "depthwise", "9b819ac16025cb44d258e676e9d3694f8afb24f58407fa5f1aa709dc8bf57d73"),
+    "resnet18": (26.47e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
+    "conv3x3": (13.70e6 + 12.85e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
+    "conv3x3_b64": (26.47e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
+    "im2col_gather": (12.98e6 + 115.65e6, "windows", "c94d4a9430ff5d2660314e68732e827be77765aacde81851a7cc52ff5e773758"),
+    "maxpool": (102.99e6 + 25.69e6, "reduce", "e7fce34a2ac6142a5da1e9f0ce59a06c855b972b8dcaafbb2ad97dad52a8186b"),
+    "reduce": (268.47e6 + 0.52e6, "reduce", "e7fce34a2ac6142a5da1e9f0ce59a06c855b972b8dcaafbb2ad97dad52a8186b"),
+    "transpose": (25.82e6 + 25.70e6, "move", "5b19fc5f9ba268368570a63f0a947a04178474e5c3493d5831c7c17a785b74b7"),
+    "dense_blocked": (50.62e6 + 16.78e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
+    "dense": (1612.14e6 + 280.37e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
+    "mlp_scaled": (28.93e6 + 16.78e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
+    "conv3x3_i8": (6.96e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
+    "dense_i8": (805.92e6 + 283.21e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
+    "dense_fp8": (806.12e6 + 134.22e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
+    "depthwise": (103.12e6 + 102.78e6, "depthwise", "abfbbfe228cd124a49832220eb55be5753237ae0a79d3539f69cd21b58f425f6"),
 }
 
 

@@ -360,9 +360,9 @@ static hipError_t launch_tiles(const ConvArgs& a, const TilePlan& plan, hipStrea
 // Time of a layer in each workgroup shape, in microseconds, fitted by window size to measured times of
 // 240 (1x1), 620 (3x3) and 200 (5x5) layers of 1 to 128 images, 16 to 512 channels on either side,
 // planes of 7x7 to 112x112, strides 1 and 2, both element types (mean error 13 %).  On 500, 400 and 150
-// other layers of these ranges, weights packed: the way it picks is 2 to 3 % slower than the fastest one on
+// other layers of these ranges, weights packed: the way it picks is 2 to 4 % slower than the fastest one on
 // average (at worst 1.4 times for 3x3, 2.1 for 5x5), and 1.5, 2.8 and 4.3 times faster than the kernels
-// without this one; 2 % of the layers are slower than in those, by up to 8 % (one of 1x1 16 %).  A workgroup alone takes wg + store + cnt * alone; a compute unit that
+// without this one; 15 of the 1050 layers are slower than in those by more than 3 %, 2 by more than 10.  A workgroup alone takes wg + store + cnt * alone; a compute unit that
 // is given one after the other takes 0.6 store + cnt * busy for each.  `store` grows by `cut` for
 // planes that are no multiple of a 16-byte store's positions, the chunks by `item` for each patch
 // item of a thread beyond the first and by `strided` for stride 2.  `at_once`: workgroups that fit a
