@@ -25,10 +25,12 @@ for _tr, _tag in (("Bf16Traits", "bf16"), ("I8Traits", "i8")):
                       [f"-DGS_CONV3_TRAITS={_tr}", f"-DGS_CONV3_TILE={_tile}",
                        f"-DGS_CONV3_NAME=launch_conv3_{_tag}_t{_tile}"]))
     for _k in (1, 3, 5):
-        for _shape in range(5):
-            UNITS.append(("conv_tile_inst.hip", f"conv_tile_{_tag}_k{_k}s{_shape}.o",
-                          [f"-DGS_TILE_TRAITS={_tr}", f"-DGS_TILE_SHAPE={_shape}", f"-DGS_TILE_K={_k}",
-                           f"-DGS_TILE_NAME=launch_conv_tile_{_tag}_k{_k}s{_shape}"]))
+        for _odd, _suffix, _shapes in ((0, "", range(5)), (1, "odd", range(1, 5))):
+            for _shape in _shapes:
+                _name = f"conv_tile_{_tag}_k{_k}s{_shape}{_suffix}"
+                UNITS.append(("conv_tile_inst.hip", _name + ".o",
+                              [f"-DGS_TILE_TRAITS={_tr}", f"-DGS_TILE_SHAPE={_shape}", f"-DGS_TILE_K={_k}",
+                               f"-DGS_TILE_ODD={_odd}", f"-DGS_TILE_NAME=launch_{_name}"]))
 
 
 def _compile(unit) -> str:

@@ -154,15 +154,40 @@ int conv_check_io(const gs_ap* act, const gs_ap* w, const gs_ap* residual, int a
   return GS_OK;
 }
 
-// Arguments of the direct convolution on the packed weights `packed`, with the scratch behind them if there is room.
+// What a workspace of a direct convolution holds, from its front.
+struct PackedLayout {
+  size_t weights;         // bytes of the packed weights; the scratch of a split channel sum lies behind them
+  bool fits, blocked, split;      // room for the weights, for all their copies, for the scratch
+};
+// `bytes`: of the workspace.  Channel counts that are no whole chunks do without the blocked copy where it has no room.
+PackedLayout packed_layout(int dtype, int O, int C, int Kh, int Kw, int64_t scratch, size_t bytes) {
+  auto of = [&](bool least) { return size_t(round_up(int64_t(conv_weight_workspace(dtype, O, C, Kh, Kw, least)), 256)) + 256; };
+  PackedLayout l;
+  l.blocked = bytes >= of(false);
+  l.weights = of(!l.blocked);
+  l.fits = bytes >= l.weights;
+  l.split = scratch > 0 && bytes >= l.weights + size_t(scratch);
+  return l;
+}
+// Bytes of the partial sums where the shape's channel sum is split.
+int64_t split_scratch(int dtype, const ConvShape& cs) {
+  const int ks = conv_pick_ksplit(dtype, cs.N, cs.C, cs.O, cs.Ho, cs.Wo);
+  return ks > 1 ? int64_t(ks) * cs.N * cs.O * cs.Ho * cs.Wo * 4 : 0;
+}
+// Workspace of a direct convolution: what makes it fastest, or the least that it takes.
+size_t direct_workspace(int dtype, const ConvShape& cs, bool least) {
+  return size_t(round_up(int64_t(conv_weight_workspace(dtype, cs.O, cs.C, cs.Kh, cs.Kw, least)), 256) + 256 + split_scratch(dtype, cs));
+}
+
+// Arguments of the direct convolution on the packed weights `packed`.
 ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_ap* out, const ConvShape& cs, void* packed,
-                   bool split, size_t wneed) {
+                   const PackedLayout& layout) {
   ConvArgs a;
   memset(&a, 0, sizeof(a));
   a.ksplit = 1;
-  if (split) {
+  if (layout.split) {
     a.ksplit = conv_pick_ksplit(act->dtype, cs.N, cs.C, cs.O, cs.Ho, cs.Wo);
-    a.partial = static_cast<uint8_t*>(packed) + wneed;
+    a.partial = static_cast<uint8_t*>(packed) + layout.weights;
   }
   a.act = act->data;
   a.wr = packed;
@@ -175,7 +200,7 @@ ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_
   a.Cpad = int(round_up(cs.C, act->dtype == GS_I8 ? 32 : 16));
   if (conv_is_smallc(act->dtype, cs.C))
     a.wnat = static_cast<const uint8_t*>(packed) + conv_smallc_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
-  if (conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw))
+  if (layout.blocked && conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw))
     a.wblk = static_cast<const uint8_t*>(packed) + conv_blocked_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
   a.relu = actfn == GS_ACT_RELU;
   return a;
@@ -373,10 +398,7 @@ size_t glenside_conv2d_direct_workspace(const gs_ap* act, const gs_ap* w, const 
                                         const int64_t pad[2]) {
   ConvShape cs;
   if (conv_shape(act, w, stride, pad, &cs)) return 0;
-  const int64_t wbytes = round_up(int64_t(conv_weight_workspace(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)), 256) + 256;
-  const int ks = conv_pick_ksplit(act->dtype, cs.N, cs.C, cs.O, cs.Ho, cs.Wo);
-  const int64_t scratch = ks > 1 ? int64_t(ks) * cs.N * cs.O * cs.Ho * cs.Wo * 4 : 0;
-  return size_t(wbytes + scratch);
+  return direct_workspace(act->dtype, cs, false);
 }
 
 size_t glenside_conv2d_im2col_workspace(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
@@ -398,10 +420,9 @@ int glenside_conv2d_pack_weights(const gs_ap* w, void* packed, size_t packed_byt
     if (w->shape[i] > INT_MAX / 4) return GS_ERR_UNSUPPORTED;
   if (w->shape[1] < 1 || w->shape[2] < 1 || w->shape[3] < 1) return GS_ERR_SHAPE;
   const int O = int(w->shape[0]), C = int(w->shape[1]), Kh = int(w->shape[2]), Kw = int(w->shape[3]);
-  const size_t need = size_t(round_up(int64_t(conv_weight_workspace(w->dtype, O, C, Kh, Kw)), 256)) + 256;
-  if (!packed || packed_bytes < need || reinterpret_cast<uintptr_t>(packed) % 16)
-    return GS_ERR_WORKSPACE;
-  return launch_status(launch_conv_repack(w->data, packed, w->dtype, O, C, Kh, Kw,
+  const PackedLayout layout = packed_layout(w->dtype, O, C, Kh, Kw, 0, packed_bytes);
+  if (!packed || !layout.fits || reinterpret_cast<uintptr_t>(packed) % 16) return GS_ERR_WORKSPACE;
+  return launch_status(launch_conv_repack(w->data, packed, w->dtype, O, C, Kh, Kw, layout.blocked,
                                           static_cast<hipStream_t>(stream)));
 }
 
@@ -417,11 +438,9 @@ int glenside_conv2d_direct_packed(const gs_ap* act, const gs_ap* w, const int64_
   st = conv_check_io(act, &wshape, residual, actfn, out, cs);
   if (st) return st;
   // The packed weights must be there; the scratch behind them (split channel sums) is optional.
-  const size_t wneed = size_t(round_up(int64_t(conv_weight_workspace(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)), 256)) + 256;
-  const size_t need = glenside_conv2d_direct_workspace(act, w, stride, pad);
-  if (!packed || packed_bytes < wneed || reinterpret_cast<uintptr_t>(packed) % 16)
-    return GS_ERR_WORKSPACE;
-  const ConvArgs a = conv_args(act, residual, actfn, out, cs, packed, need > wneed && packed_bytes >= need, wneed);
+  const PackedLayout layout = packed_layout(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, split_scratch(act->dtype, cs), packed_bytes);
+  if (!packed || !layout.fits || reinterpret_cast<uintptr_t>(packed) % 16) return GS_ERR_WORKSPACE;
+  const ConvArgs a = conv_args(act, residual, actfn, out, cs, packed, layout);
   return launch_status(launch_conv(a, static_cast<hipStream_t>(stream)));
 }
 
@@ -435,12 +454,11 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
   if (st) return st;
   st = conv_check_io(act, w, residual, actfn, out, cs);
   if (st) return st;
-  const size_t need = glenside_conv2d_direct_workspace(act, w, stride, pad);
-  if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16)
+  if (!workspace || workspace_bytes < direct_workspace(act->dtype, cs, true) || reinterpret_cast<uintptr_t>(workspace) % 16)
     return GS_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t wneed = size_t(round_up(int64_t(conv_weight_workspace(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)), 256)) + 256;
-  const ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, need > wneed, wneed);
+  const PackedLayout layout = packed_layout(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, split_scratch(act->dtype, cs), workspace_bytes);
+  const ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, layout);
   // Few channels: the kernel takes the weights as they are and writes the copies on the side.
   if (conv_is_smallc(act->dtype, cs.C) && int64_t(cs.N) * cs.Ho * cs.Wo > 0) {
     ConvArgs b = a;
@@ -448,7 +466,7 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
     const hipError_t e = launch_conv_smallc(b, workspace, s);
     if (e != hipErrorInvalidValue) return launch_status(e);
   }
-  const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, s);
+  const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, layout.blocked, s);
   if (e != hipSuccess) return launch_status(e);
   return launch_status(launch_conv(a, s));
 }
@@ -467,7 +485,7 @@ int gs_test_conv_tile(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
   } else {
     none.dtype = act->dtype == GS_I8 ? GS_I32 : GS_BF16;
   }
-  ConvArgs a = conv_args(act, residual, actfn, out ? out : &none, cs, packed, false, 0);
+  ConvArgs a = conv_args(act, residual, actfn, out ? out : &none, cs, packed, PackedLayout{0, true, true, false});
   if (!packed) {
     a.wr = w->data;
     a.wblk = nullptr;
@@ -518,7 +536,7 @@ int glenside_conv2d_direct_static(const gs_ap* act, const gs_ap* w, const int64_
   if (st) return st;
   st = conv_check_io(act, w, residual, actfn, out, cs);
   if (st) return st;
-  if (glenside_conv2d_direct_workspace(act, w, stride, pad) > kStaticScratchBytes) return GS_ERR_WORKSPACE;
+  if (direct_workspace(act->dtype, cs, true) > kStaticScratchBytes) return GS_ERR_WORKSPACE;
   void* ws = nullptr;
   st = static_scratch(&ws);
   if (st) return st;

@@ -273,7 +273,7 @@ struct ConvArgs {
   const void* act;        // N x C x H x W
   const void* wr;         // repacked weights: O x (Kh*Kw) x Cpad, channel fastest, zero padded
   const void* wnat;       // fewer channels than a chunk: ((O up to 64s),(K up to 32 B)) copy, else null
-  const void* wblk;       // whole chunks only (C == Cpad): the copy in 1 KB blocks (see conv_blocked_weight_offset), else null
+  const void* wblk;       // the copy in 1 KB blocks (see conv_blocked_weight_offset), null if there is none
   void* out;              // N x O x Ho x Wo
   const void* residual;
   int in_dtype, out_dtype;
@@ -283,13 +283,14 @@ struct ConvArgs {
   int ksplit;             // 1, 2 or 4: the channel chunks are divided among ksplit workgroups
   void* partial;          // ksplit > 1: [ksplit][N*O*Ho*Wo] 32-bit partial sums
 };
-size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw);
+// All copies; `least`: without the blocked copy of channel counts that are no whole chunks, which kernels can do without.
+size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw, bool least);
 // Few-channel inputs (conv_smallc.hip): a second, natural-order weight copy behind the first.
 bool conv_is_smallc(int in_dtype, int C);
 size_t conv_smallc_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_smallc_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
-// Channel counts that are whole chunks (32 bytes per tap): a third copy behind the others, cut
-// into blocks of 1 KB = 32 output channels x one chunk of one tap, ordered [O / 32][chunk][tap],
+// Channel counts that are whole chunks (32 bytes per tap), and others with 1x1, 3x3 and 5x5 windows (the last
+// chunk filled up with zeros): a third copy behind the others, cut into blocks of 1 KB = 32 output channels x one chunk of one tap, ordered [O / 32][chunk][tap],
 // each block the exact image of the LDS block the convolution's weight transfers fill (lane i of a
 // transfer moves bytes 16 i .. 16 i + 15), so that one transfer reads 1 KB of consecutive memory
 // instead of 32 pieces of 32 bytes from 32 rows.  Bytes of that copy (0 if there is none) and its
@@ -301,8 +302,9 @@ hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, in
 // Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there.
 hipError_t launch_conv_smallc(const ConvArgs& a, void* packed, hipStream_t s);
 bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo);   // does the kernel take the layer?
+// blocked: the workspace has room for the blocked copy.
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
-                              hipStream_t s);
+                              bool blocked, hipStream_t s);
 // Returns hipErrorInvalidValue if no tile configuration fits the LDS for this shape.  With
 // a.ksplit > 1 and a.partial set, kernels that support it split the channel sum (Fig. 6's last
 // blocking rule: partial dot products combined by reduceSum over a pair); others ignore it.

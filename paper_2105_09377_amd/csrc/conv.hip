@@ -5,8 +5,8 @@
 //
 // Kernels, in the order they are tried:
 //   * conv_smallc_kernel  (conv_smallc.hip)  fewer input channels than one 32-byte chunk;
-//   * conv_tile_kernel    (conv_tile_kernel.h)  3x3, 5x5 and (whole groups of channel chunks, no
-//                                            padding) 1x1 windows of strides 1 and 2: small
+//   * conv_tile_kernel    (conv_tile_kernel.h)  3x3, 5x5 and (no padding) 1x1 windows of strides 1
+//                                            and 2, any channel count: small
 //                                            independent workgroups, weights from L2 into registers;
 //                                            in the workgroup shape that a cost model picks, unless it
 //                                            expects the next one to be faster;
@@ -27,10 +27,9 @@
 
 namespace gs {
 
-// wr[o][tap][c] = w[o][c][tap] for c < C, zero for C <= c < Cpad.  With `wb` (channel counts
-// that are whole chunks, C == Cpad) also the blocked copy (see conv_blocked_weight_offset):
-// element e of 16-byte piece i of block (ob, chunk, tap) is
-// w[ob * 32 + i / 2][chunk * CCH + h * G + e][tap], G = elements in 16 bytes, CCH = 2 G,
+// wr[o][tap][c] = w[o][c][tap] for c < C, zero for C <= c < Cpad.  With `wb` also the blocked
+// copy (see conv_blocked_weight_offset): element e of 16-byte piece i of block (ob, chunk, tap) is
+// w[ob * 32 + i / 2][chunk * CCH + h * G + e][tap] (zero past C), G = elements in 16 bytes, CCH = 2 G,
 // h = (i % 2) ^ (((r >> 2) ^ (r >> 3)) & 1) with r = i / 2 -- the swizzle the consumers'
 // fragment reads undo; rows past O are zero.  A thread gathers one 16-byte piece, its G elements T_ apart,
 // and writes it to both copies (packing and convolving 512 x 7x7 -> 512, 3x3: 18.3 us, 24.9 with an element per
@@ -84,28 +83,31 @@ static size_t conv_weight_front_bytes(int in_dtype, int O, int C, int Kh, int Kw
 }
 
 size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw) {
-  if (C != conv_cpad(in_dtype, C)) return 0;
-  return size_t(round_up(O, 32)) * Kh * Kw * C * dtype_size(in_dtype);
+  // (channel counts that are no whole chunks: only conv_tile_kernel takes them)
+  if (C != conv_cpad(in_dtype, C) && (conv_is_smallc(in_dtype, C) || Kh != Kw || (Kh != 1 && Kh != 3 && Kh != 5))) return 0;
+  return size_t(round_up(O, 32)) * Kh * Kw * conv_cpad(in_dtype, C) * dtype_size(in_dtype);
 }
 
 size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw) {
   return size_t(round_up(int64_t(conv_weight_front_bytes(in_dtype, O, C, Kh, Kw)), 256));
 }
 
-size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw) {
-  const size_t blocked = conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw);
+bool conv_blocked_optional(int in_dtype, int C) { return C != conv_cpad(in_dtype, C); }
+
+size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw, bool least) {
+  const size_t blocked = least && conv_blocked_optional(in_dtype, C) ? 0 : conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw);
   return blocked ? conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw) + blocked
                  : conv_weight_front_bytes(in_dtype, O, C, Kh, Kw);
 }
 
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
-                              hipStream_t s) {
+                              bool blocked, hipStream_t s) {
   const int Cpad = conv_cpad(in_dtype, C);
   if (int64_t(O) * Kh * Kw * Cpad == 0) return hipSuccess;
   if (conv_is_smallc(in_dtype, C)) return launch_conv_smallc_pack(w, wr, in_dtype, O, C, Kh, Kw, s);
   const int64_t b = ceil_div(round_up(O, 32) * Kh * Kw * Cpad * int64_t(dtype_size(in_dtype)) / 16, 256);
   const dim3 grid(unsigned(b < 65536 ? b : 65536));
-  uint8_t* wb = conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
+  uint8_t* wb = blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
                     ? static_cast<uint8_t*>(wr) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw)
                     : nullptr;
   if (in_dtype == GS_I8)
@@ -341,7 +343,9 @@ using TileLaunch = hipError_t (*)(const ConvArgs&, const TilePlan&, hipStream_t)
 #define GS_TILE_DECL(k, i)                                                                 \
   hipError_t launch_conv_tile_bf16_k##k##s##i(const ConvArgs&, const TilePlan&, hipStream_t); \
   hipError_t launch_conv_tile_i8_k##k##s##i(const ConvArgs&, const TilePlan&, hipStream_t);
-#define GS_TILE_DECLS(k) GS_TILE_DECL(k, 0) GS_TILE_DECL(k, 1) GS_TILE_DECL(k, 2) GS_TILE_DECL(k, 3) GS_TILE_DECL(k, 4)
+#define GS_TILE_DECLS(k)                                                                        \
+  GS_TILE_DECL(k, 0) GS_TILE_DECL(k, 1) GS_TILE_DECL(k, 2) GS_TILE_DECL(k, 3) GS_TILE_DECL(k, 4) \
+  GS_TILE_DECL(k, 1odd) GS_TILE_DECL(k, 2odd) GS_TILE_DECL(k, 3odd) GS_TILE_DECL(k, 4odd)
 GS_TILE_DECLS(1) GS_TILE_DECLS(3) GS_TILE_DECLS(5)
 #undef GS_TILE_DECLS
 #undef GS_TILE_DECL
@@ -354,6 +358,13 @@ static hipError_t launch_tiles(const ConvArgs& a, const TilePlan& plan, hipStrea
   static constexpr TileLaunch bf16[3][kNumTileShapes] = {GS_TILE_ROW(bf16, 1), GS_TILE_ROW(bf16, 3), GS_TILE_ROW(bf16, 5)};
   static constexpr TileLaunch i8[3][kNumTileShapes] = {GS_TILE_ROW(i8, 1), GS_TILE_ROW(i8, 3), GS_TILE_ROW(i8, 5)};
 #undef GS_TILE_ROW
+#define GS_TILE_ROW(t, k)                                                                                       \
+  {nullptr, launch_conv_tile_##t##_k##k##s1odd, launch_conv_tile_##t##_k##k##s2odd, launch_conv_tile_##t##_k##k##s3odd, \
+   launch_conv_tile_##t##_k##k##s4odd}
+  static constexpr TileLaunch bf16_odd[3][kNumTileShapes] = {GS_TILE_ROW(bf16, 1), GS_TILE_ROW(bf16, 3), GS_TILE_ROW(bf16, 5)};
+  static constexpr TileLaunch i8_odd[3][kNumTileShapes] = {GS_TILE_ROW(i8, 1), GS_TILE_ROW(i8, 3), GS_TILE_ROW(i8, 5)};
+#undef GS_TILE_ROW
+  if (plan.odd) return (TR::kEsz == 1 ? i8_odd : bf16_odd)[a.Kh / 2][plan.shape](a, plan, s);
   return (TR::kEsz == 1 ? i8 : bf16)[a.Kh / 2][plan.shape](a, plan, s);
 }
 
@@ -425,8 +436,10 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, int 
   if (a.Kh == 5 && sh.nj > 2) return false;              // a ring of 25 taps leaves no registers for it
   p->maxi = items <= threads ? 1 : items <= 2 * threads ? 2 : 4;
   if (items > 4 * threads || (sh.nj > 2 && p->maxi > 2)) return false;
-  const int nchunk = a.Cpad * int(dtype_size(a.in_dtype)) / (32 * cm), cnt = int(ceil_div(nchunk, sh.ks));
-  p->one = sh.ks > 1 && cnt == 1;
+  const int nchunk = int(ceil_div(a.Cpad * int64_t(dtype_size(a.in_dtype)), 32 * cm)), cnt = int(ceil_div(nchunk, sh.ks));
+  p->odd = a.C * int(dtype_size(a.in_dtype)) % (32 * cm) != 0;
+  if (p->odd && shape == 0) return false;                // not built
+  p->one = sh.ks > 1 && cnt == 1 && !p->odd;
   const int PH = p->il * S;
   const int lastcol = a.W + a.Pw - 1 > (a.Wo - 1) * S + a.Kw - 1 ? a.W + a.Pw - 1 : (a.Wo - 1) * S + a.Kw - 1;
   const int64_t php = (lastcol / PH + 1) * 16, bufb = 2 * cm * max_rows * PH * php;
@@ -456,7 +469,7 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, int 
   const int64_t rows = ceil_div(g.tps, a.Wo);
   const float per_thread = point ? float(2 * cm * (whole ? rows : rows + 1) * ceil_div(a.W, kTileItem)) / threads
                                  : float((rows * S + a.Kh) * a.W) / (2 * threads);
-  const float chunk = 1 + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
+  const float chunk = (p->odd ? 1.1f : 1.0f) + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
   const float store = c.store * (g.HWo % group ? 1 + c.cut : 1.0f);
   const float alone = c.wg + store + c.alone * cnt * chunk, busy = c.busy * cnt * chunk + 0.6f * store;
   const float by_rounds = alone * ceil_div(tiles, int64_t(256 * c.at_once));
@@ -504,9 +517,11 @@ static float gathered_cost(const ConvArgs& a, const ConvGeom& g) {
 // Does conv_tile_kernel take the layer, in a workgroup shape that fits?
 template <typename TR>
 static bool tile_takes(const ConvArgs& a, bool natural) {
-  const bool window = a.Kh == a.Kw && (a.Kh == 3 || a.Kh == 5 ||
-                                       (a.Kh == 1 && a.Ph + a.Pw == 0 && a.Cpad * TR::kEsz % (32 * kTileChunks) == 0));
-  return (a.wblk || (natural && a.Kh == 1)) && window && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem && a.C == a.Cpad &&
+  const bool window = a.Kh == a.Kw && (a.Kh == 3 || a.Kh == 5 || (a.Kh == 1 && a.Ph + a.Pw == 0));
+  // Weights as they come are read in 16-byte pieces; channels that do not fill the last chunk: 32-bit offsets of planes.
+  const bool whole = a.C * TR::kEsz % (a.Kh == 1 ? 32 * kTileChunks : 32) == 0;
+  if (!whole && ((natural && a.C * TR::kEsz % 16 != 0) || int64_t(a.H) * a.W * TR::kEsz >= (1 << 24))) return false;
+  return (a.wblk || (natural && a.Kh == 1)) && window && a.Sh == a.Sw && a.Sh <= 2 && a.W >= kTileItem &&
          round_up(a.O, 32) * a.Kh * a.Kw * a.Cpad * TR::kEsz < (int64_t(1) << 32);
 }
 

@@ -93,6 +93,7 @@ struct TilePlan {
   int shape;                // index into kTileShapes, or -1: the kernel does not take the layer
   int il, maxi;             // interleaved blocks, patch items per thread
   bool one;                 // a single chunk per group
+  bool odd;                 // channels that do not fill the last chunk (of a step, for 1x1 windows)
   int tiles, lds_bytes;
   ConvGeom g;
 };

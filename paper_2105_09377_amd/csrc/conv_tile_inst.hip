@@ -1,6 +1,7 @@
 // One translation unit per (element type, workgroup shape, window size) of conv_tile_kernel, so that the
 // instances compile in parallel.  Built several times with different -DGS_TILE_TRAITS /
-// -DGS_TILE_SHAPE / -DGS_TILE_K / -DGS_TILE_NAME (see build.py).
+// -DGS_TILE_SHAPE / -DGS_TILE_K / -DGS_TILE_ODD / -DGS_TILE_NAME (see build.py).  GS_TILE_ODD: channels that do not fill
+// the last chunk; not in the largest workgroups, and groups of a single chunk take the kernels for several.
 #include "conv_tile_kernel.h"
 
 #include <mutex>
@@ -11,7 +12,7 @@ constexpr TileShape kShape = kTileShapes[GS_TILE_SHAPE];
 
 template <int K, int CM, bool NAT, int S, int IL, int MAXI, bool ONE>
 static hipError_t launch_tile_inst(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
-  auto kern = conv_tile_kernel<GS_TILE_TRAITS, K, K, CM, NAT, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE>;
+  auto kern = conv_tile_kernel<GS_TILE_TRAITS, K, K, CM, NAT, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE, bool(GS_TILE_ODD)>;
   static std::once_flag once;              // the attribute is set once, whichever thread comes first
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&]() {
@@ -25,7 +26,7 @@ static hipError_t launch_tile_inst(const ConvArgs& a, const TilePlan& p, hipStre
 
 template <int K, int CM, bool NAT, int S, int IL>
 static hipError_t launch_tile_items(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
-  if constexpr (kShape.ks > 1) {
+  if constexpr (kShape.ks > 1 && !GS_TILE_ODD) {
     if (p.one && p.maxi == 1) return launch_tile_inst<K, CM, NAT, S, IL, 1, true>(a, p, s);
     if (p.one && p.maxi == 2) return launch_tile_inst<K, CM, NAT, S, IL, 2, true>(a, p, s);
     if (p.one) return launch_tile_inst<K, CM, NAT, S, IL, 4, true>(a, p, s);

@@ -622,6 +622,65 @@ def test_conv_tile_instances(dtype, k, natural, shape):
             assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# The same instances with channels that do not fill the last chunk: one short, one more than the chunk before, and 1x1
+# steps that lack whole chunks.  Infinities in the last channel and in the channels that follow it in memory.
+@pytest.mark.parametrize("shape", tile_instances.SHAPES[1:])
+@pytest.mark.parametrize("k,natural", [(1, False), (1, True), (3, False), (5, False)])
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+def test_conv_tile_instances_odd_channels(dtype, k, natural, shape):
+    unit = 32 if dtype == "i8" else 16
+    reached = set()
+    for (s, *_rest), (way, (n, c, h, w, o, p)) in tile_instances.layers(dtype, k, natural, shape).items():
+        for less in ((unit // 2, 5 * unit // 2, 3 * unit) if natural else (1, unit - 1, unit + 3)):
+            cfg = synth.conv_layer(n, c - less, h, w, o, k, s, p, dtype, 9300 + h + w)
+            if dtype == "bf16":
+                cfg["x"][0, -1, 0, 0] = float("inf")
+                cfg["x"][n - 1, 0, h - 1, w - 1] = float("-inf")
+            x, wt = cfg["x"].to(DEV), cfg["w"].to(DEV)
+            want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p)
+            packed = gs.conv2d_pack_weights(wt, for_input=(x, (s, s), (p, p)))
+            odt = torch.int32 if dtype == "i8" else torch.bfloat16
+            buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
+            out = buf[256:256 + want.numel()].view(want.shape)
+            st, plan = tile_instances.call(gs.make_ap(x, 1), gs.make_ap(wt, 1), s, p, None, gs.GS_ACT_NONE, gs.make_ap(out, 4),
+                                           None if natural else packed.data_ptr(), way, gs._stream(x))
+            if _rest[2] and st == gs.GS_ERR_UNSUPPORTED:
+                continue                # built for several chunks only, whose three patch buffers do not fit
+            assert (st, plan[0], plan[3]) == (gs.GS_OK, shape, 0)
+            reached.add((s, *plan[1:4]))
+            got = out.double().cpu()
+            same = torch.isfinite(want)
+            assert torch.equal(torch.nan_to_num(got[~same], nan=7.0), torch.nan_to_num(want[~same], nan=7.0))
+            assert torch.isfinite(got[same]).all()
+            got, want = torch.where(same, got, 0.0).numpy(), torch.where(same, want, 0.0).numpy()
+            if dtype == "i8":
+                assert np.array_equal(got, want), f"{plan} {(n, c - less, h, w)} stride {s}"
+            else:       # one rounding to bfloat16
+                assert np.abs(got - want).max() <= 2.0 ** -8 * np.abs(want).max(), f"{plan} {(n, c - less, h, w)} stride {s}"
+            assert (buf[:256] == 77).all() and (buf[256 + want.size:] == 77).all()
+    assert reached == {i for i in tile_instances.built(dtype, k, shape) if not i[3]}
+
+
+@pytest.mark.parametrize("k,c,dtype", [(3, 33, "bf16"), (5, 50, "i8"), (1, 40, "bf16")])
+def test_conv2d_odd_channels_in_the_least_workspace(k, c, dtype):
+    """The blocked copy of the weights is optional where channels do not fill a chunk: a workspace without room for it
+    is taken, and gives the same result."""
+    cfg = synth.conv_layer(2, c, 9, 11, 40, k, 1, k // 2, dtype, 9400 + c)
+    x, wt, pad = cfg["x"].to(DEV), cfg["w"].to(DEV), (k // 2, k // 2)
+    want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), padding=k // 2).numpy()
+    want = want.astype(np.int64) if dtype == "i8" else want
+    step = 32 if dtype == "i8" else 16
+    front = 40 * k * k * -(-c // step) * 32
+    least = -(-front // 256) * 256 + 256
+    full = gs.conv2d_pack_weights(wt).numel()
+    assert least < full
+    for size in (least, full - 1, full):
+        packed = gs.conv2d_pack_weights(wt, packed=torch.empty(size, dtype=torch.uint8, device=DEV))
+        assert_parity(gs.conv2d_direct_packed(x, wt, packed, (1, 1), pad), want, what=f"packed in {size} bytes")
+    with pytest.raises(Exception):
+        gs.conv2d_pack_weights(wt, packed=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
+
+
 # Few channels and many output rows: tasks of two rows (conv_rows_kernel).  Odd row counts, rows cut inside a
 # 16-byte store, several position and channel tiles, windows of one row, 16-byte loads and element by element.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
