@@ -123,7 +123,7 @@ int glenside_cartesian_dot_blocked(const gs_ap* a0, const gs_ap* a1, int64_t til
  *   _im2col : the rewritten program of Fig. 5: flatten(windows ...) is written to the workspace,
  *             then contracted with flatten(weights) by the same kernel as glenside_cartesian_dot
  *             (for 1x1 windows without padding the matrix's rows are the pixels themselves, which a
- *             kernel may read where they lie).
+ *             kernel may read where they lie; for small images the rows may be formed on chip).
  * Both need a workspace of the size their *_workspace query returns (16-byte aligned).
  * The two forms give bit-identical integer results and float results equal up to summation
  * order.                                                                                       */

@@ -463,7 +463,8 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
   if (conv_is_smallc(act->dtype, cs.C) && int64_t(cs.N) * cs.Ho * cs.Wo > 0) {
     ConvArgs b = a;
     b.wr = w->data;
-    const hipError_t e = launch_conv_smallc(b, workspace, s);
+    hipError_t e = launch_conv_images(b, workspace, s);
+    if (e == hipErrorInvalidValue) e = launch_conv_smallc(b, workspace, s);
     if (e != hipErrorInvalidValue) return launch_status(e);
   }
   const hipError_t e = launch_conv_repack(w->data, workspace, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, layout.blocked, s);
@@ -561,20 +562,23 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   uint8_t* cols = static_cast<uint8_t*>(workspace);
   uint8_t* wpad = cols + round_up(M * ld * esz, 256);
 
+  ConvArgs a;
+  memset(&a, 0, sizeof(a));
+  a.act = act->data;
+  a.wr = w->data;
+  a.out = out->data;
+  a.residual = residual ? residual->data : nullptr;
+  a.in_dtype = act->dtype;
+  a.out_dtype = out->dtype;
+  a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = cs.Kh; a.Kw = cs.Kw;
+  a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ph = cs.Ph; a.Pw = cs.Pw; a.Ho = cs.Ho; a.Wo = cs.Wo;
+  a.relu = actfn == GS_ACT_RELU;
+  // Small images: the rows of the matrix are formed on chip, in the launch that multiplies them.
+  hipError_t e = launch_conv_images(a, nullptr, s);
+  if (e != hipErrorInvalidValue) return launch_status(e);
   // A window of one pixel: the rows of the matrix are the pixels themselves, read where they lie.
   if (cs.Kh == 1 && cs.Kw == 1 && cs.Ph == 0 && cs.Pw == 0) {
-    ConvArgs a;
-    memset(&a, 0, sizeof(a));
-    a.act = act->data;
-    a.wr = w->data;
-    a.out = out->data;
-    a.residual = residual ? residual->data : nullptr;
-    a.in_dtype = act->dtype;
-    a.out_dtype = out->dtype;
-    a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = 1; a.Kw = 1;
-    a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ho = cs.Ho; a.Wo = cs.Wo;
-    a.relu = actfn == GS_ACT_RELU;
-    const hipError_t e = launch_conv_point(a, s);
+    e = launch_conv_point(a, s);
     if (e != hipErrorInvalidValue) return launch_status(e);
   }
 
@@ -594,7 +598,7 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   }
   wa.fill_bits = 0;
   wa.out_row_stride = ld;
-  hipError_t e = launch_windows(wa, s);
+  e = launch_windows(wa, s);
   if (e != hipSuccess) return launch_status(e);
 
   // flatten (access weights 1): already ((O),(K)) in memory; copied only when rows need padding.

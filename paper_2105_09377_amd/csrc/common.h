@@ -88,6 +88,27 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
   return uint32_t(uintptr_t((const __attribute__((address_space(3))) uint8_t*)p));
 }
 
+// 16 bytes at any address: the memory pipeline takes any alignment.
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// The 16 bytes of a row that start at byte kb, zero beyond the row's Kb bytes, without touching a
+// byte outside the row: rows of at least 16 bytes are read at min(kb, Kb - 16) and the bytes moved
+// down afterwards (row_piece_fix), which only the last slab of a row needs.
+__device__ __forceinline__ i32x4 row_piece_fix(i32x4 v, int64_t over) {
+  if (over <= 0) return v;
+  uint64_t lo = uint32_t(v[0]) | (uint64_t(uint32_t(v[1])) << 32), hi = uint32_t(v[2]) | (uint64_t(uint32_t(v[3])) << 32);
+  if (over >= 16) {
+    lo = hi = 0;
+  } else if (over >= 8) {
+    lo = hi >> (8 * (over - 8));
+    hi = 0;
+  } else {
+    lo = (lo >> (8 * over)) | (hi << (64 - 8 * over));
+    hi >>= 8 * over;
+  }
+  return i32x4{int32_t(uint32_t(lo)), int32_t(uint32_t(lo >> 32)), int32_t(uint32_t(hi)), int32_t(uint32_t(hi >> 32))};
+}
+
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
@@ -302,6 +323,9 @@ hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, in
 // Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there.
 hipError_t launch_conv_smallc(const ConvArgs& a, void* packed, hipStream_t s);
 bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo);   // does the kernel take the layer?
+// Small images, weights as they come (conv_images.hip): one launch; with `packed`, their copies are written there on the
+// side.  hipErrorInvalidValue where the kernel does not take the call, or where it is not the fastest way.
+hipError_t launch_conv_images(const ConvArgs& a, void* packed, hipStream_t s);
 // blocked: the workspace has room for the blocked copy.
 hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int C, int Kh, int Kw,
                               bool blocked, hipStream_t s);

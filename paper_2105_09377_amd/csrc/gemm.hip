@@ -111,9 +111,6 @@ __device__ inline TileBox tile_box(const GemmArgs& a, int64_t ti, int64_t tj) {
   return b;
 }
 
-// 16 bytes at any address: the memory pipeline takes any alignment.
-typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
-
 // Result write-back of one wave: acc[m][n] holds the 32x32 blocks of rows iw .. and columns jw ..
 // (a lane holds column lane % 32, rows 8*(v/4) + 4*(lane/32) + v%4 of a block).
 //
@@ -280,23 +277,6 @@ __device__ __forceinline__ void write_tile(const GemmArgs& a, const TileBox& box
 // ---------------------------------------------------------------------------------------------
 // Rows at any byte address: 16-byte pieces are loaded where they lie and pass through registers, so that LDS rows can be aligned and padded.
 // ---------------------------------------------------------------------------------------------
-// The 16 bytes of a row that start at byte kb, zero beyond the row's Kb bytes, without touching a
-// byte outside the row: rows of at least 16 bytes are read at min(kb, Kb - 16) and the bytes moved
-// down afterwards (row_piece_fix), which only the last slab of a row needs.
-__device__ __forceinline__ i32x4 row_piece_fix(i32x4 v, int64_t over) {
-  if (over <= 0) return v;
-  uint64_t lo = uint32_t(v[0]) | (uint64_t(uint32_t(v[1])) << 32), hi = uint32_t(v[2]) | (uint64_t(uint32_t(v[3])) << 32);
-  if (over >= 16) {
-    lo = hi = 0;
-  } else if (over >= 8) {
-    lo = hi >> (8 * (over - 8));
-    hi = 0;
-  } else {
-    lo = (lo >> (8 * over)) | (hi << (64 - 8 * over));
-    hi >>= 8 * over;
-  }
-  return i32x4{int32_t(uint32_t(lo)), int32_t(uint32_t(lo >> 32)), int32_t(uint32_t(hi)), int32_t(uint32_t(hi >> 32))};
-}
 // A row of Kb < 16 bytes as one piece: every byte requested at once, the ones past the end replaced by zero.
 __device__ __forceinline__ i32x4 short_row(const uint8_t* row, int64_t Kb) {
   if (Kb <= 0) return i32x4{0, 0, 0, 0};

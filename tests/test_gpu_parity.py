@@ -622,6 +622,29 @@ def test_conv_tile_instances(dtype, k, natural, shape):
             assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# Small images in one launch (conv_images_kernel), both forms: images and weight rows shorter than a 16-byte piece, several images
+# in a tile, tiles cut by the end, windows that reach past the image on all sides, the longest contraction.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("n,c,h,w,o,kh,kw,s,p", [
+    (1, 1, 1, 1, 1, 1, 1, 1, 0), (1, 1, 2, 3, 33, 1, 1, 1, 0), (3, 1, 1, 1, 5, 1, 1, 1, 1), (1, 3, 8, 8, 4, 3, 3, 1, 0), (40, 2, 3, 5, 7, 2, 3, 1, 1), (2, 7, 9, 4, 32, 5, 5, 2, 2),
+    (1, 13, 31, 32, 48, 3, 3, 1, 1), (4, 14, 32, 20, 26, 1, 1, 1, 1), (1, 2, 190, 11, 9, 7, 3, 3, 3), (2, 15, 12, 12, 64, 5, 5, 1, 2), (1, 5, 4, 192, 40, 4, 9, 2, 4),
+    (3, 12, 6, 6, 31, 6, 6, 1, 0), (64, 1, 4, 4, 65, 4, 4, 1, 3), (2, 4, 7, 7, 16, 9, 9, 1, 1), (1, 1, 40, 40, 8, 22, 23, 1, 5)])
+def test_conv2d_small_images(n, c, h, w, o, kh, kw, s, p, dtype, odt):
+    x, wt = gen(dtype, (n, c, h, w), 9500 + h), gen(dtype, (o, c, kh, kw), 9600 + o, (c * kh * kw) ** -0.5)
+    want = torch.nn.functional.conv2d(x.double(), wt.double(), stride=s, padding=p)
+    res = gen("i32" if dtype == "i8" else ("bf16" if odt == torch.bfloat16 else "f32"), tuple(want.shape), 9700 + o)
+    xd, wd = x.to(DEV), wt.to(DEV)
+    buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
+    out = buf[256:256 + want.numel()].view(want.shape)
+    for fn in (gs.conv2d_direct, gs.conv2d_im2col):
+        for residual, act in ((None, gs.GS_ACT_NONE), (res, gs.GS_ACT_RELU)):
+            ref = want if residual is None else (want + res.double()).clamp_min(0)
+            ref = ref.numpy().astype(np.int64) if dtype == "i8" else ref.numpy()
+            fn(xd, wd, (s, s), (p, p), act=act, out=out, residual=None if residual is None else residual.to(DEV))
+            assert_parity(out, ref, what=fn.__name__)
+            assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
+
+
 # The same instances with channels that do not fill the last chunk: one short, one more than the chunk before, and 1x1
 # steps that lack whole chunks.  Infinities in the last channel and in the channels that follow it in memory.
 @pytest.mark.parametrize("shape", tile_instances.SHAPES[1:])
