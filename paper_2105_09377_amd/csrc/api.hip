@@ -179,6 +179,23 @@ size_t direct_workspace(int dtype, const ConvShape& cs, bool least) {
   return size_t(round_up(int64_t(conv_weight_workspace(dtype, cs.O, cs.C, cs.Kh, cs.Kw, least)), 256) + 256 + split_scratch(dtype, cs));
 }
 
+// Arguments of a convolution on weights as they come.
+ConvArgs unpacked_args(const gs_ap* act, const gs_ap* w, const gs_ap* residual, int actfn, const gs_ap* out, const ConvShape& cs) {
+  ConvArgs a;
+  memset(&a, 0, sizeof(a));
+  a.act = act->data;
+  a.wr = w->data;
+  a.out = out->data;
+  a.residual = residual ? residual->data : nullptr;
+  a.in_dtype = act->dtype;
+  a.out_dtype = out->dtype;
+  a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = cs.Kh; a.Kw = cs.Kw;
+  a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ph = cs.Ph; a.Pw = cs.Pw; a.Ho = cs.Ho; a.Wo = cs.Wo;
+  a.relu = actfn == GS_ACT_RELU;
+  a.ksplit = 1;
+  return a;
+}
+
 // Arguments of the direct convolution on the packed weights `packed`.
 ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_ap* out, const ConvShape& cs, void* packed,
                    const PackedLayout& layout) {
@@ -204,6 +221,19 @@ ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_
     a.wblk = static_cast<const uint8_t*>(packed) + conv_blocked_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
   a.relu = actfn == GS_ACT_RELU;
   return a;
+}
+
+// The rewritten form in one launch, on weights as they come (a.wr); hipErrorInvalidValue where no kernel does it.
+// A window of one pixel: the rows of the matrix are the pixels themselves, read where they lie.  Small images: they are
+// formed on chip.  Of the layers that both take, those of whole steps of channels (128 bytes) are faster as pixels (1
+// image of 64 channels 14x14 -> 64 bf16 3.7 us against 4.6, of 256 8x8 -> 512 at stride 2 3.7 against 5.8), the
+// others as images (16 of 24 channels 9x9 -> 32 5.9 against 4.3, 1 of 32 channels 38x14 -> 24 int8 at stride 2 6.4 against 4.4).
+hipError_t conv_one_launch(const ConvArgs& a, hipStream_t s) {
+  const bool point = a.Kh == 1 && a.Kw == 1 && a.Ph == 0 && a.Pw == 0;
+  const bool steps = int64_t(a.C) * int64_t(dtype_size(a.in_dtype)) % 128 == 0;
+  hipError_t e = point && steps ? launch_conv_point(a, s) : launch_conv_images(a, nullptr, s);
+  if (e == hipErrorInvalidValue && point) e = steps ? launch_conv_images(a, nullptr, s) : launch_conv_point(a, s);
+  return e;
 }
 
 // Row stride of the im2col matrix (and of the padded weight matrix): K rounded up to the 32-byte
@@ -544,6 +574,18 @@ int glenside_conv2d_direct_static(const gs_ap* act, const gs_ap* w, const int64_
   return glenside_conv2d_direct(act, w, stride, pad, residual, actfn, out, ws, kStaticScratchBytes, stream);
 }
 
+}  // extern "C"
+
+int gs::conv2d_one_launch(const gs_ap* act, const gs_ap* w, const int64_t stride[2], const int64_t pad[2], const gs_ap* out,
+                          void* stream) {
+  ConvShape cs;
+  if (conv_shape(act, w, stride, pad, &cs) || conv_check_io(act, w, nullptr, GS_ACT_NONE, out, cs)) return -1;
+  const hipError_t e = conv_one_launch(unpacked_args(act, w, nullptr, GS_ACT_NONE, out, cs), static_cast<hipStream_t>(stream));
+  return e == hipErrorInvalidValue ? -1 : launch_status(e);
+}
+
+extern "C" {
+
 int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
                            const int64_t pad[2], const gs_ap* residual, int actfn, gs_ap* out,
                            void* workspace, size_t workspace_bytes, void* stream) {
@@ -562,25 +604,8 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   uint8_t* cols = static_cast<uint8_t*>(workspace);
   uint8_t* wpad = cols + round_up(M * ld * esz, 256);
 
-  ConvArgs a;
-  memset(&a, 0, sizeof(a));
-  a.act = act->data;
-  a.wr = w->data;
-  a.out = out->data;
-  a.residual = residual ? residual->data : nullptr;
-  a.in_dtype = act->dtype;
-  a.out_dtype = out->dtype;
-  a.N = cs.N; a.C = cs.C; a.H = cs.H; a.W = cs.W; a.O = cs.O; a.Kh = cs.Kh; a.Kw = cs.Kw;
-  a.Sh = cs.Sh; a.Sw = cs.Sw; a.Ph = cs.Ph; a.Pw = cs.Pw; a.Ho = cs.Ho; a.Wo = cs.Wo;
-  a.relu = actfn == GS_ACT_RELU;
-  // Small images: the rows of the matrix are formed on chip, in the launch that multiplies them.
-  hipError_t e = launch_conv_images(a, nullptr, s);
-  if (e != hipErrorInvalidValue) return launch_status(e);
-  // A window of one pixel: the rows of the matrix are the pixels themselves, read where they lie.
-  if (cs.Kh == 1 && cs.Kw == 1 && cs.Ph == 0 && cs.Pw == 0) {
-    e = launch_conv_point(a, s);
-    if (e != hipErrorInvalidValue) return launch_status(e);
-  }
+  const hipError_t one = conv_one_launch(unpacked_args(act, w, residual, actfn, out, cs), s);
+  if (one != hipErrorInvalidValue) return launch_status(one);
 
   // flatten (windows (access activations 1) (C Kh Kw) (1 Sh Sw)), rows padded to 16 bytes.
   WindowsArgs wa;
@@ -598,7 +623,7 @@ int glenside_conv2d_im2col(const gs_ap* act, const gs_ap* w, const int64_t strid
   }
   wa.fill_bits = 0;
   wa.out_row_stride = ld;
-  e = launch_windows(wa, s);
+  hipError_t e = launch_windows(wa, s);
   if (e != hipSuccess) return launch_status(e);
 
   // flatten (access weights 1): already ((O),(K)) in memory; copied only when rows need padding.

@@ -339,13 +339,16 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 hipError_t conv_tile_forced(const ConvArgs& a, int way, bool launch, int* out, hipStream_t s);
 // 1x1 windows without padding on unpacked weights (a.wr), where a kernel takes them: hipErrorInvalidValue otherwise.
 hipError_t launch_conv_point(const ConvArgs& a, hipStream_t s);
+// The im2col form of a convolution where one launch does it without a workspace: a status, or -1 (nothing launched).
+int conv2d_one_launch(const gs_ap* act, const gs_ap* w, const int64_t stride[2], const int64_t pad[2], const gs_ap* out, void* stream);
 // Split the channel sum of this shape?  Returns 1, 2 or 4 (host heuristic: few tiles, many chunks).
 int conv_pick_ksplit(int in_dtype, int N, int C, int O, int Ho, int Wo);
 // True where some direct kernel is sure to take the layer (its patch fits the LDS, a tile spans few images);
 // only the shape is read.
 bool conv_direct_fits(const ConvArgs& a);
-// True where the producer / consumer kernel takes the layer; only the shape is read.
+// True where the producer / consumer kernel, or conv_tile_kernel, takes the layer; only the shape is read.
 bool conv_pipelined_takes(const ConvArgs& a);
+bool conv_tiles_take(const ConvArgs& a);
 
 struct ReduceArgs {       // out[r] = reduce over `cols` contiguous values
   const void* in;

@@ -673,6 +673,17 @@ bool conv_pipelined_takes(const ConvArgs& a_in) {
   return takes(ksplit) || (ksplit > 1 && takes(1));
 }
 
+bool conv_tiles_take(const ConvArgs& a_in) {
+  ConvArgs a = a_in;
+  a.Cpad = conv_cpad(a.in_dtype, a.C);
+  a.ksplit = 1;
+  if (conv_is_smallc(a.in_dtype, a.C) || !conv_blocked_weight_bytes(a.in_dtype, a.O, a.C, a.Kh, a.Kw)) return false;
+  a.wblk = &a;      // asked for, never read
+  const ConvGeom g = conv_geom(a);
+  if (g.M == 0 || a.O == 0) return false;
+  return (a.in_dtype == GS_I8 ? plan_tiles<I8Traits>(a, g) : plan_tiles<Bf16Traits>(a, g)).shape >= 0;
+}
+
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
   return a.in_dtype == GS_I8 ? launch_conv_t<I8Traits>(a, s) : launch_conv_t<Bf16Traits>(a, s);
 }

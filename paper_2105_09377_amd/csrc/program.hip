@@ -7,8 +7,8 @@
 //   * evaluates a program by dispatching its nodes to the library's kernels: the pattern the
 //     paper maps to hardware, (compute dotProd (cartProd ?a0 ?a1)) (Fig. 3, Sec. 5.2), becomes one
 //     MFMA contraction without the Cartesian product ever existing in memory; the whole listing
-//     of Fig. 2a, and the whole of Fig. 5 that Fig. 4's rules derive from it where that is faster, becomes the
-//     direct convolution; (compute reduceX (windows ...)) becomes the fused
+//     of Fig. 2a becomes the direct convolution, the whole of Fig. 5 that Fig. 4's rules derive from it the
+//     direct or the im2col convolution, whichever is faster; (compute reduceX (windows ...)) becomes the fused
 //     pooling kernel; (compute reduceX (pair a b)) the element-wise kernel; every other
 //     transformer is a descriptor change (access, squeeze, flatten, reshape, outermost slice) or
 //     one of the data-moving kernels (transpose, slice, concat, pair, pad, windows); zero padding
@@ -30,7 +30,6 @@
 #include <string>
 #include <vector>
 
-extern "C" size_t glenside_conv2d_direct_workspace(const gs_ap*, const gs_ap*, const int64_t*, const int64_t*);
 
 namespace {
 
@@ -507,45 +506,61 @@ struct ConvMatch {
   TreeP act, weights;
   std::vector<int64_t> window, stride;
   int64_t pad[2] = {0, 0};
+  bool flat = false;       // the flat form
+  bool im2col = false;     // evaluated by glenside_conv2d_im2col
 };
-// Is some direct kernel sure to take the convolution?  `flat`: and is it the faster way than the listing node
-// by node (windows gathered in memory, one contraction, one transposition)?
-//
-// The lines were drawn over 1267 layers, a whole evaluation with the packing of the weights (us, direct / node by
-// node), before conv_tile_kernel took most layers of whole channel chunks from the kernels named here and packing
-// became one launch.  As a caller met it then, passes among others, the rule was 1.03 times the better of the two
-// on average (at worst 1.65), 1.18 always directly, 1.21 never.  Now, over 400 others: 1.28, 1.22 and 1.41.  No
-// layer is more than 6 % slower than it was, but all 153 that conv_tile_kernel takes are faster directly, by 1.27
-// to 5 times, and the rule still sends 75 of them node by node, 32 of 33 with 5x5 windows among them (3 of 160
-// channels in bytes, 43x21, 5x5 to 23: 11.8 / 43.4).
-//
-//   where the producer / consumer kernel takes windows of up to 3x3 it is the faster one nearly always (64
-//   channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192; 1x1 on average 0.8 of the time);
+// Bytes of the gathered windows below which a launch more costs more than what it saves.
+constexpr int64_t kFewWindows = 512 << 10;
+
+// How the flat form is evaluated; Fig. 2a always is the direct convolution, bit for bit.  The two ways are one launch for the packing of the weights and one for the
+// convolution, against the windows gathered in memory (unless one launch does all, see conv2d_one_launch) and the
+// contraction that stores its result transposed.  Over 70 layers of up to 32 images of 16 to 64 channels, 14x14 to
+// 56x56, us, direct / im2col:
+//   1x1 windows: im2col, mostly one launch (1 image of 32 channels 25x36 -> 120 bf16 7.4 / 5.2, 23 of 48, 48x32,
+//   padded, -> 128 19.4 / 13.0; of 36 layers one was slower, 9 of 16 channels 41x34 in bytes, padded, 10.7 / 12.1);
+//   larger ones directly where conv_tile_kernel takes them and the windows are not few (21 of 48, 29x26, 3x3 stride 2
+//   8.7 / 11.2; 5 of 48, 51x55, 3x3 9.9 / 19.3); with few windows the launches decide and either way takes 6 to 8;
+//   what conv_tile_kernel does not take, directly by the lines below, drawn over 1267 layers on the other kernels (us,
+//   direct / gather, contraction and transposition in launches of their own, as the flat listing went then):
+//   the producer / consumer kernel nearly always (64 channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192);
 //   the general and the few-channel kernel need positions to fill the chip, more for large windows of two-byte
-//   values, and form the windows once for every 64 output channels (48 channels, 3x3: 0.6 of the time at 6e4
-//   positions, 1.3 times at 2e3; 64 images of 3 channels, 112x115, 5x5 to 64: 106 / 422; 256 of 8 channels,
-//   14x15, 5x5 to 256: 173 / 41; 16 of 96, 57x58, 5x5 stride 2 to 128: 60 / 78 in bytes, 100 / 65 in bf16);
+//   values, and form the windows once for every 64 output channels (64 images of 3 channels, 112x115, 5x5 to 64:
+//   106 / 422; 256 of 8 channels, 14x15, 5x5 to 256: 173 / 41);
 //   short windows (in bytes, times the stride and 2 for odd rows, which are read pixel by pixel) are over before
 //   the launches of the other way are issued, 17 us: 2 images of 16 channels, 25x38, 3x3 stride 2 13.3 / 17.1
-//   from the caller's side, 11.8 / 10.7 on the device; with more bytes, 2 of 32, 51x47, padded, 3x3 stride 2: 29.9 / 18.1;
+//   from the caller's side; with more bytes, 2 of 32, 51x47, padded, 3x3 stride 2: 29.9 / 18.1;
 //   strides above 2 stage many times the pixels that are used (8 of 512 channels, 28x28, 1x1 stride 4: 234 / 15).
-bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result, bool flat) {
+struct ConvShapes {
+  gs::ConvArgs a;
+  bool valid = false;      // the convolution's entry points take it
+  int64_t gathered = 0;    // bytes of its windows
+};
+ConvShapes conv_shapes(const ConvMatch& m, const Env& env, const Shape& w, const Shape& result) {
+  ConvShapes c;
   Shape act;
-  if (infer(m.act, env, &act)) return false;
+  if (infer(m.act, env, &act)) return c;
   act.na = 1;
   Shape weights = w;
   weights.na = 1;
   const gs_ap aa = make_ap(nullptr, act), wa = make_ap(nullptr, weights);
   const int64_t stride[2] = {m.stride[1], m.stride[2]};
-  if (act.numel() == 0 || glenside_conv2d_direct_workspace(&aa, &wa, stride, m.pad) == 0) return false;
-  gs::ConvArgs a;
+  if (act.numel() == 0 || glenside_conv2d_direct_workspace(&aa, &wa, stride, m.pad) == 0) return c;
+  gs::ConvArgs& a = c.a;
   memset(&a, 0, sizeof(a));
   a.in_dtype = act.dtype;
+  a.out_dtype = act.dtype == GS_I8 ? GS_I32 : GS_BF16;
   a.N = int(act.d[0]); a.C = int(act.d[1]); a.H = int(act.d[2]); a.W = int(act.d[3]);
   a.O = int(w.d[0]); a.Kh = int(w.d[2]); a.Kw = int(w.d[3]);
   a.Sh = int(stride[0]); a.Sw = int(stride[1]); a.Ph = int(m.pad[0]); a.Pw = int(m.pad[1]);
   a.Ho = int(result.d[2]); a.Wo = int(result.d[3]);
-  if (!gs::conv_direct_fits(a)) return false;
+  c.valid = true;
+  c.gathered = int64_t(a.N) * a.Ho * a.Wo * a.C * a.Kh * a.Kw * int64_t(gs::dtype_size(a.in_dtype));
+  return c;
+}
+// Directly?  Only where some direct kernel is sure to take it.
+bool direct_fits(const ConvShapes& c, bool flat) {
+  const gs::ConvArgs& a = c.a;
+  if (!c.valid || !gs::conv_direct_fits(a)) return false;
   if (!flat) return true;
   const bool small_window = a.Kh <= 3 && a.Kw <= 3;
   const int64_t plane = int64_t(a.Ho) * a.Wo, esz = int64_t(gs::dtype_size(a.in_dtype));
@@ -554,7 +569,11 @@ bool direct_fits(const ConvMatch& m, const Env& env, const Shape& w, const Shape
     const int64_t window_bytes = int64_t(a.C) * a.Kh * a.Kw * esz;
     if (small_window && a.C * esz >= 32 && window_bytes * std::max(a.Sh, a.Sw) * (1 + a.W % 2) <= 1152) return true;
   }
-  return small_window && gs::conv_pipelined_takes(a);
+  return (small_window && gs::conv_pipelined_takes(a)) || (c.gathered >= kFewWindows && gs::conv_tiles_take(a));
+}
+// 1x1 windows that one launch does not do as it is (see eval_conv2d), few of them, without padding.
+bool point_windows(const ConvShapes& c) {
+  return c.valid && c.a.Kh == 1 && c.a.Kw == 1 && c.gathered > 0 && c.a.O > 0 && (c.a.Ph + c.a.Pw > 0 || c.gathered >= kFewWindows);
 }
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
@@ -563,7 +582,7 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   if (perm != std::vector<int64_t>({0, 3, 1, 2})) return false;
   const TreeP& sq = arg(t, 0);
   if (!is_call(sq, "squeeze", 2) || !env.integer(arg(sq, 1), &one) || one != 1) return false;
-  const bool flat = is_call(arg(sq, 0), "reshape", 3);
+  const bool flat = m->flat = is_call(arg(sq, 0), "reshape", 3);
   const TreeP& cp = flat ? arg(arg(sq, 0), 0) : arg(sq, 0);
   if (!is_call(cp, "compute", 2) || arg(cp, 0)->kind != Tree::kSymbol || arg(cp, 0)->sym != "dotProd") return false;
   const TreeP& c = arg(cp, 1);
@@ -587,24 +606,33 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
     return false;
   // (N, O, H', W'): what the reshape of the flat form must restore
   if (all.d.size() != 4 || all.d[0] != a.d[0] || all.d[1] != b.d[0] || all.d[2] != win.d[2] || all.d[3] != win.d[3]) return false;
-  // Symmetric zero padding of H and W is the convolution's own where a kernel is sure to take it so: a patch
-  // row with odd padding is up to two pixels longer than a row of the padded tensor, and may be the one
-  // that no longer fits.
+  // Symmetric zero padding of H and W is the convolution's own, for the direct kernels where one is sure to take it
+  // so: a patch row with odd padding is up to two pixels longer than a row of the padded tensor, and may be the
+  // one that no longer fits.
+  ConvMatch folded = *m;
+  ConvShapes with_pad;
   TreeP inner;
   int64_t lo[GS_MAX_RANK], hi[GS_MAX_RANK];
   if (strip_pads(m->act, env, 2, &inner, lo, hi) && lo[2] == hi[2] && lo[3] == hi[3] && lo[2] <= 64 && lo[3] <= 64) {
-    ConvMatch folded = *m;
     folded.act = inner;
     folded.pad[0] = lo[2];
     folded.pad[1] = lo[3];
-    if (direct_fits(folded, env, b, all, flat)) {
-      *m = folded;
-      return true;
-    }
+    with_pad = conv_shapes(folded, env, b, all);
   }
-  // What no direct kernel is sure to take (strides, windows and rows too large for the LDS, more images
-  // in a tile than it counts), or takes longer for, the flat form evaluates node by node.
-  return !flat || direct_fits(*m, env, b, all, flat);
+  folded.im2col = flat && point_windows(with_pad);
+  if (folded.im2col || direct_fits(with_pad, flat)) {
+    *m = folded;
+    return true;
+  }
+  const ConvShapes as_is = conv_shapes(*m, env, b, all);
+  if (!flat || direct_fits(as_is, flat)) return true;
+  // What no direct kernel is sure to take (strides, windows and rows too large for the LDS, more images in a tile
+  // than it counts), or takes longer for; node by node what the im2col entry point refuses, and padding that is
+  // not the same on both sides, which the gather of the windows takes as it is.
+  if (!with_pad.valid || with_pad.gathered == 0 || with_pad.a.O == 0) return false;
+  *m = folded;
+  m->im2col = true;
+  return true;
 }
 
 struct Evaluator {
@@ -878,13 +906,19 @@ struct Evaluator {
     w.s.na = 1;
     gs_ap aa = make_ap(a.data, a.s), wa = make_ap(w.data, w.s);
     const int64_t stride[2] = {m.stride[1], m.stride[2]}, *pad = m.pad;
-    const size_t cws = glenside_conv2d_direct_workspace(&aa, &wa, stride, pad);
+    const size_t cws = m.im2col ? glenside_conv2d_im2col_workspace(&aa, &wa, stride, pad) : glenside_conv2d_direct_workspace(&aa, &wa, stride, pad);
     if (cws == 0) return GS_ERR_UNSUPPORTED;
     void* scratch = alloc(int64_t(cws), &st);
     if (st) return st;
     if ((st = materialize(s, dst, out))) return st;
     if (dry) return GS_OK;
     gs_ap oa = make_ap(out->data, s);
+    if (m.im2col) return glenside_conv2d_im2col(&aa, &wa, stride, pad, nullptr, GS_ACT_NONE, &oa, scratch, cws, stream);
+    // Few windows: one launch instead of two, where a kernel does it.
+    if (m.flat && s.numel() > 0 && s.numel() / w.s.d[0] * (w.s.numel() / w.s.d[0]) * int64_t(gs::dtype_size(w.s.dtype)) < kFewWindows) {
+      st = gs::conv2d_one_launch(&aa, &wa, stride, pad, &oa, stream);
+      if (st >= 0) return st;
+    }
     return glenside_conv2d_direct(&aa, &wa, stride, pad, nullptr, GS_ACT_NONE, &oa, scratch, cws, stream);
   }
 

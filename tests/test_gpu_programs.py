@@ -160,6 +160,23 @@ def test_matmul_listing_and_its_rewrites(dtype, dims):
     assert_parity(gs.program_eval(systolic, dev), ref, what="systolicArray (Fig. 3)", slack=slack)
 
 
+# Both listings where one launch or the im2col entry point evaluates them: 1x1 windows with and without padding, whole
+# and broken steps of channels, small images, few windows just below and above the line, strides that no direct kernel takes.
+@pytest.mark.parametrize("dtype,odt", [("i8", torch.int32), ("bf16", torch.bfloat16), ("bf16", torch.float32)])
+@pytest.mark.parametrize("n,c,h,w,o,k,s,p", [
+    (2, 64, 14, 15, 40, 1, 1, 0), (3, 48, 17, 22, 33, 1, 2, 0), (9, 16, 41, 34, 20, 1, 1, 1), (1, 33, 9, 7, 65, 1, 2, 1), (1, 24, 60, 70, 10, 1, 1, 0),
+    (5, 32, 14, 18, 48, 3, 1, 0), (1, 48, 31, 43, 50, 3, 2, 0), (2, 64, 23, 44, 30, 3, 1, 1), (4, 48, 18, 25, 17, 3, 1, 1), (2, 7, 20, 20, 9, 3, 4, 1), (1, 40, 9, 9, 5, 4, 1, 0)])
+def test_convolution_listings_in_one_launch_and_as_im2col(n, c, h, w, o, k, s, p, dtype, odt):
+    cfg = synth.conv_layer(n, c, h, w, o, k, s, p, dtype, 9650 + c + o)
+    want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p).numpy()
+    want = want.astype(np.int64) if dtype == "i8" else want
+    dev = {"activations": cfg["x"].to(DEV), "weights": cfg["w"].to(DEV)}
+    ints = dict(C=c, Kh=k, Kw=k, Sh=s, Sw=s, Ph=p, Pw=p)
+    meta = {name: (tuple(v.shape), v.dtype) for name, v in dev.items()}
+    for text in (listings.CONV2D_PADDED, gs.program_rewrite(listings.CONV2D_PADDED, "im2col", meta, ints)):
+        assert_parity(gs.program_eval(text, dev, ints, out_dtype=odt), want, what=text)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f32"])
 def test_maxpool_listing(dtype):
     x = {"i8": synth.uniform_int8((3, 5, 17, 18), -127, 127, 9600), "bf16": synth.normal_bf16((3, 5, 17, 18), 1.0, 9600),
