@@ -5,6 +5,8 @@ relative error (floor 1e-3 * max|ref| on the denominator).  Sizes span several t
 tails of the kernels' 32/64/128-wide tiles.
 """
 
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -620,6 +622,27 @@ def test_conv_tile_instances(dtype, k, natural, shape):
             ref = want if res is None else (want + res.double()).clamp_min(0)
             assert_parity(out, ref.numpy().astype(np.int64) if dtype == "i8" else ref.numpy(), what=f"{plan} {(n, c, h, w)} stride {s}")
             assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
+
+
+# Rows of any length in 16-byte vectors (reduce_rows_any_kernel): the rows' first and last vectors shared in every phase,
+# each lane group, a workgroup per row, several rounds of rows, the tensor ending inside a vector; lowest values at the rows'
+# ends, which a neighbour's value must not replace.
+@pytest.mark.parametrize("op", [gs.GS_SUM, gs.GS_MAX])
+@pytest.mark.parametrize("dtype,odt", [("f32", None), ("i32", None), ("i8", None), ("bf16", torch.bfloat16), ("bf16", torch.float32)])
+@pytest.mark.parametrize("rows,cols", [(16411, 67), (8193, 129), (4099, 259), (2053, 517), (1031, 1029), (130, 2403), (17, 9001), (3, 40003), (40011, 131)])
+def test_reduce_rows_of_any_length(rows, cols, dtype, odt, op):
+    x = gen(dtype, (rows, cols), 9800 + cols)
+    if op == gs.GS_MAX:
+        x[1::3] = LOWEST[dtype] if dtype in ("i8", "i32") else float("-inf")
+    got = gs.reduce(x.to(DEV), 1, op, out_dtype=odt)
+    if op == gs.GS_MAX:
+        assert torch.equal(got.cpu().double(), x.double().amax(1))
+    elif dtype in ("i8", "i32"):
+        assert torch.equal(got.cpu().long(), x.long().sum(1))
+    else:       # pairwise sums: 2^-24 per level of some log2(cols) + 3 of the magnitudes, then the store's rounding
+        want = x.double().sum(1)
+        slack = (math.log2(cols) + 3) * 2.0 ** -24 * x.double().abs().sum(1) + (2.0 ** -8 if odt == torch.bfloat16 else 0) * want.abs()
+        assert ((got.cpu().double() - want).abs() <= slack).all()
 
 
 # Small images in one launch (conv_images_kernel), both forms: images and weight rows shorter than a 16-byte piece, several images
