@@ -2,7 +2,7 @@
 //
 // Both operands are K-contiguous (each access index of a0 / a1 owns one contiguous compute
 // element), which is exactly the operand order the MFMA wants, so tiles are copied global -> LDS
-// with 16-byte loads and no transposition.  A workgroup of 4 or 8 waves owns a BM x BN output tile
+// with 16-byte loads and no transposition.  A workgroup of 4 to 16 waves owns a BM x BN output tile
 // (the concat-on-access-dimensions blocking of Sec. 5.4); the K loop walks 128-byte slabs (the
 // pair/reduceSum blocking on the compute dimension) through two to four LDS buffers, the next slabs'
 // global loads in flight while the current one feeds the MFMAs; fragment reads run one K step
@@ -292,8 +292,9 @@ __device__ __forceinline__ i32x4 short_row(const uint8_t* row, int64_t Kb) {
 // Any alignment, any K of at least 16 bytes.  Slabs of 128 bytes of K go global -> registers -> LDS;
 // two slabs are in flight in registers while one is multiplied and the next sits in the other LDS
 // buffer.  Bound by LDS traffic (a slab of a 128x128 tile is written once, 436 cycles at 75 bytes per
-// cycle, and read as 98 KB of fragments, 610 at 160, against 256-512 of MFMAs).  2047 x 1531 x 1001:
-// e4m3 70.6 -> 13.2 us, int8 74.7 -> 15.1, bf16 155.8 -> 18.1 (before: 16-byte pieces gathered byte by byte).
+// cycle, and read as 98 to 128 KB of fragments, 610 to 800 at 160, against 256-512 of MFMAs) and by what rows
+// off the 16-byte boundary cost the loads (2047 x 1531 x 1001 e4m3 13.5 us, x 1008 10.5).  2047 x 1531 x 1001:
+// e4m3 70.6 -> 12.6 us, int8 74.7 -> 15.1, bf16 155.8 -> 16.5 (first: 16-byte pieces gathered byte by byte).
 // SHORT: rows of fewer than 16 bytes (empty ones included): one piece per row, one MFMA step, and the
 // result is what takes the time.
 template <typename TR, int BM, int BN, int WGM, int WGN, bool SHORT>
@@ -816,7 +817,6 @@ __global__ void __launch_bounds__(WGM * WGN * 64) gemm_nt_dma_kernel(GemmArgs a)
   });
   __syncthreads();   // every wave is done with the slabs: their memory becomes epilogue staging
 
-  static_assert(NW * 32 * (WN * 4 + 16) <= NS * (kXBytes + kYBytes), "staging must fit in the slab buffers");
   write_tile<TR, MI, NJ>(a, box, acc, i0 + wm * WM, j0 + wn * WN, lds + wave * (32 * (WN * 4 + 16)), lane);
 }
 
@@ -836,7 +836,8 @@ static hipError_t launch_tiles(const GemmArgs& a, int bm, int bn, int threads, i
 }
 template <typename TR, int BM, int BN, int WGM, int WGN, int SB, int NS>
 static hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
-  constexpr int lds_bytes = NS * (BM + BN) * SB;
+  constexpr int slab_bytes = NS * (BM + BN) * SB, staging = WGM * WGN * 32 * (BN / WGN * 4 + 16);
+  constexpr int lds_bytes = slab_bytes > staging ? slab_bytes : staging;     // (the staging of the results takes the slabs' place)
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
   return launch_tiles<gemm_nt_dma_kernel<TR, BM, BN, WGM, WGN, SB, NS>>(a, BM, BN, WGM * WGN * 64, lds_bytes, s);
 }
@@ -873,7 +874,12 @@ static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
   const int64_t t256 = tile_count(a.I, a.bm, 256) * tile_count(a.J, a.bn, 256);
   // extent a tile can fill: the block when the result is cut into blocks
   const int64_t fi = a.bm > 0 && a.bm < a.I ? a.bm : a.I, fj = a.bn > 0 && a.bn < a.J ? a.bn : a.J;
-  if (t256 >= 256 && fi >= 256 && fj >= 256) return launch_dma<TR, 256, 256, 2, 4, 128, 2>(a, s);
+  const int64_t slabs = ceil_div(a.K * TR::kEsz, kSlabBytes);
+  // Short K: the write-back of smaller tiles overlaps another tile's products (6271 x 7864 x 64 34.1 in 256x256
+  // tiles, 26.5 in 128x128).  Long K: from 180 tiles on the larger ones pay although they do not fill the chip (2272 x 5160 x
+  // 1536, 189 tiles, 46.7 in 128x128 tiles, 43.6).
+  if (((t256 >= 256 && slabs > 4) || (t256 >= 180 && slabs >= 16)) && fi >= 256 && fj >= 256)
+    return launch_dma<TR, 256, 256, 2, 4, 128, 2>(a, s);
   // few rows (a convolution's output channels against many positions) or few columns (100352 x 64 x 576
   // takes 32.2 against 36.2 in half-empty 128x128 tiles)
   if (a.I <= 64 && ceil_div(fj, 256) * ceil_div(a.J, fj) >= 192) return launch_dma<TR, 64, 256, 1, 4, 128, 2>(a, s);
@@ -882,11 +888,18 @@ static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
   if (few_tiles<TR>(a, &eight))
     return eight ? launch_ksplit<TR, 8, kDirect>(a, s) : launch_ksplit<TR, 4, kDirect>(a, s);
   if (t128 >= 192 && (a.bm <= 0 || fi >= 128) && (a.bn <= 0 || fj >= 128)) {
-    // one tile per compute unit: a third slab buffer takes the place of the second workgroup
-    // (2048^3: 25.3 against 29.9; with 512 tiles 49.2 against 40.1)
-    if (t128 <= 256) return launch_dma<TR, 128, 128, 2, 2, 128, 3>(a, s);
-    return launch_dma<TR, 128, 128, 2, 2, 128, 2>(a, s);
+    // One tile per compute unit: halves of it where K is short, since two workgroups overlap what is not a
+    // product (2936 x 1112 x 256 to f32 8.9 in 128x128 tiles, 8.3), else a third slab buffer in the place of the
+    // second workgroup (2048^3 20.9 against 23.1 in halves).  Eight waves: with four, what each does between its
+    // products lies open (2746 x 1408 x 2112 e4m3 14.1 against 13.5, 3230 x 1704 x 128 8.0 against 7.0, 7413 x 3000 x 256 25.9
+    // against 23.4; over 46 of 388 products of up to 8192 more than 3 % faster, one slower).
+    if (t128 <= 256 && slabs <= 16) return launch_dma<TR, 64, 128, 2, 4, 128, 3>(a, s);
+    if (t128 <= 256) return launch_dma<TR, 128, 128, 2, 4, 128, 3>(a, s);
+    return launch_dma<TR, 128, 128, 2, 4, 128, 2>(a, s);
   }
+  // more tiles of 64x64 than one round of the chip, fewer of 64x128, long K: 7519 x 240 x 7232 e4m3 31.7 / 25.1
+  if (t64 > 256 && slabs > 16 && tile_count(a.I, a.bm, 64) * tile_count(a.J, a.bn, 128) <= 256 && (a.bn <= 0 || fj >= 128))
+    return launch_dma<TR, 64, 128, 2, 4, 128, 3>(a, s);
   // 1024^3: 10.9 with two slab buffers, 7.9 with three, 7.4 with four; 1024 x 2048 x 1024, two
   // workgroups per compute unit: 11.4, 9.6, 9.9
   if (t64 <= 256) return launch_dma<TR, 64, 64, 2, 2, 128, 4>(a, s);
@@ -921,14 +934,21 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   bool eight;
   if (!is_short && few_tiles<TR>(v, &eight))
     return eight ? launch_ksplit<TR, 8, kStaged>(v, s) : launch_ksplit<TR, 4, kStaged>(v, s);
-  // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 13.2 us
-  // against 17.0 in 64x64 tiles, 1024 x 2048 x 1001 int8 (128 tiles) 13.4 against 12.6.  Results (or
+  // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 12.6 us
+  // against 16.9 in 64x64 tiles, 1702 x 1221 x 300 (140 tiles) 7.8 against 7.4.  One for each compute unit: 16 waves, whose
+  // loads and write-back overlap (13.5 with 8; 3000^3 bf16, 576 tiles, 97.7 against 91.3).  Fewer: 128x64 tiles where those are one
+  // round and 64x64 ones more (1103 x 1072 x 1893 e4m3 15.9 in 64x64 tiles, 12.3; 780 x 1730 x 987 bf16 16.1, 13.8).  Results (or
   // blocks) of up to 64 rows or columns would leave half of every tile empty (100000 x 10 x 65 bf16 to
   // bf16: 17.4 against 12.0; 64 x 40000 x 1001 bf16 to f32: 30.4 against 24.0).
   const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
   const int64_t fi = a.bm > 0 && a.bm < a.I ? a.bm : a.I, fj = a.bn > 0 && a.bn < a.J ? a.bn : a.J;
-  if (t128 >= 160 && fi > 64 && fj > 64)
-    return is_short ? launch_any<TR, 128, 128, 2, 4, true>(v, s) : launch_any<TR, 128, 128, 2, 4, false>(v, s);
+  if (t128 >= 160 && fi > 64 && fj > 64) {
+    if (is_short) return launch_any<TR, 128, 128, 2, 4, true>(v, s);
+    return t128 <= 256 ? launch_any<TR, 128, 128, 4, 4, false>(v, s) : launch_any<TR, 128, 128, 2, 4, false>(v, s);
+  }
+  if (!is_short && fi > 64 && tile_count(a.I, a.bm, 64) * tile_count(a.J, a.bn, 64) > 256 &&
+      tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 64) <= 256)
+    return launch_any<TR, 128, 64, 4, 2, false>(v, s);
   return is_short ? launch_any<TR, 64, 64, 2, 2, true>(v, s) : launch_any<TR, 64, 64, 2, 2, false>(v, s);
 }
 

@@ -168,6 +168,29 @@ def test_cartesian_dot_tile_edges(mnk, dtype, odt):
     assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
 
 
+# The tile shapes between one and two rounds of the chip, cut by both ends of the result: 64x128 (short K, and long K of few
+# columns), 128x128 with two and three slab buffers, 256x256 that do not fill the chip, and unaligned rows in 128x64 and in
+# 128x128 tiles of sixteen waves; K of one slab, a broken one and several.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("i8", torch.int32), ("fp8", torch.float32)])
+@pytest.mark.parametrize("mnk", [(1500, 2101, 64), (1499, 2104, 448), (1501, 2100, 4160), (2201, 2310, 192), (4610, 262, 4608), (3601, 3590, 2112),
+                                 (1103, 1073, 189), (1105, 1071, 1021), (1700, 2045, 131), (1701, 2047, 643)])
+def test_cartesian_dot_tile_shapes(mnk, dtype, odt):
+    m, n, k = mnk
+    a0, a1 = gen(dtype, (m, k), 1410 + m, 1.0), gen(dtype, (n, k), 1510 + n, 1.0 if dtype == "i8" else k ** -0.5)
+    buf = torch.full((m * n + 512,), 77, dtype=odt, device=DEV)
+    got = gs.cartesian_dot(a0.to(DEV), a1.to(DEV), out=buf[256:256 + m * n].view(m, n)).cpu().double()
+    x, y = torch.from_numpy(np.asarray(to_oracle(a0), dtype=np.float64)), torch.from_numpy(np.asarray(to_oracle(a1), dtype=np.float64))
+    want = x @ y.T
+    if dtype == "i8":
+        assert torch.equal(got, want)
+    else:       # fp32 sums of k products, pairwise in parts, and one rounding to bfloat16; 8-bit floats: see fp8_slack
+        slack = k * 2.0 ** -24 * (x.abs() @ y.abs().T) + (2.0 ** -8 * want.abs() if odt == torch.bfloat16 else 0)
+        if dtype == "fp8":
+            slack = slack + torch.from_numpy(fp8_slack(x.numpy(), y.numpy()))
+        assert ((got - want).abs() <= slack).all()
+    assert (buf[:256] == 77).all() and (buf[256 + m * n:] == 77).all()
+
+
 # Many 128x128 tiles that a narrow result would leave half empty, and the first width at which it does not.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("i8", torch.int32)])
 @pytest.mark.parametrize("mnk", [(20600, 64, 65), (64, 20600, 33), (20600, 65, 33), (65, 20600, 65), (1, 20600, 129), (20600, 1, 129)])
