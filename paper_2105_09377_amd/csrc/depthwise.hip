@@ -3,9 +3,10 @@
 // In the paper's operators (Table 1, Table 2) this is the concat, along the channel dimension, of
 // the 2D-convolution program of Fig. 2a applied to channel c of the activations and filter c of
 // the weights (slice ... 1 c c+1 / slice ... 0 c c+1): C independent one-channel convolutions.
-// No contraction over channels is left, so there is nothing for the matrix units: 2*Kh*Kw
-// operations per 2-byte input element.  The kernel is bound by memory traffic and is built like the
-// pooling kernel: every input byte leaves HBM once, however much the windows overlap.
+// No contraction over channels is left: 2*Kh*Kw operations per 2-byte input element.  The kernels are built
+// like the pooling kernel: every input byte leaves HBM once, however much the windows overlap.
+// depthwise_kernel multiplies and adds in scalar registers, depthwise_tile_kernel makes a contraction over
+// columns of it, with a banded matrix of the taps.
 //
 // A task is a contiguous run of the input: G whole planes (small images) or a band of rows of one
 // plane (large images).  Its workgroup copies the run into LDS with aligned 16-byte reads -- a plain
@@ -24,6 +25,7 @@ namespace {
 
 constexpr int kVX = 8;             // outputs per strip
 constexpr int kMaxVec = 8;         // 16-byte loads per thread and task
+constexpr int kDwTileLds = 40 * 1024;   // of a workgroup of depthwise_tile_kernel
 constexpr int kGuard = 64;         // bytes of LDS in front of the copy (reads of columns < 0 land here)
 
 struct DwArgs {
@@ -317,6 +319,211 @@ depthwise_kernel(DwArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Unit strides on the matrix units.  A tile is 16 x 16 results of one plane: for every filter row, a banded matrix of
+// the filter's taps (16 result columns x the 64 bytes of input columns around them) times the input rows in LDS
+// (those columns x 16 result rows), as one 16x16 MFMA.  Both operands are 16 bytes per lane: the input as it lies in a
+// padded row of LDS, the band from a row of zeros with the taps in its middle, read once per plane.  With columns on
+// the MFMA rows a lane holds four neighbouring results of a row.
+//
+// A band's zeros meet input values too, so an infinity or NaN in the 64 bytes reaches results that it is no
+// part of.  It makes them NaN, and a tile with a result that is not finite is worked out again tap by tap.
+//
+// What bounds it: a wave waits for its stores before it writes the next plane into LDS (loads and stores share a
+// counter), and each pair of tiles is a chain of LDS reads, products and stores.  The kernels of scalar
+// multiply-adds are bound by their instructions, 300 per eight results against some 60 per 512 here.  Errors
+// of f32 results against 64 bits are 0.90 to 0.95 of theirs.  See launch_depthwise_t for times.
+// ---------------------------------------------------------------------------------------------
+struct DwTileArgs {
+  const void* in;
+  const void* w;
+  void* out;
+  int relu, C, H, W, Ho, Wo, P;       // P: padding on every side
+  int G;                              // planes per task
+  int cpr;                            // 16-byte pieces of a row
+  int pitch, plane_lds, lds_w;        // LDS: bytes of a row, of a plane; where the taps are
+  int64_t planes, tasks;
+  int dx, dy, second;                 // from a pair's first tile to its second: columns, rows, bytes of LDS
+  FastDiv dcpr, dH, dT, dTX;          // pieces per row, rows, pairs of tiles per plane and in a row of them
+  int pieces;                         // of a plane
+};
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// K: window; OUT: GS_BF16, GS_F32 or GS_I32.
+template <typename T, int K, int OUT>
+__global__ void __launch_bounds__(256, 4) depthwise_tile_kernel(DwTileArgs a) {
+  constexpr int ESZ = int(sizeof(T)), E = 16 / ESZ;     // elements of a piece; zeros in front of a row too
+  constexpr bool INT = __is_same(T, int8_t);
+  using A = typename DwElem<T>::acc;
+  typedef A acc4_t __attribute__((ext_vector_type(4)));
+  constexpr int kBand = 96 * ESZ;                       // a row of taps: zeros around them on both sides
+  extern __shared__ __attribute__((aligned(16))) uint8_t dw_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* const in = static_cast<const T*>(a.in);
+  const int64_t plane_in = int64_t(a.H) * a.W;
+
+  // Pieces of a task: row by row, the last of a row moved down to its start (zeros behind the row's end).
+  // Where they come from and go to is the same for every task: bytes from its first plane's start; LDS offset, and in
+  // its low bit whether the row ends there.
+  i32x4 val[kMaxVec];
+  uint32_t src[kMaxVec], dst[kMaxVec];
+#pragma unroll
+  for (int u = 0; u < kMaxVec; ++u) {
+    uint32_t row, c, g, y;                              // (planes lie one behind the other)
+    a.dcpr.divmod(uint32_t(u * 256 + tid), &row, &c);
+    a.dH.divmod(row, &g, &y);
+    const int col = int(c) * E < a.W - E ? int(c) * E : a.W - E;
+    src[u] = (row * uint32_t(a.W) + uint32_t(col)) * ESZ;
+    dst[u] = (g * uint32_t(a.plane_lds) + (y + uint32_t(a.P)) * uint32_t(a.pitch) + (c + 1) * 16) | (int(c) + 1 == a.cpr ? 1u : 0u);
+  }
+  const int over = (a.cpr * E - a.W) * ESZ;             // bytes by which a row's last piece is moved down
+  auto gcount_of = [&](int64_t task) { return int(a.planes - task * a.G < a.G ? a.planes - task * a.G : a.G); };
+  auto issue_loads = [&](int64_t task) {
+    const int n = gcount_of(task) * a.pieces;
+    const uint8_t* const base = reinterpret_cast<const uint8_t*>(in + task * a.G * plane_in);
+#pragma unroll
+    for (int u = 0; u < kMaxVec; ++u)
+      if (u * 256 + tid < n) val[u] = __builtin_nontemporal_load(reinterpret_cast<const i32x4_any*>(base + src[u]));
+  };
+  int64_t task = blockIdx.x;
+  if (task >= a.tasks) return;
+  issue_loads(task);
+  // Cells around the planes stay zero for good.
+  for (int off = tid * 16; off < a.lds_w + a.G * K * kBand; off += 256 * 16) *reinterpret_cast<i32x4*>(dw_lds + off) = i32x4{0, 0, 0, 0};
+
+  const int n16 = lane & 15, grp = lane >> 4;
+  for (; task < a.tasks; task += gridDim.x) {
+    const int gcount = gcount_of(task);
+    __syncthreads();                                    // the previous task has been computed
+#pragma unroll
+    for (int u = 0; u < kMaxVec; ++u) {
+      if (u * 256 + tid < gcount * a.pieces) {
+        if (over) val[u] = row_piece_fix(val[u], dst[u] & 1 ? over : 0);      // uniform
+        *reinterpret_cast<i32x4*>(dw_lds + (dst[u] & ~1u)) = val[u];
+      }
+    }
+    for (int id = tid; id < gcount * K * K; id += 256) {
+      const int g = id / (K * K), i = id - g * (K * K), c = int((task * a.G + g) % a.C);
+      reinterpret_cast<T*>(dw_lds + a.lds_w + (g * K + i / K) * kBand)[32 + i % K] =
+          static_cast<const T*>(a.w)[int64_t(c) * (K * K) + i];
+    }
+    __syncthreads();
+    const int64_t plane0 = task * a.G;
+    if (task + gridDim.x < a.tasks) issue_loads(task + gridDim.x);
+
+    // Two tiles side by side (one above the other in planes of one column of tiles) at a time; a run of them for each
+    // wave.
+    const int pairs = gcount * int(a.dT.d);
+    int t = wave * pairs / 4;
+    const int t_end = (wave + 1) * pairs / 4;
+    int have = -1;
+    i32x4 band[K];
+    for (; t < t_end; ++t) {                            // uniform
+      uint32_t g, r, ty, tx;
+      a.dT.divmod(uint32_t(t), &g, &r);
+      a.dTX.divmod(r, &ty, &tx);
+      if (int(g) != have) {
+        have = int(g);
+        // band[m][k] = tap k - E - m + P: element j of this lane is k = grp E + j of row m = n16
+#pragma unroll
+        for (int dy = 0; dy < K; ++dy) {
+          const T* const from = reinterpret_cast<const T*>(dw_lds + a.lds_w + (have * K + dy) * kBand) + 32 + grp * E - E - n16 + a.P;
+          band[dy] = *reinterpret_cast<const i32x4_any*>(from);
+        }
+      }
+      const int x0 = int(tx) * (16 + a.dx), y0 = int(ty) * (16 + a.dy);
+      const uint8_t* const rows = dw_lds + have * a.plane_lds + (y0 + n16) * a.pitch + x0 * ESZ + grp * 16;
+      i32x4 x[2][K];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int dy = 0; dy < K; ++dy) x[q][dy] = *reinterpret_cast<const i32x4*>(rows + q * a.second + dy * a.pitch);
+      acc4_t acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+      for (int dy = 0; dy < K; ++dy)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if constexpr (INT) acc[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(band[dy], x[q][dy], acc[q], 0, 0, 0);
+          else acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, band[dy]), __builtin_bit_cast(bf16x8, x[q][dy]), acc[q], 0, 0, 0);
+        }
+      // This lane's results: of tile q row y0 + q dy + n16, columns x0 + q dx + 4 grp ..
+      if constexpr (!INT) {
+        float zero[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) zero[q] = (acc[q][0] * 0.0f + acc[q][1] * 0.0f) + (acc[q][2] * 0.0f + acc[q][3] * 0.0f);
+        const float z = zero[0] + zero[1];              // NaN if any of them is not finite
+        if (__any(z != z)) {
+#pragma unroll 1
+          for (int i = 0; i < 8; ++i) {
+            const int q = i >> 2;
+            const T* const cells = reinterpret_cast<const T*>(dw_lds + have * a.plane_lds + (y0 + q * a.dy + n16) * a.pitch) + E + x0 + q * a.dx + 4 * grp + (i & 3) - a.P;
+            const T* const taps = reinterpret_cast<const T*>(dw_lds + a.lds_w + have * K * kBand) + 32;
+            float sum = 0.0f;
+#pragma unroll 1
+            for (int dy = 0; dy < K; ++dy)
+#pragma unroll 1
+              for (int dx = 0; dx < K; ++dx)
+                sum += DwElem<T>::cvt(cells[dy * (a.pitch / ESZ) + dx]) * DwElem<T>::cvt(taps[dy * (kBand / ESZ) + dx]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (e == i) acc[e >> 2][e & 3] = sum;
+          }
+        }
+      }
+      if (a.relu) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[q][i] = acc[q][i] > A(0) ? acc[q][i] : A(0);
+      }
+      const int64_t oplane = (plane0 + have) * a.Ho;
+      if constexpr (OUT == GS_BF16) {
+        // The tiles' halves change places between neighbouring groups of lanes: then a lane holds eight neighbouring
+        // columns of one tile, lanes of even groups of the first.
+        uint32_t lo[2], hi[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          lo[q] = pack_bf16x2(acc[q][0], acc[q][1]);
+          hi[q] = pack_bf16x2(acc[q][2], acc[q][3]);
+        }
+        const auto l = __builtin_amdgcn_permlane16_swap(lo[0], lo[1], false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi[0], hi[1], false, false);
+        const i32x4 v = {int32_t(l[0]), int32_t(h[0]), int32_t(l[1]), int32_t(h[1])};
+        const int q = grp & 1, y = y0 + q * a.dy + n16, xs = x0 + q * a.dx + 8 * (grp >> 1);
+        if (y < a.Ho && xs < a.Wo) {
+          uint16_t* const dst = static_cast<uint16_t*>(a.out) + (oplane + y) * a.Wo + xs;
+          if (xs + 8 <= a.Wo) {
+            typedef int32_t i32x4_half __attribute__((ext_vector_type(4), aligned(2)));
+            *reinterpret_cast<i32x4_half*>(dst) = v;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 7; ++i)
+              if (xs + i < a.Wo) dst[i] = uint16_t(uint32_t(v[i >> 1]) >> (16 * (i & 1)));
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int y = y0 + q * a.dy + n16, xs = x0 + q * a.dx + 4 * grp;
+          if (y < a.Ho && xs < a.Wo) {
+            typedef int32_t i32x4_word __attribute__((ext_vector_type(4), aligned(4)));
+            A* const dst = static_cast<A*>(a.out) + (oplane + y) * a.Wo + xs;
+            if (xs + 4 <= a.Wo) {
+              *reinterpret_cast<i32x4_word*>(dst) = __builtin_bit_cast(i32x4, acc[q]);
+            } else {
+#pragma unroll
+              for (int i = 0; i < 3; ++i)
+                if (xs + i < a.Wo) dst[i] = acc[q][i];
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
 int dw_num_cus() {
   static int n = [] {
     int dev = 0, cus = 0;
@@ -421,8 +628,81 @@ hipError_t launch_depthwise_rows(const DepthwiseArgs& d, hipStream_t s) {
   return hipGetLastError();
 }
 
+// hipErrorInvalidValue where the kernel does not take the call.
+template <typename T>
+hipError_t launch_depthwise_tiles(const DepthwiseArgs& d, hipStream_t s) {
+  constexpr int ESZ = int(sizeof(T)), E = 16 / ESZ;
+  const int K = d.Kh;
+  if (d.Sh != 1 || d.Sw != 1 || K != d.Kw || (K != 3 && K != 5) || d.Ph != d.Pw || d.Ph > K / 2 || d.W < E) return hipErrorInvalidValue;
+  DwTileArgs a;
+  memset(&a, 0, sizeof(a));
+  a.in = d.in; a.w = d.w; a.out = d.out; a.relu = d.relu;
+  a.C = d.C; a.H = d.H; a.W = d.W; a.Ho = d.Ho; a.Wo = d.Wo; a.P = d.Ph;
+  a.planes = int64_t(d.N) * d.C;
+  if (a.planes == 0 || d.Ho <= 0 || d.Wo <= 0) return hipSuccess;
+  if (a.planes * d.H * d.W >= (int64_t(1) << 40) || int64_t(d.H) * d.W >= (1 << 20)) return hipErrorInvalidValue;
+  a.cpr = int(ceil_div(d.W, E));
+  a.pieces = d.H * a.cpr;
+  const bool beside = d.Wo > 16;                         // pairs of tiles
+  const int TX = int(ceil_div(d.Wo, beside ? 32 : 16)), TY = int(ceil_div(d.Ho, beside ? 16 : 32));
+  a.dx = beside ? 16 : 0;
+  a.dy = 16 - a.dx;
+  // A tile reads the 64 bytes from a piece in front of its first column on, in 16 + K - 1 rows; a row holds the pieces
+  // of the data behind one of zeros.  An odd number of pieces: the 16 rows of a read on 16 bank groups.
+  int64_t pitch = 16 * (1 + a.cpr);
+  const int64_t reach = (int64_t(TX) * (16 + a.dx) - 16) * ESZ + 64;
+  if (pitch < reach) pitch = reach;
+  if (pitch / 16 % 2 == 0) pitch += 16;
+  int64_t rows = int64_t(TY) * (16 + a.dy) + K - 1;
+  if (rows < d.H + 2 * d.Ph) rows = d.H + 2 * d.Ph;
+  a.pitch = int(pitch);
+  a.plane_lds = int(rows * pitch);
+  a.second = beside ? 16 * ESZ : 16 * a.pitch;
+  const int taps = K * 96 * ESZ;
+  if (a.pieces > kMaxVec * 256 || a.plane_lds + taps > kDwTileLds) return hipErrorInvalidValue;
+  // As many planes as a task's loads and a quarter of the LDS hold, but four tasks for every compute unit.
+  int64_t G = kMaxVec * 256 / a.pieces, fit = kDwTileLds / (a.plane_lds + taps), fill = a.planes / (4 * dw_num_cus());
+  G = G < fit ? G : fit;
+  G = G < fill ? G : fill;
+  a.G = int(G < 1 ? 1 : G);
+  a.tasks = ceil_div(a.planes, a.G);
+  a.lds_w = a.G * a.plane_lds;
+  a.dcpr = FastDiv::make(uint32_t(a.cpr));
+  a.dH = FastDiv::make(uint32_t(d.H));
+  a.dT = FastDiv::make(uint32_t(TX * TY));
+  a.dTX = FastDiv::make(uint32_t(TX));
+  const size_t lds = size_t(a.lds_w) + size_t(a.G) * taps;
+  int64_t grid = int64_t(dw_num_cus()) * 4;
+  if (grid > a.tasks) grid = a.tasks;
+  grid = ceil_div(a.tasks, ceil_div(a.tasks, grid));     // the same number of tasks for everyone
+  const dim3 g{unsigned(grid)}, b{256};
+  if constexpr (__is_same(T, int8_t)) {
+    if (K == 3) hipLaunchKernelGGL((depthwise_tile_kernel<T, 3, GS_I32>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((depthwise_tile_kernel<T, 5, GS_I32>), g, b, lds, s, a);
+  } else if (d.out_dtype == GS_BF16) {
+    if (K == 3) hipLaunchKernelGGL((depthwise_tile_kernel<T, 3, GS_BF16>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((depthwise_tile_kernel<T, 5, GS_BF16>), g, b, lds, s, a);
+  } else {
+    if (K == 3) hipLaunchKernelGGL((depthwise_tile_kernel<T, 3, GS_F32>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((depthwise_tile_kernel<T, 5, GS_F32>), g, b, lds, s, a);
+  }
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
+  // Unit strides on the matrix units where the 16x32 or 32x16 results of a step are mostly results, there are enough of them, and,
+  // for 3x3, columns are unaligned (us, strips / tiles):
+  //   5x5: 32 images of 128 planes of 112x112 99 / 63, 11 of 330 51x101 64 / 39, 3 of 314 100x17 15.9 / 11.9; but 18 of 361
+  //   planes of 8x49 13.8 / 18.0, 8 of 30 40x33 6.0 / 6.3, 3 of 237 37x31 int8 9.0 / 9.9;
+  //   3x3: 17 of 313 80x99 86 / 60, 14 of 276 28x68 int8 26 / 18, 32 of 256 28x28 16.9 / 14.3; but 32 of 128 112x112 (aligned) 51.5 /
+  //   54.8, 32 of 512 14x14 9.6 / 16.8, 2 of 361 51x19 to f32 6.4 / 6.9.
+  const int64_t step = d.Wo > 16 ? round_up(d.Wo, 32) * round_up(d.Ho, 16) : round_up(d.Wo, 16) * round_up(d.Ho, 32);
+  const int64_t plane = int64_t(d.Ho) * d.Wo, results = int64_t(d.N) * d.C * plane;
+  if (d.Kh == 5 ? plane * 100 >= step * 45 && results >= (__is_same(T, int8_t) ? 2000000 : 300000) : plane * 100 >= step * 70 && results >= 900000 && !dw_edge(d)) {
+    const hipError_t e = launch_depthwise_tiles<T>(d, s);
+    if (e != hipErrorInvalidValue) return e;
+  }
   // Several rows per strip (four for 3x3; two for 5x5, whose twenty-five filter taps leave registers for no
   // more) where every compute unit still has 256 strips, few of the rows are past the end, and it was the
   // faster way over 32 images (us, one row per strip against several):

@@ -647,6 +647,33 @@ def test_conv_tile_instances(dtype, k, natural, shape):
             assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# Depth-wise windows on the matrix units: tiles beside and above each other, cut at both ends, one and several planes to a task, rows
+# that end inside a piece, padding and none; infinities and NaN, which reach only the results whose windows hold them.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("n,c,h,w,k,p", [(3, 100, 63, 62, 3, 1), (40, 90, 15, 31, 3, 1), (9, 130, 31, 29, 3, 0), (2, 50, 95, 111, 5, 2), (25, 80, 27, 16, 5, 2),
+                                         (7, 64, 29, 32, 5, 0), (3, 64, 44, 100, 5, 1), (4, 33, 112, 112, 5, 2), (20, 90, 33, 62, 5, 2), (1, 40, 93, 125, 3, 1)])
+def test_depthwise_tiles(n, c, h, w, k, p, dtype, odt):
+    x, wt = gen(dtype, (n, c, h, w), 9900 + h), gen(dtype, (c, k, k), 9950 + w, 1.0 / k)
+    if dtype == "bf16":
+        x[0, 0, 0, 0], x[-1, -1, -1, -1], x[0, 1, h // 2, w // 2], x[n // 2, 2, h - 1, 7] = float("inf"), float("-inf"), float("nan"), float("inf")
+    want = torch.nn.functional.conv2d(x.double(), wt.double()[:, None], padding=p, groups=c)
+    buf = torch.full((want.numel() + 512,), 77, dtype=odt, device=DEV)
+    out = buf[256:256 + want.numel()].view(want.shape)
+    for act in (gs.GS_ACT_NONE, gs.GS_ACT_RELU):
+        gs.depthwise_conv2d(x.to(DEV), wt.to(DEV), (1, 1), (p, p), act=act, out=out)
+        got, ref = out.cpu().double(), want if act == gs.GS_ACT_NONE else torch.where(want > 0, want, torch.zeros_like(want))
+        if dtype == "i8":
+            assert torch.equal(got, ref)
+        else:
+            # k k products and sums in fp32 (2^-24 each), one rounding to bfloat16
+            mag = torch.nn.functional.conv2d(torch.nan_to_num(x.double(), posinf=0, neginf=0).abs(), wt.double().abs()[:, None], padding=p, groups=c)
+            slack = k * k * 2.0 ** -24 * mag + (2.0 ** -8 * torch.nan_to_num(ref, posinf=0, neginf=0).abs() if odt == torch.bfloat16 else 0)
+            fine = torch.isfinite(ref)
+            assert torch.equal(torch.nan_to_num(got[~fine], nan=7.0), torch.nan_to_num(ref[~fine], nan=7.0))
+            assert torch.isfinite(got[fine]).all() and ((got - ref).abs()[fine] <= slack[fine]).all()
+        assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
+
+
 # Rows of any length in 16-byte vectors (reduce_rows_any_kernel): the rows' first and last vectors shared in every phase,
 # each lane group, a workgroup per row, several rounds of rows, the tensor ending inside a vector; lowest values at the rows'
 # ends, which a neighbour's value must not replace.
