@@ -151,7 +151,7 @@ int glenside_depthwise_conv2d(const gs_ap* activations, const gs_ap* weights, co
  *                    the contraction reads it, (O, Kh, Kw, C) with C padded to a 32-byte step --
  *                    the weight-side layout change that the systolic-array rewrite (Sec. 5.2) makes
  *                    explicit with (transpose ?a1 ...) -- and, when C is a whole number of such
- *                    steps or the window 1x1, 3x3 or 5x5, once more cut into blocks of 32 output
+ *                    steps, or half of one at least and the window 1x1, 3x3 or 5x5, once more cut into blocks of 32 output
  *                    channels x one step of one tap (1 KB each, the unit the kernel reads),
  *                    (O/32, C-step, Kh, Kw).  Needs glenside_conv2d_direct_workspace bytes.  When C
  *                    is no whole number of steps, a buffer that is too small for the second copy but

@@ -310,8 +310,8 @@ size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw, bool le
 bool conv_is_smallc(int in_dtype, int C);
 size_t conv_smallc_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_smallc_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
-// Channel counts that are whole chunks (32 bytes per tap), and others with 1x1, 3x3 and 5x5 windows (the last
-// chunk filled up with zeros): a third copy behind the others, cut into blocks of 1 KB = 32 output channels x one chunk of one tap, ordered [O / 32][chunk][tap],
+// Channel counts that are whole chunks (32 bytes per tap), and others of at least half a chunk with 1x1, 3x3 and 5x5
+// windows (the last chunk filled up with zeros): a third copy behind the others, cut into blocks of 1 KB = 32 output channels x one chunk of one tap, ordered [O / 32][chunk][tap],
 // each block the exact image of the LDS block the convolution's weight transfers fill (lane i of a
 // transfer moves bytes 16 i .. 16 i + 15), so that one transfer reads 1 KB of consecutive memory
 // instead of 32 pieces of 32 bytes from 32 rows.  Bytes of that copy (0 if there is none) and its
@@ -319,8 +319,9 @@ size_t conv_smallc_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, int O, int C, int Kh, int Kw,
-                                   hipStream_t s);
-// Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there.
+                                   bool blocked, hipStream_t s);
+// Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there (the
+// blocked one where a.wblk is set).
 hipError_t launch_conv_smallc(const ConvArgs& a, void* packed, hipStream_t s);
 bool conv_smallc_fits(int in_dtype, int C, int W, int Kh, int Kw, int Sh, int Sw, int Pw, int Wo);   // does the kernel take the layer?
 // Small images, weights as they come (conv_images.hip): one launch; with `packed`, their copies are written there on the

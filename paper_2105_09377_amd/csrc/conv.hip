@@ -4,12 +4,13 @@
 //   out[n,o,x,y] = sum_{c,dx,dy} act[n,c,Sh*x+dx-Ph,Sw*y+dy-Pw] * w[o,c,dx,dy]
 //
 // Kernels, in the order they are tried:
-//   * conv_smallc_kernel  (conv_smallc.hip)  fewer input channels than one 32-byte chunk;
 //   * conv_tile_kernel    (conv_tile_kernel.h)  3x3, 5x5 and (no padding) 1x1 windows of strides 1
 //                                            and 2, any channel count: small
 //                                            independent workgroups, weights from L2 into registers;
 //                                            in the workgroup shape that a cost model picks, unless it
-//                                            expects the next one to be faster;
+//                                            expects the next ones to be faster;
+//   * conv_smallc_kernel  (conv_smallc.hip)  fewer input channels than one 32-byte chunk, fewer than half
+//                                            a chunk first of all;
 //   * conv_direct4_kernel (conv4_kernel.h)   eight waves, producers and consumers; may split the
 //                                            channel sum among workgroups;
 //   * conv_direct3_kernel (conv_kernels.h)   four waves doing everything, same LDS layout;
@@ -84,7 +85,7 @@ static size_t conv_weight_front_bytes(int in_dtype, int O, int C, int Kh, int Kw
 
 size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw) {
   // (channel counts that are no whole chunks: only conv_tile_kernel takes them)
-  if (C != conv_cpad(in_dtype, C) && (conv_is_smallc(in_dtype, C) || Kh != Kw || (Kh != 1 && Kh != 3 && Kh != 5))) return 0;
+  if (C != conv_cpad(in_dtype, C) && (C * int64_t(dtype_size(in_dtype)) < 16 || Kh != Kw || (Kh != 1 && Kh != 3 && Kh != 5))) return 0;
   return size_t(round_up(O, 32)) * Kh * Kw * conv_cpad(in_dtype, C) * dtype_size(in_dtype);
 }
 
@@ -104,7 +105,7 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
                               bool blocked, hipStream_t s) {
   const int Cpad = conv_cpad(in_dtype, C);
   if (int64_t(O) * Kh * Kw * Cpad == 0) return hipSuccess;
-  if (conv_is_smallc(in_dtype, C)) return launch_conv_smallc_pack(w, wr, in_dtype, O, C, Kh, Kw, s);
+  if (conv_is_smallc(in_dtype, C)) return launch_conv_smallc_pack(w, wr, in_dtype, O, C, Kh, Kw, blocked, s);
   const int64_t b = ceil_div(round_up(O, 32) * Kh * Kw * Cpad * int64_t(dtype_size(in_dtype)) / 16, 256);
   const dim3 grid(unsigned(b < 65536 ? b : 65536));
   uint8_t* wb = blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
@@ -576,13 +577,20 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   }
   const ConvGeom g = conv_geom(a);
   if (g.M == 0 || a.O == 0) return hipSuccess;
-  if (a.wnat) {                        // fewer channels than a chunk: windows formed as im2col rows in LDS
+  // Fewer channels than a chunk: half of one at least on conv_tile_kernel, but 1x1 windows and few results, and all
+  // others, as im2col rows formed in LDS.  60 layers of 8 to 15 channels (16 to 31 in bytes), us, in LDS rows / in tiles:
+  // 1.6 times faster on average (64 images of 15, 26x14 -> 384, 3x3 stride 2 88 / 6.5; 34 of 29 in bytes, 18x46 -> 400
+  // 108 / 20; 2 of 8, 26x20 -> 96 5.7 / 5.6), at worst 0.65 (35 of 16 in bytes, 9x35 -> 32, 5x5, 8.4 / 12.8; six of 110 below 0.95); 1x1: 10 of 25 in
+  // bytes, 73x26 -> 208 53 / 11, but 10 of 9, 12x53 -> 16 5.4 / 6.9.
+  const bool rows_first = a.wnat && a.Kh == 1 && a.O <= 64;
+  const TilePlan& plan = plan_tiles<TR>(a, g);
+  if (plan.shape >= 0 && !rows_first) return launch_tiles<TR>(a, plan, s);
+  if (a.wnat) {
     ConvArgs b = a;
     b.wr = a.wnat;
     const hipError_t es = launch_conv_smallc(b, nullptr, s);
     if (es != hipErrorInvalidValue) return es;
   }
-  const TilePlan& plan = plan_tiles<TR>(a, g);
   if (plan.shape >= 0) return launch_tiles<TR>(a, plan, s);
   hipError_t e = launch_conv3<TR>(a, g, s);
   if (a.ksplit > 1) {

@@ -221,7 +221,7 @@ static hipError_t launch_images_t(const ConvArgs& a, void* packed, hipStream_t s
   int64_t grid = tiles;
   if (packed) {
     int64_t elements;
-    p.copies = smallc_copies(packed, a.in_dtype, a.O, a.C, a.Kh, a.Kw, &elements);
+    p.copies = smallc_copies(packed, a.wblk != nullptr, a.in_dtype, a.O, a.C, a.Kh, a.Kw, &elements);
     if (elements >= (int64_t(1) << 30)) return hipErrorInvalidValue;   // (32-bit indices)
     const int64_t wanted = ceil_div(elements * ESZ / 16, kImagesThreads);
     grid += wanted < 512 ? wanted : 512;

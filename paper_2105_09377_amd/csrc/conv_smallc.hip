@@ -602,25 +602,28 @@ size_t conv_smallc_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw) {
   return smallc_rows_offset(in_dtype, O, C, Kh, Kw) + size_t(round_up(O, 64)) * round_up(C * Kh, 2) * 16;
 }
 
-SmallCCopies smallc_copies(void* packed, int in_dtype, int O, int C, int Kh, int Kw, int64_t* elements) {
+SmallCCopies smallc_copies(void* packed, bool blocked, int in_dtype, int O, int C, int Kh, int Kw, int64_t* elements) {
   SmallCCopies c;
   uint8_t* const natural = static_cast<uint8_t*>(packed) + conv_smallc_weight_offset(in_dtype, O, C, Kh, Kw);
   c.taps = packed;
   c.natural = natural;
+  c.blocked = blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
+                  ? static_cast<uint8_t*>(packed) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw) : nullptr;
   c.rows = smallc_has_rows_copy(in_dtype, Kw) ? natural + smallc_rows_offset(in_dtype, O, C, Kh, Kw) : nullptr;
   c.O = O; c.O64 = int(round_up(O, 64)); c.C = C; c.Kh = Kh; c.Kw = Kw;
   c.Cpad = in_dtype == GS_I8 ? 32 : 16;                // one chunk: fewer channels than that
   c.Kp = smallc_kp(in_dtype, C, Kh, Kw);
   c.rows2 = int(round_up(C * Kh, 2));
   const int64_t taps = int64_t(O) * Kh * Kw * c.Cpad, rows = int64_t(c.O64) * c.rows2 * 16 / int64_t(dtype_size(in_dtype));
-  *elements = taps + int64_t(c.O64) * c.Kp + (c.rows ? rows : 0);
+  const int64_t blocks = c.blocked ? int64_t(conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw) / dtype_size(in_dtype)) : 0;
+  *elements = taps + int64_t(c.O64) * c.Kp + (c.rows ? rows : 0) + blocks;
   return c;
 }
 
 hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, int O, int C, int Kh, int Kw,
-                                   hipStream_t s) {
+                                   bool blocked, hipStream_t s) {
   int64_t elements;
-  const SmallCCopies c = smallc_copies(packed, in_dtype, O, C, Kh, Kw, &elements);
+  const SmallCCopies c = smallc_copies(packed, blocked, in_dtype, O, C, Kh, Kw, &elements);
   if (elements == 0) return hipSuccess;
   const int64_t b = ceil_div(elements * int64_t(dtype_size(in_dtype)) / 16, 256);   // (every copy is whole pieces)
   const dim3 grid(unsigned(b < 4096 ? b : 4096));
@@ -711,7 +714,7 @@ static hipError_t launch_smallc_t(const ConvArgs& a, void* packed, hipStream_t s
   p.tile_bytes = int(l.tile_bytes);
   int64_t elements = 0;
   if (raw) {
-    p.copies = smallc_copies(packed, a.in_dtype, a.O, a.C, a.Kh, a.Kw, &elements);
+    p.copies = smallc_copies(packed, a.wblk != nullptr, a.in_dtype, a.O, a.C, a.Kh, a.Kw, &elements);
     if (elements >= (int64_t(1) << 30)) return hipErrorInvalidValue;   // (32-bit indices, a step of at most 2^30 threads)
   }
   if (dr && !raw)

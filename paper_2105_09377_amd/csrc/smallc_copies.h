@@ -12,11 +12,12 @@ struct SmallCCopies {
   void* natural;     // ((O rounded up to 64),(Kp)), zeros in the padding
   void* rows;        // row-window copy ((O rounded up to 64),(C*Kh rounded up to 2, 16 bytes)): element dy of row
                      // r = c*Kh + dx is w[o][c][dx][dy], zeros for dy >= Kw and in the padding row; or null
+  void* blocked;     // the copy in 1 KB blocks (see conv_blocked_weight_offset), one chunk of channels; or null
   int O, O64, C, Kh, Kw, Cpad, Kp, rows2;
 };
 
 // `packed`: the copies one after the other, as the packing call leaves them.  *elements: of all of them.
-SmallCCopies smallc_copies(void* packed, int in_dtype, int O, int C, int Kh, int Kw, int64_t* elements);
+SmallCCopies smallc_copies(void* packed, bool blocked, int in_dtype, int O, int C, int Kh, int Kw, int64_t* elements);
 
 // Thread `first` of `step` writes its share of the 16-byte pieces, all copies in one loop: a thread has one
 // latency to wait for where there are threads enough (3 x 8x8 -> 4, 3x3 in bytes, the whole call, all workgroups
@@ -28,7 +29,8 @@ __device__ __forceinline__ void write_copies(const T* __restrict__ w, const Smal
   const I O = I(c.O), C = I(c.C), taps = I(c.Kh) * I(c.Kw), K = C * taps, nrows = C * I(c.Kh), rows2 = I(c.rows2);
   const I per_tap = I(c.Cpad / G), per_row = I(c.Kp / G);
   const I n_taps = O * taps * per_tap, n_natural = I(c.O64) * per_row, n_rows = c.rows ? I(c.O64) * rows2 : 0;
-  for (I f = first; f < n_taps + n_natural + n_rows; f += step) {
+  const I n_blocked = c.blocked ? I((c.O + 31) / 32) * taps * 64 : 0;
+  for (I f = first; f < n_taps + n_natural + n_rows + n_blocked; f += step) {
     // elements src, src + by, ... of the weights, `count` of them (none where it is not positive), then zeros
     I src, by = 1;
     int count;
@@ -44,6 +46,13 @@ __device__ __forceinline__ void write_copies(const T* __restrict__ w, const Smal
       src = o * K + k;
       count = o < O ? int(K) - int(k) : 0;
       dst = static_cast<piece_t*>(c.natural) + at;
+    } else if (f >= n_taps + n_natural + n_rows) {         // (the order within a block: conv_repack_kernel)
+      const I at = f - n_taps - n_natural - n_rows, block = at / 64, i = at - block * 64, r = i >> 1, ob = block / taps;
+      const I o = ob * 32 + r, ch = ((i & 1) ^ (((r >> 2) ^ (r >> 3)) & 1)) * G;
+      src = o < O ? (o * C + ch) * taps + (block - ob * taps) : 0;
+      by = taps;
+      count = o < O ? int(C) - int(ch) : 0;
+      dst = static_cast<piece_t*>(c.blocked) + at;
     } else {
       const I at = f - n_taps - n_natural, o = at / rows2, r = at - o * rows2;
       src = (o * nrows + r) * I(c.Kw);

@@ -757,6 +757,23 @@ def test_conv_tile_instances_odd_channels(dtype, k, natural, shape):
     assert reached == {i for i in tile_instances.built(dtype, k, shape) if not i[3]}
 
 
+# Half a chunk of channels and more: conv_tile_kernel, or im2col rows where results are few; packed and with weights that come
+# with the call.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("i8", torch.int32)])
+@pytest.mark.parametrize("c,n,h,w,o,k,s,p", [(8, 3, 21, 40, 33, 3, 1, 1), (15, 40, 14, 30, 65, 3, 2, 1), (9, 2, 60, 71, 70, 5, 1, 2), (11, 30, 12, 53, 16, 1, 1, 0), (13, 9, 25, 70, 96, 1, 2, 0),
+                                             (15, 1, 3, 4, 1, 3, 1, 1), (12, 5, 90, 91, 40, 5, 2, 0), (7, 4, 30, 30, 40, 3, 1, 1)])
+def test_conv2d_half_a_chunk_of_channels(c, n, h, w, o, k, s, p, dtype, odt):
+    cfg = synth.conv_layer(n, 2 * c if dtype == "i8" else c, h, w, o, k, s, p, dtype, 9350 + c + o)
+    x, wt = cfg["x"].to(DEV), cfg["w"].to(DEV)
+    want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p).numpy()
+    want = want.astype(np.int64) if dtype == "i8" else want
+    ws, packed = (torch.full((gs.conv2d_workspace(x, wt, (s, s), (p, p)),), 0x5a, dtype=torch.uint8, device=DEV) for _ in range(2))
+    gs.conv2d_pack_weights(wt, packed)
+    assert_parity(gs.conv2d_direct_packed(x, wt, packed, (s, s), (p, p), out_dtype=odt), want, what="packed")
+    assert_parity(gs.conv2d_direct(x, wt, (s, s), (p, p), out_dtype=odt, workspace=ws), want, what="packed by the call")
+    assert torch.equal(ws, packed)              # (no scratch: their channel sums are not split)
+
+
 @pytest.mark.parametrize("k,c,dtype", [(3, 33, "bf16"), (5, 50, "i8"), (1, 40, "bf16")])
 def test_conv2d_odd_channels_in_the_least_workspace(k, c, dtype):
     """The blocked copy of the weights is optional where channels do not fill a chunk: a workspace without room for it
