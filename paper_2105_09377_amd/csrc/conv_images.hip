@@ -22,7 +22,7 @@
 
 namespace gs {
 
-constexpr int kImagesThreads = 256, kImagesLds = 80 * 1024;     // two workgroups per compute unit
+constexpr int kImagesThreads = 256, kImagesLds = 158 * 1024;    // of a workgroup that has a compute unit for itself
 constexpr int kImagesRS = 160;          // row stride of a partial tile: both half-waves on other banks
 constexpr int kImagesExtent = 192;      // rows and columns of an image, at most
 
@@ -209,8 +209,8 @@ static hipError_t launch_images_t(const ConvArgs& a, void* packed, hipStream_t s
   p.lds_part = p.lds_tab + uint32_t(p.ppr) * (16 / ESZ) * 4;
   const int64_t lds_bytes = int64_t(p.lds_part) + (kImagesThreads / 64) * 32 * kImagesRS;
   const int64_t tiles_p = ceil_div(M, 32), tiles = tiles_p * ceil_div(a.O, 32);
-  // Two workgroups share a compute unit, and every tile copies its images again: up to 512 tiles, one round.
-  if (images * CHW * ESZ > kImagesLds || lds_bytes > kImagesLds || tiles > 512) return hipErrorInvalidValue;
+  // Every tile copies its images again: one round of tiles, where two workgroups share a compute unit or one has it.
+  if (images * CHW * ESZ > kImagesLds || lds_bytes > kImagesLds || tiles > (lds_bytes <= 80 * 1024 ? 512 : 256)) return hipErrorInvalidValue;
   p.tiles = unsigned(tiles);
   p.dHWo = FastDiv::make(uint32_t(HWo));
   p.dWo = FastDiv::make(uint32_t(a.Wo));

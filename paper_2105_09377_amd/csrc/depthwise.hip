@@ -622,6 +622,8 @@ hipError_t launch_depthwise_rows(const DepthwiseArgs& d, hipStream_t s) {
     hipLaunchKernelGGL((depthwise_kernel<T, 3, 3, 2, 1, false>), g, b, lds, s, a);
   } else if (d.Kh == 5 && d.Kw == 5 && d.Sw == 1) {
     hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 1, 1, false>), g, b, lds, s, a);
+  } else if (d.Kh == 5 && d.Kw == 5 && d.Sw == 2) {    // (31 x 372 planes of 21x22 int8 34.0 us in the kernel of any window, 11.7)
+    hipLaunchKernelGGL((depthwise_kernel<T, 5, 5, 2, 1, false>), g, b, lds, s, a);
   } else {
     hipLaunchKernelGGL((depthwise_kernel<T, 0, 0, 0, 1, false>), g, b, lds, s, a);
   }

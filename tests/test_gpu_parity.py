@@ -674,6 +674,16 @@ def test_depthwise_tiles(n, c, h, w, k, p, dtype, odt):
         assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# 5x5 windows at stride 2: strips cut by the row's end, odd planes, several planes to a task and bands of one.
+@pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
+@pytest.mark.parametrize("n,c,h,w,p", [(1, 1, 5, 5, 0), (3, 17, 12, 17, 2), (2, 9, 31, 46, 1), (20, 24, 8, 16, 2), (1, 3, 203, 301, 2)])
+def test_depthwise_5x5_stride_2(n, c, h, w, p, dtype, odt):
+    x, wt = gen(dtype, (n, c, h, w), 9960 + h), gen(dtype, (c, 5, 5), 9970 + w, 0.2)
+    want = torch.nn.functional.conv2d(x.double(), wt.double()[:, None], padding=p, stride=2, groups=c).numpy()
+    got = gs.depthwise_conv2d(x.to(DEV), wt.to(DEV), (2, 2), (p, p), out_dtype=odt)
+    assert_parity(got, want.astype(np.int64) if dtype == "i8" else want, what=str((n, c, h, w, p)))
+
+
 # Rows of any length in 16-byte vectors (reduce_rows_any_kernel): the rows' first and last vectors shared in every phase,
 # each lane group, a workgroup per row, several rounds of rows, the tensor ending inside a vector; lowest values at the rows'
 # ends, which a neighbour's value must not replace.
