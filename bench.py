@@ -264,7 +264,8 @@ class ResNet18:
             if name in spec:
                 cin, cout, k = spec[name]
                 o = net.bufs[name]
-                rows.append((name, call, 2.0 * o.shape[0] * o.shape[2] * o.shape[3] * cout * cin * k * k, "TFLOP/s"))
+                taps = k * k + (1 if name.endswith("c1") and name[:-2] + "proj" in spec else 0)   # the shortcut in the same call
+                rows.append((name, call, 2.0 * o.shape[0] * o.shape[2] * o.shape[3] * cout * cin * taps, "TFLOP/s"))
             elif name == "pool":
                 rows.append((name, call, (net.bufs["conv1"].numel() + net.bufs["pool"].numel()) * 2.0, "GB/s"))
             elif name == "avg":

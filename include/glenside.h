@@ -170,6 +170,13 @@ int glenside_conv2d_direct_packed(const gs_ap* activations, const gs_ap* weights
                                   const int64_t stride[2], const int64_t pad[2],
                                   const gs_ap* residual, int act, gs_ap* out, void* packed,
                                   size_t packed_bytes, void* stream);
+/* glenside_conv2d_direct_packed(activations, weights, stride, pad, NULL, act, out, packed ..), and beside it
+ * glenside_conv2d_direct_packed(activations, weights_proj, stride, (0, 0), NULL, GS_ACT_NONE, out_proj, packed_proj ..): the two
+ * convolutions of a residual block that read the same input, in one launch where a kernel does both. */
+int glenside_conv2d_direct_packed_with_projection(const gs_ap* activations, const gs_ap* weights, const int64_t stride[2],
+                                                  const int64_t pad[2], int act, gs_ap* out, void* packed, size_t packed_bytes,
+                                                  const gs_ap* weights_proj, gs_ap* out_proj, void* packed_proj,
+                                                  size_t packed_proj_bytes, void* stream);
 /* Workspace bytes the two forms need; 0 if the arguments are invalid.  Host only. */
 size_t glenside_conv2d_direct_workspace(const gs_ap* activations, const gs_ap* weights,
                                         const int64_t stride[2], const int64_t pad[2]);

@@ -38,7 +38,7 @@ EXPORTS = (
     "glenside_pad", "glenside_pair", "glenside_cartesian_dot_blocked",
     "glenside_conv2d_direct_static", "glenside_conv2d_direct_static_limit",
     "glenside_program_shape", "glenside_program_eval", "glenside_program_workspace",
-    "glenside_program_rewrite", "glenside_depthwise_conv2d",
+    "glenside_program_rewrite", "glenside_depthwise_conv2d", "glenside_conv2d_direct_packed_with_projection",
 )
 
 
@@ -99,6 +99,8 @@ def lib() -> ctypes.CDLL:
                                                ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t)]
         L.glenside_conv2d_pack_weights.argtypes = [ap_p, vp, ctypes.c_size_t, vp]
         L.glenside_conv2d_direct_packed.argtypes = conv
+        L.glenside_conv2d_direct_packed_with_projection.argtypes = [ap_p, ap_p, i64_p, i64_p, ctypes.c_int, ap_p, vp, ctypes.c_size_t,
+                                                                    ap_p, ap_p, vp, ctypes.c_size_t, vp]
         L.glenside_reduce.argtypes = [ap_p, ctypes.c_int, ctypes.c_float, ap_p, vp]
         L.glenside_windows_reduce.argtypes = [ap_p, i64_p, i64_p, i64_p, i64_p, ctypes.c_int,
                                               ctypes.c_float, ap_p, vp]
@@ -267,6 +269,13 @@ def conv2d_direct_packed(x, w, packed, stride=(1, 1), pad=(0, 0), residual=None,
                          out_dtype=None, out=None) -> torch.Tensor:
     """Fig. 2a reading weights from `conv2d_pack_weights(w)`; `w` supplies shape and dtype only."""
     return _m().conv(1, x, w, stride, pad, residual, act, out_dtype, out, packed)
+
+
+def conv2d_direct_packed_with_projection(x, w, packed, w_proj, packed_proj, stride, pad, act, out, out_proj) -> torch.Tensor:
+    """`conv2d_direct_packed(x, w, ..)` into `out`, and of the same input `conv2d_direct_packed(x, w_proj, ..)` at the
+    same stride without padding into `out_proj`: a residual block's convolution and its shortcut, in one launch
+    where a kernel does both."""
+    return _m().conv_with_projection(x, w, packed, w_proj, packed_proj, stride, pad, act, out, out_proj)
 
 
 def conv2d_im2col(x, w, stride=(1, 1), pad=(0, 0), residual=None, act=GS_ACT_NONE, out_dtype=None,

@@ -474,6 +474,39 @@ int glenside_conv2d_direct_packed(const gs_ap* act, const gs_ap* w, const int64_
   return launch_status(launch_conv(a, static_cast<hipStream_t>(stream)));
 }
 
+int glenside_conv2d_direct_packed_with_projection(const gs_ap* act, const gs_ap* w, const int64_t stride[2], const int64_t pad[2],
+                                                  int actfn, gs_ap* out, void* packed, size_t packed_bytes, const gs_ap* w_proj,
+                                                  gs_ap* out_proj, void* packed_proj, size_t packed_proj_bytes, void* stream) {
+  const int64_t none[2] = {0, 0};
+  ConvShape cs, cp;
+  int st = conv_shape(act, w, stride, pad, &cs);
+  if (!st) st = conv_shape(act, w_proj, stride, none, &cp);
+  if (st) return st;
+  gs_ap wshape = *w, pshape = *w_proj;      // the packed forms carry the data; only the shapes are used
+  wshape.data = packed;
+  pshape.data = packed_proj;
+  st = conv_check_io(act, &wshape, nullptr, actfn, out, cs);
+  if (!st) st = conv_check_io(act, &pshape, nullptr, GS_ACT_NONE, out_proj, cp);
+  if (st) return st;
+  const PackedLayout layout = packed_layout(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, split_scratch(act->dtype, cs), packed_bytes);
+  const PackedLayout lp = packed_layout(act->dtype, cp.O, cp.C, cp.Kh, cp.Kw, split_scratch(act->dtype, cp), packed_proj_bytes);
+  if (!packed || !layout.fits || reinterpret_cast<uintptr_t>(packed) % 16 || !packed_proj || !lp.fits ||
+      reinterpret_cast<uintptr_t>(packed_proj) % 16)
+    return GS_ERR_WORKSPACE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  ConvArgs a = conv_args(act, nullptr, actfn, out, cs, packed, layout);
+  const ConvArgs b = conv_args(act, nullptr, GS_ACT_NONE, out_proj, cp, packed_proj, lp);
+  if (same_shape(out, out_proj) && out->dtype == out_proj->dtype && cp.Kh == 1 && cp.Kw == 1) {
+    a.wproj = b.wblk;
+    a.out_proj = b.out;
+    const hipError_t e = launch_conv_with_projection(a, s);
+    if (e != hipErrorInvalidValue) return launch_status(e);
+    a.wproj = nullptr;
+  }
+  st = launch_status(launch_conv(a, s));
+  return st ? st : launch_status(launch_conv(b, s));
+}
+
 int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
                            const int64_t pad[2], const gs_ap* residual, int actfn, gs_ap* out,
                            void* workspace, size_t workspace_bytes, void* stream) {
@@ -522,6 +555,26 @@ int gs_test_conv_tile(const gs_ap* act, const gs_ap* w, const int64_t stride[2],
     a.wblk = nullptr;
   }
   return launch_status(conv_tile_forced(a, way, out != nullptr, plan, static_cast<hipStream_t>(stream)));
+}
+
+// The same with a projection in the launch (glenside_conv2d_direct_packed_with_projection).
+int gs_test_conv_tile_with_projection(const gs_ap* act, const gs_ap* w, const int64_t stride[2], const int64_t pad[2], int actfn,
+                                      gs_ap* out, void* packed, const gs_ap* w_proj, gs_ap* out_proj, void* packed_proj, int way,
+                                      int plan[5], void* stream) {
+  const int64_t none[2] = {0, 0};
+  ConvShape cs, cp;
+  int st = conv_shape(act, w, stride, pad, &cs);
+  if (!st) st = conv_shape(act, w_proj, stride, none, &cp);
+  if (!st) st = conv_check_io(act, w, nullptr, actfn, out, cs);
+  if (!st) st = conv_check_io(act, w_proj, nullptr, GS_ACT_NONE, out_proj, cp);
+  if (st) return st;
+  const PackedLayout blocked{0, true, true, false};
+  ConvArgs a = conv_args(act, nullptr, actfn, out, cs, packed, blocked);
+  a.wproj = conv_args(act, nullptr, GS_ACT_NONE, out_proj, cp, packed_proj, blocked).wblk;
+  a.out_proj = out_proj->data;
+  if (!conv_projection_fits(a) || cp.Kh != 1 || cp.Kw != 1 || !same_shape(out, out_proj) || out->dtype != out_proj->dtype)
+    return GS_ERR_UNSUPPORTED;
+  return launch_status(conv_tile_forced(a, way, true, plan, static_cast<hipStream_t>(stream)));
 }
 
 }  // extern "C"

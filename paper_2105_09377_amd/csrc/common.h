@@ -301,6 +301,8 @@ struct ConvArgs {
   int N, C, H, W, O, Kh, Kw, Sh, Sw, Ph, Pw, Ho, Wo;
   int Cpad;               // channels per tap in `wr`
   int relu;
+  const void* wproj;      // a 1x1 projection of the same input beside the layer: its blocked copy, or null
+  void* out_proj;         // and its result, alike in shape and type, as it is
   int ksplit;             // 1, 2 or 4: the channel chunks are divided among ksplit workgroups
   void* partial;          // ksplit > 1: [ksplit][N*O*Ho*Wo] 32-bit partial sums
 };
@@ -334,6 +336,9 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
 // a.ksplit > 1 and a.partial set, kernels that support it split the channel sum (Fig. 6's last
 // blocking rule: partial dot products combined by reduceSum over a pair); others ignore it.
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
+// a.wproj and a.out_proj set: both results in one launch, or hipErrorInvalidValue (nothing launched).
+hipError_t launch_conv_with_projection(const ConvArgs& a, hipStream_t s);
+bool conv_projection_fits(const ConvArgs& a);      // whether conv_tile_kernel is built for the two in one
 // For tests: the layer on conv_tile_kernel cut in way `way` (tile_way in conv.hip; below zero: the one that the cost
 // model picks), whether or not a call would go there; only planned unless `launch`.  a.wblk null: weights in the listing's
 // order (a.wr).  out: shape, interleaved blocks, patch items per thread, a single chunk per group, positions of a tile.

@@ -666,6 +666,21 @@ hipError_t conv_tile_forced(const ConvArgs& a, int way, bool launch, int* out, h
                              : conv_tile_forced_t<Bf16Traits>(a, way, launch, out, s);
 }
 
+// A residual block's shortcut: its pixels are the centre taps of 3x3 windows padded by one, and both strides are two.
+bool conv_projection_fits(const ConvArgs& a) {
+  return a.in_dtype == GS_BF16 && a.Kh == 3 && a.Kw == 3 && a.Sh == 2 && a.Sw == 2 && a.Ph == 1 && a.Pw == 1 && a.wblk && a.wproj && a.C == a.Cpad;
+}
+hipError_t launch_conv_with_projection(const ConvArgs& a_in, hipStream_t s) {
+  ConvArgs a = a_in;
+  if (!conv_projection_fits(a)) return hipErrorInvalidValue;
+  a.ksplit = 1;
+  a.partial = nullptr;
+  const ConvGeom g = conv_geom(a);
+  if (g.M == 0 || a.O == 0) return hipErrorInvalidValue;
+  const TilePlan& plan = plan_tiles<Bf16Traits>(a, g);
+  return plan.shape >= 0 ? launch_tiles<Bf16Traits>(a, plan, s) : hipErrorInvalidValue;
+}
+
 bool conv_pipelined_takes(const ConvArgs& a_in) {
   ConvArgs a = a_in;
   a.Cpad = conv_cpad(a.in_dtype, a.C);

@@ -10,9 +10,12 @@ namespace gs {
 
 constexpr TileShape kShape = kTileShapes[GS_TILE_SHAPE];
 
-template <int K, int CM, bool NAT, int S, int IL, int MAXI, bool ONE>
+template <int K, int CM, bool NAT, int S, int IL, int MAXI, bool ONE, bool PROJ = false>
 static hipError_t launch_tile_inst(const ConvArgs& a, const TilePlan& p, hipStream_t s) {
-  auto kern = conv_tile_kernel<GS_TILE_TRAITS, K, K, CM, NAT, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE, bool(GS_TILE_ODD)>;
+  // With a projection: bfloat16, 3x3 at stride 2 (see launch_conv_with_projection).
+  if constexpr (!PROJ && K == 3 && S == 2 && !GS_TILE_ODD && GS_TILE_TRAITS::kEsz == 2)
+    if (a.wproj) return launch_tile_inst<K, CM, NAT, S, IL, MAXI, ONE, true>(a, p, s);
+  auto kern = conv_tile_kernel<GS_TILE_TRAITS, K, K, CM, NAT, S, IL, kShape.nj, kShape.wo, kShape.wp, kShape.ks, MAXI, ONE, bool(GS_TILE_ODD), PROJ>;
   static std::once_flag once;              // the attribute is set once, whichever thread comes first
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&]() {

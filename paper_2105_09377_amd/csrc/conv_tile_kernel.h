@@ -56,11 +56,17 @@ typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   /
 // their own.  50 random layers of 16 to 480 channels, us against the kernels of whole LDS rows that they took before:
 // 3.4 times faster on average, at least 1.05 (29 images of 148 channels 18x10 -> 44, 3x3 bf16, 32.1 -> 7.3; 20 of 166 channels
 // 75x14 -> 16 int8 at stride 2 37.0 -> 8.1; 7 of 161 channels 67x37 -> 64, 1x1, 32.5 -> 9.2).
+//
+// PROJ: a 1x1 projection of the same input at the same stride beside a 3x3 convolution padded by one (a residual
+// block's shortcut).  Its pixels are the centre tap's: one more weight fragment and NJ more MFMAs a chunk on fragments that
+// are in registers anyway, and a second write-back, instead of a launch that stages the input again.  The ResNet-18-shaped
+// stack with its three projections so, us: one image 145 -> 134, 64 images 530 -> 510 (128 to 512 channels at 28x28 to 7x7).
 template <typename TR, int KH, int KW, int CM, bool NAT, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE,
-          bool ODD>
+          bool ODD, bool PROJ = false>
 __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArgs a, ConvGeom g) {
   static_assert(NJ % IL == 0, "whole groups of interleaved blocks");
   static_assert(CM == 1 || KH * KW == 1, "chunks take the place of taps");
+  static_assert(!PROJ || (KH == 3 && KW == 3 && !ODD), "the centre tap's fragments, whole chunks");
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int ESZ = TR::kEsz;
   constexpr int G = 16 / ESZ;             // channels per 16-byte cell
@@ -129,7 +135,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     const int o = o0 + wo * 32 + (lane & 31);
     wlane = uint32_t(o < a.O ? o : a.O - 1) * uint32_t(a.C * ESZ) + uint32_t(lane >> 5) * 16u;   // (fits: host check)
   }
-  i32x4 ring[T];
+  i32x4 ring[T], proj_tap;
   auto load_tap = [&](int ch, auto tap_) {
     constexpr int tap = decltype(tap_)::value;
     const uint8_t* at = wsrc + int64_t(ch) * (T * kTap) + tap * kTap + wlane;
@@ -140,6 +146,15 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     }
     ring[tap] = *reinterpret_cast<const i32x4*>(at);
   };
+
+  // (the projection's blocks: one tap)
+  const uint8_t* psrc = nullptr;
+  if constexpr (PROJ) {
+    asm volatile("" ::"s"(a.wproj), "s"(a.out_proj));
+    const int n_oblk = (a.O + 31) / 32, ob = o0 / 32 + wo < n_oblk ? o0 / 32 + wo : n_oblk - 1;
+    psrc = static_cast<const uint8_t*>(a.wproj) + (int64_t(ob) * n_blocks + first) * 1024 + wlane;
+  }
+  auto load_proj = [&](int ch) { proj_tap = *reinterpret_cast<const i32x4*>(psrc + int64_t(ch) * 1024); };
 
   // ---- patch items: VW pixels, consecutive in the rows a segment needs, x one half of a chunk ----
   const int64_t plane = int64_t(a.H) * a.W * ESZ;
@@ -295,6 +310,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
       });
     constexpr int kw = s / GP - (IL - 1) * S, gi = step % NSG * GP + s % GP;   // the last use of tap kw in its row
     if constexpr (gi == NG - 1 && kw >= 0) load_tap(ch, std::integral_constant<int, step / NSG * KW + kw>{});
+    if constexpr (PROJ && gi == NG - 1 && kw == 1 && step / NSG == 1) load_proj(ch);
   };
   // The first loads, in the order in which the loop issues them, so that its waits (loads complete
   // in order) are exact from the first chunk on.
@@ -338,10 +354,13 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     fb[gi] = (lane >> 5) * g.halfb + (base + ho * SR - Ph - ihlo) * g.rowp + (wo_ / IL) * 16;
   }
 
-  typename TR::accv_t acc[NJ];
+  typename TR::accv_t acc[NJ], pacc[PROJ ? NJ : 1];
   static_for<NJ>([&](auto j_) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[decltype(j_)::value][v] = 0;
+    for (int v = 0; v < 16; ++v) {
+      acc[decltype(j_)::value][v] = 0;
+      if constexpr (PROJ) pacc[decltype(j_)::value][v] = 0;
+    }
   });
 
   lds_barrier();                          // zeros are in place
@@ -380,6 +399,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
           constexpr int j = IL - 1 - decltype(j_)::value, kw = q - j * S;
           if constexpr (kw >= 0 && kw < KW)
             acc[gi * IL + j] = TR::mfma(fr[s], ring[kh * KW + kw], acc[gi * IL + j]);
+          if constexpr (PROJ && kw == 1 && kh == 1) pacc[gi * IL + j] = TR::mfma(fr[s], proj_tap, pacc[gi * IL + j]);
         });
         if constexpr (step + 1 < STEPS) request(pb, std::integral_constant<int, step + 1>{}, s_);
         else if constexpr (!LAST) request(nb, std::integral_constant<int, 0>{}, s_);
@@ -414,6 +434,8 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   // ---- write-back: out[(img*O + o)*HWo + p] -----------------------------------------------------
   // SP positions at a time: staged in LDS of the wave's own as [channel][position] rows of 32-bit
   // values (16-byte stores), read back along the rows and written PG positions per lane.
+  // (both results one after the other: the staging of one may not meet the reads of the other)
+  auto write_back = [&](auto& acc, void* out, const void* residual, int relu) {
   constexpr int SP = 32 * (NJ < 4 ? NJ : 4), RS = SP * 4 + 16;
   constexpr int kRed = KS > 1 ? KS * NW * NJ * 4096 : 0;
   uint8_t* const stage = lds + kRed + w * (32 * RS);
@@ -444,10 +466,10 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     lds_barrier();
   }
   const int ow = o0 + wo * 32;
-  const bool has_res = a.residual != nullptr;
+  const bool has_res = residual != nullptr;
   // ReLU as one maximum with a run-time operand: zero, or a NaN, which fmaxf ignores.
-  const float lo_f = a.relu ? 0.0f : __builtin_nanf("");
-  const int lo_i = a.relu ? 0 : INT_MIN;
+  const float lo_f = relu ? 0.0f : __builtin_nanf("");
+  const int lo_i = relu ? 0 : INT_MIN;
   auto stage_pass = [&](auto ps_) {       // positions ps * SP .. of this wave
     constexpr int ps = decltype(ps_)::value;
     uint8_t* const row = stage + (lane & 31) * RS;
@@ -489,7 +511,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
 #pragma unroll
       for (int it = 0; it < NIT; ++it)
         if (mine(it))
-          res[it] = *reinterpret_cast<const i32x4_bytes*>(static_cast<const uint8_t*>(a.residual) +
+          res[it] = *reinterpret_cast<const i32x4_bytes*>(static_cast<const uint8_t*>(residual) +
                                                           int64_t(addr_of(it)) * (kind == 2 ? 2 : 4));
     }
     i32x4 raw[NIT][PG / 4];
@@ -503,7 +525,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
       if (!mine(it)) continue;
       const bool ok = whole && ow + it * RPI + rsub < a.O;
       i32x4_bytes* const dst =
-          reinterpret_cast<i32x4_bytes*>(static_cast<uint8_t*>(a.out) + int64_t(addr_of(it)) * (kind == 2 ? 2 : 4));
+          reinterpret_cast<i32x4_bytes*>(static_cast<uint8_t*>(out) + int64_t(addr_of(it)) * (kind == 2 ? 2 : 4));
       i32x4 r;
       if constexpr (kind == 0) {
         r = raw[it][0];
@@ -547,8 +569,8 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
         for (int it = 0; it < PG / 2; ++it) {
           const int row = it * (64 / PG) + lane / PG;
           if (mine(it) && mm < mend && ow + row < a.O)
-            store_result<acc_t>(a.out, a.residual, a.out_dtype, at + uint32_t(ow + row) * uint32_t(g.HWo),
-                                *reinterpret_cast<const acc_t*>(stage + row * RS + (gpos + e) * 4), a.relu);
+            store_result<acc_t>(out, residual, a.out_dtype, at + uint32_t(ow + row) * uint32_t(g.HWo),
+                                *reinterpret_cast<const acc_t*>(stage + row * RS + (gpos + e) * 4), relu);
         }
       }
       if (end >= len) break;
@@ -560,6 +582,12 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     else if (a.out_dtype == GS_BF16) write_rows(ps_, std::integral_constant<int, 2>{});
     else write_rows(ps_, std::integral_constant<int, 1>{});
   });
+  };
+  write_back(acc, a.out, a.residual, a.relu);
+  if constexpr (PROJ) {
+    lds_barrier();
+    write_back(pacc, a.out_proj, nullptr, 0);
+  }
 }
 
 }  // namespace gs

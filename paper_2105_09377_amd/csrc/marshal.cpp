@@ -26,6 +26,7 @@ struct Api {
   decltype(&glenside_access_windows) access_windows;
   decltype(&glenside_cartesian_dot) cartesian_dot;
   decltype(&glenside_conv2d_direct) conv2d_direct, conv2d_im2col, conv2d_direct_packed;
+  decltype(&glenside_conv2d_direct_packed_with_projection) conv2d_direct_packed_with_projection;
   decltype(&glenside_conv2d_direct_workspace) conv2d_direct_workspace, conv2d_im2col_workspace;
   decltype(&glenside_reduce) reduce;
   decltype(&glenside_windows_reduce) windows_reduce;
@@ -310,6 +311,24 @@ PyObject* py_conv(PyObject*, PyObject* const* p, Py_ssize_t n) {
   });
 }
 
+// conv_with_projection(x, w, packed, w_proj, packed_proj, stride, pad, act, out, out_proj)
+PyObject* py_conv_with_projection(PyObject*, PyObject* const* p, Py_ssize_t n) {
+  return guarded(n, 10, [&](PyObject*& r) {
+    const at::Tensor &x = tensor(p[0]), &packed = tensor(p[2]), &packed_proj = tensor(p[4]);
+    const Ints stride(p[5]), pad(p[6]);
+    const int act = code(p[7]);
+    const gs_ap xa = describe(x, 1), wa = describe(tensor(p[1]), 1), pa = describe(tensor(p[3]), 1);
+    gs_ap oa = describe(tensor(p[8]), 4), qa = describe(tensor(p[9]), 4);
+    void* s = stream_of(x);
+    call("glenside_conv2d_direct_packed_with_projection", [&] {
+      return api.conv2d_direct_packed_with_projection(&xa, &wa, stride.get(), pad.get(), act, &oa, packed.data_ptr(), size_t(packed.numel()),
+                                                      &pa, &qa, packed_proj.data_ptr(), size_t(packed_proj.numel()), s);
+    });
+    Py_INCREF(p[8]);
+    r = p[8];
+  });
+}
+
 at::ScalarType reduce_type(const at::Tensor& x, int op) {
   if (x.scalar_type() == at::kChar) return op == GS_SUM ? at::kInt : at::kChar;
   return x.scalar_type();
@@ -515,6 +534,7 @@ PyObject* py_bind(PyObject*, PyObject* const* p, Py_ssize_t n) {
     get("glenside_conv2d_direct", api.conv2d_direct);
     get("glenside_conv2d_im2col", api.conv2d_im2col);
     get("glenside_conv2d_direct_packed", api.conv2d_direct_packed);
+    get("glenside_conv2d_direct_packed_with_projection", api.conv2d_direct_packed_with_projection);
     get("glenside_conv2d_direct_workspace", api.conv2d_direct_workspace);
     get("glenside_conv2d_im2col_workspace", api.conv2d_im2col_workspace);
     get("glenside_reduce", api.reduce);
@@ -535,7 +555,7 @@ PyObject* py_bind(PyObject*, PyObject* const* p, Py_ssize_t n) {
 
 #define GS_FN(name, fn) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(fn)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    GS_FN("bind", py_bind), GS_FN("cartesian_dot", py_cartesian_dot), GS_FN("conv", py_conv), GS_FN("reduce", py_reduce),
+    GS_FN("bind", py_bind), GS_FN("cartesian_dot", py_cartesian_dot), GS_FN("conv", py_conv), GS_FN("conv_with_projection", py_conv_with_projection), GS_FN("reduce", py_reduce),
     GS_FN("windows_reduce", py_windows_reduce), GS_FN("access_windows", py_access_windows),
     GS_FN("depthwise_conv2d", py_depthwise), GS_FN("pair_reduce", py_pair_reduce), GS_FN("transpose", py_transpose),
     GS_FN("program_eval", py_program_eval),

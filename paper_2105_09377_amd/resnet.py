@@ -4,9 +4,8 @@ Every layer is one access-pattern program of the paper evaluated by the HIP libr
 
 * 3x3 and 7x7 convolutions are Fig. 2a (`conv2d_direct_packed`, windows formed on chip; the
   3-channel stem takes the library's few-channel kernel, which forms im2col rows in LDS);
-* the 1x1 stride-2 shortcut projections have no window overlap to exploit, so they run in the
-  im2col-rewritten form of Fig. 5 (`conv2d_im2col`), whose matrix rows are then the pixels
-  themselves: the library reads them where they lie;
+* a 1x1 stride-2 shortcut projection reads the centre pixels of the windows of the 3x3 stride-2
+  convolution beside it, so the two are one call (`conv2d_direct_packed_with_projection`);
 * ReLU and the residual addition (the `reduceSum (pair a b)` idiom of Sec. 5.4) are fused into the
   convolution epilogues;
 * max pooling is Fig. 2c (`windows_reduce`), the global average is `compute reduceSum` with a
@@ -42,7 +41,6 @@ class ResNet18Stack:
         # into a buffer sized for its layer's call (weights plus that call's scratch).
         self.packed: Dict[str, torch.Tensor] = {}
         self.packed["conv1"] = self._pack("conv1", tuple(self.x.shape), 2, 3)
-        ws_bytes = 0
         for name, (cin, cout, k, s, p) in self.spec.items():
             if name == "conv1":
                 continue
@@ -52,13 +50,8 @@ class ResNet18Stack:
             elif name.endswith("proj"):
                 assert self._out(hin, k, s, p) == h
             src_hw = hin if name.endswith(("c1", "proj")) else h
-            if name.endswith("proj"):
-                ws_bytes = max(ws_bytes, gs.conv2d_workspace(self.x, self.w[name], (s, s), (p, p), form="im2col",
-                                                             x_shape=(batch, cin, src_hw, src_hw)))
-            else:
-                self.packed[name] = self._pack(name, (batch, cin, src_hw, src_hw), s, p)
+            self.packed[name] = self._pack(name, (batch, cin, src_hw, src_hw), s, p)
             self._alloc(name, (batch, cout, h, h))
-        self.ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=self.dev)   # shared by the projections
         self._alloc("avg", (batch, 512))
         self.logits = torch.empty((batch, self.w["fc"].shape[0]), dtype=torch.float32, device=self.dev)
         self.steps = self.plan()
@@ -75,18 +68,19 @@ class ResNet18Stack:
     def _alloc(self, name: str, shape: Tuple[int, ...]) -> None:
         self.bufs[name] = torch.empty(shape, dtype=torch.bfloat16, device=self.dev)
 
-    def _conv(self, name: str, x: torch.Tensor, residual=None, relu=True) -> torch.Tensor:
-        _cin, _cout, k, s, p = self.spec[name]
-        if name.endswith("proj"):
-            return gs.conv2d_im2col(x, self.w[name], (s, s), (p, p), residual=residual,
-                                    act=gs.GS_ACT_RELU if relu else gs.GS_ACT_NONE, out=self.bufs[name],
-                                    workspace=self.ws)
+    def _conv(self, name: str, x: torch.Tensor, residual=None) -> torch.Tensor:
+        _cin, _cout, _k, s, p = self.spec[name]
         return gs.conv2d_direct_packed(x, self.w[name], self.packed[name], (s, s), (p, p), residual=residual,
-                                       act=gs.GS_ACT_RELU if relu else gs.GS_ACT_NONE, out=self.bufs[name])
+                                       act=gs.GS_ACT_RELU, out=self.bufs[name])
+
+    def _conv_with_projection(self, name: str, proj: str, x: torch.Tensor) -> torch.Tensor:
+        _cin, _cout, _k, s, p = self.spec[name]
+        return gs.conv2d_direct_packed_with_projection(x, self.w[name], self.packed[name], self.w[proj], self.packed[proj], (s, s),
+                                                       (p, p), gs.GS_ACT_RELU, self.bufs[name], self.bufs[proj])
 
     def layer_calls(self) -> List[str]:
-        """Names of the library calls of one forward pass, in order."""
-        return ["conv1", "pool"] + [n for n in self.spec if n != "conv1"] + ["avg", "fc"]
+        """Names of the library calls of one forward pass, in order (a projection goes with the convolution beside it)."""
+        return [name for name, _call in self.steps]
 
     def plan(self) -> List[Tuple[str, Callable[[], torch.Tensor]]]:
         """The forward pass as (layer name, call) pairs in execution order.  Every call reads and
@@ -101,11 +95,12 @@ class ResNet18Stack:
         for stage in (1, 2, 3, 4):
             for block in (1, 2):
                 pre = f"s{stage}b{block}"
-                steps.append((pre + "c1", lambda pre=pre, y=y: self._conv(pre + "c1", b[y])))
                 shortcut = y
                 if (pre + "proj") in self.spec:
-                    steps.append((pre + "proj", lambda pre=pre, y=y: self._conv(pre + "proj", b[y], relu=False)))
                     shortcut = pre + "proj"
+                    steps.append((pre + "c1", lambda pre=pre, y=y: self._conv_with_projection(pre + "c1", pre + "proj", b[y])))
+                else:
+                    steps.append((pre + "c1", lambda pre=pre, y=y: self._conv(pre + "c1", b[y])))
                 steps.append((pre + "c2", lambda pre=pre, sc=shortcut: self._conv(pre + "c2", b[pre + "c1"], residual=b[sc])))
                 y = pre + "c2"
         hw = b[y].shape[-1] * b[y].shape[-2]

@@ -767,6 +767,50 @@ def test_conv_tile_instances_odd_channels(dtype, k, natural, shape):
     assert reached == {i for i in tile_instances.built(dtype, k, shape) if not i[3]}
 
 
+# A 3x3 convolution and a 1x1 projection of the same input, both at stride 2, in one launch: every instance, and through the
+# entry point also what no instance takes (odd channels, bytes, other windows).
+@pytest.mark.parametrize("shape", tile_instances.SHAPES)
+def test_conv_tile_instances_with_projection(shape):
+    reached = set()
+    for (s, *_rest), (way, (n, c, h, w, o, p)) in tile_instances.layers("bf16", 3, False, shape).items():
+        if s == 1:
+            continue
+        cfg, proj = (synth.conv_layer(n, c, h, w, o, k, s, p, "bf16", 9380 + h + w) for k in (3, 1))
+        x, w3, w1 = cfg["x"].to(DEV), cfg["w"].to(DEV), proj["w"].to(DEV)
+        wants = [torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=p).clamp_min(0),
+                 torch.nn.functional.conv2d(cfg["x"].double(), proj["w"].double(), stride=s)]
+        packed, packed1 = gs.conv2d_pack_weights(w3), gs.conv2d_pack_weights(w1)
+        numel = wants[0].numel()
+        buf = torch.full((2, numel + 512), 77, dtype=torch.bfloat16, device=DEV)
+        outs = [b[256:256 + numel].view(wants[0].shape) for b in buf]
+        st, plan = tile_instances.call_with_projection(gs.make_ap(x, 1), gs.make_ap(w3, 1), s, p, gs.GS_ACT_RELU, gs.make_ap(outs[0], 4),
+                                                       packed.data_ptr(), gs.make_ap(w1, 1), gs.make_ap(outs[1], 4), packed1.data_ptr(),
+                                                       way, gs._stream(x))
+        assert (st, plan[0]) == (gs.GS_OK, shape)
+        reached.add((s, *plan[1:4]))
+        for out, want in zip(outs, wants):      # one rounding to bfloat16
+            assert (out.double().cpu() - want).abs().max() <= 2.0 ** -8 * want.abs().max(), f"{plan} {(n, c, h, w)}"
+        assert (buf[:, :256] == 77).all() and (buf[:, 256 + numel:] == 77).all()
+    assert reached == {i for i in tile_instances.built("bf16", 3, shape) if i[0] == 2}
+
+
+@pytest.mark.parametrize("n,c,h,w,o,k,s,dtype,odt", [
+    (1, 64, 57, 56, 128, 3, 2, "bf16", torch.bfloat16), (5, 32, 14, 15, 33, 3, 2, "bf16", torch.float32), (2, 24, 9, 9, 40, 3, 2, "bf16", torch.bfloat16),
+    (3, 64, 28, 28, 64, 3, 2, "i8", torch.int32), (2, 32, 12, 12, 32, 3, 1, "bf16", torch.bfloat16), (2, 32, 12, 12, 32, 5, 2, "bf16", torch.bfloat16)])
+def test_conv2d_with_projection(n, c, h, w, o, k, s, dtype, odt):
+    cfg, proj = (synth.conv_layer(n, c, h, w, o, k_, s, k_ // 2, dtype, 9390 + c + o) for k_ in (k, 1))
+    x, wk, w1 = cfg["x"].to(DEV), cfg["w"].to(DEV), proj["w"].to(DEV)
+    wants = [torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), stride=s, padding=k // 2).clamp_min(0).numpy(),
+             torch.nn.functional.conv2d(cfg["x"].double(), proj["w"].double(), stride=s).numpy()]
+    outs = [torch.full(want.shape, 77, dtype=odt, device=DEV) for want in wants]
+    packed, packed1 = gs.conv2d_pack_weights(wk, for_input=(x, (s, s), (k // 2, k // 2))), gs.conv2d_pack_weights(w1, for_input=(x, (s, s), (0, 0)))
+    gs.conv2d_direct_packed_with_projection(x, wk, packed, w1, packed1, (s, s), (k // 2, k // 2), gs.GS_ACT_RELU, *outs)
+    for out, want in zip(outs, wants):
+        assert_parity(out, want.astype(np.int64) if dtype == "i8" else want)
+    with pytest.raises(gs.GlensideError):
+        gs.conv2d_direct_packed_with_projection(x, wk, packed, w1[:, 1:].contiguous(), packed1, (s, s), (k // 2, k // 2), gs.GS_ACT_RELU, *outs)
+
+
 # Half a chunk of channels and more: conv_tile_kernel, or im2col rows where results are few; packed and with weights that come
 # with the call.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("i8", torch.int32)])

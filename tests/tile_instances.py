@@ -29,6 +29,15 @@ def call(x, w, stride, pad, residual, act, out, packed, way, stream):
     return st, tuple(plan)
 
 
+def call_with_projection(x, w, stride, pad, act, out, packed, w_proj, out_proj, packed_proj, way, stream):
+    plan = (ctypes.c_int * 5)()
+    pair = lambda v: (ctypes.c_int64 * 2)(v, v)
+    st = gs.lib().gs_test_conv_tile_with_projection(ctypes.byref(x), ctypes.byref(w), pair(stride), pair(pad), act, ctypes.byref(out),
+                                                    ctypes.c_void_p(packed), ctypes.byref(w_proj), ctypes.byref(out_proj),
+                                                    ctypes.c_void_p(packed_proj), way, plan, ctypes.c_void_p(stream))
+    return st, tuple(plan)
+
+
 def built(dtype, k, shape):
     """(stride, interleaved blocks, items per thread, a single chunk) of the instances that conv_tile_inst.hip builds."""
     nj, ks = BLOCKS[shape], GROUPS[shape]
