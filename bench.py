@@ -49,20 +49,20 @@ KERNEL_SOURCES = {
 # workload -> (fetch + write bytes per launch of its dominant kernel, source group, digest of the
 # sources the counters were taken with)
 TRAFFIC = {
-    "resnet18": (26.47e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
-    "conv3x3": (13.70e6 + 12.85e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
-    "conv3x3_b64": (26.47e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
-    "im2col_gather": (12.98e6 + 115.65e6, "windows", "c94d4a9430ff5d2660314e68732e827be77765aacde81851a7cc52ff5e773758"),
-    "maxpool": (102.99e6 + 25.69e6, "reduce", "e7fce34a2ac6142a5da1e9f0ce59a06c855b972b8dcaafbb2ad97dad52a8186b"),
-    "reduce": (268.47e6 + 0.52e6, "reduce", "e7fce34a2ac6142a5da1e9f0ce59a06c855b972b8dcaafbb2ad97dad52a8186b"),
-    "transpose": (25.82e6 + 25.70e6, "move", "5b19fc5f9ba268368570a63f0a947a04178474e5c3493d5831c7c17a785b74b7"),
-    "dense_blocked": (50.62e6 + 16.78e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
-    "dense": (1612.14e6 + 280.37e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
-    "mlp_scaled": (28.93e6 + 16.78e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
-    "conv3x3_i8": (6.96e6 + 25.69e6, "conv", "159a6a65da99c28ee355331f149115e70b66a1cda631adbd401b319669e57728"),
-    "dense_i8": (805.92e6 + 283.21e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
-    "dense_fp8": (806.12e6 + 134.22e6, "gemm", "8c93511cd81b5417243aa987b800270b0314f048058cd9c08e019c4abb55854e"),
-    "depthwise": (103.12e6 + 102.78e6, "depthwise", "abfbbfe228cd124a49832220eb55be5753237ae0a79d3539f69cd21b58f425f6"),
+    "resnet18": (26.47e6 + 25.69e6, "conv", "034e625140d43fb499f30cd8da962f7ba55c1668cc9befd8f677e485dcf5f280"),       # the stage-1 convolution measured on its own (conv3x3_b64), without the residual every second launch reads
+    "conv3x3": (13.66e6 + 12.85e6, "conv", "034e625140d43fb499f30cd8da962f7ba55c1668cc9befd8f677e485dcf5f280"),
+    "conv3x3_b64": (26.47e6 + 25.69e6, "conv", "034e625140d43fb499f30cd8da962f7ba55c1668cc9befd8f677e485dcf5f280"),
+    "im2col_gather": (12.98e6 + 115.65e6, "windows", "e894c71f2a4c8cbe3c2cb39c94aa5bcc87f612dd98d5016aa7abc87602e585a4"),
+    "maxpool": (103.00e6 + 25.69e6, "reduce", "ef15a36e497c1d56323143057adec14e70c481dfd8c9ec19b786e4430335028d"),
+    "reduce": (268.47e6 + 0.52e6, "reduce", "ef15a36e497c1d56323143057adec14e70c481dfd8c9ec19b786e4430335028d"),
+    "transpose": (25.82e6 + 25.70e6, "move", "23b12e8be428598b4f9f446c74efae659342ef6083e39f6b0f689ca683d2a1a2"),
+    "dense_blocked": (50.54e6 + 16.78e6, "gemm", "fdd1721df1e40400c6de8ad01870ec7e02d69311d51bda985d6b39c053e2ed7b"),
+    "dense": (1611.64e6 + 279.41e6, "gemm", "fdd1721df1e40400c6de8ad01870ec7e02d69311d51bda985d6b39c053e2ed7b"),
+    "mlp_scaled": (28.97e6 + 16.78e6, "gemm", "fdd1721df1e40400c6de8ad01870ec7e02d69311d51bda985d6b39c053e2ed7b"),
+    "conv3x3_i8": (6.94e6 + 25.69e6, "conv", "034e625140d43fb499f30cd8da962f7ba55c1668cc9befd8f677e485dcf5f280"),
+    "dense_i8": (805.92e6 + 285.55e6, "gemm", "fdd1721df1e40400c6de8ad01870ec7e02d69311d51bda985d6b39c053e2ed7b"),
+    "dense_fp8": (806.17e6 + 134.22e6, "gemm", "fdd1721df1e40400c6de8ad01870ec7e02d69311d51bda985d6b39c053e2ed7b"),
+    "depthwise": (103.11e6 + 102.78e6, "depthwise", "af6c373ceb0ba76077862fe1bdd7412f1e6a67cab9a564d06b86c0f1356ed4ee"),
 }
 
 
@@ -209,7 +209,7 @@ class Conv3x3Batch64(Conv3x3):
 class ResNet18:
     """ResNet-18-shaped stack forward at batch 64 (the largest of the five workloads): 7x7 stem
     convolution, max pooling, sixteen 3x3 convolutions (direct form) and three 1x1 stride-2
-    projections (im2col form) with fused residual / ReLU, global average, classifier."""
+    projections (in the launches of the 3x3 ones beside them) with fused residual / ReLU, global average, classifier."""
 
     name = "resnet18-shaped conv stack forward, batch 64, 3x224x224, bf16 in/out, fp32 accumulate"
     dominant = "conv_tile_kernel (stage 1: N=64 C=64 56x56 -> 64, 3x3 s1 p1; 4 of the 20 convolutions)"

@@ -187,7 +187,7 @@ def test_config5_whole_stack_reduced_size():
 
 def test_config5_whole_stack_full_size():
     """The workload that `bench.py` times: batch 64 at 224x224, every layer buffer and the logits
-    (projections in the im2col form, residual + ReLU at 56/28/14/7, the split channel sums of the
+    (projections beside the 3x3 convolutions, residual + ReLU at 56/28/14/7, the split channel sums of the
     last stage), on whole images."""
     cfg = synth.resnet18_stack(batch=64)
     net = ResNet18Stack(cfg["weights"], batch=64, image=224, device=DEV)
