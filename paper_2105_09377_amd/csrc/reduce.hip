@@ -241,6 +241,29 @@ reduce_rows_any_kernel(const T* __restrict__ in, void* __restrict__ out, int out
   }
 }
 
+// One workgroup of 256 threads per row, a value per thread and step: rows of few steps.
+template <typename T>
+__global__ void __launch_bounds__(256)
+reduce_rows_block_kernel(const T* __restrict__ in, void* __restrict__ out, int out_dtype, int op,
+                         int64_t rows, int64_t cols, float scale) {
+  using A = typename Elem<T>::acc;
+  __shared__ A part[4];
+  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+    A acc = ident<A>(op);
+    for (int64_t c = threadIdx.x; c < cols; c += 256)
+      acc = combine(acc, Elem<T>::load(in, row * cols + c), op);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc = combine(acc, __shfl_xor(acc, off, 64), op);
+    if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      A r = combine(combine(part[0], part[1], op), combine(part[2], part[3], op), op);
+      store_out<A>(out, out_dtype, row, finish(r, scale));
+    }
+    __syncthreads();
+  }
+}
+
 static int reduce_num_cus() {
   static int cus = 0;
   if (!cus) {
@@ -254,7 +277,9 @@ static int reduce_num_cus() {
 }
 
 // Lanes per row of reduce_rows_any_kernel: as few as have four vectors each, and a workgroup for rows of more than a
-// wavefront's four where there are few of them.
+// wavefront's four while rows are few: the fewer vectors a row has, the sooner a wavefront for each is the better way (us, in
+// wavefronts / in workgroups: f32 1125 values in 1000 rows 4.0 / 4.2, in 4000 5.0 / 8.0; bf16 3101 in 1000 4.4 / 4.4, 6251 in 2000 6.7 /
+// 6.3, in 3000 8.7 / 8.6; f32 4101 in 1500 7.4 / 5.4, in 3000 9.6 / 11.7).
 template <typename T, int OP>
 static hipError_t launch_reduce_any(const ReduceArgs& a, hipStream_t s) {
   const int64_t nv = a.cols * int64_t(sizeof(T)) / 16 + 2, cap = int64_t(reduce_num_cus()) * 32;
@@ -264,7 +289,7 @@ static hipError_t launch_reduce_any(const ReduceArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((reduce_rows_any_kernel<T, OP, G>), dim3(unsigned(want < cap ? want : cap)), dim3(256), 0, s, \
                        static_cast<const T*>(a.in), a.out, a.out_dtype, a.rows, a.cols, a.scale);                   \
   }
-  if (nv > 256 && a.rows < 4096) GS_LAUNCH_ANY(256)
+  if (nv > 256 && a.rows < (nv > 400 ? 2000 : 1000)) GS_LAUNCH_ANY(256)
   else if (nv > 128) GS_LAUNCH_ANY(64)
   else if (nv > 64) GS_LAUNCH_ANY(32)
   else if (nv > 32) GS_LAUNCH_ANY(16)
@@ -299,11 +324,15 @@ static hipError_t launch_reduce_t(const ReduceArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   // Rows that are no whole vectors: a lane per value is the better way while the whole input is on its way at once (711
-  // rows of 201 int32 3.2 us against 3.5), rows of few values come through LDS (82183 of 25 f32 5.9 / 7.2, but 16453 of
-  // 106 int8 6.7 / 4.5).
-  const int64_t row_bytes = a.cols * int64_t(sizeof(T));
-  if ((((row_bytes >= 128 || a.cols >= 64) && a.rows >= (int64_t(1) << 20) / row_bytes) || row_bytes >= 2400) && reinterpret_cast<uintptr_t>(a.in) % 16 == 0 &&
-      a.cols <= (int64_t(1) << 40) / a.rows)
+  // rows of 201 int32 3.2 us against 3.5, 2726 of 153 f32 3.05 / 3.3, 9000 of 153 4.5 / 3.5).  Rows of few values come through
+  // LDS (82183 of 25 f32 5.9 / 7.2; int8 maxima 485771 of 77 12.9 / 28.5, 409200 of 82 10.3 / 26.8), but int8 rows of some hundred
+  // values while there are not many (15280 of 99 5.5 / 3.6, 34594 of 96 5.4 / 4.2, 50975 of 103 5.7 / 5.5).  A workgroup for each
+  // while it takes a thread nine values at most and rows are not many (1211 of 2183 bfloat16, maxima, 4.3 / 4.9; 1106 of 2207
+  // f32 4.1 / 4.8), or rows are short in bytes (22 of 2263 int8 3.5 us against 3.9).
+  const int64_t row_bytes = a.cols * int64_t(sizeof(T)), bytes = a.rows * row_bytes;
+  const bool nine = a.cols > 2048 && a.cols <= 9 * 256 && a.rows < 1600;
+  const bool many = a.cols < 8 * EPV ? a.cols >= 85 && a.rows < 35000 && bytes >= 1 << 20 : bytes >= (row_bytes < 512 ? 1400000 : 1 << 20);
+  if (!nine && (many || row_bytes >= 2400) && reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && a.cols <= (int64_t(1) << 40) / a.rows)
     return a.op == GS_SUM ? launch_reduce_any<T, GS_SUM>(a, s) : launch_reduce_any<T, GS_MAX>(a, s);
   if (a.cols > 8 && a.cols < 8 * EPV && a.rows >= 4 * kShortRows && reinterpret_cast<uintptr_t>(a.in) % 16 == 0) {
     const size_t lds = size_t(round_up(int64_t(kShortRows) * a.cols * int64_t(sizeof(T)), 16));
@@ -317,7 +346,12 @@ static hipError_t launch_reduce_t(const ReduceArgs& a, hipStream_t s) {
   else if (a.cols <= 8) GS_LAUNCH_GROUP(8);
   else if (a.cols <= 16) GS_LAUNCH_GROUP(16);
   else if (a.cols <= 32) GS_LAUNCH_GROUP(32);
-  else GS_LAUNCH_GROUP(64);
+  else if (a.cols <= 2048) GS_LAUNCH_GROUP(64);
+  else {
+    const int64_t blocks = a.rows < 65536 ? a.rows : 65536;
+    hipLaunchKernelGGL((reduce_rows_block_kernel<T>), dim3(unsigned(blocks)), dim3(256), 0, s, in, a.out, a.out_dtype, a.op,
+                       a.rows, a.cols, a.scale);
+  }
 #undef GS_LAUNCH_GROUP
   return hipGetLastError();
 }

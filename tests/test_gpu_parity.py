@@ -685,11 +685,13 @@ def test_depthwise_5x5_stride_2(n, c, h, w, p, dtype, odt):
 
 
 # Rows of any length in 16-byte vectors (reduce_rows_any_kernel): the rows' first and last vectors shared in every phase,
-# each lane group, a workgroup per row, several rounds of rows, the tensor ending inside a vector; lowest values at the rows'
-# ends, which a neighbour's value must not replace.
+# each lane group, a workgroup per row (and the numbers of rows from which it is a wavefront), several rounds of rows, the tensor
+# ending inside a vector; lowest values at the rows' ends, which a neighbour's value must not replace.
 @pytest.mark.parametrize("op", [gs.GS_SUM, gs.GS_MAX])
 @pytest.mark.parametrize("dtype,odt", [("f32", None), ("i32", None), ("i8", None), ("bf16", torch.bfloat16), ("bf16", torch.float32)])
-@pytest.mark.parametrize("rows,cols", [(16411, 67), (8193, 129), (4099, 259), (2053, 517), (1031, 1029), (130, 2403), (17, 9001), (3, 40003), (40011, 131)])
+@pytest.mark.parametrize("rows,cols", [(16411, 67), (8193, 129), (4099, 259), (2053, 517), (1031, 1029), (130, 2403), (17, 9001), (3, 40003), (40011, 131),
+                                       (999, 1125), (1000, 1125), (999, 4497), (1000, 4497), (1999, 6689), (2000, 6689), (5, 2049), (430, 2399),
+                                       (1599, 2301), (1600, 2301), (1599, 2305), (12337, 85), (34999, 87), (35000, 87)])
 def test_reduce_rows_of_any_length(rows, cols, dtype, odt, op):
     x = gen(dtype, (rows, cols), 9800 + cols)
     if op == gs.GS_MAX:
