@@ -140,8 +140,9 @@ int glenside_conv2d_im2col(const gs_ap* activations, const gs_ap* weights, const
  * activations ((N),(C,H,W)), weights ((C),(Kh,Kw)) -> out ((N,C,H',W'),()):
  *   out[n,c,y,x] = sum_{ky,kx} activations[n,c, y*Sh - Ph + ky, x*Sw - Pw + kx] * weights[c,ky,kx],
  * cells outside the image counting as zero (EXT pad[2], symmetric, each smaller than its window
- * dimension); act applies ReLU.  Types: i8 x i8 -> i32; bf16 x bf16 -> bf16 or f32 (fp32
- * accumulate, taps in the order ky, kx).  No workspace.  Windows or strides above 64, or rows too
+ * dimension); act applies ReLU.  Types: i8 x i8 -> i32; bf16 x bf16 -> bf16 or f32: products and
+ * sums in fp32, in an order that is a kernel's own (sizes and types choose the kernel); what a
+ * window does not hold never changes its result.  No workspace.  Windows or strides above 64, or rows too
  * long for the on-chip copy (about 16000 elements), return GS_ERR_UNSUPPORTED.                   */
 int glenside_depthwise_conv2d(const gs_ap* activations, const gs_ap* weights, const int64_t stride[2],
                               const int64_t pad[2], int act, gs_ap* out, void* stream);

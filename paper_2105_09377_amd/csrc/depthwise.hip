@@ -327,10 +327,13 @@ depthwise_kernel(DwArgs a) {
 // the MFMA rows a lane holds four neighbouring results of a row.
 //
 // A band's zeros meet input values too, so an infinity or NaN in the 64 bytes reaches results that it is no
-// part of.  It makes them NaN, and a tile with a result that is not finite is worked out again tap by tap.
+// part of, as NaN.  A tile with a result that is not finite is worked out again with zeros in the place of such values, and
+// tap by tap where a window holds one: a result never depends on what its window does not hold.
 //
 // What bounds it: a wave waits for its stores before it writes the next plane into LDS (loads and stores share a
-// counter), and each pair of tiles is a chain of LDS reads, products and stores.  The kernels of scalar
+// counter), and each pair of tiles is a chain of LDS reads, products and stores.  It needs 106 to 123 registers, of 128 for four
+// workgroups on a compute unit; with the places of the pieces in two registers each it spilled 8 to 26 and kept that
+// counter busy with scratch (5x5 to f32, 351 planes of 89x45 in 7 images, 23.6 -> 21.9).  The kernels of scalar
 // multiply-adds are bound by their instructions, 300 per eight results against some 60 per 512 here.  Errors
 // of f32 results against 64 bits are 0.90 to 0.95 of theirs.  See launch_depthwise_t for times.
 // ---------------------------------------------------------------------------------------------
@@ -365,18 +368,24 @@ __global__ void __launch_bounds__(256, 4) depthwise_tile_kernel(DwTileArgs a) {
   const int64_t plane_in = int64_t(a.H) * a.W;
 
   // Pieces of a task: row by row, the last of a row moved down to its start (zeros behind the row's end).
-  // Where they come from and go to is the same for every task: bytes from its first plane's start; LDS offset, and in
-  // its low bit whether the row ends there.
+  // Where they come from and go to is the same for every task, 16 bits each (a task's pieces are 32 KB): bytes from its first
+  // plane's start; above them the LDS offset, and in its low bit whether the row ends there.
   i32x4 val[kMaxVec];
-  uint32_t src[kMaxVec], dst[kMaxVec];
+  uint32_t way[kMaxVec];
+  static_assert(kMaxVec * 256 * 16 <= 0x10000 && kDwTileLds <= 0x10000, "16 bits");
+  auto way_of = [&](int u) {              // (taken apart where it is used: two registers per piece are not kept)
+    uint32_t v = way[u];
+    asm volatile("" : "+v"(v));
+    return v;
+  };
 #pragma unroll
   for (int u = 0; u < kMaxVec; ++u) {
     uint32_t row, c, g, y;                              // (planes lie one behind the other)
     a.dcpr.divmod(uint32_t(u * 256 + tid), &row, &c);
     a.dH.divmod(row, &g, &y);
     const int col = int(c) * E < a.W - E ? int(c) * E : a.W - E;
-    src[u] = (row * uint32_t(a.W) + uint32_t(col)) * ESZ;
-    dst[u] = (g * uint32_t(a.plane_lds) + (y + uint32_t(a.P)) * uint32_t(a.pitch) + (c + 1) * 16) | (int(c) + 1 == a.cpr ? 1u : 0u);
+    const uint32_t dst = (g * uint32_t(a.plane_lds) + (y + uint32_t(a.P)) * uint32_t(a.pitch) + (c + 1) * 16) | (int(c) + 1 == a.cpr ? 1u : 0u);
+    way[u] = (((row * uint32_t(a.W) + uint32_t(col)) * ESZ) & 0xffffu) | dst << 16;
   }
   const int over = (a.cpr * E - a.W) * ESZ;             // bytes by which a row's last piece is moved down
   auto gcount_of = [&](int64_t task) { return int(a.planes - task * a.G < a.G ? a.planes - task * a.G : a.G); };
@@ -385,7 +394,7 @@ __global__ void __launch_bounds__(256, 4) depthwise_tile_kernel(DwTileArgs a) {
     const uint8_t* const base = reinterpret_cast<const uint8_t*>(in + task * a.G * plane_in);
 #pragma unroll
     for (int u = 0; u < kMaxVec; ++u)
-      if (u * 256 + tid < n) val[u] = __builtin_nontemporal_load(reinterpret_cast<const i32x4_any*>(base + src[u]));
+      if (u * 256 + tid < n) val[u] = __builtin_nontemporal_load(reinterpret_cast<const i32x4_any*>(base + (way_of(u) & 0xffffu)));
   };
   int64_t task = blockIdx.x;
   if (task >= a.tasks) return;
@@ -400,8 +409,9 @@ __global__ void __launch_bounds__(256, 4) depthwise_tile_kernel(DwTileArgs a) {
 #pragma unroll
     for (int u = 0; u < kMaxVec; ++u) {
       if (u * 256 + tid < gcount * a.pieces) {
-        if (over) val[u] = row_piece_fix(val[u], dst[u] & 1 ? over : 0);      // uniform
-        *reinterpret_cast<i32x4*>(dw_lds + (dst[u] & ~1u)) = val[u];
+        const uint32_t at = way_of(u) >> 16;
+        if (over) val[u] = row_piece_fix(val[u], at & 1 ? over : 0);      // uniform
+        *reinterpret_cast<i32x4*>(dw_lds + (at & ~1u)) = val[u];
       }
     }
     for (int id = tid; id < gcount * K * K; id += 256) {
@@ -455,20 +465,44 @@ __global__ void __launch_bounds__(256, 4) depthwise_tile_kernel(DwTileArgs a) {
         for (int q = 0; q < 2; ++q) zero[q] = (acc[q][0] * 0.0f + acc[q][1] * 0.0f) + (acc[q][2] * 0.0f + acc[q][3] * 0.0f);
         const float z = zero[0] + zero[1];              // NaN if any of them is not finite
         if (__any(z != z)) {
+          // The products again with zeros in the place of what is not finite ..
+#pragma unroll
+          for (int q = 0; q < 2; ++q) acc[q] = acc4_t{0, 0, 0, 0};
+#pragma unroll 1
+          for (int dy = 0; dy < K; ++dy) {
+            const T* const from = reinterpret_cast<const T*>(dw_lds + a.lds_w + (have * K + dy) * kBand) + 32 + grp * E - E - n16 + a.P;
+            const i32x4 taps = *reinterpret_cast<const i32x4_any*>(from);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              i32x4 v = *reinterpret_cast<const i32x4*>(rows + q * a.second + dy * a.pitch);
+#pragma unroll
+              for (int d = 0; d < 4; ++d) {
+                const uint32_t u = uint32_t(v[d]);
+                const uint32_t lo = (u & 0x7f80u) == 0x7f80u ? 0 : 0xffffu, hi = (u & 0x7f800000u) == 0x7f800000u ? 0 : 0xffff0000u;
+                v[d] = int32_t(u & (lo | hi));
+              }
+              acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, taps), __builtin_bit_cast(bf16x8, v), acc[q], 0, 0, 0);
+            }
+          }
+          // .. and tap by tap the results whose windows hold it.
 #pragma unroll 1
           for (int i = 0; i < 8; ++i) {
             const int q = i >> 2;
             const T* const cells = reinterpret_cast<const T*>(dw_lds + have * a.plane_lds + (y0 + q * a.dy + n16) * a.pitch) + E + x0 + q * a.dx + 4 * grp + (i & 3) - a.P;
             const T* const taps = reinterpret_cast<const T*>(dw_lds + a.lds_w + have * K * kBand) + 32;
             float sum = 0.0f;
+            bool held = false;
 #pragma unroll 1
             for (int dy = 0; dy < K; ++dy)
 #pragma unroll 1
-              for (int dx = 0; dx < K; ++dx)
-                sum += DwElem<T>::cvt(cells[dy * (a.pitch / ESZ) + dx]) * DwElem<T>::cvt(taps[dy * (kBand / ESZ) + dx]);
+              for (int dx = 0; dx < K; ++dx) {
+                const T cell = cells[dy * (a.pitch / ESZ) + dx];
+                held = held || (cell & 0x7f80) == 0x7f80;
+                sum += DwElem<T>::cvt(cell) * DwElem<T>::cvt(taps[dy * (kBand / ESZ) + dx]);
+              }
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-              if (e == i) acc[e >> 2][e & 3] = sum;
+              if (e == i && held) acc[e >> 2][e & 3] = sum;
           }
         }
       }
@@ -695,13 +729,13 @@ template <typename T>
 hipError_t launch_depthwise_t(const DepthwiseArgs& d, hipStream_t s) {
   // Unit strides on the matrix units where the 16x32 or 32x16 results of a step are mostly results, there are enough of them, and,
   // for 3x3, columns are unaligned (us, strips / tiles):
-  //   5x5: 32 images of 128 planes of 112x112 99 / 63, 11 of 330 51x101 64 / 39, 3 of 314 100x17 15.9 / 11.9; but 18 of 361
-  //   planes of 8x49 13.8 / 18.0, 8 of 30 40x33 6.0 / 6.3, 3 of 237 37x31 int8 9.0 / 9.9;
-  //   3x3: 17 of 313 80x99 86 / 60, 14 of 276 28x68 int8 26 / 18, 32 of 256 28x28 16.9 / 14.3; but 32 of 128 112x112 (aligned) 51.5 /
-  //   54.8, 32 of 512 14x14 9.6 / 16.8, 2 of 361 51x19 to f32 6.4 / 6.9.
+  //   5x5: 32 images of 128 planes of 112x112 101 / 63, 11 of 330 51x101 64 / 36, 3 of 314 100x17 14.4 / 8.9, 10 of 65 49x19 to
+  //   f32 9.4 / 6.9; but 18 of 361 planes of 8x49 14.2 / 16.2, 16 of 511 27x20 to bfloat16 18.4 / 19.7;
+  //   3x3: 17 of 313 80x99 85 / 61, 14 of 276 28x68 int8 25 / 16, 32 of 256 28x28 16.5 / 13.9; but 32 of 128 112x112 (aligned) 52.3 /
+  //   57.3 (to f32 72 / 82), 32 of 512 14x14 9.7 / 16.0, 2 of 361 51x19 to f32 6.3 / 6.3.
   const int64_t step = d.Wo > 16 ? round_up(d.Wo, 32) * round_up(d.Ho, 16) : round_up(d.Wo, 16) * round_up(d.Ho, 32);
   const int64_t plane = int64_t(d.Ho) * d.Wo, results = int64_t(d.N) * d.C * plane;
-  if (d.Kh == 5 ? plane * 100 >= step * 45 && results >= (__is_same(T, int8_t) ? 2000000 : 300000) : plane * 100 >= step * 70 && results >= 900000 && !dw_edge(d)) {
+  if (d.Kh == 5 ? plane * 100 >= step * (d.out_dtype == GS_BF16 ? 54 : 45) && results >= (__is_same(T, int8_t) ? 2000000 : 300000) : plane * 100 >= step * 70 && results >= 900000 && !dw_edge(d)) {
     const hipError_t e = launch_depthwise_tiles<T>(d, s);
     if (e != hipErrorInvalidValue) return e;
   }

@@ -674,6 +674,21 @@ def test_depthwise_tiles(n, c, h, w, k, p, dtype, odt):
         assert (buf[:256] == 77).all() and (buf[256 + want.numel():] == 77).all()
 
 
+# What a window does not hold does not change its result by a bit, infinities and NaN included (the matrix units multiply
+# them with zeros; finite values round as they do without them).
+@pytest.mark.parametrize("odt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n,c,h,w,k,p", [(3, 100, 63, 62, 3, 1), (2, 50, 95, 111, 5, 2), (25, 80, 27, 16, 5, 2), (7, 64, 29, 32, 5, 0)])
+def test_depthwise_tiles_windows_stay_apart(n, c, h, w, k, p, odt):
+    x, wt = gen("bf16", (n, c, h, w), 9910 + h), gen("bf16", (c, k, k), 9955 + w, 1.0 / k)
+    odd = torch.zeros(x.shape, dtype=torch.bool)
+    odd[:, :, ::9, ::17] = True
+    y = torch.where(odd, torch.tensor([float("inf"), float("-inf"), float("nan")], dtype=x.dtype)[torch.arange(x.numel()).view(x.shape) % 3], x)
+    held = torch.nn.functional.conv2d(odd.float(), torch.ones(c, 1, k, k), padding=p, groups=c) > 0
+    a, b = (gs.depthwise_conv2d(t.to(DEV), wt.to(DEV), (1, 1), (p, p), out_dtype=odt).cpu() for t in (x, y))
+    assert torch.isfinite(a).all() and torch.equal(a[~held], b[~held])
+    assert not torch.isfinite(b[held]).any()
+
+
 # 5x5 windows at stride 2: strips cut by the row's end, odd planes, several planes to a task and bands of one.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
 @pytest.mark.parametrize("n,c,h,w,p", [(1, 1, 5, 5, 0), (3, 17, 12, 17, 2), (2, 9, 31, 46, 1), (20, 24, 8, 16, 2), (1, 3, 203, 301, 2)])
