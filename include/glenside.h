@@ -156,8 +156,8 @@ int glenside_depthwise_conv2d(const gs_ap* activations, const gs_ap* weights, co
  *                    channels x one step of one tap (1 KB each, the unit the kernel reads),
  *                    (O/32, C-step, Kh, Kw).  Needs glenside_conv2d_direct_workspace bytes.  When C
  *                    is no whole number of steps, a buffer that is too small for the second copy but
- *                    holds the first is taken all the same (here and by the calls that read it,
- *                    which are given the same number of bytes): slower kernels then read the first.
+ *                    holds the first is taken all the same (here and by the calls that read it, which
+ *                    may be told of another number of bytes): the first copy is read then, more slowly.
  *   _direct_packed : the convolution proper, reading weights only from `packed`; `weights` gives
  *                    shape and dtype, its data pointer is not read.  `packed` needs the bytes that
  *                    _pack_weights needs; when it has glenside_conv2d_direct_workspace bytes for

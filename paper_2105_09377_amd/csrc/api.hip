@@ -217,8 +217,10 @@ ConvArgs conv_args(const gs_ap* act, const gs_ap* residual, int actfn, const gs_
   a.Cpad = int(round_up(cs.C, act->dtype == GS_I8 ? 32 : 16));
   if (conv_is_smallc(act->dtype, cs.C))
     a.wnat = static_cast<const uint8_t*>(packed) + conv_smallc_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
-  if (layout.blocked && conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw))
+  if (layout.blocked && conv_blocked_weight_bytes(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw)) {
     a.wblk = static_cast<const uint8_t*>(packed) + conv_blocked_weight_offset(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
+    a.wmark = conv_blocked_mark(packed, act->dtype, cs.O, cs.C, cs.Kh, cs.Kw);
+  }
   a.relu = actfn == GS_ACT_RELU;
   return a;
 }
@@ -521,7 +523,8 @@ int glenside_conv2d_direct(const gs_ap* act, const gs_ap* w, const int64_t strid
     return GS_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const PackedLayout layout = packed_layout(act->dtype, cs.O, cs.C, cs.Kh, cs.Kw, split_scratch(act->dtype, cs), workspace_bytes);
-  const ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, layout);
+  ConvArgs a = conv_args(act, residual, actfn, out, cs, workspace, layout);
+  a.wmark = nullptr;      // (this call writes the copies that it reads)
   // Few channels: the kernel takes the weights as they are and writes the copies on the side.
   if (conv_is_smallc(act->dtype, cs.C) && int64_t(cs.N) * cs.Ho * cs.Wo > 0) {
     ConvArgs b = a;

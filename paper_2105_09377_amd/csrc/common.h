@@ -295,6 +295,7 @@ struct ConvArgs {
   const void* wr;         // repacked weights: O x (Kh*Kw) x Cpad, channel fastest, zero padded
   const void* wnat;       // fewer channels than a chunk: ((O up to 64s),(K up to 32 B)) copy, else null
   const void* wblk;       // the copy in 1 KB blocks (see conv_blocked_weight_offset), null if there is none
+  const uint64_t* wmark;  // unequal kBlockedMark: the blocked copy is not there after all; null: it is
   void* out;              // N x O x Ho x Wo
   const void* residual;
   int in_dtype, out_dtype;
@@ -317,9 +318,14 @@ size_t conv_smallc_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
 // each block the exact image of the LDS block the convolution's weight transfers fill (lane i of a
 // transfer moves bytes 16 i .. 16 i + 15), so that one transfer reads 1 KB of consecutive memory
 // instead of 32 pieces of 32 bytes from 32 rows.  Bytes of that copy (0 if there is none) and its
-// offset in the weight workspace.
+// offset in the weight workspace.  Of channel counts that are no whole chunks it is optional: a packing call that is told
+// of fewer bytes leaves it out.  The calls that read may be told of other sizes than the one that packed, so 256 bytes in front of the place of
+// an optional copy, in what every packing call is given, lies a mark: kBlockedMark, or zero.
 size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw);
 size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw);
+constexpr uint64_t kBlockedMark = 0x79706f63b10c4ed5u;
+// The mark in workspace `packed`, null where the copy is not optional.
+uint64_t* conv_blocked_mark(const void* packed, int in_dtype, int O, int C, int Kh, int Kw);
 hipError_t launch_conv_smallc_pack(const void* w, void* packed, int in_dtype, int O, int C, int Kh, int Kw,
                                    bool blocked, hipStream_t s);
 // Reads a.wr = natural-order copy; with `packed`, a.wr are the weights themselves and their copies are written there (the

@@ -37,8 +37,9 @@ namespace gs {
 // thread and copy).
 template <typename T>
 __global__ void __launch_bounds__(256)
-conv_repack_kernel(const T* __restrict__ w, T* __restrict__ wr, T* __restrict__ wb, int O, int C, int T_,
+conv_repack_kernel(const T* __restrict__ w, T* __restrict__ wr, T* __restrict__ wb, uint64_t* mark, int O, int C, int T_,
                    int Cpad) {
+  if (mark && blockIdx.x == 0 && threadIdx.x == 0) *mark = wb ? kBlockedMark : 0;
   constexpr int G = 16 / int(sizeof(T));
   typedef T piece_t __attribute__((ext_vector_type(G)));
   const int nchunk = Cpad / (2 * G);
@@ -89,11 +90,16 @@ size_t conv_blocked_weight_bytes(int in_dtype, int O, int C, int Kh, int Kw) {
   return size_t(round_up(O, 32)) * Kh * Kw * conv_cpad(in_dtype, C) * dtype_size(in_dtype);
 }
 
+static bool conv_blocked_optional(int in_dtype, int C) { return C != conv_cpad(in_dtype, C); }
+
 size_t conv_blocked_weight_offset(int in_dtype, int O, int C, int Kh, int Kw) {
-  return size_t(round_up(int64_t(conv_weight_front_bytes(in_dtype, O, C, Kh, Kw)), 256));
+  return size_t(round_up(int64_t(conv_weight_front_bytes(in_dtype, O, C, Kh, Kw)), 256)) + (conv_blocked_optional(in_dtype, C) ? 256 : 0);
 }
 
-bool conv_blocked_optional(int in_dtype, int C) { return C != conv_cpad(in_dtype, C); }
+uint64_t* conv_blocked_mark(const void* packed, int in_dtype, int O, int C, int Kh, int Kw) {
+  if (!conv_blocked_optional(in_dtype, C) || !conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)) return nullptr;
+  return reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(const_cast<void*>(packed)) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw) - 256);
+}
 
 size_t conv_weight_workspace(int in_dtype, int O, int C, int Kh, int Kw, bool least) {
   const size_t blocked = least && conv_blocked_optional(in_dtype, C) ? 0 : conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw);
@@ -111,13 +117,14 @@ hipError_t launch_conv_repack(const void* w, void* wr, int in_dtype, int O, int 
   uint8_t* wb = blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
                     ? static_cast<uint8_t*>(wr) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw)
                     : nullptr;
+  uint64_t* const mark = conv_blocked_mark(wr, in_dtype, O, C, Kh, Kw);
   if (in_dtype == GS_I8)
     hipLaunchKernelGGL((conv_repack_kernel<uint8_t>), grid, dim3(256), 0, s,
-                       static_cast<const uint8_t*>(w), static_cast<uint8_t*>(wr), wb, O, C, Kh * Kw, Cpad);
+                       static_cast<const uint8_t*>(w), static_cast<uint8_t*>(wr), wb, mark, O, C, Kh * Kw, Cpad);
   else
     hipLaunchKernelGGL((conv_repack_kernel<uint16_t>), grid, dim3(256), 0, s,
                        static_cast<const uint16_t*>(w), static_cast<uint16_t*>(wr),
-                       reinterpret_cast<uint16_t*>(wb), O, C, Kh * Kw, Cpad);
+                       reinterpret_cast<uint16_t*>(wb), mark, O, C, Kh * Kw, Cpad);
   return hipGetLastError();
 }
 

@@ -609,6 +609,7 @@ SmallCCopies smallc_copies(void* packed, bool blocked, int in_dtype, int O, int 
   c.natural = natural;
   c.blocked = blocked && conv_blocked_weight_bytes(in_dtype, O, C, Kh, Kw)
                   ? static_cast<uint8_t*>(packed) + conv_blocked_weight_offset(in_dtype, O, C, Kh, Kw) : nullptr;
+  c.mark = conv_blocked_mark(packed, in_dtype, O, C, Kh, Kw);
   c.rows = smallc_has_rows_copy(in_dtype, Kw) ? natural + smallc_rows_offset(in_dtype, O, C, Kh, Kw) : nullptr;
   c.O = O; c.O64 = int(round_up(O, 64)); c.C = C; c.Kh = Kh; c.Kw = Kw;
   c.Cpad = in_dtype == GS_I8 ? 32 : 16;                // one chunk: fewer channels than that

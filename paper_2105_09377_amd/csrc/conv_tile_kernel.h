@@ -53,7 +53,8 @@ typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   /
 // read past them is clamped to the last channel (in bounds) and becomes zero on its way into the LDS, so that an infinity
 // never meets the zero weights behind the last channel; 32-byte chunks that a 1x1 window's last step lacks multiply a page
 // of zeros.  That is two more instructions per load and one or two per loaded register, so whole chunks keep kernels of
-// their own.  50 random layers of 16 to 480 channels, us against the kernels of whole LDS rows that they took before:
+// their own.  Where the blocked copy turns out not to have been written (ConvArgs::wmark), the fragments come from the copy in the listing's order
+// that is always there, 32 pieces of 32 bytes each.  50 random layers of 16 to 480 channels, us against the kernels of whole LDS rows that they took before:
 // 3.4 times faster on average, at least 1.05 (29 images of 148 channels 18x10 -> 44, 3x3 bf16, 32.1 -> 7.3; 20 of 166 channels
 // 75x14 -> 16 int8 at stride 2 37.0 -> 8.1; 7 of 161 channels 67x37 -> 64, 1x1, 32.5 -> 9.2).
 //
@@ -98,6 +99,10 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
                "s"(g.dW.mul), "s"(g.dW.shift), "s"(g.dW.one), "s"(g.dTiles.d), "s"(g.dTiles.mul), "s"(g.dTiles.shift),
                "s"(g.dTiles.one), "s"(g.php), "s"(g.rowp), "s"(g.halfb), "s"(g.bufb));
 
+  uint64_t mark = kBlockedMark;           // (requested here, read where the weights' addresses are made)
+  if constexpr (ODD && !NAT)
+    if (a.wmark) mark = *a.wmark;
+
   // Tile: renumbered so that an XCD owns a contiguous range (see conv4_kernel.h).
   int m0, mend, o0;
   {
@@ -120,6 +125,7 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   // ---- weights: fragments of (32 channels, chunk, tap), 1 KB each -------------------------------
   // (rows and blocks past O are never stored)
   constexpr int kTap = NAT ? 32 : 1024;   // bytes from a tap to the next
+  int tap_step = kTap, chunk_step = T * kTap;             // (constants but where a copy may be missing)
   const uint8_t* wsrc;
   if constexpr (NAT) {
     wsrc = static_cast<const uint8_t*>(a.wr) + int64_t(first) * (T * kTap);
@@ -135,14 +141,23 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
     const int o = o0 + wo * 32 + (lane & 31);
     wlane = uint32_t(o < a.O ? o : a.O - 1) * uint32_t(a.C * ESZ) + uint32_t(lane >> 5) * 16u;   // (fits: host check)
   }
+  if constexpr (ODD && !NAT) {
+    if (mark != kBlockedMark) {           // uniform
+      const int o = o0 + wo * 32 + (lane & 31);
+      tap_step = CM > 1 ? 32 : a.Cpad * ESZ;
+      chunk_step = 32 * CM;
+      wsrc = static_cast<const uint8_t*>(a.wr) + first * chunk_step;
+      wlane = uint32_t(o < a.O ? o : a.O - 1) * uint32_t(KH * KW * a.Cpad * ESZ) + uint32_t(lane >> 5) * 16u;
+    }
+  }
   i32x4 ring[T], proj_tap;
   auto load_tap = [&](int ch, auto tap_) {
     constexpr int tap = decltype(tap_)::value;
-    const uint8_t* at = wsrc + int64_t(ch) * (T * kTap) + tap * kTap + wlane;
+    const uint8_t* at = wsrc + int64_t(ch) * chunk_step + tap * tap_step + wlane;
     if constexpr (PART) {                 // (tap: a chunk of the step)
       const int c = (first + ch) * CM + tap;
       if constexpr (NAT) at = (2 * c + (lane >> 5)) * G < a.C ? at : kTileZeros;     // rows are whole 16-byte pieces: host check
-      else at = c < n_blocks ? at : kTileZeros + wlane;
+      else at = c < n_blocks ? at : kTileZeros + lane * 16;
     }
     ring[tap] = *reinterpret_cast<const i32x4*>(at);
   };

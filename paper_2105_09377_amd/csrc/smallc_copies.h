@@ -13,6 +13,7 @@ struct SmallCCopies {
   void* rows;        // row-window copy ((O rounded up to 64),(C*Kh rounded up to 2, 16 bytes)): element dy of row
                      // r = c*Kh + dx is w[o][c][dx][dy], zeros for dy >= Kw and in the padding row; or null
   void* blocked;     // the copy in 1 KB blocks (see conv_blocked_weight_offset), one chunk of channels; or null
+  uint64_t* mark;    // whether it is there (see there); or null
   int O, O64, C, Kh, Kw, Cpad, Kp, rows2;
 };
 
@@ -26,6 +27,7 @@ template <typename T, typename I>
 __device__ __forceinline__ void write_copies(const T* __restrict__ w, const SmallCCopies& c, I first, I step) {
   constexpr int G = 16 / int(sizeof(T));
   typedef T piece_t __attribute__((ext_vector_type(G)));
+  if (c.mark && first == 0) *c.mark = c.blocked ? kBlockedMark : 0;
   const I O = I(c.O), C = I(c.C), taps = I(c.Kh) * I(c.Kw), K = C * taps, nrows = C * I(c.Kh), rows2 = I(c.rows2);
   const I per_tap = I(c.Cpad / G), per_row = I(c.Kp / G);
   const I n_taps = O * taps * per_tap, n_natural = I(c.O64) * per_row, n_rows = c.rows ? I(c.O64) * rows2 : 0;

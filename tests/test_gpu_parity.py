@@ -865,6 +865,33 @@ def test_conv2d_odd_channels_in_the_least_workspace(k, c, dtype):
         gs.conv2d_pack_weights(wt, packed=torch.empty(least - 1, dtype=torch.uint8, device=DEV))
 
 
+# Packing and convolving may be told of buffers of different sizes, each large enough, in either order; what lies in a
+# buffer from before is never taken for a copy of the weights.
+@pytest.mark.parametrize("k,c,dtype", [(3, 33, "bf16"), (5, 50, "i8"), (1, 40, "bf16"), (1, 200, "i8"), (3, 11, "bf16"), (5, 20, "i8"), (1, 12, "bf16")])
+def test_conv2d_packed_and_read_in_other_sizes(k, c, dtype):
+    cfg, other = (synth.conv_layer(3, c, 13, 18, 72, k, 1, k // 2, dtype, 9420 + c + i) for i in (0, 1))
+    x, wt, pad = cfg["x"].to(DEV), cfg["w"].to(DEV), (k // 2 if k > 1 else 0,) * 2
+    want = torch.nn.functional.conv2d(cfg["x"].double(), cfg["w"].double(), padding=pad).numpy()
+    want = want.astype(np.int64) if dtype == "i8" else want
+    full = gs.conv2d_workspace(x, wt, (1, 1), pad)
+
+    def takes(size):
+        try:
+            gs.conv2d_pack_weights(wt, packed=torch.empty(size, dtype=torch.uint8, device=DEV))
+        except gs.GlensideError:
+            return False
+        return True
+    least = next(size for size in range(256, full + 256, 256) if takes(size))
+    assert least < full
+    for before in (0x5A, None):         # a buffer of anything, and one that held other weights in all copies
+        for packs, reads in ((least, full), (least, full + 4096), (full, least), (full, full + 4096)):
+            buf = torch.full((full + 4096,), before or 0, dtype=torch.uint8, device=DEV)
+            if before is None:
+                gs.conv2d_pack_weights(other["w"].to(DEV), packed=buf)
+            gs.conv2d_pack_weights(wt, packed=buf[:packs])
+            assert_parity(gs.conv2d_direct_packed(x, wt, buf[:reads], (1, 1), pad), want, what=f"packed in {packs}, read in {reads} bytes")
+
+
 # Few channels and many output rows: tasks of two rows (conv_rows_kernel).  Odd row counts, rows cut inside a
 # 16-byte store, several position and channel tiles, windows of one row, 16-byte loads and element by element.
 @pytest.mark.parametrize("dtype,odt", [("bf16", torch.bfloat16), ("bf16", torch.float32), ("i8", torch.int32)])
