@@ -407,6 +407,16 @@ constexpr TileCost kTileCost[3][kNumTileShapes] = {   // shapes as in kTileShape
      {1.02f, 2.72f, 1.18f, 1.35f, 0.03f, 17.0f, 0.99f, 4, 0.18f}},
 };
 
+// The same where channels do not fill the last chunk: what a chunk costs in the place of one, with `item` more for each patch item of a
+// thread beyond the first; `start` us for each of those, and `groups` us in the shapes that split the channel sum, in front
+// of a workgroup's first chunk.  Fitted to 1118 layers of 3x3 and 5x5 windows and 334 of 1x1 in every shape that takes
+// them (mean error 13 and 16 %, 32 and 37 with each chunk a tenth dearer and nothing else); the shape it picks is 1.1 and 1.4 %
+// slower than the fastest on average, 7.6 and 8.7 before (47 images of 26 bytes 15x26 -> 16, 5x5: four items 15.8 us, one 6.6).
+struct TileOdd {
+  float chunk, item, start, groups;
+};
+constexpr TileOdd kTileOdd[2] = {{1.09f, 0, 1.11f, 0.72f}, {0.91f, 0.29f, 0.94f, 0.64f}};     // 1x1, others
+
 // Positions per tile of at most `tp`: fewest rounds over the compute units, then whole output rows
 // (a patch row fewer), then the widest.  Multiples of eight, so that stores are whole.
 static int tile_positions(int64_t M, int n_ot, int Wo, int tp) {
@@ -477,9 +487,14 @@ static bool tile_geometry(const ConvArgs& a, const ConvGeom& g0, int shape, int 
   const int64_t rows = ceil_div(g.tps, a.Wo);
   const float per_thread = point ? float(2 * cm * (whole ? rows : rows + 1) * ceil_div(a.W, kTileItem)) / threads
                                  : float((rows * S + a.Kh) * a.W) / (2 * threads);
-  const float chunk = (p->odd ? 1.1f : 1.0f) + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
+  // Channels that do not fill the last chunk: items beyond the first cost more, in every chunk and before the first one, and
+  // channel-sum groups, whose chunks are seldom one for each, start later (TileOdd).
+  const TileOdd& od = kTileOdd[point ? 0 : 1];
+  const float more = p->odd ? float(p->maxi - 1) : 0.0f;
+  const float chunk = (p->odd ? od.chunk + od.item * more : 1.0f) + (S == 2 ? c.strided : 0.0f) + c.item * (per_thread > 1 ? per_thread - 1 : 0.0f);
   const float store = c.store * (g.HWo % group ? 1 + c.cut : 1.0f);
-  const float alone = c.wg + store + c.alone * cnt * chunk, busy = c.busy * cnt * chunk + 0.6f * store;
+  const float start = p->odd ? od.start * more + (sh.ks > 1 ? od.groups : 0.0f) : 0.0f;
+  const float alone = c.wg + start + store + c.alone * cnt * chunk, busy = c.busy * cnt * chunk + 0.6f * store + start;
   const float by_rounds = alone * ceil_div(tiles, int64_t(256 * c.at_once));
   const float by_work = alone + busy * float(ceil_div(tiles, 256) - 1);
   *cost = c.base + (by_rounds > by_work ? by_rounds : by_work);
@@ -585,9 +600,9 @@ static hipError_t launch_conv_t(const ConvArgs& a_in, hipStream_t s) {
   const ConvGeom g = conv_geom(a);
   if (g.M == 0 || a.O == 0) return hipSuccess;
   // Fewer channels than a chunk: half of one at least on conv_tile_kernel, but 1x1 windows and few results, and all
-  // others, as im2col rows formed in LDS.  60 layers of 8 to 15 channels (16 to 31 in bytes), us, in LDS rows / in tiles:
-  // 1.6 times faster on average (64 images of 15, 26x14 -> 384, 3x3 stride 2 88 / 6.5; 34 of 29 in bytes, 18x46 -> 400
-  // 108 / 20; 2 of 8, 26x20 -> 96 5.7 / 5.6), at worst 0.65 (35 of 16 in bytes, 9x35 -> 32, 5x5, 8.4 / 12.8; six of 110 below 0.95); 1x1: 10 of 25 in
+  // others, as im2col rows formed in LDS.  350 layers of 8 to 15 channels (16 to 31 in bytes), us, in LDS rows / in tiles:
+  // 1.5 times faster on average (64 images of 15, 26x14 -> 384, 3x3 stride 2 88 / 6.5; 34 of 29 in bytes, 18x46 -> 400
+  // 108 / 20; 2 of 8, 26x20 -> 96 5.7 / 5.6), four below 0.9 (14 of 8, 9x7 -> 2, 5x5, 6.3 / 8.2); 1x1: 10 of 25 in
   // bytes, 73x26 -> 208 53 / 11, but 10 of 9, 12x53 -> 16 5.4 / 6.9.
   const bool rows_first = a.wnat && a.Kh == 1 && a.O <= 64;
   const TilePlan& plan = plan_tiles<TR>(a, g);
