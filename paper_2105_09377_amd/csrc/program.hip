@@ -545,12 +545,16 @@ constexpr int64_t kFewWindows = 512 << 10;
 
 // How the flat form is evaluated; Fig. 2a always is the direct convolution, bit for bit.  The two ways are one launch for the packing of the weights and one for the
 // convolution, against the windows gathered in memory (unless one launch does all, see conv2d_one_launch) and the
-// contraction that stores its result transposed.  Over 70 layers of up to 32 images of 16 to 64 channels, 14x14 to
-// 56x56, us, direct / im2col:
-//   1x1 windows: im2col, mostly one launch (1 image of 32 channels 25x36 -> 120 bf16 7.4 / 5.2, 23 of 48, 48x32,
-//   padded, -> 128 19.4 / 13.0; of 36 layers one was slower, 9 of 16 channels 41x34 in bytes, padded, 10.7 / 12.1);
-//   larger ones directly where conv_tile_kernel takes them and the windows are not few (21 of 48, 29x26, 3x3 stride 2
-//   8.7 / 11.2; 5 of 48, 51x55, 3x3 9.9 / 19.3); with few windows the launches decide and either way takes 6 to 8;
+// contraction that stores its result transposed.  Lines drawn over 1600 layers of up to 64 images of 1 to 200 channels, us,
+// direct / im2col; on 1070 others what they pick is 0 to 5 % slower than the faster way on average (padded 1x1; short 3x3 and 5x5):
+//   1x1 windows: im2col, mostly one launch (1 image of 32 channels 25x36 -> 120 bf16 7.4 / 5.2).  Padded ones too (23 of 48, 48x32 ->
+//   128 19.4 / 13.0; 6 of 142 bytes at stride 2, 8x21 -> 276 44 / 6.7), but where one or two tiles of 64 results hold them all and
+//   positions fill the chip at unit stride (58 of 169 bytes 57x42 -> 6 25 / 67, 22 of 32 bytes 52x54 -> 32 10.6 / 13.5; near the
+//   line 20 % are lost either way), and in the few-channel kernel while its tasks are two rounds at most (21 of 16 bytes
+//   14x37 -> 40 7.6 / 11.7, 882 tasks 12.4 / 17.4, but 1075 15.4 / 13.2 and 2240 30 / 11);
+//   larger ones directly where conv_tile_kernel takes them (21 of 48, 29x26, 3x3 stride 2 8.7 / 11.2; 5 of 48, 51x55, 3x3
+//   9.9 / 19.3; 1 of 172 bytes 22x42 -> 123, 3x3 stride 2, 13 / 29), but where windows are fewer than 256 KB and either 5x5 (4 of 91,
+//   9x8 -> 222 at stride 2 17 / 13) or so short that one launch may do them;
 //   what conv_tile_kernel does not take, directly by the lines below, drawn over 1267 layers on the other kernels (us,
 //   direct / gather, contraction and transposition in launches of their own, as the flat listing went then):
 //   the producer / consumer kernel nearly always (64 channels of 28x32, 3x3: 10.4 / 15.0; 512 of 30x30 bytes 20.3 / 192);
@@ -594,17 +598,25 @@ bool direct_fits(const ConvShapes& c, bool flat) {
   if (!c.valid || !gs::conv_direct_fits(a)) return false;
   if (!flat) return true;
   const bool small_window = a.Kh <= 3 && a.Kw <= 3;
-  const int64_t plane = int64_t(a.Ho) * a.Wo, esz = int64_t(gs::dtype_size(a.in_dtype));
+  const int64_t plane = int64_t(a.Ho) * a.Wo, esz = int64_t(gs::dtype_size(a.in_dtype)), window_bytes = int64_t(a.C) * a.Kh * a.Kw * esz;
   if (a.Sh <= 2 && a.Sw <= 2) {
     if (a.N * plane >= gs::ceil_div(a.O, 64) * (small_window ? 4096 : 4096 * esz)) return true;
-    const int64_t window_bytes = int64_t(a.C) * a.Kh * a.Kw * esz;
     if (small_window && a.C * esz >= 32 && window_bytes * std::max(a.Sh, a.Sw) * (1 + a.W % 2) <= 1152) return true;
   }
-  return (small_window && gs::conv_pipelined_takes(a)) || (c.gathered >= kFewWindows && gs::conv_tiles_take(a));
+  return (small_window && gs::conv_pipelined_takes(a)) || (a.Kh * a.Kw > 1 && (2 * c.gathered >= kFewWindows || (small_window && window_bytes > 1024)) && gs::conv_tiles_take(a));
 }
-// 1x1 windows that one launch does not do as it is (see eval_conv2d), few of them, without padding.
-bool point_windows(const ConvShapes& c) {
-  return c.valid && c.a.Kh == 1 && c.a.Kw == 1 && c.gathered > 0 && c.a.O > 0 && (c.a.Ph + c.a.Pw > 0 || c.gathered >= kFewWindows);
+// 1x1 windows: the im2col entry point for those without padding that are not few, and for padded ones but where the general
+// kernel has positions enough and few results, or the few-channel kernel two rounds of tasks at most (an output row of
+// 128 positions and 64 results each).  Left open: the others.
+enum Way { kOpen, kDirect, kIm2col };
+Way point_way(const ConvShapes& c) {
+  const gs::ConvArgs& a = c.a;
+  if (!c.valid || a.Kh != 1 || a.Kw != 1 || c.gathered == 0 || a.O == 0) return kOpen;
+  if (a.Ph + a.Pw == 0) return c.gathered >= kFewWindows ? kIm2col : kOpen;
+  const int64_t rows = int64_t(a.N) * a.Ho, tiles = gs::ceil_div(a.O, 64);
+  const bool directly = gs::conv_is_smallc(a.in_dtype, a.C) ? rows * gs::ceil_div(a.Wo, 128) * tiles <= 1024
+                                                             : a.Sh == 1 && a.Sw == 1 && tiles <= 2 && rows * a.Wo >= (tiles == 1 ? 32768 : 98304);
+  return directly && gs::conv_direct_fits(a) ? kDirect : kIm2col;
 }
 bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
   std::vector<int64_t> perm;
@@ -650,8 +662,9 @@ bool match_conv2d(const TreeP& t, const Env& env, ConvMatch* m) {
     folded.pad[1] = lo[3];
     with_pad = conv_shapes(folded, env, b, all);
   }
-  folded.im2col = flat && point_windows(with_pad);
-  if (folded.im2col || direct_fits(with_pad, flat)) {
+  const Way way = flat ? point_way(with_pad) : kOpen;
+  folded.im2col = way == kIm2col;
+  if (way != kOpen || direct_fits(with_pad, flat)) {
     *m = folded;
     return true;
   }
@@ -945,8 +958,10 @@ struct Evaluator {
     if (dry) return GS_OK;
     gs_ap oa = make_ap(out->data, s);
     if (m.im2col) return glenside_conv2d_im2col(&aa, &wa, stride, pad, nullptr, GS_ACT_NONE, &oa, scratch, cws, stream);
-    // Few windows: one launch instead of two, where a kernel does it.
-    if (m.flat && s.numel() > 0 && s.numel() / w.s.d[0] * (w.s.numel() / w.s.d[0]) * int64_t(gs::dtype_size(w.s.dtype)) < kFewWindows) {
+    // Few windows of up to 512 bytes: one launch instead of two, where a kernel does it (longer ones take it more time than the
+    // second launch does: 2 images of 48 channels 14x16 -> 104, 3x3, 6.7 us in two, 8.2 in one).
+    const int64_t window_bytes = w.s.numel() / (w.s.d[0] > 0 ? w.s.d[0] : 1) * int64_t(gs::dtype_size(w.s.dtype));
+    if (m.flat && s.numel() > 0 && window_bytes <= 512 && s.numel() / w.s.d[0] * window_bytes < kFewWindows) {
       st = gs::conv2d_one_launch(&aa, &wa, stride, pad, &oa, stream);
       if (st >= 0) return st;
     }
