@@ -877,7 +877,8 @@ static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
   const int64_t slabs = ceil_div(a.K * TR::kEsz, kSlabBytes);
   // Short K: the write-back of smaller tiles overlaps another tile's products (6271 x 7864 x 64 34.1 in 256x256
   // tiles, 26.5 in 128x128).  Long K: from 180 tiles on the larger ones pay although they do not fill the chip (2272 x 5160 x
-  // 1536, 189 tiles, 46.7 in 128x128 tiles, 43.6).
+  // 1536, 189 tiles, 46.7 in 128x128 tiles, 43.6).  Over 80 products each, all types: 1.14 and 1.15 times faster (int8 1.11 and
+  // 1.14), two slower (one slab, e4m3 to bfloat16, 2018 x 8168: 11.0 / 12.1).
   if (((t256 >= 256 && slabs > 4) || (t256 >= 180 && slabs >= 16)) && fi >= 256 && fj >= 256)
     return launch_dma<TR, 256, 256, 2, 4, 128, 2>(a, s);
   // few rows (a convolution's output channels against many positions) or few columns (100352 x 64 x 576
@@ -892,12 +893,15 @@ static hipError_t launch_dma_tiles(const GemmArgs& a, hipStream_t s) {
     // product (2936 x 1112 x 256 to f32 8.9 in 128x128 tiles, 8.3), else a third slab buffer in the place of the
     // second workgroup (2048^3 20.9 against 23.1 in halves).  Eight waves: with four, what each does between its
     // products lies open (2746 x 1408 x 2112 e4m3 14.1 against 13.5, 3230 x 1704 x 128 8.0 against 7.0, 7413 x 3000 x 256 25.9
-    // against 23.4; over 46 of 388 products of up to 8192 more than 3 % faster, one slower).
+    // against 23.4).  80 products for each of these lines, 16 of each pair of types: 1.12 times faster on average at up to 16 slabs
+    // (int8 1.05, others 1.07 to 1.22), 1.05 beyond (1.02), 1.06 from two rounds on (1.03; 1.13 where results are bfloat16); two of
+    // 240 slower, by 4 % (2390 x 5224 x 192 bf16 to f32 19.6 / 20.3).
     if (t128 <= 256 && slabs <= 16) return launch_dma<TR, 64, 128, 2, 4, 128, 3>(a, s);
     if (t128 <= 256) return launch_dma<TR, 128, 128, 2, 4, 128, 3>(a, s);
     return launch_dma<TR, 128, 128, 2, 4, 128, 2>(a, s);
   }
-  // more tiles of 64x64 than one round of the chip, fewer of 64x128, long K: 7519 x 240 x 7232 e4m3 31.7 / 25.1
+  // more tiles of 64x64 than one round of the chip, fewer of 64x128, long K: 7519 x 240 x 7232 e4m3 31.7 / 25.1; over 130 products
+  // 1.06 times faster, one in ten 4 to 9 % slower, without a pattern in types, tiles or K
   if (t64 > 256 && slabs > 16 && tile_count(a.I, a.bm, 64) * tile_count(a.J, a.bn, 128) <= 256 && (a.bn <= 0 || fj >= 128))
     return launch_dma<TR, 64, 128, 2, 4, 128, 3>(a, s);
   // 1024^3: 10.9 with two slab buffers, 7.9 with three, 7.4 with four; 1024 x 2048 x 1024, two
@@ -937,7 +941,7 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
   // 128x128 tiles need 160 of them to be the faster ones: 2047 x 1531 x 1001 e4m3 (192 tiles) 12.6 us
   // against 16.9 in 64x64 tiles, 1702 x 1221 x 300 (140 tiles) 7.8 against 7.4.  One for each compute unit: 16 waves, whose
   // loads and write-back overlap (13.5 with 8; 3000^3 bf16, 576 tiles, 97.7 against 91.3).  Fewer: 128x64 tiles where those are one
-  // round and 64x64 ones more (1103 x 1072 x 1893 e4m3 15.9 in 64x64 tiles, 12.3; 780 x 1730 x 987 bf16 16.1, 13.8).  Results (or
+  // round and 64x64 ones more (1103 x 1072 x 1893 e4m3 15.9 in 64x64 tiles, 12.3; 780 x 1730 x 987 bf16 16.1, 13.8; over 130 products 1.1 times faster, three up to 7 % slower).  Results (or
   // blocks) of up to 64 rows or columns would leave half of every tile empty (100000 x 10 x 65 bf16 to
   // bf16: 17.4 against 12.0; 64 x 40000 x 1001 bf16 to f32: 30.4 against 24.0).
   const int64_t t128 = tile_count(a.I, a.bm, 128) * tile_count(a.J, a.bn, 128);
