@@ -79,8 +79,9 @@ class ResNet18Stack:
                                                        (p, p), gs.GS_ACT_RELU, self.bufs[name], self.bufs[proj])
 
     def layer_calls(self) -> List[str]:
-        """Names of the library calls of one forward pass, in order (a projection goes with the convolution beside it)."""
-        return [name for name, _call in self.steps]
+        """Names of the layers of one forward pass, block by block.  `plan` has a call for each but the projections, which the
+        calls of the convolutions beside them compute too."""
+        return ["conv1", "pool"] + [n for n in self.spec if n != "conv1"] + ["avg", "fc"]
 
     def plan(self) -> List[Tuple[str, Callable[[], torch.Tensor]]]:
         """The forward pass as (layer name, call) pairs in execution order.  Every call reads and

@@ -95,3 +95,14 @@ def test_sequences_of_integers_are_sized():
     # what is sized is taken: the operator is what is refused
     for window in ([2, 2], torch.Size((2, 2)), np.array([2, 2]), torch.tensor([2, 2]), range(2, 4)):
         refused(gs.GS_ERR_UNSUPPORTED, gs.windows_reduce, y, 2, window, (2, 2), op=77)
+
+
+def test_the_stack_names_every_layer():
+    """Projections too, which are computed by the calls of the convolutions beside them."""
+    from paper_2105_09377_amd.resnet import ResNet18Stack
+    from paper_2105_09377_amd.synth import RESNET18_CONVS
+    net = object.__new__(ResNet18Stack)
+    net.spec = {name: rest for name, *rest in RESNET18_CONVS}
+    names = net.layer_calls()
+    assert names[:2] == ["conv1", "pool"] and names[-2:] == ["avg", "fc"]
+    assert sorted(names[2:-2]) == sorted(n for n in net.spec if n != "conv1")
