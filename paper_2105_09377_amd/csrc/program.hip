@@ -603,7 +603,11 @@ bool direct_fits(const ConvShapes& c, bool flat) {
     if (a.N * plane >= gs::ceil_div(a.O, 64) * (small_window ? 4096 : 4096 * esz)) return true;
     if (small_window && a.C * esz >= 32 && window_bytes * std::max(a.Sh, a.Sw) * (1 + a.W % 2) <= 1152) return true;
   }
-  return (small_window && gs::conv_pipelined_takes(a)) || (a.Kh * a.Kw > 1 && (2 * c.gathered >= kFewWindows || (small_window && window_bytes > 1024)) && gs::conv_tiles_take(a));
+  if (small_window && gs::conv_pipelined_takes(a)) return true;
+  // Few windows: those that the gather takes long for, whose task is an output row: many input rows, and windows that it
+  // cannot write in 16-byte pieces (1 of 102 bytes 13x63 -> 210, 3x3 stride 2, 11.8 us directly, 25 gathered).
+  const bool slow_gather = (small_window && window_bytes > 1024) || (window_bytes % 16 != 0 && int64_t(a.C) * a.Kh * a.W * esz >= 8192);
+  return a.Kh * a.Kw > 1 && (2 * c.gathered >= kFewWindows || slow_gather) && gs::conv_tiles_take(a);
 }
 // 1x1 windows: the im2col entry point for those without padding that are not few, and for padded ones but where the general
 // kernel has positions enough and few results, or the few-channel kernel two rounds of tasks at most (an output row of
@@ -958,10 +962,10 @@ struct Evaluator {
     if (dry) return GS_OK;
     gs_ap oa = make_ap(out->data, s);
     if (m.im2col) return glenside_conv2d_im2col(&aa, &wa, stride, pad, nullptr, GS_ACT_NONE, &oa, scratch, cws, stream);
-    // Few windows of up to 512 bytes: one launch instead of two, where a kernel does it (longer ones take it more time than the
-    // second launch does: 2 images of 48 channels 14x16 -> 104, 3x3, 6.7 us in two, 8.2 in one).
-    const int64_t window_bytes = w.s.numel() / (w.s.d[0] > 0 ? w.s.d[0] : 1) * int64_t(gs::dtype_size(w.s.dtype));
-    if (m.flat && s.numel() > 0 && window_bytes <= 512 && s.numel() / w.s.d[0] * window_bytes < kFewWindows) {
+    // Few windows: one launch instead of two, where a kernel does it.  Windows of more than 512 bytes take that kernel longer than the
+    // two others (2 images of 48 channels 14x16 -> 104, 3x3, 8.2 us against 6.7), but a caller waits for the second launch
+    // instead (1 of 32 36x28 -> 32, 3x3, from its side 8.5 against 11.5).
+    if (m.flat && s.numel() > 0 && s.numel() / w.s.d[0] * (w.s.numel() / w.s.d[0]) * int64_t(gs::dtype_size(w.s.dtype)) < kFewWindows) {
       st = gs::conv2d_one_launch(&aa, &wa, stride, pad, &oa, stream);
       if (st >= 0) return st;
     }

@@ -101,13 +101,13 @@ def test_flat_form_of_every_route(shape, dtype, odt):
 
 
 # Both sides of the lines between the ways that the flat form goes: padded 1x1 windows on few and many channels by results and
-# positions, windows of 512 bytes and of more that one launch would take, few 5x5 windows.
+# positions, few short windows and longer ones, few 5x5 windows.
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("shape", [(32, 32, 30, 30, 64, 1, 1, 1), (32, 32, 30, 29, 64, 1, 1, 1), (32, 32, 30, 30, 65, 1, 1, 1), (32, 35, 61, 61, 5, 1, 2, 1),
                                    (32, 9, 30, 30, 64, 1, 1, 1), (32, 9, 31, 30, 64, 1, 1, 1), (16, 11, 30, 30, 128, 1, 1, 1), (16, 11, 30, 30, 129, 1, 1, 1),
                                    (96, 32, 30, 30, 65, 1, 1, 1),
                                    (2, 28, 9, 11, 20, 3, 1, 1), (2, 29, 9, 11, 20, 3, 1, 1), (2, 56, 9, 11, 20, 3, 1, 1), (2, 57, 9, 11, 20, 3, 1, 1),
-                                   (2, 40, 9, 14, 20, 5, 1, 0), (8, 40, 14, 14, 20, 5, 1, 2)])
+                                   (2, 40, 9, 14, 20, 5, 1, 0), (8, 40, 14, 14, 20, 5, 1, 2), (1, 102, 13, 63, 70, 3, 2, 1), (1, 101, 7, 39, 70, 5, 2, 0)])
 def test_flat_form_on_both_sides_of_its_lines(shape, dtype):
     n, c, h, w, o, k, s, p = shape
     tensors = {"activations": gen_small(dtype, (n, c, h, w), 9476), "weights": gen_small(dtype, (o, c, k, k), 9477)}
