@@ -164,7 +164,9 @@ int glenside_depthwise_conv2d(const gs_ap* activations, const gs_ap* weights, co
  *                    these activations, the part behind the weights is scratch for splitting the
  *                    channel sum among workgroups (layers with few output tiles), overwritten
  *                    by every call.
- * glenside_conv2d_direct(x, w, ..., ws) == _pack_weights(w, ws) then _direct_packed(x, w, ..., ws). */
+ * glenside_conv2d_direct(x, w, ..., ws) == _pack_weights(w, ws) then _direct_packed(x, w, ..., ws): the same
+ * bytes in ws, the same integers, and floats up to the order of their sums (for few channels or small images a
+ * call that brings its weights may take another kernel). */
 int glenside_conv2d_pack_weights(const gs_ap* weights, void* packed, size_t packed_bytes,
                                  void* stream);
 int glenside_conv2d_direct_packed(const gs_ap* activations, const gs_ap* weights,
@@ -203,7 +205,8 @@ size_t glenside_conv2d_direct_static_limit(void);
 /* `compute reduceSum | reduceMax` (Table 2): in ((a..),(c..)) -> out ((a..),()).
  * Types: i8 -> i32 (sum) or i8 (max); i32 -> i32; bf16 -> bf16 or f32; f32 -> f32.  Float sums
  * accumulate in fp32.  EXT: scale multiplies a float result (1.0f = the paper's operator; must
- * be 1.0f for integers and for GS_MAX).                                                         */
+ * be 1.0f for integers and for GS_MAX).  Whether GS_MAX over values with a NaN among them gives the
+ * NaN or another of them is not specified.                                                      */
 int glenside_reduce(const gs_ap* in, int op, float scale, gs_ap* out, void* stream);
 
 /* `compute reduceMax|reduceSum (windows in window stride)` fused -- max pooling is Fig. 2c with
@@ -268,11 +271,13 @@ int glenside_program_shape(const char* text, const gs_named_ap* tensors, int n_t
  * dtype the same, or GS_BF16 where the root is a bfloat16 contraction).  Node by node:
  *   (compute dotProd (cartProd a0 a1))   one MFMA contraction; the Cartesian product is never
  *                                        formed (the pattern Fig. 3 maps to hardware);
- *   the whole listing of Fig. 2a, or,
- *   where that is the faster way, of
- *   Fig. 5 (what Fig. 4 makes of it)     the direct convolution (windows formed on chip); symmetric
+ *   the whole listing of Fig. 2a         the direct convolution (windows formed on chip); symmetric
  *                                        zero padding in front of the windows becomes its own where
  *                                        its kernels are sure to take it so;
+ *   the whole listing of Fig. 5
+ *   (what Fig. 4 makes of it)            the direct or the im2col convolution, or one launch for all,
+ *                                        whichever is faster; node by node where padding is not
+ *                                        symmetric and no direct kernel takes the padded tensor;
  *   (compute reduceX (windows ...))      the fused pooling kernel (Fig. 2c);
  *   (compute reduceX (pair a b))         the element-wise kernel (Sec. 5.4);
  *   access squeeze flatten reshape,

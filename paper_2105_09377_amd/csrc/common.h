@@ -358,8 +358,9 @@ int conv_pick_ksplit(int in_dtype, int N, int C, int O, int Ho, int Wo);
 // True where some direct kernel is sure to take the layer (its patch fits the LDS, a tile spans few images);
 // only the shape is read.
 bool conv_direct_fits(const ConvArgs& a);
-// True where the producer / consumer kernel, or conv_tile_kernel, takes the layer; only the shape is read.
+// True where the producer / consumer kernel takes the layer on packed weights; only the shape is read.
 bool conv_pipelined_takes(const ConvArgs& a);
+// The same for conv_tile_kernel, whose cost model must prefer it too; false for fewer channels than a chunk.
 bool conv_tiles_take(const ConvArgs& a);
 
 struct ReduceArgs {       // out[r] = reduce over `cols` contiguous values

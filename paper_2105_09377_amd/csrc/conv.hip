@@ -692,6 +692,9 @@ hipError_t conv_tile_forced(const ConvArgs& a, int way, bool launch, int* out, h
 bool conv_projection_fits(const ConvArgs& a) {
   return a.in_dtype == GS_BF16 && a.Kh == 3 && a.Kw == 3 && a.Sh == 2 && a.Sw == 2 && a.Ph == 1 && a.Pw == 1 && a.wblk && a.wproj && a.C == a.Cpad;
 }
+// Taken wherever the layer alone has a plan, and with that plan: 89 random layers of 16 to 480 channels, 7x7 to 112x112, were 1.11
+// to 1.95 times faster than in two launches (6 images of 448 channels 28x58 -> 19 36.5 / 32.8 us, 4 of 224 90x64 -> 112 20.1 /
+// 15.3, 1 of 48 28x28 -> 65 10.9 / 6.7), none slower.
 hipError_t launch_conv_with_projection(const ConvArgs& a_in, hipStream_t s) {
   ConvArgs a = a_in;
   if (!conv_projection_fits(a)) return hipErrorInvalidValue;

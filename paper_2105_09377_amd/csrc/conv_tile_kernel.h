@@ -60,8 +60,10 @@ typedef int32_t i32x4_bytes __attribute__((ext_vector_type(4), aligned(1)));   /
 //
 // PROJ: a 1x1 projection of the same input at the same stride beside a 3x3 convolution padded by one (a residual
 // block's shortcut).  Its pixels are the centre tap's: one more weight fragment and NJ more MFMAs a chunk on fragments that
-// are in registers anyway, and a second write-back, instead of a launch that stages the input again.  The ResNet-18-shaped
-// stack with its three projections so, us: one image 145 -> 134, 64 images 530 -> 510 (128 to 512 channels at 28x28 to 7x7).
+// are in registers anyway, and a second write-back, instead of a launch that stages the input again.  The second accumulators
+// take two workgroups of four waves to a compute unit in the place of three, and the instance of four blocks and two items
+// spills seven registers.  The ResNet-18-shaped stack with its three projections so, us: one image 145 -> 134, 64 images
+// 530 -> 510 (128 to 512 channels at 28x28 to 7x7).
 template <typename TR, int KH, int KW, int CM, bool NAT, int S, int IL, int NJ, int WO, int WP, int KS, int MAXI, bool ONE,
           bool ODD, bool PROJ = false>
 __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArgs a, ConvGeom g) {
@@ -449,7 +451,9 @@ __global__ void __launch_bounds__(64 * WO * WP * KS, 2) conv_tile_kernel(ConvArg
   // ---- write-back: out[(img*O + o)*HWo + p] -----------------------------------------------------
   // SP positions at a time: staged in LDS of the wave's own as [channel][position] rows of 32-bit
   // values (16-byte stores), read back along the rows and written PG positions per lane.
-  // (both results one after the other: the staging of one may not meet the reads of the other)
+  // (both results one after the other: the staging of one may not meet the reads of the other.  The pointers are values of the
+  // closure: read from the arguments, whether there is a residual was asked at every store, 159 waits instead of 100 in 2529
+  // instructions instead of 2168; 64 channels at 56x56, batch 32, int8 13.7 -> 12.5 us, bfloat16 15.3 -> 14.8)
   auto write_back = [&](auto& acc, void* out, const void* residual, int relu) {
   constexpr int SP = 32 * (NJ < 4 ? NJ : 4), RS = SP * 4 + 16;
   constexpr int kRed = KS > 1 ? KS * NW * NJ * 4096 : 0;
