@@ -53,8 +53,8 @@ TRAFFIC = {
     "conv3x3": (13.66e6 + 12.85e6, "conv", "52e2c39618222be1abb242f239ada16add71476ba3499b9f658aa4026a21aef6"),
     "conv3x3_b64": (26.47e6 + 25.69e6, "conv", "52e2c39618222be1abb242f239ada16add71476ba3499b9f658aa4026a21aef6"),
     "im2col_gather": (12.98e6 + 115.65e6, "windows", "2df41177093041c7f5bfc084e5c727a2086129d3dfbb9ccf1771f4c8a4584491"),
-    "maxpool": (103.00e6 + 25.69e6, "reduce", "c0a5e5e3202cbbbc8420c11a98a25c363ef9c3320908d903ecf19b74384ad78f"),
-    "reduce": (268.47e6 + 0.52e6, "reduce", "c0a5e5e3202cbbbc8420c11a98a25c363ef9c3320908d903ecf19b74384ad78f"),
+    "maxpool": (103.00e6 + 25.69e6, "reduce", "5c95e418ad8f146e8827f01a4e428c2bfd51f64fdb17593cb0276a69c39f8f6e"),
+    "reduce": (268.47e6 + 0.52e6, "reduce", "5c95e418ad8f146e8827f01a4e428c2bfd51f64fdb17593cb0276a69c39f8f6e"),
     "transpose": (25.82e6 + 25.69e6, "move", "b78cc56938cd2a7f0a717dae30806bebbc26444d9a74c7d7dadff829548ccf12"),
     "dense_blocked": (50.54e6 + 16.78e6, "gemm", "42d90e12827b66cbee6eda8901ccd9660dd358629a0b36436501a5356dbe3911"),
     "dense": (1612.13e6 + 278.26e6, "gemm", "42d90e12827b66cbee6eda8901ccd9660dd358629a0b36436501a5356dbe3911"),

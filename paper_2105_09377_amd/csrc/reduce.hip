@@ -279,7 +279,8 @@ static int reduce_num_cus() {
 // Lanes per row of reduce_rows_any_kernel: as few as have four vectors each, and a workgroup for rows of more than a
 // wavefront's four while rows are few: the fewer vectors a row has, the sooner a wavefront for each is the better way (us, in
 // wavefronts / in workgroups: f32 1125 values in 1000 rows 4.0 / 4.2, in 4000 5.0 / 8.0; bf16 3101 in 1000 4.4 / 4.4, 6251 in 2000 6.7 /
-// 6.3, in 3000 8.7 / 8.6; f32 4101 in 1500 7.4 / 5.4, in 3000 9.6 / 11.7).
+// 6.3, in 3000 8.7 / 8.6; f32 4101 in 1500 7.4 / 5.4, in 3000 9.6 / 11.7).  Sums of floats keep workgroups longer: a wavefront
+// adds four times as many values one after the other (3000 rows of 8191 f32 1.03e-7 from 64 bits against 0.98e-7).
 template <typename T, int OP>
 static hipError_t launch_reduce_any(const ReduceArgs& a, hipStream_t s) {
   const int64_t nv = a.cols * int64_t(sizeof(T)) / 16 + 2, cap = int64_t(reduce_num_cus()) * 32;
@@ -289,7 +290,8 @@ static hipError_t launch_reduce_any(const ReduceArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((reduce_rows_any_kernel<T, OP, G>), dim3(unsigned(want < cap ? want : cap)), dim3(256), 0, s, \
                        static_cast<const T*>(a.in), a.out, a.out_dtype, a.rows, a.cols, a.scale);                   \
   }
-  if (nv > 256 && a.rows < (nv > 400 ? 2000 : 1000)) GS_LAUNCH_ANY(256)
+  constexpr bool rounds = OP == GS_SUM && !__is_same(T, int8_t) && !__is_same(T, int32_t);
+  if (nv > 256 && a.rows < (nv <= 400 ? 1000 : rounds ? 4096 : 2000)) GS_LAUNCH_ANY(256)
   else if (nv > 128) GS_LAUNCH_ANY(64)
   else if (nv > 64) GS_LAUNCH_ANY(32)
   else if (nv > 32) GS_LAUNCH_ANY(16)
@@ -328,9 +330,10 @@ static hipError_t launch_reduce_t(const ReduceArgs& a, hipStream_t s) {
   // LDS (82183 of 25 f32 5.9 / 7.2; int8 maxima 485771 of 77 12.9 / 28.5, 409200 of 82 10.3 / 26.8), but int8 rows of some hundred
   // values while there are not many (15280 of 99 5.5 / 3.6, 34594 of 96 5.4 / 4.2, 50975 of 103 5.7 / 5.5).  A workgroup for each
   // while it takes a thread nine values at most and rows are not many (1211 of 2183 bfloat16, maxima, 4.3 / 4.9; 1106 of 2207
-  // f32 4.1 / 4.8), or rows are short in bytes (22 of 2263 int8 3.5 us against 3.9).
+  // f32, maxima, 4.1 / 4.8), or rows are short in bytes (22 of 2263 int8 3.5 us against 3.9).
   const int64_t row_bytes = a.cols * int64_t(sizeof(T)), bytes = a.rows * row_bytes;
-  const bool nine = a.cols > 2048 && a.cols <= 9 * 256 && a.rows < 1600;
+  constexpr bool whole = __is_same(T, int8_t) || __is_same(T, int32_t);      // (sums of floats: the vector kernel rounds less)
+  const bool nine = a.cols > 2048 && a.cols <= 9 * 256 && a.rows < 1600 && (whole || a.op == GS_MAX);
   const bool many = a.cols < 8 * EPV ? a.cols >= 85 && a.rows < 35000 && bytes >= 1 << 20 : bytes >= (row_bytes < 512 ? 1400000 : 1 << 20);
   if (!nine && (many || row_bytes >= 2400) && reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && a.cols <= (int64_t(1) << 40) / a.rows)
     return a.op == GS_SUM ? launch_reduce_any<T, GS_SUM>(a, s) : launch_reduce_any<T, GS_MAX>(a, s);
